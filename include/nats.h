@@ -51,8 +51,9 @@ typedef enum nats_dtype { NATS_F32 = 0, NATS_BF16 = 1 } nats_dtype;
 /* Arithmetic used inside the kernels.
  *   NATS_MATH_AUTO : f32 tensors -> fp32 kernels; bf16 tensors -> chunkwise bf16 MFMA kernels
  *                    with fp32 state and accumulation.
- *   NATS_MATH_FP32 : fp32 arithmetic for either tensor dtype (token-recurrent state update,
- *                    fp32 dot products); slower, used for tight-tolerance work. */
+ *   NATS_MATH_FP32 : fp32 arithmetic for either tensor dtype (the forward's linear branch by chunks on
+ *                    fp32 matrix instructions, token by token where a state per chunk would not fit);
+ *                    slower, used for tight-tolerance work. */
 typedef enum nats_math { NATS_MATH_AUTO = 0, NATS_MATH_FP32 = 1 } nats_math;
 
 /* ------------------------------------------------------------------------- *

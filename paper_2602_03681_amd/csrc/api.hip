@@ -78,7 +78,19 @@ static bool uses_chunk_path(const FwdPlan& pl) {
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl) {
+// fp32 arithmetic: the linear branch by chunks of 64 tokens on fp32 matrix instructions (the kernels the backward pass
+// makes its states with) unless a routing decision spans two chunks, or the start states of all chunks (d^2 floats
+// per chunk and output head) would take more than FP32_CHUNK_BYTES: then token by token, which needs none.  At every size
+// that fits the chunk form is the shorter chain (a step per 64 tokens instead of one per token): the linear branch of B 1,
+// H 2, L 256, d 64 takes 24 us (three launches) instead of 95, of B 2, H 3, L 704 38 instead of 266.
+constexpr size_t FP32_CHUNK_BYTES = (size_t)16 << 30;
+static bool uses_fp32_chunks(const FwdPlan& pl) {
+    return !uses_chunk_path(pl) && !(pl.routing == NATS_ROUTE_CHUNK && pl.RC != 64) &&
+           (size_t)pl.BHG * (pl.L / 64) * pl.d * pl.d * 4 <= FP32_CHUNK_BYTES;
+}
+
+// by_tokens: fp32 arithmetic takes the linear branch token by token whatever the size (the smaller workspace)
+static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl, bool by_tokens = false) {
     if (p == nullptr) { set_error("params is NULL"); return NATS_ERR_NULL; }
     if (p->dtype != NATS_F32 && p->dtype != NATS_BF16) {
         set_error("dtype %d is neither NATS_F32 nor NATS_BF16", p->dtype);
@@ -163,9 +175,13 @@ static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl) {
     pl->off_vc = off;  off = align_up(off + n_out * pl->d * esz, 256);
     pl->off_ola = off; off = align_up(off + n_out * pl->d * 4, 256);
     pl->off_tf = pl->off_p = pl->off_gamv = pl->off_kdv = pl->off_gam = pl->off_seg = pl->off_vht = pl->off_olah = 0;
-    pl->off_snap = 0;
+    pl->off_snap = pl->off_ops = pl->off_ck = 0;
+    pl->fp32_chunks = !by_tokens && uses_fp32_chunks(*pl);
     pl->off_wout = off; off = align_up(off + 2 * n_out * 4, 256);   // weights of Eq. 21 when computed by Eq. 22
-    if (!uses_chunk_path(*pl) && pl->routing == NATS_ROUTE_CHUNK) {   // chunk-start state of the fp32 recurrence
+    if (pl->fp32_chunks) {
+        pl->off_ops = off; off = align_up(off + chunk_ops_floats(*pl, false) * 4, 256);
+        pl->off_ck = off;  off = align_up(off + (size_t)pl->BHG * (pl->L / 64) * pl->d * pl->d * 4, 256);
+    } else if (!uses_chunk_path(*pl) && pl->routing == NATS_ROUTE_CHUNK) {   // chunk-start state of the fp32 recurrence
         pl->off_snap = off; off = align_up(off + (size_t)pl->BHG * pl->d * pl->d * 4, 256);
     }
     if (uses_chunk_path(*pl)) {   // per-chunk operands of the chunkwise linear branch
@@ -227,7 +243,7 @@ static void plan_bwd(const FwdPlan& pl, BwdPlan* bp) {
     bp->off_dslap = off;   off = align_up(off + ns * (n_tok / 64) * 4, 256);   // ... and the sweep's partials of Eq. 17
     // chunkwise backward of the linear branch: operands of every chunk, U and the residuals, state gradients per chunk
     const size_t ch = (pl.routing == NATS_ROUTE_CHUNK && tk) ? 0 : 1;   // (token by token with routing per chunk: own checkpoint kernel)
-    bp->off_ops = off;     off = align_up(off + ch * chunk_ops_floats(pl) * 4, 256);
+    bp->off_ops = off;     off = align_up(off + ch * chunk_ops_floats(pl, true) * 4, 256);
     bp->off_ug = off;      off = align_up(off + ch * n_tok * pl.d * 4, 256);
     bp->off_uh = off;      off = align_up(off + ch * n_tok * pl.d * 4, 256);
     bp->off_dck = off;     off = align_up(off + ch * (1 - tk) * pl.BH * (pl.L / 64) * pl.d * pl.d * 4, 256);
@@ -413,13 +429,11 @@ size_t nats_hybrid_attn_fwd_workspace_bytes(const nats_fwd_params* p) {
     return pl.total;
 }
 
-nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
-                                    const float* alpha, const float* beta, const uint8_t* mask, void* O,
-                                    const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
-                                    void* hip_stream) {
-    FwdPlan pl;
-    nats_status st = validate_fwd_params(p, &pl);
-    if (st != NATS_OK) return st;
+// the forward on a validated plan
+static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void* V, const float* alpha, const float* beta,
+                           const uint8_t* mask, void* O, const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
+                           void* hip_stream) {
+    nats_status st = NATS_OK;
     if (!Q || !K || !V || !alpha || !beta || !mask || !O) {
         set_error("Q, K, V, alpha, beta, mask and O must all be non-NULL");
         return NATS_ERR_NULL;
@@ -516,7 +530,22 @@ nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, con
             st = launch_flash_softmax(pl, Qs, Kc, VhT, Ks, V, cnt, Oh, ex.w_nla, ex.w_la, O, ex.O_nla, ex.lse, stream, W_fused);
         }
     } else {
-        {
+        if (pl.fp32_chunks) {
+            float* ops = reinterpret_cast<float*>(ws + pl.off_ops);
+            float* ck = reinterpret_cast<float*>(ws + pl.off_ck);
+            {
+                ProfScope ps("gdn_bwd_prep", stream);
+                st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, false, stream);
+                if (st != NATS_OK) return st;
+            }
+            {   // U goes where the branch's rows will be
+                ProfScope ps("gdn_chunk_states", stream);
+                st = launch_gdn_chunk_states(pl, K, V, ops, ex.initial_state, ex.final_state, ck, O_la, nullptr, stream);
+                if (st != NATS_OK) return st;
+            }
+            ProfScope ps("gdn_chunk_out", stream);
+            st = launch_gdn_chunk_out(pl, Q, ops, false, ck, O_la, O_la, stream);
+        } else {
             ProfScope ps("gdn_recurrent", stream);
             st = launch_gdn_recurrent(pl, Q, K, V, alpha, beta, mask, ex.initial_state, ex.final_state, O_la,
                                       pl.routing == NATS_ROUTE_CHUNK ? reinterpret_cast<float*>(ws + pl.off_snap) : nullptr,
@@ -527,6 +556,16 @@ nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, con
         st = launch_softmax_fp32(pl, Qs, Kc, Vc, Ks, V, cnt, O_la, ex.w_nla, ex.w_la, O, ex.O_nla, ex.lse, stream);
     }
     return st;
+}
+
+nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                                    const float* alpha, const float* beta, const uint8_t* mask, void* O,
+                                    const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
+                                    void* hip_stream) {
+    FwdPlan pl;
+    const nats_status st = validate_fwd_params(p, &pl);
+    if (st != NATS_OK) return st;
+    return run_fwd(pl, Q, K, V, alpha, beta, mask, O, extra, workspace, workspace_bytes, hip_stream);
 }
 
 size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p) {
@@ -599,11 +638,11 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     if (by_chunks || !chunk) {   // the linear branch forwards once more by chunks, leaving the state at the start of every chunk
         {
             ProfScope ps("gdn_bwd_prep", stream);
-            st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, stream);
+            st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, true, stream);
             if (st != NATS_OK) return st;
         }
         ProfScope ps("gdn_chunk_states", stream);
-        st = launch_gdn_chunk_states(pl, K, V, ops, ex.initial_state, ckpt, Ug, Uh, stream);
+        st = launch_gdn_chunk_states(pl, K, V, ops, ex.initial_state, nullptr, ckpt, Ug, Uh, stream);
         if (st != NATS_OK) return st;
     } else {   // ... token by token
         ProfScope ps("gdn_checkpoints", stream);
@@ -619,7 +658,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         float* O_la = reinterpret_cast<float*>(ws + bp.off_mola);
         if (by_chunks || !chunk) {
             ProfScope ps("gdn_chunk_out", stream);
-            st = launch_gdn_chunk_out(pl, Q, ops, ckpt, Ug, O_la, stream);
+            st = launch_gdn_chunk_out(pl, Q, ops, true, ckpt, Ug, O_la, stream);
             if (st != NATS_OK) return st;
         } else {
             ProfScope ps("gdn_recurrent", stream);
@@ -870,6 +909,8 @@ nats_status nats_hybrid_attn_fwd_noalloc(const nats_fwd_params* p, const void* Q
     FwdPlan pl;
     nats_status st = validate_fwd_params(p, &pl);
     if (st != NATS_OK) return st;
+    // fp32 arithmetic by chunks keeps a state per chunk: where that does not fit, the linear branch goes token by token
+    if (pl.total > (size_t)NATS_NOALLOC_SCRATCH_BYTES && pl.fp32_chunks) (void)validate_fwd_params(p, &pl, true);
     if (pl.total > (size_t)NATS_NOALLOC_SCRATCH_BYTES) {
         set_error("nats_hybrid_attn_fwd_noalloc: this problem needs %zu bytes of scratch memory, the built-in buffer "
                   "holds %zu; use nats_hybrid_attn_fwd with a workspace", pl.total, (size_t)NATS_NOALLOC_SCRATCH_BYTES);
@@ -879,8 +920,7 @@ nats_status nats_hybrid_attn_fwd_noalloc(const nats_fwd_params* p, const void* Q
     st = noalloc_scratch(&ws);
     if (st != NATS_OK) return st;
     // nothing in the workspace has to start at zero: every kernel writes what it later reads
-    return nats_hybrid_attn_fwd_ex(p, Q, K, V, alpha, beta, mask, O, nullptr, ws, (size_t)NATS_NOALLOC_SCRATCH_BYTES,
-                                   hip_stream);
+    return run_fwd(pl, Q, K, V, alpha, beta, mask, O, nullptr, ws, (size_t)NATS_NOALLOC_SCRATCH_BYTES, hip_stream);
 }
 
 static nats_status validate_dec_params(const nats_dec_params* p);

@@ -53,6 +53,15 @@ __device__ __forceinline__ void unpack16(const u32x4 w, float (&out)[4], float) 
     for (int q = 0; q < 4; ++q) out[q] = __uint_as_float(w[q]);
 }
 
+// x of the lane that the DPP control names (rows of the mask only; 0 where there is no source), both halves of a double
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move_f64(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xF, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // ---- operands of a chunk ---------------------------------------------------------------------------------------------
 // One block per (chunk, batch*head).  Products in fp32 from the inputs as given (bf16 converts exactly); the inverse
 // by 16 x 16 blocks: forward substitution on the diagonal, matrix instructions below it.
@@ -67,8 +76,10 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
     float* Ks = cb_smem;
     float* Qs = cb_smem + CB_C * KS;
     float* As = Qs;                         // after the products: diag(b') At, [64][CB_MS]
-    float* s_g = cb_smem + 2 * CB_C * KS;   // log2 gamma
-    float* s_bp = s_g + CB_C;
+    // log2 gamma: its prefix sums in double, so that a decay ratio gamma_r / gamma_i, the exponential of a difference of
+    // two of them, keeps fp32 accuracy whatever stands in front of token i in the chunk (alphas near 0)
+    double* s_g = reinterpret_cast<double*>(cb_smem + 2 * CB_C * KS);
+    float* s_bp = reinterpret_cast<float*>(s_g + CB_C);
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
     const int n_chunks = L / CB_C;
@@ -93,27 +104,30 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
         const bool soft = !chunk_mask && mask[tok0 + lane] != 0;
         const bool soft_chunk = chunk_mask && mask[gc] != 0;
         const float a = (freeze_on_softmax && soft) ? 1.f : alpha[tok0 + lane];
-        float g = __builtin_amdgcn_logf(fmaxf(a, 1e-30f));   // log2; inclusive scan over the 64 lanes
-        g += dpp_move<0x111>(g);
-        g += dpp_move<0x112>(g);
-        g += dpp_move<0x114>(g);
-        g += dpp_move<0x118>(g);
-        g += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(g), 0x142, 0xA, 0xF, false));
-        g += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(g), 0x143, 0xC, 0xF, false));
-        const float gC = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), 63));
-        const float gam = __builtin_amdgcn_exp2f(g);
+        double gd = (double)__builtin_amdgcn_logf(fmaxf(a, 1e-37f));   // log2; inclusive scan over the 64 lanes
+        gd += dpp_move_f64<0x111, 0xF>(gd);
+        gd += dpp_move_f64<0x112, 0xF>(gd);
+        gd += dpp_move_f64<0x114, 0xF>(gd);
+        gd += dpp_move_f64<0x118, 0xF>(gd);
+        gd += dpp_move_f64<0x142, 0xA>(gd);
+        gd += dpp_move_f64<0x143, 0xC>(gd);
+        const uint64_t gu = __builtin_bit_cast(uint64_t, gd);
+        const double gC = __builtin_bit_cast(double, ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(gu >> 32), 63) << 32) |
+                                                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)gu, 63));
+        const float g = (float)gd, gam = __builtin_amdgcn_exp2f(g);
         const float bp = soft ? 0.f : beta[tok0 + lane];
-        s_g[lane] = g;
+        s_g[lane] = gd;
         s_bp[lane] = bp;
         o.g2[tok0 + lane] = g;
         o.gam[tok0 + lane] = gam;
-        o.kd[tok0 + lane] = soft_chunk ? 0.f : __builtin_amdgcn_exp2f(gC - g);
+        o.kd[tok0 + lane] = soft_chunk ? 0.f : __builtin_amdgcn_exp2f((float)(gC - gd));
         o.bp[tok0 + lane] = bp;
         if (lane == 63) o.gamC[gc] = (freeze_on_softmax && soft_chunk) ? 1.f : gam;
     }
     __syncthreads();
     // the 10 lower tiles (a, b), b <= a, of K K^T and Q K^T: tile t of the list to wavefront t % 4
-    float* Ato = o.At + gc * (CB_C * CB_C);
+    const bool keep_at = o.At != nullptr;   // the forward has no use for it
+    float* Ato = o.At + (keep_at ? gc * (CB_C * CB_C) : 0);
     float* Pmo = o.Pm + gc * (CB_C * CB_C);
     float* Tmo = o.Tm + gc * (CB_C * CB_C);
     f32x4 keepA[3];
@@ -131,13 +145,13 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
                 accQ = mac16(ld4(Qs + (16 * a + l16) * KS + 16 * kt + 4 * lq), bk, accQ);
             }
             const int i = 16 * b + l16;
-            const float gi = s_g[i];
+            const double gi = s_g[i];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 16 * a + 4 * lq + j;
-                const float G = __builtin_amdgcn_exp2f(s_g[r] - gi);
+                const float G = __builtin_amdgcn_exp2f((float)(s_g[r] - gi));
                 const float at = (i < r && linear_op == 0) ? G * accK[j] : 0.f;
-                Ato[r * CB_C + i] = at;
+                if (keep_at) Ato[r * CB_C + i] = at;
                 Pmo[r * CB_C + i] = (i <= r) ? G * accQ[j] : 0.f;
                 keepA[s][j] = s_bp[r] * at;
             }
@@ -149,7 +163,7 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int off = (16 * a + 4 * lq + j) * CB_C + 16 * b + l16;
-            Ato[off] = 0.f;
+            if (keep_at) Ato[off] = 0.f;
             Pmo[off] = 0.f;
         }
     }
@@ -224,9 +238,11 @@ struct SeqArgs {
     const uint8_t* mask;
     const float* S_init;           // DIR 0: [BH][D][D] or NULL
     float* ck;                     // [BH][L/64][D][D]
-    float *Ug, *Uh;                // [BH][L][D]: DIR 0 writes both, DIR 1 reads Uh
-    float *dV, *dbeta_part, *dS0;  // DIR 1
-    int L, BH;
+    float *Ug, *Uh;                // [BH][L][D]: DIR 0 writes Ug (and, with RES, Uh), DIR 1 reads Uh
+    float *dV, *dbeta_part;        // DIR 1
+    float* S_end;                  // [BH][D][D] or NULL.  DIR 0: the state after the last token; DIR 1: the gradient of S_init
+    int L, BH;                     // BH: heads of V (output heads)
+    int G;                         // head grouping: K, Q, the operands and the mask are those of linear head bh / G (DIR 0 only)
     float la_scale;
     int delta;                     // 1: delta rule; 0: gated linear attention
 };
@@ -271,7 +287,8 @@ __device__ __forceinline__ float4 ldk4(const uint16_t* p) { return ldb4(p); }
 __device__ __forceinline__ float4 ldkcol(const float* p, int rs) { return ld4col(p, rs); }
 __device__ __forceinline__ float4 ldkcol(const uint16_t* p, int rs) { return ldbcol(p, rs); }
 
-template <typename T, int D, int DIR>
+// RES: also the residuals Uh (and so At); the forward alone does without.
+template <typename T, int D, int DIR, bool RES>
 __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) {
     using LY = SeqLds<T, D, DIR>;
     using KE = typename std::conditional<LY::wide, float, uint16_t>::type;   // K, Q in LDS
@@ -294,6 +311,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
     const int w = wave & 3, lt = tid & 255;
     const int l16 = lane & 15, lq = lane >> 4;
     const int bh = blockIdx.x % a.BH, slice = blockIdx.x / a.BH, v0 = CB_NV * slice;
+    const int lin = DIR ? bh : bh / a.G;   // linear head
     const int L = a.L, n_chunks = L / CB_C;
     const size_t n_tok = (size_t)a.BH * L;
     const float delta = a.delta ? 1.f : 0.f;
@@ -308,7 +326,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
         float uhn[4] = {0.f, 0.f, 0.f, 0.f}, gCn = 0.f;
         uint32_t linn = 0;
         auto fetch = [&](int c) {   // as it comes from memory: a conversion here would wait for the load
-            const size_t gc = (size_t)bh * n_chunks + c, tok0 = (size_t)bh * L + (size_t)c * CB_C;
+            const size_t gc = (size_t)lin * n_chunks + c, tok0 = (size_t)lin * L + (size_t)c * CB_C;
 #pragma unroll
             for (int i = 0; i < NP; ++i) {   // a chunk's rows are contiguous
                 kreg[i] = reinterpret_cast<const u32x4*>(a.K + tok0 * D)[lt + 256 * i];
@@ -318,7 +336,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
             if (lt == 48) gCn = a.o.gamC[gc];
             if (DIR && a.mask != nullptr && lt >= 64 && lt < 80)   // NULL: routing per chunk, every token of a chunk writes
                 linn = *reinterpret_cast<const uint32_t*>(a.mask + tok0 + 4 * (lt - 64));
-            const size_t t4 = tok0 + 16 * w + 4 * lq;
+            const size_t t4 = (size_t)bh * L + (size_t)c * CB_C + 16 * w + 4 * lq;
             if (DIR) g4n = ld4(a.o.gam + t4);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -329,7 +347,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
             const float* m2 = (DIR ? a.o.Pm : a.o.At) + gc * (CB_C * CB_C);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                m2reg[i] = ld4(m2 + 4 * (lt + 256 * i));
+                if (RES) m2reg[i] = ld4(m2 + 4 * (lt + 256 * i));
                 m1reg[i] = ld4(m1 + 4 * (lt + 256 * i));
             }
         };
@@ -380,7 +398,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
         auto chunk_at = [&](int ci) { return DIR ? n_chunks - 1 - ci : ci; };
         fetch(chunk_at(0));
         put_kq_small(0);
-        put_m(M2b(0), m2reg);
+        if (RES) put_m(M2b(0), m2reg);
         put_m(M1, m1reg);
         if (n_chunks > 1) fetch(chunk_at(1));
         __syncthreads();
@@ -391,7 +409,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
             __syncthreads();
             if (more) {
                 if (LY::two) put_kq_small(nb);
-                put_m(M2b(nb), m2reg);
+                if (RES) put_m(M2b(nb), m2reg);
                 put_m(M1, m1reg);
             }
             if (LY::two && ci + 2 < n_chunks) fetch(chunk_at(ci + 2));
@@ -492,7 +510,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
         }
         __syncthreads();
         // ---- 3: the chunk's contribution to the state ------------------------------------------------------------
-        if (DIR == 0) {
+        if (DIR == 0 && RES) {
             f32x4 AU = {0.f, 0.f, 0.f, 0.f};
             for (int tb = 0; tb <= w; ++tb)
                 AU = mac16(ld4(M2 + (16 * w + l16) * MS + 16 * tb + 4 * lq), ld4(B1 + l16 * MS + 16 * tb + 4 * lq), AU);
@@ -528,10 +546,10 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
         __syncthreads();   // every read of the chunk's operands is done, the new state is in place
         if (!LY::two) __syncthreads();   // one place for the staged operands: they are replaced in between
     }
-    if (DIR == 1 && a.dS0 != nullptr) {
+    if (a.S_end != nullptr) {
 #pragma unroll
         for (int t = 0; t < KT; ++t)
-            *reinterpret_cast<float4*>(a.dS0 + ((size_t)bh * D + v0 + l16) * D + 16 * (KT * w + t) + 4 * lq) =
+            *reinterpret_cast<float4*>(a.S_end + ((size_t)bh * D + v0 + l16) * D + 16 * (KT * w + t) + 4 * lq) =
                 make_float4(Sacc[t][0], Sacc[t][1], Sacc[t][2], Sacc[t][3]);
     }
 }
@@ -539,7 +557,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
 template <typename T, int D, int DIR>
 constexpr size_t seq_lds_bytes() { return SeqLds<T, D, DIR>::bytes; }
 template <int D>
-constexpr size_t prep_lds_bytes() { return sizeof(float) * (2 * (size_t)CB_C * (D + 4) + 2 * CB_C); }
+constexpr size_t prep_lds_bytes() { return sizeof(float) * (2 * (size_t)CB_C * (D + 4) + 3 * CB_C); }
 
 // ---- the gradients of a chunk -------------------------------------------------------------------------------------------
 // One block per (chunk, batch*head), d / 16 wavefronts; wavefront w owns the columns 16 w .. 16 w + 15 of dQ and dK
@@ -881,11 +899,14 @@ constexpr size_t grads_lds_bytes() {
 // the branch's rows (the merges that normalise them, Eq. 21).  One block per (chunk, batch*head); wavefront w owns a
 // quarter of the value columns for all 64 tokens, so every element of S0 and U is read once per block, straight
 // from memory as the right operand; Q and P, which every wavefront reads whole, go through LDS.
-template <int D>
-__global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const float* __restrict__ Q, const ChunkOps o,
-                                                           const float* __restrict__ ck, const float* __restrict__ Ug,
-                                                           float* __restrict__ O_la, const int L, const int BH,
-                                                           const float la_scale) {
+// O_la may be Ug itself: a wavefront has read all it needs of U before it writes, and both are its own columns.
+// Head grouping: BH counts output heads, Q and the operands are those of linear head bh / G.  inner: 0 leaves P U out
+// (the ablation whose linear branch reads the carried state only).
+template <typename T, int D>
+__global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict__ Q, const ChunkOps o,
+                                                           const float* __restrict__ ck, const float* Ug,
+                                                           float* O_la, const int L, const int BH, const int G,
+                                                           const int inner, const float la_scale) {
     constexpr int KS = D + 4, MS = CB_MS, VW = D / 4, VT = VW / 16;   // value columns per wavefront, in tiles of 16
     __shared__ __align__(16) float Qs[CB_C * KS];
     __shared__ __align__(16) float Ps[CB_C * MS];
@@ -895,15 +916,21 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const float* __restr
     const int n_chunks = L / CB_C;
     const int bh = blockIdx.x % BH, chunk = blockIdx.x / BH;
     const size_t gc = (size_t)bh * n_chunks + chunk, tok0 = (size_t)bh * L + (size_t)chunk * CB_C;
-    for (int e = tid; e < CB_C * D / 4; e += 256) {
-        const int row = e / (D / 4), c4 = (e % (D / 4)) * 4;
-        *reinterpret_cast<float4*>(Qs + row * KS + c4) = ld4(Q + (tok0 + row) * D + c4);
+    const size_t gl = (size_t)(bh / G) * n_chunks + chunk, tokl = (size_t)(bh / G) * L + (size_t)chunk * CB_C;
+    constexpr int E = Vec16<T>::N;
+    for (int e = tid; e < CB_C * D / E; e += 256) {
+        const int row = e / (D / E), c = (e % (D / E)) * E;
+        float tmp[E];
+        Vec16<T>::load(Q + (tokl + row) * D + c, tmp);
+#pragma unroll
+        for (int j = 0; j < E; j += 4)
+            *reinterpret_cast<float4*>(Qs + row * KS + c + j) = make_float4(tmp[j], tmp[j + 1], tmp[j + 2], tmp[j + 3]);
     }
     for (int e = tid; e < CB_C * CB_C / 4; e += 256) {
         const int row = e / 16, c4 = (e % 16) * 4;
-        *reinterpret_cast<float4*>(Ps + row * MS + c4) = ld4(o.Pm + gc * (CB_C * CB_C) + row * CB_C + c4);
+        *reinterpret_cast<float4*>(Ps + row * MS + c4) = ld4(o.Pm + gl * (CB_C * CB_C) + row * CB_C + c4);
     }
-    if (tid < CB_C) s_gam[tid] = o.gam[tok0 + tid];
+    if (tid < CB_C) s_gam[tid] = o.gam[tokl + tid];
     __syncthreads();
     const float* S0 = ck + gc * (size_t)D * D;
     f32x4 acc[4][VT];
@@ -935,6 +962,7 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const float* __restr
             for (int j = 0; j < 4; ++j) acc[tt][vt][j] *= g[j];
     }
     // + P U: A = P[token][i], B = U[i = 16 tb + 4 lq + j][v]; P is lower triangular: tiles tb <= tt
+    if (inner)
 #pragma unroll
     for (int tb = 0; tb < 4; ++tb) {
         float4 b[VT];
@@ -957,12 +985,13 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const float* __restr
                 O_la[(tok0 + 16 * tt + 4 * lq + j) * D + VW * w + 16 * vt + l16] = la_scale * acc[tt][vt][j];
 }
 
-static ChunkOps chunk_ops(const FwdPlan& pl, float* base) {
+// with_at: room for At as well (the backward pass; the forward does without)
+static ChunkOps chunk_ops(const FwdPlan& pl, float* base, bool with_at = true) {
     const size_t n_tok = (size_t)pl.BH * pl.L, n_ch = n_tok / CB_C;
     ChunkOps o;
     o.Tm = base;
-    o.At = o.Tm + n_ch * CB_C * CB_C;
-    o.Pm = o.At + n_ch * CB_C * CB_C;
+    o.At = with_at ? o.Tm + n_ch * CB_C * CB_C : nullptr;
+    o.Pm = o.Tm + (with_at ? 2 : 1) * n_ch * CB_C * CB_C;
     o.g2 = o.Pm + n_ch * CB_C * CB_C;
     o.gam = o.g2 + n_tok;
     o.kd = o.gam + n_tok;
@@ -970,9 +999,9 @@ static ChunkOps chunk_ops(const FwdPlan& pl, float* base) {
     o.gamC = o.bp + n_tok;
     return o;
 }
-size_t chunk_ops_floats(const FwdPlan& pl) {
+size_t chunk_ops_floats(const FwdPlan& pl, bool with_at) {
     const size_t n_tok = (size_t)pl.BH * pl.L, n_ch = n_tok / CB_C;
-    return 3 * n_ch * CB_C * CB_C + 4 * n_tok + align_up(n_ch, 64);
+    return (with_at ? 3 : 2) * n_ch * CB_C * CB_C + 4 * n_tok + align_up(n_ch, 64);
 }
 
 template <typename T, int D>
@@ -990,8 +1019,8 @@ static bool launch_prep_t(const FwdPlan& pl, const void* Q, const void* K, const
 
 // ops: chunk_ops_floats(pl) floats.  Either routing.
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
-                                const uint8_t* mask, float* ops, hipStream_t st) {
-    const ChunkOps o = chunk_ops(pl, ops);
+                                const uint8_t* mask, float* ops, bool with_at, hipStream_t st) {
+    const ChunkOps o = chunk_ops(pl, ops, with_at);
     bool ok;
     if (pl.dtype == NATS_BF16) ok = pl.d == 64 ? launch_prep_t<bf16_t, 64>(pl, Q, K, alpha, beta, mask, o, st)
                                                : launch_prep_t<bf16_t, 128>(pl, Q, K, alpha, beta, mask, o, st);
@@ -1001,49 +1030,56 @@ nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K,
     return check_launch("gdn_bwd_prep");
 }
 
-template <typename T, int D, int DIR>
-static bool launch_seq_t(const FwdPlan& pl, const SeqArgs<T>& a, hipStream_t st) {
-    auto kern = gdn_chunk_seq_kernel<T, D, DIR>;
+template <typename T, int D, int DIR, bool RES>
+static bool launch_seq_t(const SeqArgs<T>& a, hipStream_t st) {
+    auto kern = gdn_chunk_seq_kernel<T, D, DIR, RES>;
     constexpr size_t lds = seq_lds_bytes<T, D, DIR>();
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.BH * (D / CB_NV))), dim3(512), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * (D / CB_NV))), dim3(512), lds, st, a);
     return true;
 }
-template <typename T, int DIR>
+template <typename T, int DIR, bool RES>
 static bool launch_seq_d(const FwdPlan& pl, const SeqArgs<T>& a, hipStream_t st) {
-    return pl.d == 64 ? launch_seq_t<T, 64, DIR>(pl, a, st) : launch_seq_t<T, 128, DIR>(pl, a, st);
+    return pl.d == 64 ? launch_seq_t<T, 64, DIR, RES>(a, st) : launch_seq_t<T, 128, DIR, RES>(a, st);
 }
 
-// The states at the chunk starts, ck [BH][L/64][d][d], with U and Uh [BH][L][d] of every chunk.
+// The states at the chunk starts, ck [BHG][L/64][d][d], with U (and, unless NULL, the residuals Uh) [BHG][L][d] of every
+// chunk; S_final (or NULL): the state after the last token.  ops as launch_gdn_bwd_prep left them, with At if Uh is
+// wanted.  Head grouping (pl.G > 1): V, the states, U and Uh have pl.BHG heads.
+template <typename T>
+static bool launch_states_t(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init, float* S_final,
+                            float* ck, float* Ug, float* Uh, hipStream_t st) {
+    const SeqArgs<T> a{(const T*)K, nullptr, (const T*)V, chunk_ops(pl, ops, Uh != nullptr), nullptr, S_init, ck, Ug, Uh,
+                       nullptr, nullptr, S_final, pl.L, pl.BHG, pl.G, pl.la_scale, pl.linear_op == 0};
+    return Uh != nullptr ? launch_seq_d<T, 0, true>(pl, a, st) : launch_seq_d<T, 0, false>(pl, a, st);
+}
 nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init,
-                                    float* ck, float* Ug, float* Uh, hipStream_t st) {
-    bool ok;
-    if (pl.dtype == NATS_BF16) {
-        const SeqArgs<bf16_t> a{(const bf16_t*)K, nullptr, (const bf16_t*)V, chunk_ops(pl, ops), nullptr, S_init, ck, Ug, Uh,
-                                nullptr, nullptr, nullptr, pl.L, pl.BH, pl.la_scale, pl.linear_op == 0};
-        ok = launch_seq_d<bf16_t, 0>(pl, a, st);
-    } else {
-        const SeqArgs<float> a{(const float*)K, nullptr, (const float*)V, chunk_ops(pl, ops), nullptr, S_init, ck, Ug, Uh,
-                               nullptr, nullptr, nullptr, pl.L, pl.BH, pl.la_scale, pl.linear_op == 0};
-        ok = launch_seq_d<float, 0>(pl, a, st);
-    }
+                                    float* S_final, float* ck, float* Ug, float* Uh, hipStream_t st) {
+    const bool ok = pl.dtype == NATS_BF16 ? launch_states_t<bf16_t>(pl, K, V, ops, S_init, S_final, ck, Ug, Uh, st)
+                                          : launch_states_t<float>(pl, K, V, ops, S_init, S_final, ck, Ug, Uh, st);
     if (!ok) { set_error("gdn_chunk_states: the kernel's LDS size was refused"); return NATS_ERR_HIP; }
     return check_launch("gdn_chunk_states");
 }
 
-// O_la [BH][L][d] f32 from ops (after launch_gdn_bwd_prep), ck and Ug (after launch_gdn_chunk_states).  fp32 tensors.
-nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, const float* ck, const float* Ug,
-                                 float* O_la, hipStream_t st) {
-    if (pl.dtype != NATS_F32) { set_error("gdn_chunk_out: fp32 tensors only"); return NATS_ERR_UNSUPPORTED; }
-    const ChunkOps o = chunk_ops(pl, ops);
-    const dim3 grid((unsigned)(pl.BH * (pl.L / CB_C)));
+// O_la [BHG][L][d] f32 from ops (after launch_gdn_bwd_prep), ck and Ug (after launch_gdn_chunk_states; O_la may be Ug).
+template <typename T>
+static void launch_out_t(const FwdPlan& pl, const void* Q, const ChunkOps& o, const float* ck, const float* Ug, float* O_la,
+                         hipStream_t st) {
+    const dim3 grid((unsigned)(pl.BHG * (pl.L / CB_C)));
+    const int inner = pl.inner_chunk != 1;
     if (pl.d == 64)
-        hipLaunchKernelGGL(gdn_chunk_out_kernel<64>, grid, dim3(256), 0, st, (const float*)Q, o, ck, Ug, O_la, pl.L, pl.BH,
-                           pl.la_scale);
+        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 64>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Ug, O_la, pl.L, pl.BHG,
+                           pl.G, inner, pl.la_scale);
     else
-        hipLaunchKernelGGL(gdn_chunk_out_kernel<128>, grid, dim3(256), 0, st, (const float*)Q, o, ck, Ug, O_la, pl.L, pl.BH,
-                           pl.la_scale);
+        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 128>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Ug, O_la, pl.L, pl.BHG,
+                           pl.G, inner, pl.la_scale);
+}
+nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Ug,
+                                 float* O_la, hipStream_t st) {
+    const ChunkOps o = chunk_ops(pl, ops, with_at);
+    if (pl.dtype == NATS_BF16) launch_out_t<bf16_t>(pl, Q, o, ck, Ug, O_la, st);
+    else launch_out_t<float>(pl, Q, o, ck, Ug, O_la, st);
     return check_launch("gdn_chunk_out");
 }
 
@@ -1055,12 +1091,12 @@ nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const
     bool ok;
     if (pl.dtype == NATS_BF16) {
         const SeqArgs<bf16_t> a{(const bf16_t*)K, (const bf16_t*)Q, (const bf16_t*)dO, chunk_ops(pl, ops), tok_mask, nullptr, dck,
-                                nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, pl.la_scale, pl.linear_op == 0};
-        ok = launch_seq_d<bf16_t, 1>(pl, a, st);
+                                nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, 1, pl.la_scale, pl.linear_op == 0};
+        ok = launch_seq_d<bf16_t, 1, true>(pl, a, st);
     } else {
         const SeqArgs<float> a{(const float*)K, (const float*)Q, (const float*)dO, chunk_ops(pl, ops), tok_mask, nullptr, dck,
-                               nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, pl.la_scale, pl.linear_op == 0};
-        ok = launch_seq_d<float, 1>(pl, a, st);
+                               nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, 1, pl.la_scale, pl.linear_op == 0};
+        ok = launch_seq_d<float, 1, true>(pl, a, st);
     }
     if (!ok) { set_error("gdn_chunk_state_grads: the kernel's LDS size was refused"); return NATS_ERR_HIP; }
     return check_launch("gdn_chunk_state_grads");

@@ -214,6 +214,9 @@ struct FwdPlan {
     size_t off_cnt, off_idx, off_ns, off_kc, off_vc, off_ola, total;
     // chunkwise (MFMA) linear branch: per-chunk operands
     size_t off_tf, off_p, off_gamv, off_kdv, off_gam, off_seg, off_vht, off_olah, off_snap, off_wout;
+    // fp32 arithmetic, linear branch by chunks: operands and start state of every chunk
+    int fp32_chunks;
+    size_t off_ops, off_ck;
 };
 
 // kernel launchers (one per .hip file); every pointer is a device pointer
@@ -282,11 +285,11 @@ nats_status launch_gdn_recurrent_bwd(const FwdPlan& pl, const void* Q, const voi
 nats_status launch_gdn_checkpoints(const FwdPlan& pl, const void* K, const void* V, const float* alpha, const float* beta,
                                    const uint8_t* mask, const float* S0, float* ckpt, hipStream_t st);
 // chunkwise backward of the linear branch (fp32 matrix instructions), routing per token
-size_t chunk_ops_floats(const FwdPlan& pl);
+size_t chunk_ops_floats(const FwdPlan& pl, bool with_at);
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
-                                const uint8_t* mask, float* ops, hipStream_t st);
+                                const uint8_t* mask, float* ops, bool with_at, hipStream_t st);
 nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init,
-                                    float* ck, float* Ug, float* Uh, hipStream_t st);
+                                    float* S_final, float* ck, float* Ug, float* Uh, hipStream_t st);
 nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO,
                                          const uint8_t* mask, float* ops, float* dck, float* Uh, float* dV,
                                          float* dbeta_part, float* dS0, hipStream_t st);
@@ -306,7 +309,7 @@ nats_status launch_zero_f32(float* dst, size_t n, hipStream_t st);
 nats_status launch_merge_bwd(const FwdPlan& pl, int mode, float eps, const float* O_la, const float* O_nla,
                              const float* dO, const float* w_nla, const float* w_la, float* dO_la, float* dO_nla,
                              float* dw_nla, float* dw_la, hipStream_t st);
-nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, const float* ck, const float* Ug,
+nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Ug,
                                  float* O_la, hipStream_t st);
 nats_status launch_widen_bf16(const void* src, float* dst, size_t n, hipStream_t st);
 nats_status launch_score_gradients_chunk(const FwdPlan& pl, const float* g_nla, const float* ds_la_part, float* dscore_nla,
