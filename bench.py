@@ -38,8 +38,8 @@ def kernel_work(name, cfg, sum_cnt):
         return "hbm", n_tok * (1 + 4) + n_soft * (4 + 4 * d * esz)
     if name == "gdn_recurrent":     # per row-token: decay d, S.k 2d, rank-1 2d, S.q 2d (fp32 VALU)
         return "alu_f32", n_tok * d * (7 * d)
-    if name == "softmax_fp32":      # QK^T and PV: 4 d FLOP per visible (query, key) pair (fp32 VALU)
-        return "alu_f32", 4 * d * sum_cnt
+    if name == "softmax_terms_fwd": # QK^T and PV: 4 d FLOP per visible (query, key) pair
+        return "mfma", 4 * d * sum_cnt
     if name == "gdn_chunk_inv":     # K K^T and Q K^T (2 x 2 C d per token) and the triangular solve (C^2 / 3)
         return "mfma", n_tok * (4 * C * d + C * C / 3.0)
     if name == "gdn_seg_scan":      # K S0^T, Q S0^T, U^T K (3 x 2 d^2) and T (.), P U and the W-type product (3 x 2 C d)

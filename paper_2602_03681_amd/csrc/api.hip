@@ -552,8 +552,8 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
                                       stream);
         }
         if (st != NATS_OK) return st;
-        ProfScope ps("softmax_fp32", stream);
-        st = launch_softmax_fp32(pl, Qs, Kc, Vc, Ks, V, cnt, O_la, ex.w_nla, ex.w_la, O, ex.O_nla, ex.lse, stream);
+        ProfScope ps("softmax_terms_fwd", stream);
+        st = launch_softmax_terms_fwd(pl, Qs, Kc, Vc, Ks, V, cnt, O_la, ex.w_nla, ex.w_la, O, ex.O_nla, ex.lse, stream);
     }
     return st;
 }
@@ -626,8 +626,8 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         st = launch_flash_softmax(pl, Qs, Kc, VhT, Ks, V, cnt, nullptr, nullptr, nullptr, nullptr, O_nla, lse, stream);
         if (st != NATS_OK) return st;
     } else {
-        ProfScope ps("softmax_fp32", stream);
-        st = launch_softmax_fp32(pl, Qs, Kc, Vc, Ks, V, cnt, nullptr, nullptr, nullptr, nullptr, O_nla, lse, stream);
+        ProfScope ps("softmax_terms_fwd", stream);
+        st = launch_softmax_terms_fwd(pl, Qs, Kc, Vc, Ks, V, cnt, nullptr, nullptr, nullptr, nullptr, O_nla, lse, stream);
         if (st != NATS_OK) return st;
     }
     float* ops = reinterpret_cast<float*>(ws + bp.off_ops);
@@ -675,6 +675,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         dO_s = don;
         dO_l = dol;
     }
+    const bool dO_f32 = bp.merge_mode != 0;   // the branches' gradients behind the merge's adjoint are fp32
     const int32_t* vis = cnt;   // compacted rows visible to a query
     if (chunk) {
         ProfScope ps("visible_rows", stream);
@@ -683,9 +684,9 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         if (st != NATS_OK) return st;
         vis = v;
     }
-    {   // dQ = the softmax branch's share over the compacted rows (written); also D_i
+    {   // dQ = the softmax branch's share (written); also D_i
         ProfScope ps("softmax_bwd_dq", stream);
-        st = launch_softmax_bwd_dq(pl, Qs, Kc, Vc, dO_s, vis, O_nla, lse, Dvec, dQs, stream);
+        st = launch_softmax_bwd_dq(pl, Qs, Kc, Vc, Ks, V, dO_s, dO_f32, vis, O_nla, lse, Dvec, dQs, stream);
         if (st != NATS_OK) return st;
     }
     if (own_qk) {   // the linear branch adds onto dQ, the softmax branch's key gradients scatter into dKs
@@ -717,14 +718,14 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         st = launch_bwd_combine(pl, dqp, dkp, dap, dbp, dQ, dK, dalpha, dbeta, ex.g_nla, stream);
         if (st != NATS_OK) return st;
     }
-    if (chunk) {   // every chunk's inner part of the softmax branch: added to dQ, dK, dV
+    if (chunk) {   // every chunk's inner part of the softmax branch: added to dK, dV (dQ has it already)
         ProfScope ps("softmax_bwd_own_chunk", stream);
-        st = launch_softmax_bwd_own_chunk(pl, Qs, Ks, V, dO_s, lse, Dvec, dQs, dKs, dV, stream);
+        st = launch_softmax_bwd_own_chunk(pl, Qs, Ks, V, dO_s, dO_f32, lse, Dvec, dKs, dV, stream);
         if (st != NATS_OK) return st;
     }
     {   // rows of the softmax tokens in dK, dV (routing per token: their linear share is zero; per chunk: added) and g_nla
         ProfScope ps("softmax_bwd_dkv", stream);
-        st = launch_softmax_bwd_dkv(pl, Qs, Kc, Vc, dO_s, vis, idx, n_s, lse, Dvec, dKs, dV, ex.g_nla,
+        st = launch_softmax_bwd_dkv(pl, Qs, Kc, Vc, dO_s, dO_f32, vis, idx, n_s, lse, Dvec, dKs, dV, ex.g_nla,
                                     reinterpret_cast<float*>(ws + bp.off_skp), reinterpret_cast<float*>(ws + bp.off_svp),
                                     reinterpret_cast<float*>(ws + bp.off_sgp), stream);
         if (st != NATS_OK) return st;

@@ -236,11 +236,9 @@ nats_status launch_gdn_seg_scan(const FwdPlan& pl, const void* Q, const void* K,
                                 const void* PF, const float* gamv, const float* kdv, const float* gamC,
                                 const float* S0, float* S_final, float* seg_ws, void* O_la_h, float* O_la_f32,
                                 hipStream_t st);
-nats_status launch_softmax_fp32(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc,
-                                const void* K, const void* V,
-                                const int32_t* cnt, const float* O_la, const float* w_nla,
-                                const float* w_la, void* O, float* O_nla_out, float* lse_out,
-                                hipStream_t st);
+nats_status launch_softmax_terms_fwd(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* K,
+                                     const void* V, const int32_t* cnt, const float* O_la, const float* w_nla,
+                                     const float* w_la, void* O, float* O_nla_out, float* lse_out, hipStream_t st);
 nats_status launch_flash_softmax(const FwdPlan& pl, const void* Q, const void* Kc, const void* VhT,
                                  const void* K, const void* V,
                                  const int32_t* cnt, const void* O_la, const float* w_nla,
@@ -271,13 +269,13 @@ nats_status launch_decode_commit(const nats_dec_params& p, float* state, const f
                                  const uint8_t* mask_c, int32_t* err_flags, hipStream_t st);
 
 // ---- backward pass (fp32 arithmetic) ----
-nats_status launch_softmax_bwd_dq(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* dO,
-                                  const int32_t* cnt, const float* O_nla, const float* lse, float* Dvec, float* dQ,
-                                  hipStream_t st);
-nats_status launch_softmax_bwd_dkv(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* dO,
-                                   const int32_t* cnt, const int32_t* idx, const int32_t* n_s, const float* lse,
-                                   const float* Dvec, float* dK, float* dV, float* g_nla, float* dk_part, float* dv_part, float* g_part,
-                                   hipStream_t st);
+nats_status launch_softmax_bwd_dq(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* K, const void* V,
+                                  const void* dO, bool dO_f32, const int32_t* vis, const float* O_nla, const float* lse,
+                                  float* Dvec, float* dQ, hipStream_t st);
+nats_status launch_softmax_bwd_dkv(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* dO, bool dO_f32,
+                                   const int32_t* vis, const int32_t* idx, const int32_t* n_s, const float* lse,
+                                   const float* Dvec, float* dK, float* dV, float* g_nla, float* dk_part, float* dv_part,
+                                   float* g_part, hipStream_t st);
 nats_status launch_gdn_recurrent_bwd(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* dO,
                                      const float* alpha, const float* beta, const uint8_t* mask, const float* ckpt,
                                      float* scratch, float* dq_part, float* dk_part, float* dalpha_part,
@@ -299,8 +297,7 @@ nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void*
                                    float* dbeta, float* g_nla, float* dscore_la, hipStream_t st);
 nats_status launch_visible_rows(const FwdPlan& pl, const int32_t* cnt, int32_t* vis, hipStream_t st);
 nats_status launch_softmax_bwd_own_chunk(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* dO,
-                                         const float* lse, const float* Dvec, float* dQ, float* dK, float* dV,
-                                         hipStream_t st);
+                                         bool dO_f32, const float* lse, const float* Dvec, float* dK, float* dV, hipStream_t st);
 // head grouping in the backward pass (head_group.hip)
 nats_status launch_copy_rows(const void* src, size_t src_stride_bytes, void* dst, size_t dst_stride_bytes,
                              size_t row_bytes, size_t n_rows, hipStream_t st);
