@@ -302,8 +302,11 @@ typedef struct nats_dec_params {
     size_t workspace_bytes;    /* nats_hybrid_attn_decode: the step then runs as many blocks of equal size (state
                                   rows and cache rows of a (b,h) spread over blocks, partial results merged by a
                                   second kernel) instead of one block per (b,h); same result up to the order of
-                                  the softmax sums.  Worth it when cache lengths differ across the batch.
-                                  Contents undefined afterwards; calls in flight must not share it             */
+                                  the softmax sums.  Worth it when cache lengths differ across the batch, or with
+                                  few (batch, head) pairs.  With room for a partial result per 64 cache rows
+                                  instead of per 256 (B H (ceil(cap / 64) (d + 4) + d) floats) the blocks are a quarter
+                                  of the size.  nats_hybrid_attn_decode_chunk takes it too (and leaves aside one
+                                  that does not serve).  Contents undefined afterwards; calls in flight must not share it */
 } nats_dec_params;
 
 /* Bytes of the optional workspace of nats_hybrid_attn_decode (0 if the params are invalid).  Host-only. */

@@ -16,6 +16,7 @@ import torch
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libnats.so")
 _lib = None
+_host = None   # host path of the per-token calls (csrc/host.cpp)
 
 NATS_F32, NATS_BF16 = 0, 1
 NATS_MATH_AUTO, NATS_MATH_FP32 = 0, 1
@@ -91,7 +92,9 @@ def load_library():
         raise FileNotFoundError(
             f"{_LIB_PATH} is missing: build it with `python -m paper_2602_03681_amd.build` "
             "(there is no fallback path)")
+    global _host
     lib = ctypes.CDLL(_LIB_PATH)
+    from . import _nats_host as _host   # built beside the library
     vp = ctypes.c_void_p
     lib.nats_hybrid_attn_fwd_workspace_bytes.restype = ctypes.c_size_t
     lib.nats_hybrid_attn_fwd_workspace_bytes.argtypes = [ctypes.POINTER(FwdParams)]
@@ -370,8 +373,16 @@ def hybrid_attn_decode(state, k_cache, v_cache, cache_len, q, k, v, alpha, beta,
                        q_nla=None, k_nla=None, w_nla=None, w_la=None, out=None, err_flags=None,
                        workspace=None) -> torch.Tensor:
     """nats_hybrid_attn_decode: one token per (b,h); state, caches and cache_len are updated in place.
-    workspace: uint8 device tensor of decode_workspace_bytes(...) bytes -> the step runs as many equal blocks."""
+    workspace: uint8 device tensor of decode_workspace_bytes(...) bytes -> the step runs as many equal blocks (without one,
+    a step of few (batch, head) pairs allocates its own)."""
     lib = load_library()
+    r = _host.decode(state, k_cache, v_cache, cache_len, q, k, v, alpha, beta, mask, q_nla, k_nla, w_nla, w_la, out, err_flags,
+                     workspace, softmax_scale, la_scale, combine_mode, rms_eps, linear_op, freeze_on_softmax)
+    if r is not None:
+        if type(r) is int:
+            _check(r)
+        return r
+    # an argument that the host path does not take: the checks below say which
     B, H, cap, d = k_cache.shape
     dt = k_cache.dtype
     _require(state, "state", (B, H, d, d), torch.float32)
@@ -471,6 +482,12 @@ def hybrid_attn_decode_chunk(st, q, k, v, alpha, beta, *, softmax_scale: float =
     """nats_hybrid_attn_decode_chunk: one token per (b,h) under routing per chunk; `st` (see _chunk_state) is
     updated in place."""
     lib = load_library()
+    r = _host.decode_chunk(st, q, k, v, alpha, beta, w_nla, w_la, out, err_flags, softmax_scale, la_scale, combine_mode,
+                           rms_eps, linear_op)
+    if r is not None:
+        if type(r) is int:
+            _check(r)
+        return r
     cs, (B, H, cap, d, dt) = _chunk_state(st)
     for name, t in (("q", q), ("k", k), ("v", v)):
         _require(t, name, (B, H, d), dt)

@@ -926,6 +926,20 @@ nats_status nats_hybrid_attn_fwd_noalloc(const nats_fwd_params* p, const void* Q
 
 static nats_status validate_dec_params(const nats_dec_params* p);
 
+// the caller's workspace of a decode step, checked; *ws stays NULL if there is none
+static nats_status decode_workspace(const nats_dec_params& p, float** ws) {
+    if (p.workspace == nullptr) return NATS_OK;
+    const size_t need = decode_split_workspace_bytes(p);
+    if (p.cap > 32768) { set_error("the decode step on a workspace covers caches of at most 32768 rows (cap %d)", p.cap); return NATS_ERR_UNSUPPORTED; }
+    if (p.workspace_bytes < need) {
+        set_error("decode workspace of %zu bytes given, %zu needed", p.workspace_bytes, need);
+        return NATS_ERR_WORKSPACE;
+    }
+    if (!aligned16(p.workspace)) { set_error("the decode workspace is not 16-byte aligned"); return NATS_ERR_ALIGN; }
+    *ws = static_cast<float*>(p.workspace);
+    return NATS_OK;
+}
+
 nats_status nats_hybrid_attn_decode(const nats_dec_params* p, float* state, void* k_cache, void* v_cache,
                                     int32_t* cache_len, const void* q, const void* k, const void* v,
                                     const float* alpha, const float* beta, const uint8_t* mask,
@@ -944,21 +958,16 @@ nats_status nats_hybrid_attn_decode(const nats_dec_params* p, float* state, void
     const float la_scale = p->la_scale > 0.f ? p->la_scale : 1.0f;
     const float eps = p->rms_eps > 0.f ? p->rms_eps : 1e-6f;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    if (p->workspace != nullptr) {
-        const size_t need = decode_split_workspace_bytes(*p);
-        if (p->cap > 32768) { set_error("the decode step on a workspace covers caches of at most 32768 rows (cap %d)", p->cap); return NATS_ERR_UNSUPPORTED; }
-        if (p->workspace_bytes < need) {
-            set_error("decode workspace of %zu bytes given, %zu needed", p->workspace_bytes, need);
-            return NATS_ERR_WORKSPACE;
-        }
-        if (!aligned16(p->workspace)) { set_error("the decode workspace is not 16-byte aligned"); return NATS_ERR_ALIGN; }
-        ProfChain prof_chain;
-        return launch_decode_split(*p, scale, la_scale, eps, state, k_cache, v_cache, cache_len, q, k, v, alpha, beta,
-                                   mask, w_nla, w_la, o, err_flags, static_cast<float*>(p->workspace), stream);
-    }
+    float* ws = nullptr;
+    const nats_status wst = decode_workspace(*p, &ws);
+    if (wst != NATS_OK) return wst;
+    ProfChain prof_chain;
+    if (ws != nullptr)
+        return launch_decode(*p, scale, la_scale, eps, state, k_cache, v_cache, cache_len, q, k, v, alpha, beta,
+                             mask, w_nla, w_la, o, err_flags, ws, stream);
     ProfScope ps("decode", stream);
     return launch_decode(*p, scale, la_scale, eps, state, k_cache, v_cache, cache_len, q, k, v, alpha, beta,
-                         mask, w_nla, w_la, o, err_flags, stream);
+                         mask, w_nla, w_la, o, err_flags, nullptr, stream);
 }
 
 size_t nats_hybrid_attn_decode_workspace_bytes(const nats_dec_params* p) {
@@ -1095,10 +1104,18 @@ nats_status nats_hybrid_attn_decode_chunk(const nats_dec_params* p, const nats_d
     const float la_scale = p->la_scale > 0.f ? p->la_scale : 1.0f;
     const float eps = p->rms_eps > 0.f ? p->rms_eps : 1e-6f;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
+    // (a workspace that does not serve the step is left aside: the one-block form needs none)
+    float* ws = nullptr;
+    if (p->workspace != nullptr && decode_workspace(*p, &ws) != NATS_OK) ws = nullptr;
+    ProfChain prof_chain;
+    if (ws != nullptr)
+        return launch_decode_chunk(*p, scale, la_scale, eps, s->state, s->state_start, s->chunk_decay, s->chunk_pos,
+                                   s->k_cache, s->v_cache, s->cache_len, q, k, v, alpha, beta, w_nla, w_la, o, err_flags,
+                                   ws, stream);
     ProfScope ps("decode_chunk", stream);
     return launch_decode_chunk(*p, scale, la_scale, eps, s->state, s->state_start, s->chunk_decay, s->chunk_pos,
                                s->k_cache, s->v_cache, s->cache_len, q, k, v, alpha, beta, w_nla, w_la, o, err_flags,
-                               stream);
+                               nullptr, stream);
 }
 
 nats_status nats_hybrid_attn_decode_commit(const nats_dec_params* p, const nats_dec_chunk_state* s,

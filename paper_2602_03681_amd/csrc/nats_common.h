@@ -248,18 +248,13 @@ nats_status launch_decode(const nats_dec_params& p, float softmax_scale, float l
                           float* state, void* k_cache, void* v_cache, int32_t* cache_len, const void* q,
                           const void* k, const void* v, const float* alpha, const float* beta,
                           const uint8_t* mask, const float* w_nla, const float* w_la, void* o,
-                          int32_t* err_flags, hipStream_t st);
+                          int32_t* err_flags, float* ws, hipStream_t st);
 size_t decode_split_workspace_bytes(const nats_dec_params& p);
-nats_status launch_decode_split(const nats_dec_params& p, float softmax_scale, float la_scale, float eps,
-                                float* state, void* k_cache, void* v_cache, int32_t* cache_len, const void* q,
-                                const void* k, const void* v, const float* alpha, const float* beta,
-                                const uint8_t* mask, const float* w_nla, const float* w_la, void* o,
-                                int32_t* err_flags, float* ws, hipStream_t st);
 nats_status launch_decode_chunk(const nats_dec_params& p, float softmax_scale, float la_scale, float eps,
                                 float* state, float* state_start, float* chunk_decay, int32_t* chunk_pos,
                                 void* k_cache, void* v_cache, int32_t* cache_len, const void* q, const void* k,
                                 const void* v, const float* alpha, const float* beta, const float* w_nla,
-                                const float* w_la, void* o, int32_t* err_flags, hipStream_t st);
+                                const float* w_la, void* o, int32_t* err_flags, float* ws, hipStream_t st);
 nats_status launch_route_chunks(int B, int L, int C, int d_model, int H, int dtype, const void* X, const float* W_s,
                                 float* scores, uint8_t* mask_c, float* w_nla, float* w_la, int act, hipStream_t st);
 nats_status launch_merge_weights(int B, int H, int L, int d, int dtype, const void* Q, const float* W_out,
