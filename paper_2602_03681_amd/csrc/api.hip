@@ -213,9 +213,9 @@ struct BwdPlan {
         off_gsl, off_gqn, off_gkn, off_gdqn, off_gdkn, total_grouped;
     // the merges of Eq. 21 and its ablation (merge_mode 1, 2; 0: the plain sum): the linear branch's output rows, the
     // two branches' gradients of their rows, the snapshot rows of the token-by-token forward (routing per chunk), a
-    // member's weights and their gradients (head grouping), and fp32 copies of bf16 tensors (the pass then runs on fp32
-    // tensors: pl.dtype is NATS_F32 whatever src_dtype is)
-    int merge_mode, src_dtype;
+    // member's weights and their gradients (head grouping), and, token by token, fp32 copies of bf16 tensors (the pass
+    // then runs on fp32 tensors: pl.dtype is NATS_F32 and widen is set)
+    int merge_mode, widen;
     size_t off_mola, off_mdol, off_mdon, off_msnap, off_mwn, off_mwl, off_mdwn, off_mdwl, off_cq, off_ck, off_cv, off_cdo,
         off_cqn, off_ckn;
 };
@@ -280,7 +280,7 @@ static void plan_bwd_group(const FwdPlan& pl, int G, BwdPlan* bp) {
     bp->total_grouped = off;
 }
 
-// the buffers of the backward through Eq. 21's merge, behind everything else (pl: the fp32 plan of one member)
+// the buffers of the backward through Eq. 21's merge, behind everything else (pl: the plan of one member)
 static void plan_bwd_merge(const FwdPlan& pl, int G, BwdPlan* bp) {
     const size_t n_tok = (size_t)pl.BH * pl.L, nd = n_tok * pl.d;
     size_t off = bp->total_grouped;
@@ -292,7 +292,7 @@ static void plan_bwd_merge(const FwdPlan& pl, int G, BwdPlan* bp) {
     bp->off_mwl = off;   off = align_up(off + n_tok * 4, 256);
     bp->off_mdwn = off;  off = align_up(off + n_tok * 4, 256);
     bp->off_mdwl = off;  off = align_up(off + n_tok * 4, 256);
-    const size_t cv = bp->src_dtype == NATS_BF16 ? 1 : 0;
+    const size_t cv = bp->widen ? 1 : 0;
     bp->off_cq = off;    off = align_up(off + cv * nd * 4, 256);
     bp->off_ck = off;    off = align_up(off + cv * nd * 4, 256);
     bp->off_cv = off;    off = align_up(off + cv * nd * G * 4, 256);
@@ -311,14 +311,18 @@ static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, Bw
     if (G > 8) { set_error("group must be at most 8 (got %d)", p->group); return NATS_ERR_SHAPE; }
     one.group = 1;
     // Eq. 21's merge (and its ablation): each branch's backward runs as for the plain sum, on its own gradient of its
-    // output rows; these gradients are fp32, so the pass runs on fp32 tensors (bf16 ones are widened first)
+    // output rows; these gradients are fp32.  The kernels by chunks take them beside bf16 tensors; the token-by-token
+    // ones have one type for both, so there bf16 tensors are widened first.
     bp->merge_mode = p->combine_mode;
-    bp->src_dtype = p->dtype;
+    bp->widen = 0;
     if (p->combine_mode < 0 || p->combine_mode > 2) { set_error("combine_mode must be 0, 1 or 2 (got %d)", p->combine_mode); return NATS_ERR_SHAPE; }
     if (p->combine_mode != 0) {
         if (p->dtype != NATS_BF16 && p->dtype != NATS_F32) { set_error("dtype must be NATS_BF16 or NATS_F32"); return NATS_ERR_SHAPE; }
         one.combine_mode = 0;
-        one.dtype = NATS_F32;
+        if (p->math == NATS_MATH_FP32 && p->dtype == NATS_BF16) {
+            bp->widen = 1;
+            one.dtype = NATS_F32;
+        }
     }
     nats_status st = validate_fwd_params(&one, pl);
     if (st != NATS_OK) return st;
@@ -614,7 +618,9 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     float* dKs = own_qk ? ex.dK_nla : dK;
     const size_t n_qk = (size_t)pl.BH * pl.L * pl.d;
     ProfChain prof_chain;   // the kernels below follow each other on one stream
-    const bool mfma_stats = pl.dtype == NATS_BF16;   // the softmax branch's forward on the matrix cores
+    // The softmax branch's forward: the plain sum needs its rows for D_i alone and takes the forward's own kernel; behind
+    // a merge that normalises them they are differentiated through, in fp32 accuracy.
+    const bool mfma_stats = pl.dtype == NATS_BF16 && bp.merge_mode == 0;
     void* VhT = mfma_stats ? ws + bp.off_vht : nullptr;
     {   // what the softmax branch's backward needs from its forward: the compacted cache, lse, the branch output
         ProfScope ps("scan_compact", stream);
@@ -669,7 +675,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         ProfScope ps("merge_bwd", stream);
         float* dol = reinterpret_cast<float*>(ws + bp.off_mdol);
         float* don = reinterpret_cast<float*>(ws + bp.off_mdon);
-        st = launch_merge_bwd(pl, bp.merge_mode, pl.rms_eps, O_la, O_nla, static_cast<const float*>(dO), ex.w_nla,
+        st = launch_merge_bwd(pl, bp.merge_mode, pl.rms_eps, O_la, O_nla, dO, ex.w_nla,
                               ex.w_la, dol, don, ex.dw_nla, ex.dw_la, stream);
         if (st != NATS_OK) return st;
         dO_s = don;
@@ -698,12 +704,12 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     if (by_chunks) {
         {   // backwards along the sequence: the state gradient behind every chunk, dV, the partials of dbeta
             ProfScope ps("gdn_chunk_state_grads", stream);
-            st = launch_gdn_chunk_state_grads(pl, Q, K, dO_l, mask, ops, dck, Uh, dV, dbp, ex.d_initial_state, stream);
+            st = launch_gdn_chunk_state_grads(pl, Q, K, dO_l, dO_f32, mask, ops, dck, Uh, dV, dbp, ex.d_initial_state, stream);
             if (st != NATS_OK) return st;
         }
         // dQ += linear share; dK, dalpha, dbeta = linear share; g_nla cleared
         ProfScope ps("gdn_chunk_grads", stream);
-        st = launch_gdn_chunk_grads(pl, Q, K, dO_l, alpha, mask, ops, ckpt, dck, Ug, dV, dbp, dQ, dK, dalpha, dbeta, ex.g_nla,
+        st = launch_gdn_chunk_grads(pl, Q, K, dO_l, dO_f32, alpha, mask, ops, ckpt, dck, Ug, dV, dbp, dQ, dK, dalpha, dbeta, ex.g_nla,
                                     chunk ? ex.dscore_la : nullptr, stream);
         if (st != NATS_OK) return st;
     } else {
@@ -782,7 +788,7 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
 
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     char* ws = static_cast<char*>(workspace);
-    if (bp.merge_mode != 0 && bp.src_dtype == NATS_BF16) {   // the pass runs on fp32 copies (pl.dtype is NATS_F32)
+    if (bp.widen) {   // the pass runs on fp32 copies (pl.dtype is NATS_F32)
         ProfScope ps("widen_bf16", stream);
         const size_t nd = (size_t)pl.BH * pl.L * pl.d;
         struct { const void** src; size_t off, n; } conv[] = {

@@ -231,9 +231,10 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
 // DIR 1: backwards, the gradient of that state; leaves dS1 of every chunk (ck), dV, the block's share of dbeta and the
 // gradient of the initial state.  Wavefront w owns the chunk's tokens 16 w .. 16 w + 15 in everything that is one
 // row per token, and D / 64 of the state's 16 x 16 tiles.
-template <typename T>
+template <typename T, typename TX>
 struct SeqArgs {
-    const T *K, *Q, *X;            // X: V (DIR 0) or dO (DIR 1), [BH][L][D]
+    const T *K, *Q;
+    const TX* X;                   // V (DIR 0) or dO (DIR 1; fp32 beside bf16 tensors behind a merge's adjoint), [BH][L][D]
     ChunkOps o;
     const uint8_t* mask;
     const float* S_init;           // DIR 0: [BH][D][D] or NULL
@@ -288,8 +289,8 @@ __device__ __forceinline__ float4 ldkcol(const float* p, int rs) { return ld4col
 __device__ __forceinline__ float4 ldkcol(const uint16_t* p, int rs) { return ldbcol(p, rs); }
 
 // RES: also the residuals Uh (and so At); the forward alone does without.
-template <typename T, int D, int DIR, bool RES>
-__global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) {
+template <typename T, typename TX, int D, int DIR, bool RES>
+__global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX> a) {
     using LY = SeqLds<T, D, DIR>;
     using KE = typename std::conditional<LY::wide, float, uint16_t>::type;   // K, Q in LDS
     constexpr int KS = LY::KS, SS = D + 4, NP = CB_C * D * (int)sizeof(T) / 16 / 256, KT = D / 64, MS = CB_MS, NB = LY::NB;
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T> a) 
     if (loader) {
         u32x4 kreg[NP], qreg[DIR ? NP : 1];
         float4 m1reg[4], m2reg[4], gate4 = make_float4(0.f, 0.f, 0.f, 0.f), g4n = gate4;
-        T xvn[4];
+        TX xvn[4];
         float uhn[4] = {0.f, 0.f, 0.f, 0.f}, gCn = 0.f;
         uint32_t linn = 0;
         auto fetch = [&](int c) {   // as it comes from memory: a conversion here would wait for the load
@@ -565,9 +566,10 @@ constexpr size_t prep_lds_bytes() { return sizeof(float) * (2 * (size_t)CB_C * (
 // regions are filled in turn:   A: S0, then U with dS1 (64 rows at a time), then K with Q;   B: dO', then dP . Gamma;
 // C: dR, then the symmetric (dAt . Gamma) + (dAt . Gamma)^T.  Sums over rows, columns or wavefronts go through small
 // per-tile or per-wavefront arrays that one wavefront adds up in a fixed order (no atomics).
-template <typename T>
+template <typename T, typename TO>
 struct GradArgs {
-    const T *Q, *K, *dO;
+    const T *Q, *K;
+    const TO* dO;
     ChunkOps o;
     const float *alpha;
     const uint8_t* mask;
@@ -579,8 +581,8 @@ struct GradArgs {
     int delta, freeze_on_softmax, chunk_mask;
 };
 
-template <typename T, int D>
-__global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T> a) {
+template <typename T, typename TO, int D>
+__global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T, TO> a) {
     constexpr int NW = D / 16, NT = 64 * NW, KS = D + 4, MS = CB_MS, E = Vec16<T>::N;
     constexpr int HALF = CB_C * KS;            // floats of a [64][KS] tile
     constexpr int NS0 = D * D / 4 / NT;        // 16-byte pieces of a state per thread
@@ -610,6 +612,7 @@ __global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T
     // while the CU's miss queue is full; between matrix instructions the SIMD's other wavefront fills that time),
     // and wait in registers (one block per CU: nothing else would hide their latency).
     constexpr int NPT = 64 * D / E / NT;       // 16-byte words of a [64][D] tile of T per thread
+    constexpr int NPO = 64 * D / Vec16<TO>::N / NT;   // ... of TO
     auto put_rows_f32 = [&](float* dst, const float4 (&r)[NSH]) {   // [64][D] fp32 -> LDS rows of KS
 #pragma unroll
         for (int i = 0; i < NSH; ++i) {
@@ -617,19 +620,20 @@ __global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T
             *reinterpret_cast<float4*>(dst + row * KS + c4) = r[i];
         }
     };
-    auto put_rows_T = [&](float* dst, const u32x4 (&r)[NPT], float scale) {
+    auto put_rows_as = [&](float* dst, const auto& r, float scale, auto type) {   // 16-byte words of [64][D] of a type
+        constexpr int EW = Vec16<decltype(type)>::N;
 #pragma unroll
-        for (int i = 0; i < NPT; ++i) {
-            const int e = tid + NT * i, row = e / (D / E), c = (e % (D / E)) * E;
-            float tmp[E];
-            unpack16(r[i], tmp, T{});
+        for (int i = 0; i < 64 * D / EW / NT; ++i) {
+            const int e = tid + NT * i, row = e / (D / EW), c = (e % (D / EW)) * EW;
+            float tmp[EW];
+            unpack16(r[i], tmp, type);
 #pragma unroll
-            for (int j = 0; j < E; j += 4)
+            for (int j = 0; j < EW; j += 4)
                 *reinterpret_cast<float4*>(dst + row * KS + c + j) = make_float4(scale * tmp[j], scale * tmp[j + 1], scale * tmp[j + 2], scale * tmp[j + 3]);
         }
     };
     float4 s0reg[NS0], dRreg[NSH], Ureg[NSH], dS1a[NSH], dS1b[NSH];
-    u32x4 dOreg[NPT], Kreg[NPT], Qreg[NPT];
+    u32x4 dOreg[NPO], Kreg[NPT], Qreg[NPT];
     const float* dS1g = a.dck + gc * ((size_t)D * D);
     constexpr int NTL = (10 + NW - 1) / NW;   // lower 16 x 16 tiles of a 64 x 64 operand per wavefront
     float atv[NTL][4], pmv[NTL][4];           // At and P where this lane will hold dAt and dP
@@ -640,7 +644,7 @@ __global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T
 #pragma unroll
         for (int i = 0; i < NS0; ++i) s0reg[i] = ld4(S0g + 4 * (size_t)(tid + NT * i));   // rows of D floats: contiguous
 #pragma unroll
-        for (int i = 0; i < NPT; ++i) dOreg[i] = reinterpret_cast<const u32x4*>(a.dO + tok0 * D)[tid + NT * i];
+        for (int i = 0; i < NPO; ++i) dOreg[i] = reinterpret_cast<const u32x4*>(a.dO + tok0 * D)[tid + NT * i];
 #pragma unroll
         for (int i = 0; i < NSH; ++i) dRreg[i] = ld4(a.dR + tok0 * D + 4 * (size_t)(tid + NT * i));
     }
@@ -680,7 +684,7 @@ __global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T
         const int e = tid + NT * i, row = e / (D / 4), c4 = (e % (D / 4)) * 4;
         *reinterpret_cast<float4*>(RA + row * KS + c4) = s0reg[i];
     }
-    put_rows_T(RB, dOreg, a.la_scale);
+    put_rows_as(RB, dOreg, a.la_scale, TO{});
     put_rows_f32(RC, dRreg);
     if (tid < 3 * CB_C) s_g2[tid] = gate_in;   // s_g2, s_gam, s_kd lie one behind the other
     for (int e = tid; e < 8 * CB_C; e += NT) rs[e] = 0.f;   // rs and cs
@@ -790,8 +794,8 @@ __global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T
     }
     __syncthreads();
     // ---- stage 4: K and Q ----------------------------------------------------------------------------------------
-    put_rows_T(RA, Kreg, 1.f);
-    put_rows_T(RAhi, Qreg, 1.f);
+    put_rows_as(RA, Kreg, 1.f, T{});
+    put_rows_as(RAhi, Qreg, 1.f, T{});
     {   // <dS1, S0>: the wavefront's sum
         float x = lane_group_sum<64>(dot);
         if (lane == 0) s_dot[w] = x;
@@ -1030,18 +1034,18 @@ nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K,
     return check_launch("gdn_bwd_prep");
 }
 
-template <typename T, int D, int DIR, bool RES>
-static bool launch_seq_t(const SeqArgs<T>& a, hipStream_t st) {
-    auto kern = gdn_chunk_seq_kernel<T, D, DIR, RES>;
+template <typename T, typename TX, int D, int DIR, bool RES>
+static bool launch_seq_t(const SeqArgs<T, TX>& a, hipStream_t st) {
+    auto kern = gdn_chunk_seq_kernel<T, TX, D, DIR, RES>;
     constexpr size_t lds = seq_lds_bytes<T, D, DIR>();
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * (D / CB_NV))), dim3(512), lds, st, a);
     return true;
 }
-template <typename T, int DIR, bool RES>
-static bool launch_seq_d(const FwdPlan& pl, const SeqArgs<T>& a, hipStream_t st) {
-    return pl.d == 64 ? launch_seq_t<T, 64, DIR, RES>(a, st) : launch_seq_t<T, 128, DIR, RES>(a, st);
+template <int DIR, bool RES, typename T, typename TX>
+static bool launch_seq_d(const FwdPlan& pl, const SeqArgs<T, TX>& a, hipStream_t st) {
+    return pl.d == 64 ? launch_seq_t<T, TX, 64, DIR, RES>(a, st) : launch_seq_t<T, TX, 128, DIR, RES>(a, st);
 }
 
 // The states at the chunk starts, ck [BHG][L/64][d][d], with U (and, unless NULL, the residuals Uh) [BHG][L][d] of every
@@ -1050,9 +1054,9 @@ static bool launch_seq_d(const FwdPlan& pl, const SeqArgs<T>& a, hipStream_t st)
 template <typename T>
 static bool launch_states_t(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init, float* S_final,
                             float* ck, float* Ug, float* Uh, hipStream_t st) {
-    const SeqArgs<T> a{(const T*)K, nullptr, (const T*)V, chunk_ops(pl, ops, Uh != nullptr), nullptr, S_init, ck, Ug, Uh,
+    const SeqArgs<T, T> a{(const T*)K, nullptr, (const T*)V, chunk_ops(pl, ops, Uh != nullptr), nullptr, S_init, ck, Ug, Uh,
                        nullptr, nullptr, S_final, pl.L, pl.BHG, pl.G, pl.la_scale, pl.linear_op == 0};
-    return Uh != nullptr ? launch_seq_d<T, 0, true>(pl, a, st) : launch_seq_d<T, 0, false>(pl, a, st);
+    return Uh != nullptr ? launch_seq_d<0, true>(pl, a, st) : launch_seq_d<0, false>(pl, a, st);
 }
 nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init,
                                     float* S_final, float* ck, float* Ug, float* Uh, hipStream_t st) {
@@ -1084,27 +1088,30 @@ nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, b
 }
 
 // The state gradients behind every chunk, dck [BH][L/64][d][d]; dV (every row), dbeta_part [d/16][BH][L], dS0 (or NULL).
-nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO,
+// dO_f32: dO is fp32 whatever the tensors' type.
+template <typename T, typename TO>
+static bool launch_state_grads_t(const FwdPlan& pl, const void* Q, const void* K, const void* dO, const uint8_t* tok_mask,
+                                 float* ops, float* dck, float* Uh, float* dV, float* dbeta_part, float* dS0, hipStream_t st) {
+    const SeqArgs<T, TO> a{(const T*)K, (const T*)Q, (const TO*)dO, chunk_ops(pl, ops), tok_mask, nullptr, dck,
+                           nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, 1, pl.la_scale, pl.linear_op == 0};
+    return launch_seq_d<1, true>(pl, a, st);
+}
+nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
                                          const uint8_t* mask, float* ops, float* dck, float* Uh, float* dV,
                                          float* dbeta_part, float* dS0, hipStream_t st) {
     const uint8_t* tok_mask = pl.routing == NATS_ROUTE_CHUNK ? nullptr : mask;
     bool ok;
-    if (pl.dtype == NATS_BF16) {
-        const SeqArgs<bf16_t> a{(const bf16_t*)K, (const bf16_t*)Q, (const bf16_t*)dO, chunk_ops(pl, ops), tok_mask, nullptr, dck,
-                                nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, 1, pl.la_scale, pl.linear_op == 0};
-        ok = launch_seq_d<bf16_t, 1, true>(pl, a, st);
-    } else {
-        const SeqArgs<float> a{(const float*)K, (const float*)Q, (const float*)dO, chunk_ops(pl, ops), tok_mask, nullptr, dck,
-                               nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, 1, pl.la_scale, pl.linear_op == 0};
-        ok = launch_seq_d<float, 1, true>(pl, a, st);
-    }
+#define NATS_SG(TT, TO) launch_state_grads_t<TT, TO>(pl, Q, K, dO, tok_mask, ops, dck, Uh, dV, dbeta_part, dS0, st)
+    if (pl.dtype == NATS_F32) ok = NATS_SG(float, float);
+    else ok = dO_f32 ? NATS_SG(bf16_t, float) : NATS_SG(bf16_t, bf16_t);
+#undef NATS_SG
     if (!ok) { set_error("gdn_chunk_state_grads: the kernel's LDS size was refused"); return NATS_ERR_HIP; }
     return check_launch("gdn_chunk_state_grads");
 }
 
-template <typename T, int D>
-static bool launch_grads_t(const FwdPlan& pl, const GradArgs<T>& a, hipStream_t st) {
-    auto kern = gdn_chunk_grads_kernel<T, D>;
+template <typename T, typename TO, int D>
+static bool launch_grads_t(const FwdPlan& pl, const GradArgs<T, TO>& a, hipStream_t st) {
+    auto kern = gdn_chunk_grads_kernel<T, TO, D>;
     constexpr size_t lds = grads_lds_bytes<D>();
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
@@ -1113,23 +1120,21 @@ static bool launch_grads_t(const FwdPlan& pl, const GradArgs<T>& a, hipStream_t 
 }
 
 // dQ += the linear branch's share; dK, dalpha, dbeta = it; g_nla (optional) cleared.  ck, dck: the states and state
-// gradients per chunk; Ug, dR (= the linear branch's dV) [BH][L][d]; dbeta_part [d/16][BH][L].
-nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, const float* alpha,
-                                   const uint8_t* mask, float* ops, const float* ck, const float* dck, const float* Ug,
-                                   const float* dR, const float* dbeta_part, float* dQ, float* dK, float* dalpha,
-                                   float* dbeta, float* g_nla, float* dscore_la, hipStream_t st) {
-    bool ok;
-    if (pl.dtype == NATS_BF16) {
-        const GradArgs<bf16_t> a{(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)dO, chunk_ops(pl, ops), alpha, mask, ck, dck,
-                                 Ug, dR, dbeta_part, dQ, dK, dalpha, dbeta, g_nla, dscore_la, pl.L, pl.BH, pl.la_scale,
-                                 pl.linear_op == 0, pl.freeze_on_softmax, pl.routing == NATS_ROUTE_CHUNK};
-        ok = pl.d == 64 ? launch_grads_t<bf16_t, 64>(pl, a, st) : launch_grads_t<bf16_t, 128>(pl, a, st);
-    } else {
-        const GradArgs<float> a{(const float*)Q, (const float*)K, (const float*)dO, chunk_ops(pl, ops), alpha, mask, ck, dck,
+// gradients per chunk; Ug, dR (= the linear branch's dV) [BH][L][d]; dbeta_part [d/16][BH][L].  dO_f32: dO is fp32
+// whatever the tensors' type.
+nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
+                                   const float* alpha, const uint8_t* mask, float* ops, const float* ck, const float* dck,
+                                   const float* Ug, const float* dR, const float* dbeta_part, float* dQ, float* dK,
+                                   float* dalpha, float* dbeta, float* g_nla, float* dscore_la, hipStream_t st) {
+    auto go = [&](auto t, auto to) {
+        using T = decltype(t);
+        using TO = decltype(to);
+        const GradArgs<T, TO> a{(const T*)Q, (const T*)K, (const TO*)dO, chunk_ops(pl, ops), alpha, mask, ck, dck,
                                 Ug, dR, dbeta_part, dQ, dK, dalpha, dbeta, g_nla, dscore_la, pl.L, pl.BH, pl.la_scale,
                                 pl.linear_op == 0, pl.freeze_on_softmax, pl.routing == NATS_ROUTE_CHUNK};
-        ok = pl.d == 64 ? launch_grads_t<float, 64>(pl, a, st) : launch_grads_t<float, 128>(pl, a, st);
-    }
+        return pl.d == 64 ? launch_grads_t<T, TO, 64>(pl, a, st) : launch_grads_t<T, TO, 128>(pl, a, st);
+    };
+    const bool ok = pl.dtype == NATS_F32 ? go(float{}, float{}) : dO_f32 ? go(bf16_t{}, float{}) : go(bf16_t{}, bf16_t{});
     if (!ok) { set_error("gdn_chunk_grads: the kernel's LDS size was refused"); return NATS_ERR_HIP; }
     return check_launch("gdn_chunk_grads");
 }

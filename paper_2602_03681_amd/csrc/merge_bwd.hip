@@ -5,17 +5,28 @@
 // The merge acts row by row, so the kernel turns dO into one gradient per branch (each branch's backward then runs on
 // its own, as for the plain sum) and gives the gradients of the two weights.  fp32 throughout; a row is held by d / 4
 // adjacent lanes, four columns each.  Streams three rows in and two out: HBM-bound.
-// Also here: the widening copy bf16 -> fp32 that the backward pass with these merges runs on its inputs (the
-// branches then receive fp32 gradients of their outputs, which the kernels for bf16 tensors do not take).
+// Also here: the widening copy bf16 -> fp32 for the token-by-token pass with these merges, whose kernels take one
+// type for the tensors and the (then fp32) gradients of the branches' rows.
 #include "nats_common.h"
 
 namespace nats {
 
 constexpr int MB_THREADS = 256;
 
-template <int D>
+template <typename TO>
+__device__ __forceinline__ float4 load4(const TO* p) {
+    if constexpr (sizeof(TO) == 4) {
+        return *reinterpret_cast<const float4*>(p);
+    } else {
+        const uint2 u = *reinterpret_cast<const uint2*>(p);
+        return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                           __uint_as_float(u.y & 0xffff0000u));
+    }
+}
+
+template <typename TO, int D>
 __global__ __launch_bounds__(MB_THREADS) void merge_bwd_kernel(
-    const float* __restrict__ O_la, const float* __restrict__ O_nla, const float* __restrict__ dO,
+    const float* __restrict__ O_la, const float* __restrict__ O_nla, const TO* __restrict__ dO,
     const float* __restrict__ w_nla, const float* __restrict__ w_la, float* __restrict__ dO_la,
     float* __restrict__ dO_nla, float* __restrict__ dw_nla, float* __restrict__ dw_la, size_t n_rows, int mode,
     float eps) {
@@ -34,7 +45,7 @@ __global__ __launch_bounds__(MB_THREADS) void merge_bwd_kernel(
         const size_t off = row * D + 4 * sub;
         const float4 xl4 = *reinterpret_cast<const float4*>(O_la + off);
         const float4 xn4 = *reinterpret_cast<const float4*>(O_nla + off);
-        const float4 g4 = *reinterpret_cast<const float4*>(dO + off);
+        const float4 g4 = load4(dO + off);
         const float wn = w_nla ? w_nla[row] : w_default, wl = w_la ? w_la[row] : w_default;
         const float xl[4] = {xl4.x, xl4.y, xl4.z, xl4.w}, xn[4] = {xn4.x, xn4.y, xn4.z, xn4.w};
         const float g[4] = {g4.x, g4.y, g4.z, g4.w};
@@ -112,18 +123,21 @@ static int mb_grid(size_t units) {
     return (int)(blocks < 1 ? 1 : (blocks > 4096 ? 4096 : blocks));
 }
 
-// rows: B x H x L rows of pl.d columns (pl.d is 64 or 128).  dw_nla, dw_la may be NULL (not wanted).
+// rows: B x H x L rows of pl.d columns (pl.d is 64 or 128), dO of the tensors' type.  dw_nla, dw_la may be NULL (not wanted).
 nats_status launch_merge_bwd(const FwdPlan& pl, int mode, float eps, const float* O_la, const float* O_nla,
-                             const float* dO, const float* w_nla, const float* w_la, float* dO_la, float* dO_nla,
+                             const void* dO, const float* w_nla, const float* w_la, float* dO_la, float* dO_nla,
                              float* dw_nla, float* dw_la, hipStream_t st) {
     const size_t n_rows = (size_t)pl.BH * pl.L;
     if (n_rows == 0) return NATS_OK;
-    if (pl.d == 64)
-        hipLaunchKernelGGL(merge_bwd_kernel<64>, dim3(mb_grid(n_rows * 16)), dim3(MB_THREADS), 0, st, O_la, O_nla, dO,
-                           w_nla, w_la, dO_la, dO_nla, dw_nla, dw_la, n_rows, mode, eps);
-    else
-        hipLaunchKernelGGL(merge_bwd_kernel<128>, dim3(mb_grid(n_rows * 32)), dim3(MB_THREADS), 0, st, O_la, O_nla, dO,
-                           w_nla, w_la, dO_la, dO_nla, dw_nla, dw_la, n_rows, mode, eps);
+#define NATS_MB(TO, DD)                                                                                                 \
+    hipLaunchKernelGGL((merge_bwd_kernel<TO, DD>), dim3(mb_grid(n_rows * (DD / 4))), dim3(MB_THREADS), 0, st, O_la, O_nla, \
+                       (const TO*)dO, w_nla, w_la, dO_la, dO_nla, dw_nla, dw_la, n_rows, mode, eps)
+    if (pl.dtype == NATS_BF16) {
+        if (pl.d == 64) NATS_MB(bf16_t, 64); else NATS_MB(bf16_t, 128);
+    } else {
+        if (pl.d == 64) NATS_MB(float, 64); else NATS_MB(float, 128);
+    }
+#undef NATS_MB
     return check_launch("merge_bwd");
 }
 
