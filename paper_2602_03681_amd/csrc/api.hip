@@ -205,7 +205,7 @@ static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl, bo
 // the reverse sweep and the partial sums of its blocks.
 struct BwdPlan {
     size_t off_onla, off_lse, off_dvec, off_ckpt, off_scratch, off_dqp, off_dkp, off_dap, off_dbp, off_skp, off_svp, off_sgp,
-        off_gnla, off_vis, off_dslap, off_ops, off_ug, off_uh, off_dck, off_vht, total;
+        off_gnla, off_vis, off_dslap, off_ops, off_uh, off_dck, off_dot, off_vht, total;
     // head grouping: the pass runs once per member of the groups on `total` bytes; behind them, one member's heads
     // of V, dO, the initial state (gathered) and the member's gradients before they are added or scattered
     int G;
@@ -227,13 +227,13 @@ static void plan_bwd(const FwdPlan& pl, BwdPlan* bp) {
     bp->off_dvec = off;    off = align_up(off + n_tok * 4, 256);
     bp->off_ckpt = off;    off = align_up(off + (size_t)pl.BH * (pl.L / 64) * pl.d * pl.d * 4, 256);
     // the token-by-token adjoint of the linear branch (math = NATS_MATH_FP32): the parked rows of a chunk and the
-    // d/16 partial sums per (batch, head); by chunks only the partials of dbeta are used
+    // d/16 partial sums per (batch, head)
     const size_t tk = pl.math == NATS_MATH_FP32 ? 1 : 0;
     bp->off_scratch = off; off = align_up(off + tk * pl.BH * pl.d * 64 * pl.d * 4, 256);   // 64 tokens of every row
     bp->off_dqp = off;     off = align_up(off + tk * ns * n_tok * pl.d * 4, 256);
     bp->off_dkp = off;     off = align_up(off + tk * ns * n_tok * pl.d * 4, 256);
     bp->off_dap = off;     off = align_up(off + tk * ns * n_tok * 4, 256);
-    bp->off_dbp = off;     off = align_up(off + ns * n_tok * 4, 256);
+    bp->off_dbp = off;     off = align_up(off + tk * ns * n_tok * 4, 256);
     // partial dK, dV and column sums of the softmax branch, one per query segment and compacted key
     bp->off_skp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_tok * pl.d * 4, 256);
     bp->off_svp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_tok * pl.d * 4, 256);
@@ -241,12 +241,12 @@ static void plan_bwd(const FwdPlan& pl, BwdPlan* bp) {
     bp->off_gnla = off;    off = align_up(off + n_tok * 4, 256);   // column sums of Eq. 15 when only their chunk sums are asked for
     bp->off_vis = off;     off = align_up(off + n_tok * 4, 256);   // routing per chunk: compacted rows visible to a query
     bp->off_dslap = off;   off = align_up(off + ns * (n_tok / 64) * 4, 256);   // ... and the sweep's partials of Eq. 17
-    // chunkwise backward of the linear branch: operands of every chunk, U and the residuals, state gradients per chunk
+    // chunkwise backward of the linear branch: operands of every chunk, the residuals, state gradients per chunk
     const size_t ch = (pl.routing == NATS_ROUTE_CHUNK && tk) ? 0 : 1;   // (token by token with routing per chunk: own checkpoint kernel)
     bp->off_ops = off;     off = align_up(off + ch * chunk_ops_floats(pl, true) * 4, 256);
-    bp->off_ug = off;      off = align_up(off + ch * n_tok * pl.d * 4, 256);
     bp->off_uh = off;      off = align_up(off + ch * n_tok * pl.d * 4, 256);
     bp->off_dck = off;     off = align_up(off + ch * (1 - tk) * pl.BH * (pl.L / 64) * pl.d * pl.d * 4, 256);
+    bp->off_dot = off;     off = align_up(off + ch * (1 - tk) * pl.BH * (pl.L / 64) * (pl.d / 4) * 4, 256);
     bp->off_vht = off;     off = align_up(off + n_tok * pl.d * 2, 256);   // fp16 V^T tiles of the compacted values (bf16 tensors)
     bp->total = off;
     bp->G = 1;
@@ -542,9 +542,9 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
                 st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, false, stream);
                 if (st != NATS_OK) return st;
             }
-            {   // U goes where the branch's rows will be
+            {   // the residuals go where the branch's rows will be
                 ProfScope ps("gdn_chunk_states", stream);
-                st = launch_gdn_chunk_states(pl, K, V, ops, ex.initial_state, ex.final_state, ck, O_la, nullptr, stream);
+                st = launch_gdn_chunk_states(pl, K, V, ops, false, ex.initial_state, ex.final_state, ck, O_la, stream);
                 if (st != NATS_OK) return st;
             }
             ProfScope ps("gdn_chunk_out", stream);
@@ -637,9 +637,9 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         if (st != NATS_OK) return st;
     }
     float* ops = reinterpret_cast<float*>(ws + bp.off_ops);
-    float* Ug = reinterpret_cast<float*>(ws + bp.off_ug);
     float* Uh = reinterpret_cast<float*>(ws + bp.off_uh);
     float* dck = reinterpret_cast<float*>(ws + bp.off_dck);
+    float* dot = reinterpret_cast<float*>(ws + bp.off_dot);
     const bool by_chunks = pl.math != NATS_MATH_FP32;   // the linear branch's backward by chunks of 64 tokens
     if (by_chunks || !chunk) {   // the linear branch forwards once more by chunks, leaving the state at the start of every chunk
         {
@@ -648,7 +648,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
             if (st != NATS_OK) return st;
         }
         ProfScope ps("gdn_chunk_states", stream);
-        st = launch_gdn_chunk_states(pl, K, V, ops, ex.initial_state, nullptr, ckpt, Ug, Uh, stream);
+        st = launch_gdn_chunk_states(pl, K, V, ops, true, ex.initial_state, nullptr, ckpt, Uh, stream);
         if (st != NATS_OK) return st;
     } else {   // ... token by token
         ProfScope ps("gdn_checkpoints", stream);
@@ -656,7 +656,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         if (st != NATS_OK) return st;
     }
     // The merges of Eq. 21 and its ablation: the linear branch's rows once more in fp32 (from the chunk-start states and
-    // U just made, or token by token where the states were made token by token), then the merge's adjoint turns dO into
+    // residuals just made, or token by token where the states were made token by token), then the merge's adjoint turns dO into
     // one gradient per branch; from here on each branch runs as for the plain sum.
     const void* dO_s = dO;   // gradient of the softmax branch's rows
     const void* dO_l = dO;   // ... of the linear branch's
@@ -664,7 +664,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         float* O_la = reinterpret_cast<float*>(ws + bp.off_mola);
         if (by_chunks || !chunk) {
             ProfScope ps("gdn_chunk_out", stream);
-            st = launch_gdn_chunk_out(pl, Q, ops, true, ckpt, Ug, O_la, stream);
+            st = launch_gdn_chunk_out(pl, Q, ops, true, ckpt, Uh, O_la, stream);
             if (st != NATS_OK) return st;
         } else {
             ProfScope ps("gdn_recurrent", stream);
@@ -702,14 +702,14 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         if (st != NATS_OK) return st;
     }
     if (by_chunks) {
-        {   // backwards along the sequence: the state gradient behind every chunk, dV, the partials of dbeta
+        {   // backwards along the sequence: the state gradient behind every chunk, dV
             ProfScope ps("gdn_chunk_state_grads", stream);
-            st = launch_gdn_chunk_state_grads(pl, Q, K, dO_l, dO_f32, mask, ops, dck, Uh, dV, dbp, ex.d_initial_state, stream);
+            st = launch_gdn_chunk_state_grads(pl, Q, K, dO_l, dO_f32, ops, ckpt, dck, dot, dV, ex.d_initial_state, stream);
             if (st != NATS_OK) return st;
         }
         // dQ += linear share; dK, dalpha, dbeta = linear share; g_nla cleared
         ProfScope ps("gdn_chunk_grads", stream);
-        st = launch_gdn_chunk_grads(pl, Q, K, dO_l, dO_f32, alpha, mask, ops, ckpt, dck, Ug, dV, dbp, dQ, dK, dalpha, dbeta, ex.g_nla,
+        st = launch_gdn_chunk_grads(pl, Q, K, dO_l, dO_f32, alpha, mask, ops, ckpt, dck, Uh, dV, dot, dQ, dK, dalpha, dbeta, ex.g_nla,
                                     chunk ? ex.dscore_la : nullptr, stream);
         if (st != NATS_OK) return st;
     } else {

@@ -1,13 +1,14 @@
-// Backward of the linear branch by chunks of 64 tokens, on fp32 matrix instructions (Section 4.2; the recurrence is
+// Backward of the linear branch by chunks of 64 tokens, to fp32 accuracy on matrix instructions (Section 4.2; the recurrence is
 // Eq. 19 with the decay of Eq. 20, written for linear tokens only, Eq. 14).
 //
 // One chunk, with the state S0 [d_v][d_k] at its start, b' = beta (0 for a softmax token), gamma_r the product of the
 // chunk's alphas up to token r, Gamma_ri = gamma_r / gamma_i, kd_i = gamma_C / gamma_i:
-//     At = strict lower (Gamma . K K^T),  P = lower (Gamma . Q K^T),  T = (I + diag(b') At)^-1
-//     R = V - diag(gamma) K S0^T,   U = T diag(b') R,   Uh = R - At U  (= v_t - Sd k_t, the residual of Eq. 19),
+//     At = strict lower (Gamma . K K^T),  P = lower (Gamma . Q K^T),  T = (I + At diag(b'))^-1
+//     R = V - diag(gamma) K S0^T,   Uh = T R  (= v_t - Sd k_t, the residual of Eq. 19: Uh = R - At U),   U = diag(b') Uh,
 //     O = la (diag(gamma) Q S0^T + P U),   S1 = gamma_C S0 + U^T diag(kd) K.
 // Given dO' = la dO and dS1 (from the chunks behind):
-//     dU = P^T dO' + diag(kd) K dS1^T,   dRt = T^T dU,   dR = diag(b') dRt = dV,   dbeta_r = Uh_r . dRt_r
+//     dU = P^T dO' + diag(kd) K dS1^T,   dR = T^T diag(b') dU = dV,
+//     dbeta_r = Uh_r . (dU - At^T dR)_r = sum_i (P_ir (dO' Uh^T)_ir - At_ir (dR Uh^T)_ir) + kd_r K_r . (Uh dS1)_r
 //     dS0 = gamma_C dS1 + dO'^T diag(gamma) Q - dR^T diag(gamma) K
 //     dP = lower (dO' U^T),   dAt = - strict lower (dR U^T)
 //     dQ = diag(gamma) dO' S0 + (dP . Gamma) K
@@ -22,13 +23,12 @@
 // (parallel over chunks).  Columns of V (rows of the state) never mix along the sequence, so the two sequential
 // kernels split every (batch, head) into slices of 16 value columns, one block each.
 //
-// Matrix instruction used throughout: v_mfma_f32_16x16x4_f32 through mac16 (sixteen contraction indices in four
-// instructions, a lane's A operands four consecutive elements of a row: one 16-byte LDS read when the buffer is
-// contiguous along the contraction index).
+// The operands' and the output's products run on v_mfma_f32_16x16x4_f32 through mac16 (sixteen contraction indices in four
+// instructions), everything else on the bf16 instruction with operands as sums of bf16 terms (softmax_terms.h).
 #include <type_traits>
 
 #include "nats_common.h"
-#include "mfma_util.h"
+#include "softmax_terms.h"
 
 namespace nats {
 
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
     extern __shared__ __align__(16) float cb_smem[];
     float* Ks = cb_smem;
     float* Qs = cb_smem + CB_C * KS;
-    float* As = Qs;                         // after the products: diag(b') At, [64][CB_MS]
+    float* As = Qs;                         // after the products: At diag(b'), [64][CB_MS]
     // log2 gamma: its prefix sums in double, so that a decay ratio gamma_r / gamma_i, the exponential of a difference of
     // two of them, keeps fp32 accuracy whatever stands in front of token i in the chunk (alphas near 0)
     double* s_g = reinterpret_cast<double*>(cb_smem + 2 * CB_C * KS);
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
                 const float at = (i < r && linear_op == 0) ? G * accK[j] : 0.f;
                 if (keep_at) Ato[r * CB_C + i] = at;
                 Pmo[r * CB_C + i] = (i <= r) ? G * accQ[j] : 0.f;
-                keepA[s][j] = s_bp[r] * at;
+                keepA[s][j] = at * s_bp[i];
             }
         }
     }
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
             Pmo[off] = 0.f;
         }
     }
-    __syncthreads();   // the Q tile is dead: its region takes diag(b') At
+    __syncthreads();   // the Q tile is dead: its region takes At diag(b')
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
         const int t = w + 4 * s;
@@ -227,325 +227,402 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
 }
 
 // ---- the states along the sequence -------------------------------------------------------------------------------------
-// DIR 0: forwards, the state S^T [d_k][16] of the block's 16 value columns; leaves S0 of every chunk (ck), U and Uh.
-// DIR 1: backwards, the gradient of that state; leaves dS1 of every chunk (ck), dV, the block's share of dbeta and the
-// gradient of the initial state.  Wavefront w owns the chunk's tokens 16 w .. 16 w + 15 in everything that is one
+// DIR 0: forwards, the state S^T [d_k][16] of the block's 16 value columns; leaves S0 of every chunk (ck) and Uh.
+// DIR 1: backwards, the gradient of that state; leaves dS1 of every chunk (ck), <dS1, S0>, dV and the gradient of the
+// initial state.  Wavefront w owns the chunk's tokens 16 w .. 16 w + 15 in everything that is one
 // row per token, and D / 64 of the state's 16 x 16 tiles.
 template <typename T, typename TX>
 struct SeqArgs {
     const T *K, *Q;
     const TX* X;                   // V (DIR 0) or dO (DIR 1; fp32 beside bf16 tensors behind a merge's adjoint), [BH][L][D]
     ChunkOps o;
-    const uint8_t* mask;
     const float* S_init;           // DIR 0: [BH][D][D] or NULL
     float* ck;                     // [BH][L/64][D][D]
-    float *Ug, *Uh;                // [BH][L][D]: DIR 0 writes Ug (and, with RES, Uh), DIR 1 reads Uh
-    float *dV, *dbeta_part;        // DIR 1
+    float* rows;                   // [BH][L][D]: Uh (DIR 0), dV (DIR 1)
+    const float* S0;               // DIR 1: the states forwards, laid out as ck
+    float* dot;                    // DIR 1: <dS1, S0> of every chunk in parts, [BH][L/64][D/16][D/32]
     float* S_end;                  // [BH][D][D] or NULL.  DIR 0: the state after the last token; DIR 1: the gradient of S_init
     int L, BH;                     // BH: heads of V (output heads)
-    int G;                         // head grouping: K, Q, the operands and the mask are those of linear head bh / G (DIR 0 only)
+    int G;                         // head grouping: K, Q and the operands are those of linear head bh / G
     float la_scale;
     int delta;                     // 1: delta rule; 0: gated linear attention
 };
 
-// Eight wavefronts: four compute (as above), four only move the next chunk's operands from global memory to LDS.
-// A burst of loads of this size keeps a wavefront at the issue of its memory instructions for about as long as a
-// whole phase of the chunk's products takes, and there is one block per CU with nothing else to fill the time:
-// so the wavefronts that multiply issue no global loads at all.  What is staged has two places in LDS where that
-// fits (K, Q and the per-token vectors; At forwards), so the next chunk is written while this one is multiplied;
-// T and (backwards) P have one place and are replaced once their last reader of the chunk is past, behind the
-// second barrier.
-// With fp32 tensors the backward direction has room for one place only: there the staged operands are replaced
-// between the third barrier and a fourth.
-template <typename T, int D, int DIR>
+// Eight wavefronts: four compute (as above), four only move the next chunks' operands from global memory to LDS and cut
+// them into bf16 terms (softmax_terms.h), the products' operands: bf16 tensors are one term, everything else three.  A
+// burst of loads of this size keeps a wavefront at the issue of its memory instructions for about as long as a whole
+// phase of the chunk's products takes, and there is one block per CU with nothing else to fill the time: so the
+// wavefronts that multiply issue no global loads at all.
+// A chunk is a chain of three products (K S^T, the inverse, the state's update) with a barrier behind each; what stands
+// beside the chain (DIR 1: P^T dO', Q^T diag(gamma) dO') is multiplied in the first phase.  So most operands are dead
+// for a part of the chunk and have one place in LDS, replaced there:
+//     Q, P, dO (DIR 1)   behind the first barrier        T   behind the second
+// K (first and third phase) and the per-token vectors have two places.  With fp32 tensors (three terms) K has one where
+// two do not fit: it is replaced between the third barrier and a fourth; and in DIR 1 at d = 128 Q and K take turns in
+// one place, and P and T, with the products beside the chain in a phase of their own.
+// The loads of a chunk are asked for three chunks ahead (two at fp32 d = 128, for registers), into sets that take turns.
+// What leaves the chain for other kernels: U is not stored (b' Uh where it is needed), dbeta and the residuals' part of it
+// come from sums the gradient kernel has anyway, and the states are stored by the moving wavefronts, in whole rows, from
+// the terms they lie in.  On fp32 instructions, with all of that in the chain, at B 2, H 16, L 8192, d 128 bf16: forwards
+// 398 us (3.1 us per chunk), backwards 560; now 225 and 353.  Still a chain of latencies: 393 MB written and 100-300 MB
+// read from HBM would take 100-140 us.
+template <typename T, typename TX, int D, int DIR>
 struct SeqLds {
-    static constexpr bool two = !(DIR == 1 && sizeof(T) == 4);   // two places for K, Q and the small operands
-    static constexpr int NB = two ? 2 : 1;
-    static constexpr int MS = CB_MS;
-    // K and Q in LDS: fp32 forwards (the moving wavefronts widen bf16 once: widening at every read costs the
-    // multiplying wavefronts more than the second place saves); backwards, where two places for K and Q in fp32 do
-    // not fit, in the tensors' own type (bf16 is widened when read)
-    static constexpr bool wide = DIR == 0 || sizeof(T) == 4;
-    static constexpr int KE_BYTES = wide ? 4 : 2;
-    static constexpr int KS = D + (wide ? 4 : 8);                // row stride of K, Q (elements)
-    static constexpr int KQ_BYTES = CB_C * KS * KE_BYTES * (DIR ? 2 : 1);   // K, then (DIR 1) Q
-    static constexpr int M_BYTES = CB_C * MS * 4;
-    static constexpr int NB2 = DIR ? 1 : NB;                     // places of M2: At (DIR 0) as K; P (DIR 1) one
-    static constexpr int B_BYTES = CB_NV * MS * 4;               // a [16 v][MS] operand with tokens as contraction index
-    // small operands of a chunk: Xt, Gt (256 floats), and (DIR 1) dO' and diag(gamma) dO'
-    static constexpr int SM_BYTES = B_BYTES + 256 * 4 + (DIR ? 2 * B_BYTES : 0);
-    static constexpr int o_kq = 0;
-    static constexpr int o_m1 = o_kq + NB * KQ_BYTES;
-    static constexpr int o_m2 = o_m1 + M_BYTES;
-    static constexpr int o_sm = o_m2 + NB2 * M_BYTES;
-    static constexpr int o_st = o_sm + NB * SM_BYTES;
-    static constexpr int o_b = o_st + CB_NV * (D + 4) * 4;       // DIR 0: B0, B1, B2;  DIR 1: B2, B3
-    static constexpr int bytes = o_b + (DIR ? 2 : 3) * B_BYTES;
+    static constexpr int NT = terms_of<T>(), NX = DIR ? terms_of<TX>() : 1;
+    using KTile = TermTile<D, NT>;                    // K; (DIR 1) Q
+    using MTile = TermTile<64, N_TERMS>;              // T; (DIR 1) P
+    using STile = TermTile<D, N_TERMS, CB_NV>;        // the state
+    using BTile = TermTile<64, N_TERMS, CB_NV>;       // 16 value columns of a chunk's tokens
+    using XTile = TermTile<64, NX, CB_NV>;            // ... of dO as given
+    static constexpr int V_BYTES = ((DIR ? 0 : CB_NV * CB_MS) + 256) * 4;   // gam, kd, bp [64], gamC; (DIR 0) V [16 v][CB_MS]
+    static constexpr int n_b = DIR ? 3 : 2;           // DIR 0: R, kd U;  DIR 1: b' dU, -diag(gamma) dR, diag(gamma) dO'
+    static constexpr bool turns = DIR == 1 && NT > 1 && D == 128;
+    static constexpr int fixed = (DIR && !turns ? 2 : 1) * MTile::BYTES + 2 * V_BYTES + STile::BYTES + n_b * BTile::BYTES +
+                                 (DIR ? (turns ? 0 : KTile::BYTES) + XTile::BYTES : 0);
+    static constexpr bool k_one = turns || fixed + 2 * KTile::BYTES > 160 * 1024;
+    static constexpr int o_k = 0;
+    static constexpr int o_m1 = o_k + (k_one ? 1 : 2) * KTile::BYTES;
+    static constexpr int o_m2 = DIR && !turns ? o_m1 + MTile::BYTES : o_m1;
+    static constexpr int o_v = o_m2 + MTile::BYTES;
+    static constexpr int o_s = o_v + 2 * V_BYTES;
+    static constexpr int o_b = o_s + STile::BYTES;
+    static constexpr int o_x = o_b + n_b * BTile::BYTES;
+    static constexpr int o_q = turns ? o_k : o_x + XTile::BYTES;
+    static constexpr int bytes = o_k + fixed + (k_one ? 1 : 2) * KTile::BYTES;
+    static constexpr int sets = NT > 1 && D == 128 ? 1 : 2;
 };
 
-__device__ __forceinline__ float4 ldk4(const float* p) { return ld4(p); }
-__device__ __forceinline__ float4 ldk4(const uint16_t* p) { return ldb4(p); }
-__device__ __forceinline__ float4 ldkcol(const float* p, int rs) { return ld4col(p, rs); }
-__device__ __forceinline__ float4 ldkcol(const uint16_t* p, int rs) { return ldbcol(p, rs); }
-
-// RES: also the residuals Uh (and so At); the forward alone does without.
-template <typename T, typename TX, int D, int DIR, bool RES>
+template <typename T, typename TX, int D, int DIR>
 __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX> a) {
-    using LY = SeqLds<T, D, DIR>;
-    using KE = typename std::conditional<LY::wide, float, uint16_t>::type;   // K, Q in LDS
-    constexpr int KS = LY::KS, SS = D + 4, NP = CB_C * D * (int)sizeof(T) / 16 / 256, KT = D / 64, MS = CB_MS, NB = LY::NB;
-    constexpr int EPW = 16 / (int)sizeof(T);   // elements of a 16-byte word
+    using LY = SeqLds<T, TX, D, DIR>;
+    constexpr int NT = LY::NT, NX = LY::NX, KT = D / 64, MS = CB_MS, NPC = 64 * D / 8 / 256, NS = LY::sets;
     extern __shared__ __align__(16) float cb_smem[];
     unsigned char* lds = reinterpret_cast<unsigned char*>(cb_smem);
-    auto Ksb = [&](int i) { return reinterpret_cast<KE*>(lds + LY::o_kq + i * LY::KQ_BYTES); };
-    auto Qsb = [&](int i) { return Ksb(i) + CB_C * KS; };                               // DIR 1
-    float* M1 = reinterpret_cast<float*>(lds + LY::o_m1);                                 // T
-    auto M2b = [&](int i) { return reinterpret_cast<float*>(lds + LY::o_m2 + (DIR ? 0 : i) * LY::M_BYTES); };   // At / P
-    auto Xtb = [&](int i) { return reinterpret_cast<float*>(lds + LY::o_sm + i * LY::SM_BYTES); };   // V or Uh, [16 v][MS]
-    auto Gtb = [&](int i) { return Xtb(i) + CB_NV * MS; };       // gam, kd, bp [64] each, gamC, then (DIR 1) 64 mask bytes
-    auto B0b = [&](int i) { return Gtb(i) + 256; };              // DIR 1: dO' with the tokens as contraction index
-    auto B1b = [&](int i) { return B0b(i) + CB_NV * MS; };       // DIR 1: diag(gamma) dO'
-    float* St = reinterpret_cast<float*>(lds + LY::o_st);       // state, [16 v][SS]
-    float* Bx = reinterpret_cast<float*>(lds + LY::o_b);        // exchange between the wavefronts, [16 v][MS] each
+    auto at = [&](int off) { return reinterpret_cast<uint16_t*>(lds + off); };
+    auto Kt = [&](int i) { return typename LY::KTile{at(LY::o_k + (LY::k_one ? 0 : i) * LY::KTile::BYTES)}; };
+    const typename LY::MTile Tt{at(LY::o_m1)}, Pt{at(LY::o_m2)};
+    auto Gf = [&](int i) { return reinterpret_cast<float*>(lds + LY::o_v + i * LY::V_BYTES); };   // gam, kd, bp, gamC
+    auto Xf = [&](int i) { return Gf(i) + 256; };                                                 // DIR 0: V [16 v][MS]
+    const typename LY::STile St{at(LY::o_s)};
+    const typename LY::BTile B0{at(LY::o_b)}, B1{at(LY::o_b + LY::BTile::BYTES)}, B2{at(LY::o_b + 2 * LY::BTile::BYTES)};
+    const typename LY::KTile Qt{at(LY::o_q)};   // DIR 1
+    const typename LY::XTile Xt{at(LY::o_x)};   // DIR 1
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool loader = wave >= 4;
     const int w = wave & 3, lt = tid & 255;
     const int l16 = lane & 15, lq = lane >> 4;
     const int bh = blockIdx.x % a.BH, slice = blockIdx.x / a.BH, v0 = CB_NV * slice;
-    const int lin = DIR ? bh : bh / a.G;   // linear head
+    const int lin = bh / a.G;   // linear head
     const int L = a.L, n_chunks = L / CB_C;
-    const size_t n_tok = (size_t)a.BH * L;
     const float delta = a.delta ? 1.f : 0.f;
 
     // The two kinds of wavefront run loops of their own with the same number of barriers (a barrier counts
     // arrivals, wherever in the code they come from): what one kind keeps in registers across a chunk then takes
     // no registers from the other.
     if (loader) {
-        u32x4 kreg[NP], qreg[DIR ? NP : 1];
-        float4 m1reg[4], m2reg[4], gate4 = make_float4(0.f, 0.f, 0.f, 0.f), g4n = gate4;
-        TX xvn[4];
-        float uhn[4] = {0.f, 0.f, 0.f, 0.f}, gCn = 0.f;
-        uint32_t linn = 0;
-        auto fetch = [&](int c) {   // as it comes from memory: a conversion here would wait for the load
-            const size_t gc = (size_t)lin * n_chunks + c, tok0 = (size_t)lin * L + (size_t)c * CB_C;
+        struct Set {
+            Raw8<T> k[NPC], q[DIR ? NPC : 1];
+            Raw8<float> m1[2], m2[DIR ? 2 : 1];
+            float4 gate4, g4;
+            TX x[4];
+            float gC;
+        } set[NS];
+        // chunk number i of the walk; past the end: the last one once more (loads and writes stay unconditional: around
+        // a branch the compiler waits for every load in flight).  As it comes from memory: a conversion here would wait.
+        auto chunk_at = [&](int i) { i = i < n_chunks ? i : n_chunks - 1; return DIR ? n_chunks - 1 - i : i; };
+        auto fetch_k = [&](Set& s, int i) {
+            const size_t tok0 = (size_t)lin * L + (size_t)chunk_at(i) * CB_C;
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {   // a chunk's rows are contiguous
-                kreg[i] = reinterpret_cast<const u32x4*>(a.K + tok0 * D)[lt + 256 * i];
-                if (DIR) qreg[i] = reinterpret_cast<const u32x4*>(a.Q + tok0 * D)[lt + 256 * i];
+            for (int p = 0; p < NPC; ++p) s.k[p].load(a.K + tok0 * D + 8 * (lt + 256 * p));   // a chunk's rows are contiguous
+        };
+        auto fetch_m = [&](Raw8<float> (&m)[2], const float* M, int i) {
+            M += ((size_t)lin * n_chunks + chunk_at(i)) * (CB_C * CB_C);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) m[p].load(M + 8 * (lt + 256 * p));
+        };
+        auto fetch = [&](Set& s, int i) {   // all but K where it has one place and T where it takes turns
+            const int c = chunk_at(i);
+            const size_t gc = (size_t)lin * n_chunks + c, tok0 = (size_t)lin * L + (size_t)c * CB_C;
+            if (!LY::k_one) fetch_k(s, i);
+            if (DIR) {
+#pragma unroll
+                for (int p = 0; p < NPC; ++p) s.q[p].load(a.Q + tok0 * D + 8 * (lt + 256 * p));
             }
-            if (lt < 48) gate4 = ld4((lt < 16 ? a.o.gam : lt < 32 ? a.o.kd : a.o.bp) + tok0 + 4 * (lt & 15));
-            if (lt == 48) gCn = a.o.gamC[gc];
-            if (DIR && a.mask != nullptr && lt >= 64 && lt < 80)   // NULL: routing per chunk, every token of a chunk writes
-                linn = *reinterpret_cast<const uint32_t*>(a.mask + tok0 + 4 * (lt - 64));
+            if (lt < 48) s.gate4 = ld4((lt < 16 ? a.o.gam : lt < 32 ? a.o.kd : a.o.bp) + tok0 + 4 * (lt & 15));
+            if (lt == 48) s.gC = a.o.gamC[gc];
+            if (DIR) s.g4 = ld4(a.o.gam + tok0 + 16 * w + 4 * lq);
             const size_t t4 = (size_t)bh * L + (size_t)c * CB_C + 16 * w + 4 * lq;
-            if (DIR) g4n = ld4(a.o.gam + t4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s.x[j] = a.X[(t4 + j) * D + v0 + l16];
+            if constexpr (DIR) fetch_m(s.m2, a.o.Pm, i);
+            if (!LY::turns) fetch_m(s.m1, a.o.Tm, i);
+        };
+        auto put_k = [&](const typename LY::KTile& dst, const auto& r) {
+#pragma unroll
+            for (int p = 0; p < NPC; ++p) {
+                const int e = 8 * (lt + 256 * p);
+                u32x4 t[NT];
+                r[p].terms(t);
+                dst.put(e / D, e % D, t);
+            }
+        };
+        auto put_m = [&](const typename LY::MTile& dst, const auto& r) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int e = 8 * (lt + 256 * p);
+                u32x4 t[N_TERMS];
+                r[p].terms(t);
+                dst.put(e / 64, e % 64, t);
+            }
+        };
+        auto put_vectors = [&](const Set& s, int nb) {
+            float* Gt = Gf(nb);
+            if (lt < 48) *reinterpret_cast<float4*>(Gt + 4 * lt) = s.gate4;
+            if (lt == 48) Gt[3 * CB_C] = s.gC;
+            if (DIR == 0)
+                *reinterpret_cast<float4*>(Xf(nb) + l16 * MS + 16 * w + 4 * lq) =
+                    make_float4(to_float(s.x[0]), to_float(s.x[1]), to_float(s.x[2]), to_float(s.x[3]));
+        };
+        // the state of chunk ci, in whole rows: 8 columns per thread, put together from their terms
+        const int sv = lt / (D / 8), sk = 8 * (lt % (D / 8));
+        const bool has_state = lt < CB_NV * D / 8;   // uniform
+        auto state_at = [&](int i) { return (((size_t)bh * n_chunks + chunk_at(i)) * D + v0 + (has_state ? sv : 0)) * D + sk; };
+        Raw8<float> s0[DIR ? NS : 1];                // DIR 1: the same elements of S0
+        auto store_state = [&](const Raw8<float>& s0r, int ci) {
+            if (!has_state) return;
+            u32x4 t[N_TERMS];
+            St.rows(sv, sk, t);
+            float x[8], dot = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                x[i] = 0.f;
+#pragma unroll
+                for (int n = N_TERMS - 1; n >= 0; --n)   // exact: the terms of one number
+                    x[i] += __uint_as_float(i & 1 ? t[n][i / 2] & 0xffff0000u : t[n][i / 2] << 16);
+                if (DIR) dot += x[i] * __uint_as_float(s0r.w[i / 4][i % 4]);
+            }
+            float* dst = a.ck + state_at(ci);
+            *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
+            *reinterpret_cast<float4*>(dst + 4) = make_float4(x[4], x[5], x[6], x[7]);
+            if (DIR) {
+                dot = lane_group_sum<64>(dot);
+                if (lane == 0)
+                    a.dot[(((size_t)bh * n_chunks + chunk_at(ci)) * (D / CB_NV) + slice) * (D / 32) + w] = dot;
+            }
+        };
+        auto put_first = [&](const Set& s) {   // DIR 1: what the first phase alone reads
+            if (!LY::turns) put_k(Qt, s.q);
+            const float gg[4] = {s.g4.x, s.g4.y, s.g4.z, s.g4.w};
+            float x[4], y[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                xvn[j] = a.X[(t4 + j) * D + v0 + l16];
-                if (DIR) uhn[j] = a.Uh[(t4 + j) * D + v0 + l16];
+                x[j] = to_float(s.x[j]);
+                y[j] = gg[j] * (a.la_scale * x[j]);
             }
-            const float* m1 = a.o.Tm + gc * (CB_C * CB_C);
-            const float* m2 = (DIR ? a.o.Pm : a.o.At) + gc * (CB_C * CB_C);
+            uint2 t[N_TERMS];
+            split_terms(y, t);
+            B2.put(l16, 16 * w + 4 * lq, t);
+            split_terms(x, t);
+            uint2 tx[NX];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (RES) m2reg[i] = ld4(m2 + 4 * (lt + 256 * i));
-                m1reg[i] = ld4(m1 + 4 * (lt + 256 * i));
-            }
+            for (int i = 0; i < NX; ++i) tx[i] = t[i];
+            Xt.put(l16, 16 * w + 4 * lq, tx);
         };
-        auto put_kq_small = [&](int nb) {
-            KE* Ks = Ksb(nb);
-            KE* Qs = Qsb(nb);
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int e = lt + 256 * i, row = e / (D / EPW), cc = (e % (D / EPW)) * EPW;
-                if (sizeof(KE) == sizeof(T)) {   // as they are
-                    *reinterpret_cast<u32x4*>(Ks + row * KS + cc) = kreg[i];
-                    if (DIR) *reinterpret_cast<u32x4*>(Qs + row * KS + cc) = qreg[i];
-                } else {                          // bf16 widened here (forwards only: no Q)
-                    float kf[EPW];
-                    unpack16(kreg[i], kf, T{});
-#pragma unroll
-                    for (int j = 0; j < EPW; j += 4)
-                        *reinterpret_cast<float4*>(reinterpret_cast<float*>(Ks) + row * KS + cc + j) = make_float4(kf[j], kf[j + 1], kf[j + 2], kf[j + 3]);
-                }
-            }
-            float* Gt = Gtb(nb);
-            if (lt < 48) *reinterpret_cast<float4*>(Gt + 4 * lt) = gate4;
-            if (lt == 48) Gt[3 * CB_C] = gCn;
-            if (DIR && lt >= 64 && lt < 80) reinterpret_cast<uint32_t*>(Gt + 3 * CB_C + 4)[lt - 64] = linn;
-            if (DIR == 0) {
-                *reinterpret_cast<float4*>(Xtb(nb) + l16 * MS + 16 * w + 4 * lq) =
-                    make_float4(to_float(xvn[0]), to_float(xvn[1]), to_float(xvn[2]), to_float(xvn[3]));
-            } else {   // Uh; dO' and diag(gamma) dO' with the tokens as contraction index
-                *reinterpret_cast<float4*>(Xtb(nb) + l16 * MS + 16 * w + 4 * lq) = make_float4(uhn[0], uhn[1], uhn[2], uhn[3]);
-                float4 x, y;
-                x.x = a.la_scale * to_float(xvn[0]); x.y = a.la_scale * to_float(xvn[1]);
-                x.z = a.la_scale * to_float(xvn[2]); x.w = a.la_scale * to_float(xvn[3]);
-                y.x = g4n.x * x.x; y.y = g4n.y * x.y; y.z = g4n.z * x.z; y.w = g4n.w * x.w;
-                *reinterpret_cast<float4*>(B0b(nb) + l16 * MS + 16 * w + 4 * lq) = x;
-                *reinterpret_cast<float4*>(B1b(nb) + l16 * MS + 16 * w + 4 * lq) = y;
-            }
-        };
-        auto put_m = [&](float* M, const float4 (&r)[4]) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = lt + 256 * i, row = e / 16, c4 = (e % 16) * 4;
-                *reinterpret_cast<float4*>(M + row * MS + c4) = r[i];
-            }
-        };
-        // Chunk ci + 1 is written to LDS behind the second barrier of chunk ci (by then its loads, issued a chunk
-        // earlier, have long arrived, and the readers of T and P are past), and the loads of chunk ci + 2 are issued
-        // right after: the first two barriers of a chunk never wait for these wavefronts.
-        auto chunk_at = [&](int ci) { return DIR ? n_chunks - 1 - ci : ci; };
-        fetch(chunk_at(0));
-        put_kq_small(0);
-        if (RES) put_m(M2b(0), m2reg);
-        put_m(M1, m1reg);
-        if (n_chunks > 1) fetch(chunk_at(1));
+        for (int i = 0; i < NS; ++i) {
+            fetch(set[i], i);
+            if (LY::k_one) fetch_k(set[i], i);
+            if (LY::turns) fetch_m(set[i].m1, a.o.Tm, i);
+            if constexpr (DIR == 1) s0[i].load(a.S0 + state_at(i));
+        }
+        put_k(LY::turns ? Qt : Kt(0), LY::turns ? set[0].q : set[0].k);
+        put_vectors(set[0], 0);
+        if constexpr (DIR == 1) {
+            put_first(set[0]);
+            put_m(Pt, set[0].m2);
+        }
+        if (!LY::turns) put_m(Tt, set[0].m1);
+        fetch(set[0], NS);
+        if (LY::k_one && !LY::turns) fetch_k(set[0], NS);
         __syncthreads();
-        for (int ci = 0; ci < n_chunks; ++ci) {
-            const int nb = (ci + 1) % NB;
-            const bool more = ci + 1 < n_chunks;
-            __syncthreads();
-            __syncthreads();
-            if (more) {
-                if (LY::two) put_kq_small(nb);
-                if (RES) put_m(M2b(nb), m2reg);
-                put_m(M1, m1reg);
+        auto step = [&](auto which, int ci) {   // chunk ci is multiplied, chunk ci + 1 written, chunk ci + 1 + NS asked for
+            constexpr int S = decltype(which)::value;
+            Set& s = set[S];
+            const int nb = (ci + 1) & 1;
+            if constexpr (DIR == 1) {
+                constexpr int Z = (S + NS - 1) % NS;   // chunk ci
+                store_state(s0[Z], ci);
+                s0[Z].load(a.S0 + state_at(ci + NS));
+            } else {
+                store_state(s0[0], ci);
             }
-            if (LY::two && ci + 2 < n_chunks) fetch(chunk_at(ci + 2));
             __syncthreads();
-            if (!LY::two) {   // one place for K, Q and the per-token vectors: replaced between the third barrier and a fourth
-                if (more) put_kq_small(0);
-                if (ci + 2 < n_chunks) fetch(chunk_at(ci + 2));
+            if (LY::turns) {   // chunk ci's K in Q's place, T in P's
+                put_k(Kt(0), s.k);
+                put_m(Tt, s.m1);
+                fetch_k(s, ci + 1);
+                fetch_m(s.m1, a.o.Tm, ci + 1);
                 __syncthreads();
             }
+            if constexpr (DIR == 1) put_first(s);
+            put_vectors(s, nb);
+            if (!LY::k_one) put_k(Kt(nb), s.k);
+            if constexpr (DIR == 1 && !LY::turns) put_m(Pt, s.m2);
+            __syncthreads();
+            if (LY::turns) __syncthreads();
+            if constexpr (LY::turns) put_m(Pt, s.m2);
+            else put_m(Tt, s.m1);
+            if (!LY::turns) fetch(s, ci + 1 + NS);
+            __syncthreads();
+            if constexpr (LY::turns) {
+                put_k(Qt, s.q);
+                fetch(s, ci + 1 + NS);
+                __syncthreads();
+            } else if (LY::k_one) {
+                put_k(Kt(0), s.k);
+                fetch_k(s, ci + 1 + NS);
+                __syncthreads();
+            }
+        };
+        for (int ci = 0; ci < n_chunks; ci += NS) {
+            step(std::integral_constant<int, NS - 1>{}, ci);   // chunk ci + 1 is in set (ci + 1) % NS
+            if (NS == 2 && ci + 1 < n_chunks) step(std::integral_constant<int, 0>{}, ci + 1);
         }
         return;
     }
 
     // the state: tiles kt = KT w + t, element [k = 16 kt + 4 lq + j][v = l16]
     f32x4 Sacc[KT];
+    auto put_state = [&](int t) {
+        const float x[4] = {Sacc[t][0], Sacc[t][1], Sacc[t][2], Sacc[t][3]};
+        uint2 y[N_TERMS];
+        split_terms(x, y);
+        St.put(l16, 16 * (KT * w + t) + 4 * lq, y);
+    };
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
-        const int kt = KT * w + t;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (DIR == 0 && a.S_init != nullptr) s = ld4(a.S_init + ((size_t)bh * D + v0 + l16) * D + 16 * kt + 4 * lq);
+        if (DIR == 0 && a.S_init != nullptr) s = ld4(a.S_init + ((size_t)bh * D + v0 + l16) * D + 16 * (KT * w + t) + 4 * lq);
         Sacc[t] = f32x4{s.x, s.y, s.z, s.w};
-        *reinterpret_cast<float4*>(St + l16 * SS + 16 * kt + 4 * lq) = s;
+        put_state(t);
     }
+    auto put_b = [&](const typename LY::BTile& dst, const float (&x)[4]) {   // this lane's four tokens of its value column
+        uint2 t[N_TERMS];
+        split_terms(x, t);
+        dst.put(l16, 16 * w + 4 * lq, t);
+    };
     __syncthreads();
 
     for (int ci = 0; ci < n_chunks; ++ci) {
-        const int c = DIR ? n_chunks - 1 - ci : ci, cb = ci % NB;
-        const size_t gc = (size_t)bh * n_chunks + c;
+        const int c = DIR ? n_chunks - 1 - ci : ci, cb = ci & 1;
         const size_t t4 = (size_t)bh * L + (size_t)c * CB_C + 16 * w + 4 * lq;   // the lane's first token
-        const KE* Ks = Ksb(cb);
-        const KE* Qs = Qsb(cb);
-        const float* M2 = M2b(cb);
-        const float* Gt = Gtb(cb);
-        // exchange buffers: DIR 0: B0 = b' R, B1 = U, B2 = kd U;  DIR 1: B0, B1 staged (dO', gamma dO'), B2 = dU, B3 = -gamma dR
-        float* B0 = DIR ? B0b(cb) : Bx;
-        float* B1 = DIR ? B1b(cb) : Bx + CB_NV * MS;
-        float* B2 = DIR ? Bx : Bx + 2 * CB_NV * MS;
-        float* B3 = Bx + CB_NV * MS;   // DIR 1
-        float gg[4], kk[4], bb[4], xv[4], R[4];
+        const typename LY::KTile Ks = Kt(cb);
+        const float* Gt = Gf(cb);
+        float gg[4], kk[4], bb[4], xv[4];
         {
             const float4 g4 = ld4(Gt + 16 * w + 4 * lq), kd4 = ld4(Gt + CB_C + 16 * w + 4 * lq);
-            const float4 bp4 = ld4(Gt + 2 * CB_C + 16 * w + 4 * lq), x4 = ld4(Xtb(cb) + l16 * MS + 16 * w + 4 * lq);
+            const float4 bp4 = ld4(Gt + 2 * CB_C + 16 * w + 4 * lq), x4 = DIR ? g4 : ld4(Xf(cb) + l16 * MS + 16 * w + 4 * lq);
             gg[0] = g4.x; gg[1] = g4.y; gg[2] = g4.z; gg[3] = g4.w;
             kk[0] = kd4.x; kk[1] = kd4.y; kk[2] = kd4.z; kk[3] = kd4.w;
             bb[0] = bp4.x; bb[1] = bp4.y; bb[2] = bp4.z; bb[3] = bp4.w;
             xv[0] = x4.x; xv[1] = x4.y; xv[2] = x4.z; xv[3] = x4.w;
         }
         const float gC = Gt[3 * CB_C];
-        const uint32_t lin = DIR ? reinterpret_cast<const uint32_t*>(Gt + 3 * CB_C + 4)[4 * w + lq] : 0u;
+        f32x4 upd[KT];   // what the chunk adds to the state
+#pragma unroll
+        for (int t = 0; t < KT; ++t) upd[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // DIR 1, beside the chain: P^T dO' (rows of P behind the wavefront's tokens), Q^T diag(gamma) dO'
+        f32x4 accP = {0.f, 0.f, 0.f, 0.f};
+        auto beside = [&]() {
+            for (int ks = w >> 1; ks < 2; ++ks) {
+                u32x4 p[N_TERMS], x[NX];
+                Pt.cols_in_order(32 * ks, 16 * w, l16, lq, p);
+                Xt.rows(l16, 32 * ks + 8 * lq, x);
+                accP = mfma_terms(p, x, accP);
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                u32x4 b[N_TERMS];
+                B2.rows(l16, 32 * ks + 8 * lq, b);
+#pragma unroll
+                for (int t = 0; t < KT; ++t) {
+                    u32x4 q[NT];
+                    Qt.cols_in_order(32 * ks, 16 * (KT * w + t), l16, lq, q);
+                    upd[t] = mfma_terms(q, b, upd[t]);
+                }
+            }
+        };
+        if (LY::turns) {
+            beside();
+            __syncthreads();
+            __syncthreads();   // K and T take Q's and P's places
+        }
         // ---- 1: the state seen by the wavefront's tokens: K_w S^T --------------------------------------------
         {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-            for (int kt = 0; kt < D / 16; ++kt)
-                acc = mac16(ldk4(Ks + (16 * w + l16) * KS + 16 * kt + 4 * lq), ld4(St + l16 * SS + 16 * kt + 4 * lq), acc);
-            if (DIR == 0) {
-                float4 br;
+            f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) R[j] = xv[j] - delta * gg[j] * acc[j];
-                br.x = bb[0] * R[0]; br.y = bb[1] * R[1]; br.z = bb[2] * R[2]; br.w = bb[3] * R[3];
-                *reinterpret_cast<float4*>(B0 + l16 * MS + 16 * w + 4 * lq) = br;
-            } else {
-                // dU = P^T dO' + diag(kd) K dS1^T: rows of P behind the wavefront's tokens
-                f32x4 accP = {0.f, 0.f, 0.f, 0.f};
-                for (int ta = w; ta < 4; ++ta)
-                    accP = mac16(ld4col(M2 + (16 * ta + 4 * lq) * MS + 16 * w + l16, MS), ld4(B0 + l16 * MS + 16 * ta + 4 * lq), accP);
-                float4 du;
-                du.x = kk[0] * acc[0] + accP[0]; du.y = kk[1] * acc[1] + accP[1];
-                du.z = kk[2] * acc[2] + accP[2]; du.w = kk[3] * acc[3] + accP[3];
-                *reinterpret_cast<float4*>(B2 + l16 * MS + 16 * w + 4 * lq) = du;
+            for (int ks = 0; ks < D / 32; ++ks) {
+                u32x4 k[NT], s[N_TERMS];
+                Ks.rows(16 * w + l16, 32 * ks + 8 * lq, k);
+                St.rows(l16, 32 * ks + 8 * lq, s);
+                if (ks & 1) acc1 = mfma_terms(k, s, acc1);
+                else acc0 = mfma_terms(k, s, acc0);
             }
+            acc0 += acc1;
+            float y[4];
+            if (DIR == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) y[j] = xv[j] - delta * gg[j] * acc0[j];
+            } else {   // dU = P^T dO' + diag(kd) K dS1^T
+                if (!LY::turns) beside();
+#pragma unroll
+                for (int j = 0; j < 4; ++j) y[j] = bb[j] * (kk[j] * acc0[j] + a.la_scale * accP[j]);
+            }
+            put_b(B0, y);
         }
         __syncthreads();
         // ---- 2: through the inverse ------------------------------------------------------------------------
-        if (DIR == 0) {
-            f32x4 U = {0.f, 0.f, 0.f, 0.f};
-            for (int tb = 0; tb <= w; ++tb)
-                U = mac16(ld4(M1 + (16 * w + l16) * MS + 16 * tb + 4 * lq), ld4(B0 + l16 * MS + 16 * tb + 4 * lq), U);
-            *reinterpret_cast<float4*>(B1 + l16 * MS + 16 * w + 4 * lq) = make_float4(U[0], U[1], U[2], U[3]);
-            *reinterpret_cast<float4*>(B2 + l16 * MS + 16 * w + 4 * lq) = make_float4(kk[0] * U[0], kk[1] * U[1], kk[2] * U[2], kk[3] * U[3]);
+        {
+            f32x4 X = {0.f, 0.f, 0.f, 0.f};   // Uh (DIR 0), dR (DIR 1)
+            auto half = [&](int ks) {         // 32 tokens of the contraction
+                u32x4 m[N_TERMS], b[N_TERMS];
+                if (DIR == 0) Tt.rows(16 * w + l16, 32 * ks + 8 * lq, m);
+                else Tt.cols_in_order(32 * ks, 16 * w, l16, lq, m);
+                B0.rows(l16, 32 * ks + 8 * lq, b);
+                X = mfma_terms(m, b, X);
+            };
+            if (DIR == 0 || w < 2) half(0);   // T is lower triangular; uniform
+            if (DIR == 1 || w >= 2) half(1);
+            float y[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) a.Ug[(t4 + j) * D + v0 + l16] = U[j];
-        } else {
-            f32x4 Rt = {0.f, 0.f, 0.f, 0.f};
-            for (int ta = w; ta < 4; ++ta)
-                Rt = mac16(ld4col(M1 + (16 * ta + 4 * lq) * MS + 16 * w + l16, MS), ld4(B2 + l16 * MS + 16 * ta + 4 * lq), Rt);
-            float4 ng;
-            float dr[4];
+            for (int j = 0; j < 4; ++j) y[j] = DIR == 0 ? kk[j] * (bb[j] * X[j]) : -delta * gg[j] * X[j];
+            put_b(B1, y);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                dr[j] = bb[j] * Rt[j];
-                a.dV[(t4 + j) * D + v0 + l16] = dr[j];
-                const float sdb = lane_group_sum<16>(xv[j] * Rt[j]);   // xv: Uh
-                if (l16 == 0) a.dbeta_part[(size_t)slice * n_tok + t4 + j] = ((lin >> (8 * j)) & 0xff) ? 0.f : sdb;
-            }
-            ng.x = -delta * gg[0] * dr[0]; ng.y = -delta * gg[1] * dr[1]; ng.z = -delta * gg[2] * dr[2]; ng.w = -delta * gg[3] * dr[3];
-            *reinterpret_cast<float4*>(B3 + l16 * MS + 16 * w + 4 * lq) = ng;
+            for (int j = 0; j < 4; ++j) a.rows[(t4 + j) * D + v0 + l16] = X[j];
         }
         __syncthreads();
         // ---- 3: the chunk's contribution to the state ------------------------------------------------------------
-        if (DIR == 0 && RES) {
-            f32x4 AU = {0.f, 0.f, 0.f, 0.f};
-            for (int tb = 0; tb <= w; ++tb)
-                AU = mac16(ld4(M2 + (16 * w + l16) * MS + 16 * tb + 4 * lq), ld4(B1 + l16 * MS + 16 * tb + 4 * lq), AU);
+        // (summed from zero and added by vector adds: the matrix instruction's own accumulation does not round to nearest)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) a.Uh[(t4 + j) * D + v0 + l16] = R[j] - AU[j];
-        }
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            const int kt = KT * w + t;
-            *reinterpret_cast<float4*>(a.ck + (gc * D + v0 + l16) * D + 16 * kt + 4 * lq) =
-                make_float4(Sacc[t][0], Sacc[t][1], Sacc[t][2], Sacc[t][3]);
-            Sacc[t][0] *= gC; Sacc[t][1] *= gC; Sacc[t][2] *= gC; Sacc[t][3] *= gC;
-        }
-#pragma unroll 2
-        for (int tb = 0; tb < 4; ++tb) {   // token tiles outside: their operands serve all of the wavefront's state tiles
-            const float4 b2 = ld4((DIR ? B1 : B2) + l16 * MS + 16 * tb + 4 * lq);
-            const float4 b3 = DIR ? ld4(B3 + l16 * MS + 16 * tb + 4 * lq) : b2;
+        for (int ks = 0; ks < 2; ++ks) {   // token tiles outside: their operands serve all of the wavefront's state tiles
+            u32x4 b[N_TERMS];
+            B1.rows(l16, 32 * ks + 8 * lq, b);
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const int kt = KT * w + t;
-                if (DIR == 0) {
-                    Sacc[t] = mac16(ldkcol(Ks + (16 * tb + 4 * lq) * KS + 16 * kt + l16, KS), b2, Sacc[t]);
-                } else {
-                    Sacc[t] = mac16(ldkcol(Qs + (16 * tb + 4 * lq) * KS + 16 * kt + l16, KS), b2, Sacc[t]);
-                    Sacc[t] = mac16(ldkcol(Ks + (16 * tb + 4 * lq) * KS + 16 * kt + l16, KS), b3, Sacc[t]);
-                }
+                u32x4 k[NT];
+                Ks.cols_in_order(32 * ks, 16 * (KT * w + t), l16, lq, k);
+                upd[t] = mfma_terms(k, b, upd[t]);
             }
         }
         // the state for the next chunk's first phase (nothing reads it in between)
 #pragma unroll
-        for (int t = 0; t < KT; ++t)
-            *reinterpret_cast<float4*>(St + l16 * SS + 16 * (KT * w + t) + 4 * lq) = make_float4(Sacc[t][0], Sacc[t][1], Sacc[t][2], Sacc[t][3]);
+        for (int t = 0; t < KT; ++t) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) Sacc[t][j] = fmaf(gC, Sacc[t][j], upd[t][j]);
+            put_state(t);
+        }
         __syncthreads();   // every read of the chunk's operands is done, the new state is in place
-        if (!LY::two) __syncthreads();   // one place for the staged operands: they are replaced in between
+        if (LY::k_one) __syncthreads();   // K is replaced in between
     }
     if (a.S_end != nullptr) {
 #pragma unroll
@@ -555,17 +632,19 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
     }
 }
 
-template <typename T, int D, int DIR>
-constexpr size_t seq_lds_bytes() { return SeqLds<T, D, DIR>::bytes; }
 template <int D>
 constexpr size_t prep_lds_bytes() { return sizeof(float) * (2 * (size_t)CB_C * (D + 4) + 3 * CB_C); }
 
 // ---- the gradients of a chunk -------------------------------------------------------------------------------------------
-// One block per (chunk, batch*head), d / 16 wavefronts; wavefront w owns the columns 16 w .. 16 w + 15 of dQ and dK
-// (all 64 rows: four accumulator tiles each) and of the three products with the states that feed them.  Three LDS
-// regions are filled in turn:   A: S0, then U with dS1 (64 rows at a time), then K with Q;   B: dO', then dP . Gamma;
-// C: dR, then the symmetric (dAt . Gamma) + (dAt . Gamma)^T.  Sums over rows, columns or wavefronts go through small
-// per-tile or per-wavefront arrays that one wavefront adds up in a fixed order (no atomics).
+// One block per (chunk, batch*head), 4 wavefronts; wavefront w owns a quarter of the columns of dQ and dK (all 64 rows)
+// and of the three products with the states that feed them.  Every element of S0 and dS1 is then the operand of one
+// wavefront alone and goes from memory to its registers; what all read (dO, dR, Uh in turn; then K, Q and the two
+// 64 x 64 operands) goes through LDS.  At d = 128 a lane's two columns are neighbours (8-byte loads and stores, whole
+// lines per 16 lanes): column 32 w + 2 l16 + ct; K and Q lie in LDS in that order.
+// All products on bf16 terms (softmax_terms.h).  On the fp32 instruction they took as long as the bytes (1.5 GB at
+// B 2, H 16, L 8192, d 128), one behind the other with one block of 139 KB of LDS per CU: 555 us; with two blocks per CU
+// and the terms 377, 1.0 GB at 2.7 TB/s.  Sums over rows,
+// columns or wavefronts go through small per-tile or per-wavefront arrays that one wavefront adds up in a fixed order.
 template <typename T, typename TO>
 struct GradArgs {
     const T *Q, *K;
@@ -573,7 +652,7 @@ struct GradArgs {
     ChunkOps o;
     const float *alpha;
     const uint8_t* mask;
-    const float *ck, *dck, *Ug, *dR, *dbeta_part;
+    const float *ck, *dck, *Uh, *dR, *dot;
     float *dQ, *dK, *dalpha, *dbeta, *g_nla;
     float* dscore_la;   // optional, routing per chunk: Eq. 17 per chunk
     int L, BH;
@@ -582,291 +661,374 @@ struct GradArgs {
 };
 
 template <typename T, typename TO, int D>
-__global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T, TO> a) {
-    constexpr int NW = D / 16, NT = 64 * NW, KS = D + 4, MS = CB_MS, E = Vec16<T>::N;
-    constexpr int HALF = CB_C * KS;            // floats of a [64][KS] tile
-    constexpr int NS0 = D * D / 4 / NT;        // 16-byte pieces of a state per thread
-    constexpr int NSH = 64 * D / 4 / NT;       // ... of 64 rows of it (or of a [64][D] fp32 tile)
+struct GradLds {
+    using RTile = TermTile<D, N_TERMS>;      // dO, dR, Uh, in turn
+    using KTile = TermTile<D, terms_of<T>()>;
+    static constexpr int o_q = KTile::BYTES, o_p = 2 * KTile::BYTES, o_a = o_p + CB_C * CB_MS * 4;
+    static constexpr int last = o_a + CB_C * CB_MS * 4;
+    static constexpr int first = RTile::BYTES + (terms_of<TO>() == 1 ? TermTile<D, 1>::BYTES : 0);
+    static constexpr int o_small = first > last ? first : last;
+    static constexpr int bytes = o_small + (4 + 8 + 8) * CB_C * 4 + 4 * 4;
+    static constexpr int blocks = 2 * bytes <= 160 * 1024 ? 2 : 1;   // per CU
+};
+
+template <typename T, typename TO, int D>
+__global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_grads_kernel(const GradArgs<T, TO> a) {
+    using LY = GradLds<T, TO, D>;
+    constexpr int NT = terms_of<T>(), NO = terms_of<TO>(), NCT = D / 64, KS = D / 32, MS = CB_MS, NPC = D / 32;
+    constexpr int NTL = 3;   // lower 16 x 16 tiles of a 64 x 64 operand per wavefront
     extern __shared__ __align__(16) float cb_smem[];
-    float* RA = cb_smem;
-    float* RAhi = RA + HALF;
-    float* RB = RA + 2 * HALF;
-    float* RC = RB + HALF;
-    float* s_g2 = RC + HALF;
+    unsigned char* lds = reinterpret_cast<unsigned char*>(cb_smem);
+    const typename LY::RTile Rt{reinterpret_cast<uint16_t*>(lds)};
+    const TermTile<D, NO> Ot{reinterpret_cast<uint16_t*>(lds + (NO == 1 ? LY::RTile::BYTES : 0))};
+    const typename LY::KTile Kt{reinterpret_cast<uint16_t*>(lds)}, Qt{reinterpret_cast<uint16_t*>(lds + LY::o_q)};
+    float* Pf = reinterpret_cast<float*>(lds + LY::o_p);       // dP . Gamma
+    float* Af = reinterpret_cast<float*>(lds + LY::o_a);       // (dAt . Gamma) + (dAt . Gamma)^T
+    float* s_g2 = reinterpret_cast<float*>(lds + LY::o_small);
     float* s_gam = s_g2 + CB_C;
     float* s_kd = s_gam + CB_C;
-    float* rs = s_kd + CB_C;                   // [4 column tiles][64 rows]: row sums of dAt . At + dP . P per tile
-    float* cs = rs + 4 * CB_C;                 // [4 row tiles][64 columns]: column sums
-    float* gk = cs + 4 * CB_C;                 // [NW][64]: the state terms of d ln gamma, per wavefront's columns
-    float* ge = gk + NW * CB_C;                // [NW]: the sum of E_r over the chunk, likewise
-    float* s_dot = ge + NW * CB_C;             // [NW]: <dS1, S0>
+    float* s_bp = s_kd + CB_C;
+    float* rs = s_bp + CB_C;                   // [4 column tiles][64 rows]: row sums of dAt . At + dP . P per tile
+    float* cs = rs + 4 * CB_C;                 // [4 row tiles][64 columns]: column sums of the same without the factor b'
+    float* gk = cs + 4 * CB_C;                 // [4 wavefronts][64]: the state terms of d ln gamma, per wavefront's columns
+    float* gu = gk + 4 * CB_C;                 // ...: kd K . (Uh dS1), likewise
+    float* ge = gu + 4 * CB_C;                 // [4]: the sum of E_r over the chunk, likewise
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
     const int n_chunks = a.L / CB_C;
     const int bh = blockIdx.x % a.BH, chunk = blockIdx.x / a.BH;
     const size_t gc = (size_t)bh * n_chunks + chunk, tok0 = (size_t)bh * a.L + (size_t)chunk * CB_C;
     const float delta = a.delta ? 1.f : 0.f;
+    const int col0 = 16 * NCT * w + NCT * l16;   // the lane's NCT columns
 
-    // The block's global loads: what stage 1 needs goes out first; the later stages' operands are asked for from
-    // inside stage 1's product loop, a few loads per step (the issue of a load costs a wavefront 100 cycles and more
-    // while the CU's miss queue is full; between matrix instructions the SIMD's other wavefront fills that time),
-    // and wait in registers (one block per CU: nothing else would hide their latency).
-    constexpr int NPT = 64 * D / E / NT;       // 16-byte words of a [64][D] tile of T per thread
-    constexpr int NPO = 64 * D / Vec16<TO>::N / NT;   // ... of TO
-    auto put_rows_f32 = [&](float* dst, const float4 (&r)[NSH]) {   // [64][D] fp32 -> LDS rows of KS
+    using Strip = float[KS][8][NCT];             // rows 32 ks + 8 lq + i of the lane's columns of a state
+    auto load_strip = [&](float (&s)[8][NCT], const float* S, int ks) {
 #pragma unroll
-        for (int i = 0; i < NSH; ++i) {
-            const int e = tid + NT * i, row = e / (D / 4), c4 = (e % (D / 4)) * 4;
-            *reinterpret_cast<float4*>(dst + row * KS + c4) = r[i];
+        for (int i = 0; i < 8; ++i) {
+            const float* p = S + (size_t)(32 * ks + 8 * lq + i) * D + col0;
+            if constexpr (NCT == 2) {
+                const float2 x = *reinterpret_cast<const float2*>(p);
+                s[i][0] = x.x;
+                s[i][1] = x.y;
+            } else {
+                s[i][0] = p[0];
+            }
         }
     };
-    auto put_rows_as = [&](float* dst, const auto& r, float scale, auto type) {   // 16-byte words of [64][D] of a type
-        constexpr int EW = Vec16<decltype(type)>::N;
+    auto strip_terms = [&](const float (&s)[8][NCT], u32x4 (&t)[NCT][N_TERMS]) {
 #pragma unroll
-        for (int i = 0; i < 64 * D / EW / NT; ++i) {
-            const int e = tid + NT * i, row = e / (D / EW), c = (e % (D / EW)) * EW;
-            float tmp[EW];
-            unpack16(r[i], tmp, type);
+        for (int ct = 0; ct < NCT; ++ct) {
+            float x[8];
 #pragma unroll
-            for (int j = 0; j < EW; j += 4)
-                *reinterpret_cast<float4*>(dst + row * KS + c + j) = make_float4(scale * tmp[j], scale * tmp[j + 1], scale * tmp[j + 2], scale * tmp[j + 3]);
+            for (int i = 0; i < 8; ++i) x[i] = s[i][ct];
+            split_terms(x, t[ct]);
         }
     };
-    float4 s0reg[NS0], dRreg[NSH], Ureg[NSH], dS1a[NSH], dS1b[NSH];
-    u32x4 dOreg[NPO], Kreg[NPT], Qreg[NPT];
+    auto put_rows = [&](const auto& dst, const auto& r) {   // [64][D] -> terms
+#pragma unroll
+        for (int p = 0; p < NPC; ++p) {
+            const int e = 8 * (tid + 256 * p);
+            std::remove_const_t<std::remove_reference_t<decltype(r[0])>> x = r[p];
+            typename std::remove_const_t<std::remove_reference_t<decltype(dst)>>::Terms t;
+            x.terms(t);
+            dst.put(e / D, e % D, t);
+        }
+    };
+    const float* S0g = a.ck + gc * ((size_t)D * D);
     const float* dS1g = a.dck + gc * ((size_t)D * D);
-    constexpr int NTL = (10 + NW - 1) / NW;   // lower 16 x 16 tiles of a 64 x 64 operand per wavefront
-    float atv[NTL][4], pmv[NTL][4];           // At and P where this lane will hold dAt and dP
-    float gate_in = 0.f;   // threads 0..191: one of g2, gam, kd of the chunk's tokens
-    if (tid < 3 * CB_C) gate_in = (tid < CB_C ? a.o.g2 : tid < 2 * CB_C ? a.o.gam : a.o.kd)[tok0 + (tid & 63)];
-    {
-        const float* S0g = a.ck + gc * ((size_t)D * D);
+    Strip S0;
+    Raw8<TO> dOr[NPC];
+    Raw8<float> Rr[NPC];
+    // one of g2, gam, kd, b' of the chunk's tokens
+    const float gate_in = (w == 0 ? a.o.g2 : w == 1 ? a.o.gam : w == 2 ? a.o.kd : a.o.bp)[tok0 + lane];
 #pragma unroll
-        for (int i = 0; i < NS0; ++i) s0reg[i] = ld4(S0g + 4 * (size_t)(tid + NT * i));   // rows of D floats: contiguous
+    for (int p = 0; p < NPC; ++p) dOr[p].load(a.dO + tok0 * D + 8 * (tid + 256 * p));
 #pragma unroll
-        for (int i = 0; i < NPO; ++i) dOreg[i] = reinterpret_cast<const u32x4*>(a.dO + tok0 * D)[tid + NT * i];
+    for (int ks = 0; ks < KS; ++ks) load_strip(S0[ks], S0g, ks);
 #pragma unroll
-        for (int i = 0; i < NSH; ++i) dRreg[i] = ld4(a.dR + tok0 * D + 4 * (size_t)(tid + NT * i));
-    }
-    auto issue_later = [&](int step) {   // step: a compile-time constant where it is called
-        if (step == 0) {
-#pragma unroll
-            for (int i = 0; i < NSH; ++i) Ureg[i] = ld4(a.Ug + tok0 * D + 4 * (size_t)(tid + NT * i));
-        } else if (step == 1) {
-#pragma unroll
-            for (int i = 0; i < NSH; ++i) dS1a[i] = ld4(dS1g + 4 * (size_t)(tid + NT * i));
-        } else if (step == 2) {
-#pragma unroll
-            for (int i = 0; i < NSH; ++i) dS1b[i] = (D > 64) ? ld4(dS1g + (size_t)64 * D + 4 * (size_t)(tid + NT * i)) : make_float4(0.f, 0.f, 0.f, 0.f);
-        } else if (step == 3) {
-#pragma unroll
-            for (int i = 0; i < NPT; ++i) {
-                Kreg[i] = reinterpret_cast<const u32x4*>(a.K + tok0 * D)[tid + NT * i];
-                Qreg[i] = reinterpret_cast<const u32x4*>(a.Q + tok0 * D)[tid + NT * i];
-            }
-        } else if (step == 4) {
-#pragma unroll
-            for (int s = 0; s < NTL; ++s) {
-                const int t = w + NW * s < 10 ? w + NW * s : 0;
-                const int ta = (0x3333222110 >> (4 * t)) & 15, tb = (0x3210210100 >> (4 * t)) & 15;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const size_t off = gc * (CB_C * CB_C) + (16 * ta + 4 * lq + j) * CB_C + 16 * tb + l16;
-                    atv[s][j] = a.o.At[off];
-                    pmv[s][j] = a.o.Pm[off];
-                }
-            }
-        }
-    };
-    // ---- stage 1: S0, dO', dR ------------------------------------------------------------------------------
-#pragma unroll
-    for (int i = 0; i < NS0; ++i) {
-        const int e = tid + NT * i, row = e / (D / 4), c4 = (e % (D / 4)) * 4;
-        *reinterpret_cast<float4*>(RA + row * KS + c4) = s0reg[i];
-    }
-    put_rows_as(RB, dOreg, a.la_scale, TO{});
-    put_rows_f32(RC, dRreg);
-    if (tid < 3 * CB_C) s_g2[tid] = gate_in;   // s_g2, s_gam, s_kd lie one behind the other
-    for (int e = tid; e < 8 * CB_C; e += NT) rs[e] = 0.f;   // rs and cs
+    for (int p = 0; p < NPC; ++p) Rr[p].load(a.dR + tok0 * D + 8 * (tid + 256 * p));
+    // ---- stage 1: dO S0 and dR S0, with dO and dR in LDS together where dO is one term ------------------------------
+    constexpr bool together = NO == 1;
+    put_rows(Ot, dOr);
+    if (together) put_rows(Rt, Rr);
+    s_g2[tid] = gate_in;   // s_g2, s_gam, s_kd, s_bp lie one behind the other
+    for (int e = tid; e < 8 * CB_C; e += 256) rs[e] = 0.f;   // rs and cs
     __syncthreads();
-    f32x4 Gdq[4], Gdk[4], Gu[4];
+    f32x4 Gdq[4][NCT], Gdk[4][NCT], Gu[4][NCT];
+    auto clear = [&](f32x4 (&G)[4][NCT]) {
 #pragma unroll
-    for (int ta = 0; ta < 4; ++ta) {
-        Gdq[ta] = f32x4{0.f, 0.f, 0.f, 0.f};
-        Gdk[ta] = f32x4{0.f, 0.f, 0.f, 0.f};
-        Gu[ta] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
-    for (int kv = 0; kv < D / 16; ++kv) {
-        issue_later(kv);
-        const float4 bs = ld4col(RA + (16 * kv + 4 * lq) * KS + 16 * w + l16, KS);
+            for (int ct = 0; ct < NCT; ++ct) G[ta][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto add_product = [&](const auto& X, const u32x4 (&b)[NCT][N_TERMS], int ks, f32x4 (&G)[4][NCT]) {
 #pragma unroll
         for (int ta = 0; ta < 4; ++ta) {
-            Gdq[ta] = mac16(ld4(RB + (16 * ta + l16) * KS + 16 * kv + 4 * lq), bs, Gdq[ta]);
-            Gdk[ta] = mac16(ld4(RC + (16 * ta + l16) * KS + 16 * kv + 4 * lq), bs, Gdk[ta]);
+            typename std::remove_const_t<std::remove_reference_t<decltype(X)>>::Terms x;
+            X.rows(16 * ta + l16, 32 * ks + 8 * lq, x);
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) G[ta][ct] = mfma_terms(x, b[ct], G[ta][ct]);
         }
+    };
+    // (the scheduling barriers keep the reads and the splitting of later steps from being drawn forward: ahead of their
+    // place they cost registers that are not there)
+    clear(Gdq);
+    if (together) clear(Gdk);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        u32x4 b[NCT][N_TERMS];
+        strip_terms(S0[ks], b);
+        add_product(Ot, b, ks, Gdq);
+        if (together) add_product(Rt, b, ks, Gdk);
+        __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int step = D / 16; step < 5; ++step) issue_later(step);
     __syncthreads();
-    // ---- stage 2: U and the first 64 rows of dS1; dP and dAt ---------------------------------------------------
-    float dot = 0.f;
-    put_rows_f32(RA, Ureg);
-    put_rows_f32(RAhi, dS1a);
+    if (!together) {
+        put_rows(Rt, Rr);
+        __syncthreads();
+        clear(Gdk);
 #pragma unroll
-    for (int i = 0; i < NSH; ++i)
-        dot += dS1a[i].x * s0reg[i].x + dS1a[i].y * s0reg[i].y + dS1a[i].z * s0reg[i].z + dS1a[i].w * s0reg[i].w;
-    __syncthreads();
-#pragma unroll 2
-    for (int kv = 0; kv < 4; ++kv) {
-        const float4 bs = ld4col(RAhi + (16 * kv + 4 * lq) * KS + 16 * w + l16, KS);
-#pragma unroll
-        for (int ta = 0; ta < 4; ++ta) Gu[ta] = mac16(ld4(RA + (16 * ta + l16) * KS + 16 * kv + 4 * lq), bs, Gu[ta]);
+        for (int ks = 0; ks < KS; ++ks) {
+            u32x4 b[NCT][N_TERMS];
+            strip_terms(S0[ks], b);
+            add_product(Rt, b, ks, Gdk);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
     }
-    f32x4 DPv[NTL], DAv[NTL];
+    // ---- stage 2: Uh dS1; dP and dAt, whose left operands (one tile of 16 rows each) come from memory -----------------
+#pragma unroll
+    for (int p = 0; p < NPC; ++p) Rr[p].load(a.Uh + tok0 * D + 8 * (tid + 256 * p));
+    Strip dS1;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) load_strip(dS1[ks], dS1g, ks);
+    put_rows(Rt, Rr);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    clear(Gu);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        u32x4 b[NCT][N_TERMS];
+        strip_terms(dS1[ks], b);
+        add_product(Rt, b, ks, Gu);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    Raw8<T> Kr[NPC], Qr[NPC];
+#pragma unroll
+    for (int p = 0; p < NPC; ++p) {
+        Kr[p].load(a.K + tok0 * D + 8 * (tid + 256 * p));
+        Qr[p].load(a.Q + tok0 * D + 8 * (tid + 256 * p));
+    }
+    f32x4 DPv[NTL], DAv[NTL];   // tile t of the list to wavefront t % 4
 #pragma unroll
     for (int s = 0; s < NTL; ++s) {
-        const int t = w + NW * s;   // uniform
+        const int t = w + 4 * s;   // uniform
+        DPv[s] = DAv[s] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (t < 10) {
             const int ta = (0x3333222110 >> (4 * t)) & 15, tb = (0x3210210100 >> (4 * t)) & 15;
+            const size_t row = (tok0 + 16 * ta + l16) * D + 8 * lq;
+            Raw8<TO> xo[KS];
+            Raw8<float> xr[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                xo[ks].load(a.dO + row + 32 * ks);
+                xr[ks].load(a.dR + row + 32 * ks);
+            }
+            float atv[4], pmv[4];   // At and P where this lane holds dAt and dP
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const size_t off = gc * (CB_C * CB_C) + (16 * ta + 4 * lq + j) * CB_C + 16 * tb + l16;
+                atv[j] = a.o.At[off];
+                pmv[j] = a.o.Pm[off];
+            }
             f32x4 accP = {0.f, 0.f, 0.f, 0.f}, accA = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-            for (int kv = 0; kv < D / 16; ++kv) {
-                const float4 bu = ld4(RA + (16 * tb + l16) * KS + 16 * kv + 4 * lq);
-                accP = mac16(ld4(RB + (16 * ta + l16) * KS + 16 * kv + 4 * lq), bu, accP);
-                accA = mac16(ld4(RC + (16 * ta + l16) * KS + 16 * kv + 4 * lq), bu, accA);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                u32x4 u[N_TERMS], o[NO], r[N_TERMS];
+                Rt.rows(16 * tb + l16, 32 * ks + 8 * lq, u);
+                xo[ks].terms(o);
+                xr[ks].terms(r);
+                accP = mfma_terms(o, u, accP);
+                accA = mfma_terms(r, u, accA);
             }
             const int i = 16 * tb + l16;
-            const float gi = s_g2[i];
+            const float gi = s_g2[i], bi = s_bp[i];
             float csum = 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 16 * ta + 4 * lq + j;
                 const float G = __builtin_amdgcn_exp2f(s_g2[r] - gi);
-                const float dp = (i <= r) ? accP[j] : 0.f, da = (i < r) ? -delta * accA[j] : 0.f;   // no At without the delta rule
-                const float e = da * atv[s][j] + dp * pmv[s][j];
-                const float rsum = lane_group_sum<16>(e);
+                const float dp = (i <= r) ? a.la_scale * accP[j] : 0.f, da = (i < r) ? -delta * accA[j] : 0.f;   // no At without the delta rule
+                const float e = da * atv[j] + dp * pmv[j];   // dP = dO' U^T, dAt = - dR U^T: these times b'_i
+                const float rsum = lane_group_sum<16>(bi * e);
                 if (l16 == 0) rs[tb * CB_C + r] = rsum;
                 csum += e;
-                DPv[s][j] = dp * G;
-                DAv[s][j] = da * G;
+                DPv[s][j] = (i <= r) ? bi * dp * G : 0.f;
+                DAv[s][j] = (i < r) ? bi * da * G : 0.f;
             }
             csum += lane_xor16(csum, lane);
             csum += lane_xor32(csum, lane);
             if (lq == 0) cs[ta * CB_C + i] = csum;
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
-    // ---- stage 3: the two 64 x 64 operands take the places of dO' and dR; the rest of dS1 ------------------------
+    // ---- stage 3: K, Q and the two 64 x 64 operands ---------------------------------------------------------------
+    auto put_paired = [&](const typename LY::KTile& dst, const Raw8<T> (&r)[NPC]) {
+#pragma unroll
+        for (int p = 0; p < NPC; ++p) {
+            const int e = 8 * (tid + 256 * p), row = e / D, c = e % D;
+            u32x4 t[NT];
+            r[p].terms(t);
+            if constexpr (NCT == 2) {   // columns 32 g + 2 m + ct to places 32 g + 16 ct + m
+                uint2 even[NT], odd[NT];
+#pragma unroll
+                for (int i = 0; i < NT; ++i) {
+                    even[i] = make_uint2(__builtin_amdgcn_perm(t[i][1], t[i][0], 0x05040100u), __builtin_amdgcn_perm(t[i][3], t[i][2], 0x05040100u));
+                    odd[i] = make_uint2(__builtin_amdgcn_perm(t[i][1], t[i][0], 0x07060302u), __builtin_amdgcn_perm(t[i][3], t[i][2], 0x07060302u));
+                }
+                dst.put(row, (c & ~31) + (c & 31) / 2, even);
+                dst.put(row, (c & ~31) + 16 + (c & 31) / 2, odd);
+            } else {
+                dst.put(row, c, t);
+            }
+        }
+    };
+    put_paired(Kt, Kr);
+    put_paired(Qt, Qr);
 #pragma unroll
     for (int s = 0; s < NTL; ++s) {
-        const int t = w + NW * s;
-        if (t < 10) {
-            const int ta = (0x3333222110 >> (4 * t)) & 15, tb = (0x3210210100 >> (4 * t)) & 15;
-            const int i = 16 * tb + l16;
+        const int t = w + 4 * s;   // tiles 10, 11 of the list: those above the diagonal that a product over 32 tokens meets
+        const int ta = (int)((0x203333222110ull >> (4 * t)) & 15), tb = (int)((0x313210210100ull >> (4 * t)) & 15);
+        const int i = 16 * tb + l16;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = 16 * ta + 4 * lq + j;
+            Pf[r * MS + i] = DPv[s][j];
+            if (i < r) {
+                Af[r * MS + i] = DAv[s][j];
+                Af[i * MS + r] = DAv[s][j];
+            } else if (i == r) {
+                Af[r * MS + i] = 0.f;
+            }
+        }
+    }
+    // the softmax branch's share of dQ, which the result is added to: asked for before the products below
+    float oldq[4][4][NCT];
+#pragma unroll
+    for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float* p = a.dQ + (tok0 + 16 * ta + 4 * lq + j) * D + col0;
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) oldq[ta][j][ct] = p[ct];
+        }
+    __syncthreads();
+    f32x4 dQa[4][NCT], dKa[4][NCT];
+    float esum = 0.f;   // E_r is needed only as its sum over the chunk
+#pragma unroll
+    for (int tp = 0; tp < 2; ++tp) {
+        float kc[NCT][8], qc[NCT][8];   // K and Q: the lane's columns, rows 4 lq + j of token tiles 2 tp and 2 tp + 1
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct) {
+            u32x4 tk[NT], tq[NT];
+            Kt.cols(32 * tp, 16 * (NCT * w + ct), l16, lq, tk);
+            Qt.cols(32 * tp, 16 * (NCT * w + ct), l16, lq, tq);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                kc[ct][i] = qc[ct][i] = 0.f;
+#pragma unroll
+                for (int n = NT - 1; n >= 0; --n) {   // exact: the terms of one number
+                    kc[ct][i] += __uint_as_float(i & 1 ? tk[n][i / 2] & 0xffff0000u : tk[n][i / 2] << 16);
+                    qc[ct][i] += __uint_as_float(i & 1 ? tq[n][i / 2] & 0xffff0000u : tq[n][i / 2] << 16);
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ta = 2 * tp + h;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 16 * ta + 4 * lq + j;
-                RB[r * MS + i] = DPv[s][j];
-                if (i < r) {
-                    RC[r * MS + i] = DAv[s][j];
-                    RC[i * MS + r] = DAv[s][j];
-                } else if (i == r) {
-                    RC[r * MS + i] = 0.f;
+                const float gam = s_gam[r], kd = s_kd[r], bp = s_bp[r];
+                float x = 0.f, u = 0.f;
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    const float k = kc[ct][4 * h + j], q = qc[ct][4 * h + j], gq = a.la_scale * Gdq[ta][ct][j];
+                    const float ku = kd * Gu[ta][ct][j], eu = k * ku;
+                    u += eu;
+                    x += gam * (q * gq - delta * k * Gdk[ta][ct][j]) - bp * eu;
+                    dQa[ta][ct][j] = gam * gq;
+                    dKa[ta][ct][j] = bp * ku - delta * gam * Gdk[ta][ct][j];
+                }
+                esum += bp * u;
+                const float xs = lane_group_sum<16>(x), us = lane_group_sum<16>(u);
+                if (l16 == 0) {
+                    gk[w * CB_C + r] = xs;
+                    gu[w * CB_C + r] = us;
                 }
             }
         }
     }
-    if (D > 64) {
-        put_rows_f32(RAhi, dS1b);
-#pragma unroll
-        for (int i = 0; i < NSH; ++i) {
-            const float4 x = dS1b[i], y = s0reg[(NS0 > NSH ? NSH : 0) + i];
-            dot += x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
-        }
-        __syncthreads();
-#pragma unroll 2
-        for (int kv = 4; kv < D / 16; ++kv) {
-            const float4 bs = ld4col(RAhi + (16 * (kv - 4) + 4 * lq) * KS + 16 * w + l16, KS);
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta) Gu[ta] = mac16(ld4(RA + (16 * ta + l16) * KS + 16 * kv + 4 * lq), bs, Gu[ta]);
-        }
-    }
-    __syncthreads();
-    // ---- stage 4: K and Q ----------------------------------------------------------------------------------------
-    put_rows_as(RA, Kreg, 1.f, T{});
-    put_rows_as(RAhi, Qreg, 1.f, T{});
-    {   // <dS1, S0>: the wavefront's sum
-        float x = lane_group_sum<64>(dot);
-        if (lane == 0) s_dot[w] = x;
-    }
-    __syncthreads();
-    f32x4 dQa[4], dKa[4];
-    float4 kcs[4], qcs[4];   // K and Q: rows 4 lq + j of every token tile, the wavefront's own columns
-#pragma unroll
-    for (int tb = 0; tb < 4; ++tb) {
-        kcs[tb] = ld4col(RA + (16 * tb + 4 * lq) * KS + 16 * w + l16, KS);
-        qcs[tb] = ld4col(RAhi + (16 * tb + 4 * lq) * KS + 16 * w + l16, KS);
-    }
-    float esum = 0.f;   // E_r is needed only as its sum over the chunk
-#pragma unroll
-    for (int ta = 0; ta < 4; ++ta) {
-        const float kq[4] = {kcs[ta].x, kcs[ta].y, kcs[ta].z, kcs[ta].w}, qq[4] = {qcs[ta].x, qcs[ta].y, qcs[ta].z, qcs[ta].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = 16 * ta + 4 * lq + j;
-            const float gam = s_gam[r], kd = s_kd[r];
-            const float eu = kd * kq[j] * Gu[ta][j];
-            const float x = gam * (qq[j] * Gdq[ta][j] - delta * kq[j] * Gdk[ta][j]) - eu;
-            const float xs = lane_group_sum<16>(x);
-            esum += eu;
-            if (l16 == 0) gk[w * CB_C + r] = xs;
-            dQa[ta][j] = gam * Gdq[ta][j];
-            dKa[ta][j] = kd * Gu[ta][j] - delta * gam * Gdk[ta][j];
-        }
-    }
     esum = lane_group_sum<64>(esum);
     if (lane == 0) ge[w] = esum;
-    // the softmax branch's share of dQ, which the result is added to: asked for before the products below
-    float oldq[4][4];
+    auto row_terms = [&](const float* M, int row, int col, u32x4 (&t)[N_TERMS]) {   // 8 of a row
+        const float4 lo = ld4(M + row * MS + col), hi = ld4(M + row * MS + col + 4);
+        const float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        split_terms(x, t);
+    };
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        u32x4 kb[NCT][NT], qb[NCT][NT];
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct) {
+            Kt.cols_in_order(32 * ks, 16 * (NCT * w + ct), l16, lq, kb[ct]);
+            Qt.cols_in_order(32 * ks, 16 * (NCT * w + ct), l16, lq, qb[ct]);
+        }
+#pragma unroll
+        for (int ta = 0; ta < 4; ++ta) {
+            u32x4 m[N_TERMS];
+            if (ks <= ta >> 1) {
+                row_terms(Pf, 16 * ta + l16, 32 * ks + 8 * lq, m);
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) dQa[ta][ct] = mfma_terms(m, kb[ct], dQa[ta][ct]);
+            }
+            row_terms(Af, 16 * ta + l16, 32 * ks + 8 * lq, m);
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) dKa[ta][ct] = mfma_terms(m, kb[ct], dKa[ta][ct]);
+            if (ks >= ta >> 1) {   // (dP . Gamma)^T Q
+                float x[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] = Pf[(32 * ks + 8 * lq + i) * MS + 16 * ta + l16];
+                split_terms(x, m);
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) dKa[ta][ct] = mfma_terms(m, qb[ct], dKa[ta][ct]);
+            }
+        }
+    }
 #pragma unroll
     for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) oldq[ta][j] = a.dQ[(tok0 + 16 * ta + 4 * lq + j) * D + 16 * w + l16];
-#pragma unroll
-    for (int tb = 0; tb < 4; ++tb) {
-        const float4 kc = kcs[tb], qc = qcs[tb];
-#pragma unroll
-        for (int ta = 0; ta < 4; ++ta) {
-            if (tb <= ta) dQa[ta] = mac16(ld4(RB + (16 * ta + l16) * MS + 16 * tb + 4 * lq), kc, dQa[ta]);
-            dKa[ta] = mac16(ld4(RC + (16 * ta + l16) * MS + 16 * tb + 4 * lq), kc, dKa[ta]);
-            // (dP . Gamma)^T Q: rows tb of dP (as contraction index) against the columns of tile ta
-            if (tb >= ta) dKa[ta] = mac16(ld4col(RB + (16 * tb + 4 * lq) * MS + 16 * ta + l16, MS), qc, dKa[ta]);
-        }
-    }
-#pragma unroll
-    for (int ta = 0; ta < 4; ++ta) {
-#pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const size_t off = (tok0 + 16 * ta + 4 * lq + j) * D + 16 * w + l16;
-            a.dQ[off] = oldq[ta][j] + dQa[ta][j];
-            a.dK[off] = dKa[ta][j];
+            const size_t off = (tok0 + 16 * ta + 4 * lq + j) * D + col0;
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) {
+                a.dQ[off + ct] = oldq[ta][j][ct] + dQa[ta][ct][j];
+                a.dK[off + ct] = dKa[ta][ct][j];
+            }
         }
-    }
     __syncthreads();
     // ---- the gates: d ln gamma of every token, its sum from the back, dalpha; dbeta ----------------------------
     if (w == 0) {
         const int r = 63 - lane;   // reversed, so that the inclusive scan below sums from the chunk's end
-        float dl = 0.f, et = 0.f;
+        float dl = 0.f, et = 0.f, db = 0.f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) dl += rs[q * CB_C + r];
+        for (int q = 0; q < 4; ++q) { dl += rs[q * CB_C + r]; db += cs[q * CB_C + r]; }
+        dl -= s_bp[r] * db;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) dl -= cs[q * CB_C + r];
-#pragma unroll
-        for (int q = 0; q < NW; ++q) { dl += gk[q * CB_C + r]; et += ge[q]; }
-        float dt = 0.f;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) dt += s_dot[q];
+        for (int q = 0; q < 4; ++q) { dl += gk[q * CB_C + r]; et += ge[q]; db += gu[q * CB_C + r]; }
+        constexpr int ND = D / CB_NV * (D / 32);
+        const float dt = lane_group_sum<64>(lane < ND ? a.dot[gc * ND + lane] : 0.f);   // <dS1, S0>
         // the decay carried over the chunk: not a function of the alphas for a softmax chunk in the variant without decay
         const bool carry_fixed = a.chunk_mask && a.freeze_on_softmax && a.mask[gc] != 0;
         if (r == 63) dl += et + (carry_fixed ? 0.f : a.o.gamC[gc] * dt);
@@ -882,33 +1044,24 @@ __global__ __launch_bounds__(D * 4) void gdn_chunk_grads_kernel(const GradArgs<T
         const size_t t = tok0 + r;
         const bool frozen = a.freeze_on_softmax && !a.chunk_mask && a.mask[t] != 0;   // its alpha counted as 1
         a.dalpha[t] = frozen ? 0.f : dl / fmaxf(a.alpha[t], 1e-30f);
-        float db = 0.f;
-        const size_t n_tok = (size_t)a.BH * a.L;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) db += a.dbeta_part[(size_t)q * n_tok + t];
-        a.dbeta[t] = db;
+        a.dbeta[t] = !a.chunk_mask && a.mask[t] != 0 ? 0.f : db;   // routing per token: a softmax token does not write
         if (a.g_nla != nullptr) a.g_nla[t] = 0.f;
     }
 }
-
-template <int D>
-constexpr size_t grads_lds_bytes() {
-    return sizeof(float) * (4 * (size_t)CB_C * (D + 4) + 3 * CB_C + 8 * CB_C + 2 * (D / 16) * CB_C + 64);
-}
-
 
 // ---- the linear branch's output rows from what the forward-by-chunks leaves ---------------------------------------------
 // O = la (diag(gamma) Q S0^T + P U) for every chunk at once, fp32: S0 the state at the chunk's start (ck), U the rows
 // gdn_chunk_seq_kernel<.., 0> wrote, P and gamma from the chunk's operands.  Needed where the backward pass must know
 // the branch's rows (the merges that normalise them, Eq. 21).  One block per (chunk, batch*head); wavefront w owns a
 // quarter of the value columns for all 64 tokens, so every element of S0 and U is read once per block, straight
-// from memory as the right operand; Q and P, which every wavefront reads whole, go through LDS.
-// O_la may be Ug itself: a wavefront has read all it needs of U before it writes, and both are its own columns.
+// from memory as the right operand; Q and P, which every wavefront reads whole, go through LDS (P with its columns times
+// b': P U = P diag(b') Uh).
+// O_la may be Uh itself: a wavefront has read all it needs of it before it writes, and both are its own columns.
 // Head grouping: BH counts output heads, Q and the operands are those of linear head bh / G.  inner: 0 leaves P U out
 // (the ablation whose linear branch reads the carried state only).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict__ Q, const ChunkOps o,
-                                                           const float* __restrict__ ck, const float* Ug,
+                                                           const float* __restrict__ ck, const float* Uh,
                                                            float* O_la, const int L, const int BH, const int G,
                                                            const int inner, const float la_scale) {
     constexpr int KS = D + 4, MS = CB_MS, VW = D / 4, VT = VW / 16;   // value columns per wavefront, in tiles of 16
@@ -932,7 +1085,8 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
     }
     for (int e = tid; e < CB_C * CB_C / 4; e += 256) {
         const int row = e / 16, c4 = (e % 16) * 4;
-        *reinterpret_cast<float4*>(Ps + row * MS + c4) = ld4(o.Pm + gl * (CB_C * CB_C) + row * CB_C + c4);
+        const float4 p = ld4(o.Pm + gl * (CB_C * CB_C) + row * CB_C + c4), b = ld4(o.bp + tokl + c4);
+        *reinterpret_cast<float4*>(Ps + row * MS + c4) = make_float4(p.x * b.x, p.y * b.y, p.z * b.z, p.w * b.w);
     }
     if (tid < CB_C) s_gam[tid] = o.gam[tokl + tid];
     __syncthreads();
@@ -972,7 +1126,7 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
         float4 b[VT];
 #pragma unroll
         for (int vt = 0; vt < VT; ++vt)
-            b[vt] = ld4col(Ug + (tok0 + 16 * tb + 4 * lq) * D + VW * w + 16 * vt + l16, D);
+            b[vt] = ld4col(Uh + (tok0 + 16 * tb + 4 * lq) * D + VW * w + 16 * vt + l16, D);
 #pragma unroll
         for (int tt = tb; tt < 4; ++tt) {
             const float4 a = ld4(Ps + (16 * tt + l16) * MS + 16 * tb + 4 * lq);
@@ -1034,77 +1188,73 @@ nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K,
     return check_launch("gdn_bwd_prep");
 }
 
-template <typename T, typename TX, int D, int DIR, bool RES>
+template <typename T, typename TX, int D, int DIR>
 static bool launch_seq_t(const SeqArgs<T, TX>& a, hipStream_t st) {
-    auto kern = gdn_chunk_seq_kernel<T, TX, D, DIR, RES>;
-    constexpr size_t lds = seq_lds_bytes<T, D, DIR>();
+    auto kern = gdn_chunk_seq_kernel<T, TX, D, DIR>;
+    constexpr size_t lds = SeqLds<T, TX, D, DIR>::bytes;
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * (D / CB_NV))), dim3(512), lds, st, a);
     return true;
 }
-template <int DIR, bool RES, typename T, typename TX>
+template <int DIR, typename T, typename TX>
 static bool launch_seq_d(const FwdPlan& pl, const SeqArgs<T, TX>& a, hipStream_t st) {
-    return pl.d == 64 ? launch_seq_t<T, TX, 64, DIR, RES>(a, st) : launch_seq_t<T, TX, 128, DIR, RES>(a, st);
+    return pl.d == 64 ? launch_seq_t<T, TX, 64, DIR>(a, st) : launch_seq_t<T, TX, 128, DIR>(a, st);
 }
 
-// The states at the chunk starts, ck [BHG][L/64][d][d], with U (and, unless NULL, the residuals Uh) [BHG][L][d] of every
-// chunk; S_final (or NULL): the state after the last token.  ops as launch_gdn_bwd_prep left them, with At if Uh is
-// wanted.  Head grouping (pl.G > 1): V, the states, U and Uh have pl.BHG heads.
-template <typename T>
-static bool launch_states_t(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init, float* S_final,
-                            float* ck, float* Ug, float* Uh, hipStream_t st) {
-    const SeqArgs<T, T> a{(const T*)K, nullptr, (const T*)V, chunk_ops(pl, ops, Uh != nullptr), nullptr, S_init, ck, Ug, Uh,
-                       nullptr, nullptr, S_final, pl.L, pl.BHG, pl.G, pl.la_scale, pl.linear_op == 0};
-    return Uh != nullptr ? launch_seq_d<0, true>(pl, a, st) : launch_seq_d<0, false>(pl, a, st);
-}
-nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init,
-                                    float* S_final, float* ck, float* Ug, float* Uh, hipStream_t st) {
-    const bool ok = pl.dtype == NATS_BF16 ? launch_states_t<bf16_t>(pl, K, V, ops, S_init, S_final, ck, Ug, Uh, st)
-                                          : launch_states_t<float>(pl, K, V, ops, S_init, S_final, ck, Ug, Uh, st);
-    if (!ok) { set_error("gdn_chunk_states: the kernel's LDS size was refused"); return NATS_ERR_HIP; }
+// The states at the chunk starts, ck [BHG][L/64][d][d], with the residuals Uh [BHG][L][d] of every chunk; S_final (or
+// NULL): the state after the last token.  ops as launch_gdn_bwd_prep left them (with_at as there).  Head grouping
+// (pl.G > 1): V, the states and Uh have pl.BHG heads.
+nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, bool with_at,
+                                    const float* S_init, float* S_final, float* ck, float* Uh, hipStream_t st) {
+    auto go = [&](auto t) {
+        using T = decltype(t);
+        const SeqArgs<T, T> a{(const T*)K, nullptr, (const T*)V, chunk_ops(pl, ops, with_at), S_init, ck, Uh, nullptr, nullptr, S_final, pl.L,
+                              pl.BHG, pl.G, pl.la_scale, pl.linear_op == 0};
+        return launch_seq_d<0>(pl, a, st);
+    };
+    if (!(pl.dtype == NATS_BF16 ? go(bf16_t{}) : go(float{}))) {
+        set_error("gdn_chunk_states: the kernel's LDS size was refused");
+        return NATS_ERR_HIP;
+    }
     return check_launch("gdn_chunk_states");
 }
 
-// O_la [BHG][L][d] f32 from ops (after launch_gdn_bwd_prep), ck and Ug (after launch_gdn_chunk_states; O_la may be Ug).
+// O_la [BHG][L][d] f32 from ops (after launch_gdn_bwd_prep), ck and Uh (after launch_gdn_chunk_states; O_la may be Uh).
 template <typename T>
-static void launch_out_t(const FwdPlan& pl, const void* Q, const ChunkOps& o, const float* ck, const float* Ug, float* O_la,
+static void launch_out_t(const FwdPlan& pl, const void* Q, const ChunkOps& o, const float* ck, const float* Uh, float* O_la,
                          hipStream_t st) {
     const dim3 grid((unsigned)(pl.BHG * (pl.L / CB_C)));
     const int inner = pl.inner_chunk != 1;
     if (pl.d == 64)
-        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 64>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Ug, O_la, pl.L, pl.BHG,
+        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 64>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Uh, O_la, pl.L, pl.BHG,
                            pl.G, inner, pl.la_scale);
     else
-        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 128>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Ug, O_la, pl.L, pl.BHG,
+        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 128>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Uh, O_la, pl.L, pl.BHG,
                            pl.G, inner, pl.la_scale);
 }
-nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Ug,
+nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Uh,
                                  float* O_la, hipStream_t st) {
     const ChunkOps o = chunk_ops(pl, ops, with_at);
-    if (pl.dtype == NATS_BF16) launch_out_t<bf16_t>(pl, Q, o, ck, Ug, O_la, st);
-    else launch_out_t<float>(pl, Q, o, ck, Ug, O_la, st);
+    if (pl.dtype == NATS_BF16) launch_out_t<bf16_t>(pl, Q, o, ck, Uh, O_la, st);
+    else launch_out_t<float>(pl, Q, o, ck, Uh, O_la, st);
     return check_launch("gdn_chunk_out");
 }
 
-// The state gradients behind every chunk, dck [BH][L/64][d][d]; dV (every row), dbeta_part [d/16][BH][L], dS0 (or NULL).
-// dO_f32: dO is fp32 whatever the tensors' type.
-template <typename T, typename TO>
-static bool launch_state_grads_t(const FwdPlan& pl, const void* Q, const void* K, const void* dO, const uint8_t* tok_mask,
-                                 float* ops, float* dck, float* Uh, float* dV, float* dbeta_part, float* dS0, hipStream_t st) {
-    const SeqArgs<T, TO> a{(const T*)K, (const T*)Q, (const TO*)dO, chunk_ops(pl, ops), tok_mask, nullptr, dck,
-                           nullptr, Uh, dV, dbeta_part, dS0, pl.L, pl.BH, 1, pl.la_scale, pl.linear_op == 0};
-    return launch_seq_d<1, true>(pl, a, st);
-}
+// The state gradients behind every chunk, dck [BH][L/64][d][d], their products with the states ck (dot: at most d / 4 parts
+// per chunk); dV (every row), dS0 (or NULL).  dO_f32: dO is fp32 whatever the tensors' type.
 nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
-                                         const uint8_t* mask, float* ops, float* dck, float* Uh, float* dV,
-                                         float* dbeta_part, float* dS0, hipStream_t st) {
-    const uint8_t* tok_mask = pl.routing == NATS_ROUTE_CHUNK ? nullptr : mask;
-    bool ok;
-#define NATS_SG(TT, TO) launch_state_grads_t<TT, TO>(pl, Q, K, dO, tok_mask, ops, dck, Uh, dV, dbeta_part, dS0, st)
-    if (pl.dtype == NATS_F32) ok = NATS_SG(float, float);
-    else ok = dO_f32 ? NATS_SG(bf16_t, float) : NATS_SG(bf16_t, bf16_t);
-#undef NATS_SG
+                                         float* ops, const float* ck, float* dck, float* dot, float* dV, float* dS0,
+                                         hipStream_t st) {
+    auto go = [&](auto t, auto to) {
+        using T = decltype(t);
+        using TO = decltype(to);
+        const SeqArgs<T, TO> a{(const T*)K, (const T*)Q, (const TO*)dO, chunk_ops(pl, ops), nullptr, dck, dV, ck, dot, dS0, pl.L,
+                               pl.BH, 1, pl.la_scale, pl.linear_op == 0};
+        return launch_seq_d<1>(pl, a, st);
+    };
+    const bool ok = pl.dtype == NATS_F32 ? go(float{}, float{}) : dO_f32 ? go(bf16_t{}, float{}) : go(bf16_t{}, bf16_t{});
     if (!ok) { set_error("gdn_chunk_state_grads: the kernel's LDS size was refused"); return NATS_ERR_HIP; }
     return check_launch("gdn_chunk_state_grads");
 }
@@ -1112,25 +1262,24 @@ nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const
 template <typename T, typename TO, int D>
 static bool launch_grads_t(const FwdPlan& pl, const GradArgs<T, TO>& a, hipStream_t st) {
     auto kern = gdn_chunk_grads_kernel<T, TO, D>;
-    constexpr size_t lds = grads_lds_bytes<D>();
+    constexpr size_t lds = GradLds<T, TO, D>::bytes;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.BH * (pl.L / CB_C))), dim3(D * 4), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.BH * (pl.L / CB_C))), dim3(256), lds, st, a);
     return true;
 }
 
 // dQ += the linear branch's share; dK, dalpha, dbeta = it; g_nla (optional) cleared.  ck, dck: the states and state
-// gradients per chunk; Ug, dR (= the linear branch's dV) [BH][L][d]; dbeta_part [d/16][BH][L].  dO_f32: dO is fp32
-// whatever the tensors' type.
+// gradients per chunk; Uh, dR (= the linear branch's dV) [BH][L][d]; dot as launch_gdn_chunk_state_grads left it.  dO_f32: dO is fp32 whatever the tensors' type.
 nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
                                    const float* alpha, const uint8_t* mask, float* ops, const float* ck, const float* dck,
-                                   const float* Ug, const float* dR, const float* dbeta_part, float* dQ, float* dK,
+                                   const float* Uh, const float* dR, const float* dot, float* dQ, float* dK,
                                    float* dalpha, float* dbeta, float* g_nla, float* dscore_la, hipStream_t st) {
     auto go = [&](auto t, auto to) {
         using T = decltype(t);
         using TO = decltype(to);
         const GradArgs<T, TO> a{(const T*)Q, (const T*)K, (const TO*)dO, chunk_ops(pl, ops), alpha, mask, ck, dck,
-                                Ug, dR, dbeta_part, dQ, dK, dalpha, dbeta, g_nla, dscore_la, pl.L, pl.BH, pl.la_scale,
+                                Uh, dR, dot, dQ, dK, dalpha, dbeta, g_nla, dscore_la, pl.L, pl.BH, pl.la_scale,
                                 pl.linear_op == 0, pl.freeze_on_softmax, pl.routing == NATS_ROUTE_CHUNK};
         return pl.d == 64 ? launch_grads_t<T, TO, 64>(pl, a, st) : launch_grads_t<T, TO, 128>(pl, a, st);
     };

@@ -281,14 +281,14 @@ nats_status launch_gdn_checkpoints(const FwdPlan& pl, const void* K, const void*
 size_t chunk_ops_floats(const FwdPlan& pl, bool with_at);
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
                                 const uint8_t* mask, float* ops, bool with_at, hipStream_t st);
-nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, const float* S_init,
-                                    float* S_final, float* ck, float* Ug, float* Uh, hipStream_t st);
+nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, bool with_at,
+                                    const float* S_init, float* S_final, float* ck, float* Uh, hipStream_t st);
 nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
-                                         const uint8_t* mask, float* ops, float* dck, float* Uh, float* dV,
-                                         float* dbeta_part, float* dS0, hipStream_t st);
+                                         float* ops, const float* ck, float* dck, float* dot, float* dV, float* dS0,
+                                         hipStream_t st);
 nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
                                    const float* alpha, const uint8_t* mask, float* ops, const float* ck, const float* dck,
-                                   const float* Ug, const float* dR, const float* dbeta_part, float* dQ, float* dK,
+                                   const float* Uh, const float* dR, const float* dot, float* dQ, float* dK,
                                    float* dalpha, float* dbeta, float* g_nla, float* dscore_la, hipStream_t st);
 nats_status launch_visible_rows(const FwdPlan& pl, const int32_t* cnt, int32_t* vis, hipStream_t st);
 nats_status launch_softmax_bwd_own_chunk(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* dO,
@@ -301,7 +301,7 @@ nats_status launch_zero_f32(float* dst, size_t n, hipStream_t st);
 nats_status launch_merge_bwd(const FwdPlan& pl, int mode, float eps, const float* O_la, const float* O_nla,
                              const void* dO, const float* w_nla, const float* w_la, float* dO_la, float* dO_nla,
                              float* dw_nla, float* dw_la, hipStream_t st);
-nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Ug,
+nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Uh,
                                  float* O_la, hipStream_t st);
 nats_status launch_widen_bf16(const void* src, float* dst, size_t n, hipStream_t st);
 nats_status launch_score_gradients_chunk(const FwdPlan& pl, const float* g_nla, const float* ds_la_part, float* dscore_nla,

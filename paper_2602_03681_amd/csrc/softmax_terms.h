@@ -90,16 +90,34 @@ struct Raw8 {
     }
 };
 
+// 4 floats -> their bf16 terms
+__device__ __forceinline__ void split_terms(const float (&x)[4], uint2 (&t)[N_TERMS]) {
+    float r[4], q[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        r[k] = x[k] - __uint_as_float(__float_as_uint(x[k]) & 0xffff0000u);
+        q[k] = r[k] - __uint_as_float(__float_as_uint(r[k]) & 0xffff0000u);
+    }
+    t[0] = make_uint2(high_halves(x[0], x[1]), high_halves(x[2], x[3]));
+    t[1] = make_uint2(high_halves(r[0], r[1]), high_halves(r[2], r[3]));
+    t[2] = make_uint2(high_halves(q[0], q[1]), high_halves(q[2], q[3]));
+}
+
 // A tile of 64 rows of D elements in LDS: one plane [64][D + LDS_PAD] of bf16 per term.  Operand of a product over the
 // columns: 16-byte reads along a row (rows()).  Operand of a product over the rows: the transposing read of gfx950
 // (cols()), so that no transposed copy is made.
-template <int D, int N>
+template <int D, int N, int ROWS = 64>
 struct TermTile {
-    static constexpr int RS = D + LDS_PAD, PLANE = 64 * RS, BYTES = N * PLANE * 2;
+    static constexpr int RS = D + LDS_PAD, PLANE = ROWS * RS, BYTES = N * PLANE * 2;
+    using Terms = u32x4[N];
     uint16_t* p;
     __device__ __forceinline__ void put(int row, int col, const u32x4 (&t)[N]) const {
 #pragma unroll
         for (int i = 0; i < N; ++i) *reinterpret_cast<u32x4*>(p + i * PLANE + row * RS + col) = t[i];
+    }
+    __device__ __forceinline__ void put(int row, int col, const uint2 (&t)[N]) const {   // four elements
+#pragma unroll
+        for (int i = 0; i < N; ++i) *reinterpret_cast<uint2*>(p + i * PLANE + row * RS + col) = t[i];
     }
     // row `row`, columns col .. col + 7 (16x16x32 operand with the columns as contraction index: row l16, col + 8 lq)
     __device__ __forceinline__ void rows(int row, int col, u32x4 (&t)[N]) const {
@@ -111,13 +129,21 @@ struct TermTile {
     // a lane's registers.  The read hands a group of 16 lanes, each of which names 4 elements of one row, the 4 x 16
     // block transposed: lane 4 m + n of the group names columns 4 n .. 4 n + 3 of row m and receives column 4 m + n.
     __device__ __forceinline__ void cols(int r0, int col, int l16, int lq, u32x4 (&t)[N]) const {
+        cols_from<4, 16>(r0, col, l16, lq, t);
+    }
+    // the same with rows r0 + 8 lq + j in slots j < 8: the order in which rows() reads the other operand
+    __device__ __forceinline__ void cols_in_order(int r0, int col, int l16, int lq, u32x4 (&t)[N]) const {
+        cols_from<8, 4>(r0, col, l16, lq, t);
+    }
+    template <int STEP, int HI>   // slots j < 4: rows r0 + STEP lq + j; the others: HI rows further
+    __device__ __forceinline__ void cols_from(int r0, int col, int l16, int lq, u32x4 (&t)[N]) const {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            const uint16_t* a = p + i * PLANE + (r0 + 4 * lq + (l16 >> 2)) * RS + col + 4 * (l16 & 3);
+            const uint16_t* a = p + i * PLANE + (r0 + STEP * lq + (l16 >> 2)) * RS + col + 4 * (l16 & 3);
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)a);
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(a + 16 * RS));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(a + HI * RS));
             const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
             t[i] = u32x4{l2.x, l2.y, h2.x, h2.y};
         }
