@@ -205,9 +205,11 @@ static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl, bo
 // the reverse sweep and the partial sums of its blocks.
 struct BwdPlan {
     size_t off_onla, off_lse, off_dvec, off_ckpt, off_scratch, off_dqp, off_dkp, off_dap, off_dbp, off_skp, off_svp, off_sgp,
-        off_gnla, off_vis, off_dslap, off_ops, off_uh, off_dck, off_dot, off_vht, total;
-    // head grouping: the pass runs once per member of the groups on `total` bytes; behind them, one member's heads
-    // of V, dO, the initial state (gathered) and the member's gradients before they are added or scattered
+        off_gnla, off_vis, off_dslap, off_ops, off_uh, off_dck, off_dot, off_vht, off_pdq, off_pdk, off_pda, off_pdb, off_pgn,
+        off_psl, total;
+    // head grouping member by member (G > 1): the pass runs once per member of the groups on `total` bytes; behind them,
+    // one member's heads of V, dO, the initial state (gathered) and the member's gradients before they are added or
+    // scattered
     int G;
     size_t off_gv, off_gdo, off_gdv, off_gdq, off_gdk, off_gda, off_gdb, off_gs0, off_gds0, off_ggn, off_ggl, off_gsn,
         off_gsl, off_gqn, off_gkn, off_gdqn, off_gdkn, total_grouped;
@@ -221,11 +223,12 @@ struct BwdPlan {
 };
 static void plan_bwd(const FwdPlan& pl, BwdPlan* bp) {
     const size_t n_tok = (size_t)pl.BH * pl.L, ns = (size_t)pl.d / BWD_SWEEP_ROWS;
+    const size_t n_out = (size_t)pl.BHG * pl.L;   // per output head (pl.G = 1: the same)
     size_t off = align_up(pl.off_ola, 256);   // first byte behind cnt, idx, n_s, Kc, Vc
-    bp->off_onla = off;    off = align_up(off + n_tok * pl.d * 4, 256);
-    bp->off_lse = off;     off = align_up(off + n_tok * 4, 256);
-    bp->off_dvec = off;    off = align_up(off + n_tok * 4, 256);
-    bp->off_ckpt = off;    off = align_up(off + (size_t)pl.BH * (pl.L / 64) * pl.d * pl.d * 4, 256);
+    bp->off_onla = off;    off = align_up(off + n_out * pl.d * 4, 256);
+    bp->off_lse = off;     off = align_up(off + n_out * 4, 256);
+    bp->off_dvec = off;    off = align_up(off + n_out * 4, 256);
+    bp->off_ckpt = off;    off = align_up(off + (size_t)pl.BHG * (pl.L / 64) * pl.d * pl.d * 4, 256);
     // the token-by-token adjoint of the linear branch (math = NATS_MATH_FP32): the parked rows of a chunk and the
     // d/16 partial sums per (batch, head)
     const size_t tk = pl.math == NATS_MATH_FP32 ? 1 : 0;
@@ -235,19 +238,27 @@ static void plan_bwd(const FwdPlan& pl, BwdPlan* bp) {
     bp->off_dap = off;     off = align_up(off + tk * ns * n_tok * 4, 256);
     bp->off_dbp = off;     off = align_up(off + tk * ns * n_tok * 4, 256);
     // partial dK, dV and column sums of the softmax branch, one per query segment and compacted key
-    bp->off_skp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_tok * pl.d * 4, 256);
-    bp->off_svp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_tok * pl.d * 4, 256);
-    bp->off_sgp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_tok * 4, 256);
+    bp->off_skp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_out * pl.d * 4, 256);
+    bp->off_svp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_out * pl.d * 4, 256);
+    bp->off_sgp = off;     off = align_up(off + (size_t)BWD_DKV_SEGMENTS * n_out * 4, 256);
     bp->off_gnla = off;    off = align_up(off + n_tok * 4, 256);   // column sums of Eq. 15 when only their chunk sums are asked for
     bp->off_vis = off;     off = align_up(off + n_tok * 4, 256);   // routing per chunk: compacted rows visible to a query
     bp->off_dslap = off;   off = align_up(off + ns * (n_tok / 64) * 4, 256);   // ... and the sweep's partials of Eq. 17
     // chunkwise backward of the linear branch: operands of every chunk, the residuals, state gradients per chunk
     const size_t ch = (pl.routing == NATS_ROUTE_CHUNK && tk) ? 0 : 1;   // (token by token with routing per chunk: own checkpoint kernel)
     bp->off_ops = off;     off = align_up(off + ch * chunk_ops_floats(pl, true) * 4, 256);
-    bp->off_uh = off;      off = align_up(off + ch * n_tok * pl.d * 4, 256);
-    bp->off_dck = off;     off = align_up(off + ch * (1 - tk) * pl.BH * (pl.L / 64) * pl.d * pl.d * 4, 256);
-    bp->off_dot = off;     off = align_up(off + ch * (1 - tk) * pl.BH * (pl.L / 64) * (pl.d / 4) * 4, 256);
-    bp->off_vht = off;     off = align_up(off + n_tok * pl.d * 2, 256);   // fp16 V^T tiles of the compacted values (bf16 tensors)
+    bp->off_uh = off;      off = align_up(off + ch * n_out * pl.d * 4, 256);
+    bp->off_dck = off;     off = align_up(off + ch * (1 - tk) * pl.BHG * (pl.L / 64) * pl.d * pl.d * 4, 256);
+    bp->off_dot = off;     off = align_up(off + ch * (1 - tk) * pl.BHG * (pl.L / 64) * (pl.d / 4) * 4, 256);
+    bp->off_vht = off;     off = align_up(off + n_out * pl.d * 2, 256);   // fp16 V^T tiles of the compacted values (bf16 tensors)
+    // head grouping in one pass: the output heads' shares of the gradients of what a group shares
+    const size_t gr = pl.G > 1 ? 1 : 0;
+    bp->off_pdq = off;     off = align_up(off + gr * n_out * pl.d * 4, 256);
+    bp->off_pdk = off;     off = align_up(off + gr * n_out * pl.d * 4, 256);
+    bp->off_pda = off;     off = align_up(off + gr * n_out * 4, 256);
+    bp->off_pdb = off;     off = align_up(off + gr * n_out * 4, 256);
+    bp->off_pgn = off;     off = align_up(off + gr * n_out * 4, 256);
+    bp->off_psl = off;     off = align_up(off + gr * (n_out / 64) * 4, 256);
     bp->total = off;
     bp->G = 1;
     bp->total_grouped = off;
@@ -280,13 +291,13 @@ static void plan_bwd_group(const FwdPlan& pl, int G, BwdPlan* bp) {
     bp->total_grouped = off;
 }
 
-// the buffers of the backward through Eq. 21's merge, behind everything else (pl: the plan of one member)
+// the buffers of the backward through Eq. 21's merge, behind everything else (pl: the plan of the pass)
 static void plan_bwd_merge(const FwdPlan& pl, int G, BwdPlan* bp) {
-    const size_t n_tok = (size_t)pl.BH * pl.L, nd = n_tok * pl.d;
+    const size_t n_tok = (size_t)pl.BH * pl.L, nd = n_tok * pl.d, n_out = (size_t)pl.BHG * pl.L;
     size_t off = bp->total_grouped;
-    bp->off_mola = off;  off = align_up(off + nd * 4, 256);
-    bp->off_mdol = off;  off = align_up(off + nd * 4, 256);
-    bp->off_mdon = off;  off = align_up(off + nd * 4, 256);
+    bp->off_mola = off;  off = align_up(off + n_out * pl.d * 4, 256);
+    bp->off_mdol = off;  off = align_up(off + n_out * pl.d * 4, 256);
+    bp->off_mdon = off;  off = align_up(off + n_out * pl.d * 4, 256);
     bp->off_msnap = off; off = align_up(off + (size_t)pl.BH * pl.d * pl.d * 4, 256);
     bp->off_mwn = off;   off = align_up(off + n_tok * 4, 256);
     bp->off_mwl = off;   off = align_up(off + n_tok * 4, 256);
@@ -302,8 +313,13 @@ static void plan_bwd_merge(const FwdPlan& pl, int G, BwdPlan* bp) {
     bp->total_grouped = off;
 }
 
-// pl: the plan of the pass itself.  With head grouping (p->group = G > 1) that is the plan of one member of the groups,
-// B x H heads with G = 1, and bp->G = G.
+// pl: the plan of the pass itself.  With head grouping (p->group = G > 1) that is the plan of all output heads (pl->G = G,
+// bp->G = 1): the kernels by chunks find the shared inputs of an output head by its index, its shares of their gradients
+// are added up behind them (a training step of B 4, H 6, G 2, L 4096, d 128: 2377 us member by member, with copies of each
+// member's rows and launches of 192 blocks, 2146 in one pass).  Where that pass would take more
+// than BWD_ONE_PASS_BYTES, and token by token, it is the plan of one member of the groups, B x H heads with pl->G = 1, and
+// bp->G = G.
+constexpr size_t BWD_ONE_PASS_BYTES = (size_t)16 << 30;
 static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, BwdPlan* bp) {
     if (p == nullptr) { set_error("params is NULL"); return NATS_ERR_NULL; }
     nats_fwd_params one = *p;
@@ -323,6 +339,17 @@ static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, Bw
             bp->widen = 1;
             one.dtype = NATS_F32;
         }
+    }
+    if (G > 1 && p->math != NATS_MATH_FP32) {
+        one.group = G;
+        const bool fits = validate_fwd_params(&one, pl) == NATS_OK && pl->inner_chunk == 0 &&
+                          !(pl->routing == NATS_ROUTE_CHUNK && pl->RC != 64);
+        if (fits) {
+            plan_bwd(*pl, bp);
+            if (bp->merge_mode != 0) plan_bwd_merge(*pl, 1, bp);
+            if (bp->total_grouped <= BWD_ONE_PASS_BYTES) return NATS_OK;
+        }
+        one.group = 1;
     }
     nats_status st = validate_fwd_params(&one, pl);
     if (st != NATS_OK) return st;
@@ -579,7 +606,8 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p) {
     return bp.total_grouped;
 }
 
-// The backward pass on B x H heads without grouping (pl.G = 1).  ex by value: the optional outputs may be redirected.
+// The backward pass on the plan's heads (pl.G > 1: all output heads of the groups).  ex by value: the optional outputs
+// may be redirected.
 static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q, const void* K, const void* V,
                             const float* alpha, const float* beta, const uint8_t* mask, const void* dO, float* dQ,
                             float* dK, float* dV, float* dalpha, float* dbeta, nats_bwd_extra ex, char* ws,
@@ -608,6 +636,24 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     // routing per chunk, token by token: the sweep's partials of Eq. 17 (by chunks the gradient kernel writes dscore_la)
     float* dslap = (chunk && ex.dscore_la != nullptr && pl.math == NATS_MATH_FP32)
                        ? reinterpret_cast<float*>(ws + bp.off_dslap) : nullptr;
+    // Gradients of what a group shares: with grouping the output heads' shares go to the workspace and are added up at
+    // the end.
+    const bool grouped = pl.G > 1;
+    float* const dQ_sum = dQ;
+    float* const dK_sum = dK;
+    float* const dalpha_sum = dalpha;
+    float* const dbeta_sum = dbeta;
+    float* const g_nla_sum = ex.g_nla;
+    float* const dsl_sum = chunk ? ex.dscore_la : nullptr;
+    float* dsl = dsl_sum;
+    if (grouped) {
+        dQ = reinterpret_cast<float*>(ws + bp.off_pdq);
+        dK = reinterpret_cast<float*>(ws + bp.off_pdk);
+        dalpha = reinterpret_cast<float*>(ws + bp.off_pda);
+        dbeta = reinterpret_cast<float*>(ws + bp.off_pdb);
+        if (ex.g_nla != nullptr) ex.g_nla = reinterpret_cast<float*>(ws + bp.off_pgn);
+        if (dsl != nullptr) dsl = reinterpret_cast<float*>(ws + bp.off_psl);
+    }
     // The softmax branch's queries and keys, and where their gradients go: with tensors of their own (Section 4.3:
     // the two operations normalise the shared projections differently) dQs / dKs are separate outputs, start from zero,
     // and dQ, dK hold the linear branch's gradients alone.
@@ -616,7 +662,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     const void* Ks = own_qk ? ex.K_nla : K;
     float* dQs = own_qk ? ex.dQ_nla : dQ;
     float* dKs = own_qk ? ex.dK_nla : dK;
-    const size_t n_qk = (size_t)pl.BH * pl.L * pl.d;
+    const size_t n_qk = (size_t)pl.BHG * pl.L * pl.d;
     ProfChain prof_chain;   // the kernels below follow each other on one stream
     // The softmax branch's forward: the plain sum needs its rows for D_i alone and takes the forward's own kernel; behind
     // a merge that normalises them they are differentiated through, in fp32 accuracy.
@@ -710,7 +756,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         // dQ += linear share; dK, dalpha, dbeta = linear share; g_nla cleared
         ProfScope ps("gdn_chunk_grads", stream);
         st = launch_gdn_chunk_grads(pl, Q, K, dO_l, dO_f32, alpha, mask, ops, ckpt, dck, Uh, dV, dot, dQ, dK, dalpha, dbeta, ex.g_nla,
-                                    chunk ? ex.dscore_la : nullptr, stream);
+                                    dsl, stream);
         if (st != NATS_OK) return st;
     } else {
         {
@@ -735,6 +781,16 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
                                     reinterpret_cast<float*>(ws + bp.off_skp), reinterpret_cast<float*>(ws + bp.off_svp),
                                     reinterpret_cast<float*>(ws + bp.off_sgp), stream);
         if (st != NATS_OK) return st;
+    }
+    if (grouped) {
+        ProfScope ps("sum_groups", stream);
+        const size_t row = (size_t)pl.L;
+        const GroupSum sums[] = {{dQ, dQ_sum, row * pl.d}, {dK, dK_sum, row * pl.d}, {dalpha, dalpha_sum, row},
+                                 {dbeta, dbeta_sum, row}, {ex.g_nla, g_nla_sum, row}, {dsl, dsl_sum, row / 64}};
+        st = launch_sum_groups(pl.BH, pl.G, sums, 6, stream);
+        if (st != NATS_OK) return st;
+        dbeta = dbeta_sum;
+        ex.g_nla = g_nla_sum;
     }
     if (ex.g_la != nullptr || ex.dscore_nla != nullptr || ex.dscore_la != nullptr) {   // Eq. 16, Eq. 17
         ProfScope ps("score_gradients", stream);
@@ -802,9 +858,10 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
             *c.src = dst;
         }
     }
+    pl.qk_per_out_head = pl.G > 1 && ex.Q_nla != nullptr;
     if (bp.G == 1) return bwd_core(pl, bp, Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha, dbeta, ex, ws, stream);
 
-    // Head grouping (Section 4.3): member g of every group, i.e. the output heads bh G + g, is a problem of B x H heads
+    // Head grouping (Section 4.3) member by member: member g of every group, i.e. the output heads bh G + g, is a problem of B x H heads
     // with the linear heads' Q, K, alpha, beta and mask.  Its V, dO and initial state are gathered, the pass runs on
     // them, its dV and state gradient go back to its heads, and what it sends to the shared inputs (dQ, dK, dalpha,
     // dbeta, the score gradients) is added up over the members.

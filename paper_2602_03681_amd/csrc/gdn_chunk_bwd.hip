@@ -655,7 +655,7 @@ struct GradArgs {
     const float *ck, *dck, *Uh, *dR, *dot;
     float *dQ, *dK, *dalpha, *dbeta, *g_nla;
     float* dscore_la;   // optional, routing per chunk: Eq. 17 per chunk
-    int L, BH;
+    int L, BH, G;       // BH: output heads; the G of a group share Q, K, alpha, the mask and the operands
     float la_scale;
     int delta, freeze_on_softmax, chunk_mask;
 };
@@ -698,6 +698,7 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
     const int n_chunks = a.L / CB_C;
     const int bh = blockIdx.x % a.BH, chunk = blockIdx.x / a.BH;
     const size_t gc = (size_t)bh * n_chunks + chunk, tok0 = (size_t)bh * a.L + (size_t)chunk * CB_C;
+    const size_t gcl = (size_t)(bh / a.G) * n_chunks + chunk, tokl = (size_t)(bh / a.G) * a.L + (size_t)chunk * CB_C;
     const float delta = a.delta ? 1.f : 0.f;
     const int col0 = 16 * NCT * w + NCT * l16;   // the lane's NCT columns
 
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
     Raw8<TO> dOr[NPC];
     Raw8<float> Rr[NPC];
     // one of g2, gam, kd, b' of the chunk's tokens
-    const float gate_in = (w == 0 ? a.o.g2 : w == 1 ? a.o.gam : w == 2 ? a.o.kd : a.o.bp)[tok0 + lane];
+    const float gate_in = (w == 0 ? a.o.g2 : w == 1 ? a.o.gam : w == 2 ? a.o.kd : a.o.bp)[tokl + lane];
 #pragma unroll
     for (int p = 0; p < NPC; ++p) dOr[p].load(a.dO + tok0 * D + 8 * (tid + 256 * p));
 #pragma unroll
@@ -816,8 +817,8 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
     Raw8<T> Kr[NPC], Qr[NPC];
 #pragma unroll
     for (int p = 0; p < NPC; ++p) {
-        Kr[p].load(a.K + tok0 * D + 8 * (tid + 256 * p));
-        Qr[p].load(a.Q + tok0 * D + 8 * (tid + 256 * p));
+        Kr[p].load(a.K + tokl * D + 8 * (tid + 256 * p));
+        Qr[p].load(a.Q + tokl * D + 8 * (tid + 256 * p));
     }
     f32x4 DPv[NTL], DAv[NTL];   // tile t of the list to wavefront t % 4
 #pragma unroll
@@ -837,7 +838,7 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
             float atv[4], pmv[4];   // At and P where this lane holds dAt and dP
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const size_t off = gc * (CB_C * CB_C) + (16 * ta + 4 * lq + j) * CB_C + 16 * tb + l16;
+                const size_t off = gcl * (CB_C * CB_C) + (16 * ta + 4 * lq + j) * CB_C + 16 * tb + l16;
                 atv[j] = a.o.At[off];
                 pmv[j] = a.o.Pm[off];
             }
@@ -1030,8 +1031,8 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
         constexpr int ND = D / CB_NV * (D / 32);
         const float dt = lane_group_sum<64>(lane < ND ? a.dot[gc * ND + lane] : 0.f);   // <dS1, S0>
         // the decay carried over the chunk: not a function of the alphas for a softmax chunk in the variant without decay
-        const bool carry_fixed = a.chunk_mask && a.freeze_on_softmax && a.mask[gc] != 0;
-        if (r == 63) dl += et + (carry_fixed ? 0.f : a.o.gamC[gc] * dt);
+        const bool carry_fixed = a.chunk_mask && a.freeze_on_softmax && a.mask[gcl] != 0;
+        if (r == 63) dl += et + (carry_fixed ? 0.f : a.o.gamC[gcl] * dt);
         // Eq. 17 for a chunk: <dS1, what the chunk added to the carried state> = sum_i kd_i K_i . (U dS1)_i (kd = 0 for
         // a softmax chunk)
         if (lane == 0 && a.dscore_la != nullptr) a.dscore_la[gc] = et;
@@ -1041,10 +1042,10 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
         dl += dpp_move<0x118>(dl);
         dl += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dl), 0x142, 0xA, 0xF, false));
         dl += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dl), 0x143, 0xC, 0xF, false));
-        const size_t t = tok0 + r;
-        const bool frozen = a.freeze_on_softmax && !a.chunk_mask && a.mask[t] != 0;   // its alpha counted as 1
-        a.dalpha[t] = frozen ? 0.f : dl / fmaxf(a.alpha[t], 1e-30f);
-        a.dbeta[t] = !a.chunk_mask && a.mask[t] != 0 ? 0.f : db;   // routing per token: a softmax token does not write
+        const size_t t = tok0 + r, tl = tokl + r;
+        const bool frozen = a.freeze_on_softmax && !a.chunk_mask && a.mask[tl] != 0;   // its alpha counted as 1
+        a.dalpha[t] = frozen ? 0.f : dl / fmaxf(a.alpha[tl], 1e-30f);
+        a.dbeta[t] = !a.chunk_mask && a.mask[tl] != 0 ? 0.f : db;   // routing per token: a softmax token does not write
         if (a.g_nla != nullptr) a.g_nla[t] = 0.f;
     }
 }
@@ -1242,7 +1243,7 @@ nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, b
     return check_launch("gdn_chunk_out");
 }
 
-// The state gradients behind every chunk, dck [BH][L/64][d][d], their products with the states ck (dot: at most d / 4 parts
+// The state gradients behind every chunk, dck [BHG][L/64][d][d], their products with the states ck (dot: at most d / 4 parts
 // per chunk); dV (every row), dS0 (or NULL).  dO_f32: dO is fp32 whatever the tensors' type.
 nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
                                          float* ops, const float* ck, float* dck, float* dot, float* dV, float* dS0,
@@ -1251,7 +1252,7 @@ nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const
         using T = decltype(t);
         using TO = decltype(to);
         const SeqArgs<T, TO> a{(const T*)K, (const T*)Q, (const TO*)dO, chunk_ops(pl, ops), nullptr, dck, dV, ck, dot, dS0, pl.L,
-                               pl.BH, 1, pl.la_scale, pl.linear_op == 0};
+                               pl.BHG, pl.G, pl.la_scale, pl.linear_op == 0};
         return launch_seq_d<1>(pl, a, st);
     };
     const bool ok = pl.dtype == NATS_F32 ? go(float{}, float{}) : dO_f32 ? go(bf16_t{}, float{}) : go(bf16_t{}, bf16_t{});
@@ -1265,12 +1266,12 @@ static bool launch_grads_t(const FwdPlan& pl, const GradArgs<T, TO>& a, hipStrea
     constexpr size_t lds = GradLds<T, TO, D>::bytes;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.BH * (pl.L / CB_C))), dim3(256), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.BHG * (pl.L / CB_C))), dim3(256), lds, st, a);
     return true;
 }
 
 // dQ += the linear branch's share; dK, dalpha, dbeta = it; g_nla (optional) cleared.  ck, dck: the states and state
-// gradients per chunk; Uh, dR (= the linear branch's dV) [BH][L][d]; dot as launch_gdn_chunk_state_grads left it.  dO_f32: dO is fp32 whatever the tensors' type.
+// gradients per chunk; Uh, dR (= the linear branch's dV) [BHG][L][d], and so everything written; dot as launch_gdn_chunk_state_grads left it.  dO_f32: dO is fp32 whatever the tensors' type.
 nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
                                    const float* alpha, const uint8_t* mask, float* ops, const float* ck, const float* dck,
                                    const float* Uh, const float* dR, const float* dot, float* dQ, float* dK,
@@ -1279,7 +1280,7 @@ nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void*
         using T = decltype(t);
         using TO = decltype(to);
         const GradArgs<T, TO> a{(const T*)Q, (const T*)K, (const TO*)dO, chunk_ops(pl, ops), alpha, mask, ck, dck,
-                                Uh, dR, dot, dQ, dK, dalpha, dbeta, g_nla, dscore_la, pl.L, pl.BH, pl.la_scale,
+                                Uh, dR, dot, dQ, dK, dalpha, dbeta, g_nla, dscore_la, pl.L, pl.BHG, pl.G, pl.la_scale,
                                 pl.linear_op == 0, pl.freeze_on_softmax, pl.routing == NATS_ROUTE_CHUNK};
         return pl.d == 64 ? launch_grads_t<T, TO, 64>(pl, a, st) : launch_grads_t<T, TO, 128>(pl, a, st);
     };

@@ -1,8 +1,8 @@
 // Head grouping (Section 4.3) in the backward pass: G output heads (own V, own state) share the Q, K, alpha, beta
 // and mask of one linear head, so the gradient of a shared input is the sum of what each of the G heads sends back.
-// The backward pass runs once per member of the groups on that member's heads, gathered into contiguous tensors;
-// the two kernels here move a member's rows in and out of the [B, H G, ...] tensors and add a member's share onto
-// the sums.  Both only stream memory.  (Also here: the zero fill the pass needs when the softmax branch has queries
+// Where the pass runs over all output heads at once, their shares are added up here, all gradients in one launch.  Where
+// it runs once per member of the groups on that member's heads, gathered into contiguous tensors, two kernels move a
+// member's rows in and out of the [B, H G, ...] tensors and add a member's share onto the sums.  All only stream memory.  (Also here: the zero fill the pass needs when the softmax branch has queries
 // and keys of its own, whose gradients are then tensors of their own.)
 #include "nats_common.h"
 
@@ -35,7 +35,38 @@ __global__ __launch_bounds__(HG_THREADS) void add_f32_kernel(float4* __restrict_
     }
 }
 
-// the same for any length and alignment
+// sum[h][i] = the G rows part[h G + g][i] in order; one gradient per blockIdx.y
+constexpr int MAX_SUMS = 6;
+struct GroupSums {
+    GroupSum s[MAX_SUMS];
+    int BH, G;
+};
+__global__ __launch_bounds__(HG_THREADS) void sum_groups_kernel(const GroupSums a) {
+    const GroupSum s = a.s[blockIdx.y];
+    const size_t at = (size_t)blockIdx.x * HG_THREADS + threadIdx.x, step = (size_t)gridDim.x * HG_THREADS;
+    if (s.row % 4 == 0) {
+        const size_t row = s.row / 4, n = row * a.BH;
+        for (size_t e = at; e < n; e += step) {
+            const float4* p = reinterpret_cast<const float4*>(s.part) + (e / row) * a.G * row + e % row;
+            float4 x = p[0];
+            for (int g = 1; g < a.G; ++g) {
+                const float4 y = p[g * row];
+                x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+            }
+            reinterpret_cast<float4*>(s.sum)[e] = x;
+        }
+    } else {   // a row per chunk, of any number of chunks
+        const size_t n = s.row * a.BH;
+        for (size_t e = at; e < n; e += step) {
+            const float* p = s.part + (e / s.row) * a.G * s.row + e % s.row;
+            float x = p[0];
+            for (int g = 1; g < a.G; ++g) x += p[g * s.row];
+            s.sum[e] = x;
+        }
+    }
+}
+
+// dst += src for any length and alignment
 __global__ __launch_bounds__(HG_THREADS) void add_f32_scalar_kernel(float* __restrict__ dst, const float* __restrict__ src,
                                                                    size_t n) {
     for (size_t e = (size_t)blockIdx.x * HG_THREADS + threadIdx.x; e < n; e += (size_t)gridDim.x * HG_THREADS)
@@ -74,6 +105,24 @@ nats_status launch_add_f32(float* dst, const float* src, size_t n, hipStream_t s
     else
         hipLaunchKernelGGL(add_f32_scalar_kernel, dim3(hg_grid(n)), dim3(HG_THREADS), 0, st, dst, src, n);
     return check_launch("add_f32");
+}
+
+// part and sum 16-byte aligned (rows of a multiple of four floats are read and written 16 bytes at a time)
+nats_status launch_sum_groups(int BH, int G, const GroupSum* sums, int n, hipStream_t st) {
+    GroupSums a;
+    a.BH = BH;
+    a.G = G;
+    int m = 0;
+    size_t most = 0;
+    for (int i = 0; i < n; ++i) {
+        if (sums[i].sum == nullptr) continue;
+        if (m == MAX_SUMS) { set_error("sum_groups: too many sums"); return NATS_ERR_SHAPE; }
+        a.s[m++] = sums[i];
+        if (sums[i].row > most) most = sums[i].row;
+    }
+    if (m == 0 || most == 0) return NATS_OK;
+    hipLaunchKernelGGL(sum_groups_kernel, dim3(hg_grid(most * BH / 4), m), dim3(HG_THREADS), 0, st, a);
+    return check_launch("sum_groups");
 }
 
 nats_status launch_zero_f32(float* dst, size_t n, hipStream_t st) {

@@ -123,11 +123,11 @@ static int mb_grid(size_t units) {
     return (int)(blocks < 1 ? 1 : (blocks > 4096 ? 4096 : blocks));
 }
 
-// rows: B x H x L rows of pl.d columns (pl.d is 64 or 128), dO of the tensors' type.  dw_nla, dw_la may be NULL (not wanted).
+// rows: BHG x L rows of pl.d columns (pl.d is 64 or 128), dO of the tensors' type.  dw_nla, dw_la may be NULL (not wanted).
 nats_status launch_merge_bwd(const FwdPlan& pl, int mode, float eps, const float* O_la, const float* O_nla,
                              const void* dO, const float* w_nla, const float* w_la, float* dO_la, float* dO_nla,
                              float* dw_nla, float* dw_la, hipStream_t st) {
-    const size_t n_rows = (size_t)pl.BH * pl.L;
+    const size_t n_rows = (size_t)pl.BHG * pl.L;
     if (n_rows == 0) return NATS_OK;
 #define NATS_MB(TO, DD)                                                                                                 \
     hipLaunchKernelGGL((merge_bwd_kernel<TO, DD>), dim3(mb_grid(n_rows * (DD / 4))), dim3(MB_THREADS), 0, st, O_la, O_nla, \

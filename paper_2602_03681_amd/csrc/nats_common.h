@@ -294,6 +294,13 @@ nats_status launch_visible_rows(const FwdPlan& pl, const int32_t* cnt, int32_t* 
 nats_status launch_softmax_bwd_own_chunk(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* dO,
                                          bool dO_f32, const float* lse, const float* Dvec, float* dK, float* dV, hipStream_t st);
 // head grouping in the backward pass (head_group.hip)
+// part: [BH G][row] -> sum: [BH][row], the G shares of a group in order (NULL sum: skipped); row in floats
+struct GroupSum {
+    const float* part;
+    float* sum;
+    size_t row;
+};
+nats_status launch_sum_groups(int BH, int G, const GroupSum* sums, int n, hipStream_t st);
 nats_status launch_copy_rows(const void* src, size_t src_stride_bytes, void* dst, size_t dst_stride_bytes,
                              size_t row_bytes, size_t n_rows, hipStream_t st);
 nats_status launch_add_f32(float* dst, const float* src, size_t n, hipStream_t st);

@@ -243,7 +243,8 @@ struct SmDqArgs {
     const int32_t* vis;   // compacted rows visible to a query (nondecreasing within a head)
     const float *O_nla, *lse;
     float *Dvec, *dQ;
-    int L, BH, own_chunk;
+    int L, BH, own_chunk;   // BH: output heads (of V, dO, the cache and the results); the G of a group share vis and,
+    int G, qk_per_out_head; // unless the softmax heads have their own, Q and K
     float scale;
 };
 template <typename T, typename TO, int D>
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
     if (bh >= a.BH) return;
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, lq = lane >> 4;
-    const size_t tokb = (size_t)bh * a.L;
+    const size_t tokb = (size_t)bh * a.L, tokb_lin = (size_t)(bh / a.G) * a.L, tokb_qk = a.qk_per_out_head ? tokb : tokb_lin;
     const int t = q0 + 16 * w + l16;   // this lane's query
     const float scale2 = a.scale * LOG2E;
 
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
     for (int ks = 0; ks < KS; ++ks) {
         const size_t off = (tokb + t) * D + 32 * ks + 8 * lq;
         Raw8<T> r;
-        r.load(a.Q + off);
+        r.load(a.Q + (tokb_qk + t) * D + 32 * ks + 8 * lq);
         r.terms(qf[ks]);
         Raw8<TO> ro;
         ro.load(a.dO + off);
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
     Dq += lane_xor32(Dq, lane);
     if (lq == 0) a.Dvec[tokb + t] = Dq;
     const float lse2 = a.lse[tokb + t] * LOG2E;
-    const int my_cnt = a.vis[tokb + t], n_hi = a.vis[tokb + q0 + 63];
+    const int my_cnt = a.vis[tokb_lin + t], n_hi = a.vis[tokb_lin + q0 + 63];
     const int n_comp = (n_hi + 63) >> 6, n_all = n_comp + (a.own_chunk ? 1 : 0);
 
     f32x4 acc[MD];
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
     auto fetch = [&](int it) {
         const bool own = it >= n_comp;
         const int row0 = own ? q0 : 64 * it, n_rows = own ? 64 : n_hi - row0;
-        const T* kb = (own ? a.K : a.Kc) + (tokb + row0) * D;
+        const T* kb = (own ? a.K + tokb_qk * D : a.Kc + tokb * D) + (size_t)row0 * D;
         const T* vb = (own ? a.V : a.Vc) + (tokb + row0) * D;
 #pragma unroll
         for (int i = 0; i < NPC; ++i) {
@@ -377,6 +378,7 @@ struct SmDkvArgs {
     const float *lse, *Dvec;
     float *dk, *dv, *g;   // OWN: dK, dV; otherwise the shares [n_seg][BH][L][..]
     int L, BH, n_seg;
+    int G, qk_per_out_head;   // as above; the G of a group share idx and n_s too
     float scale;
 };
 template <typename T, typename TO, int D>
@@ -402,23 +404,23 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
     // claims a block's LDS and registers before it can exit: 1.2 ms instead of 0.35 in the kernel before this one.)
     const int seg = OWN ? 0 : blockIdx.x % a.n_seg, bh = (blockIdx.x / a.n_seg) % a.BH, c0 = (blockIdx.x / a.n_seg / a.BH) * 64;
     const int tid = threadIdx.x, L = a.L;
-    const int n_keys = OWN ? L : a.n_s[bh];
+    const int n_keys = OWN ? L : a.n_s[bh / a.G];
     if (c0 >= n_keys) return;                          // uniform: this tile holds no key
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, lq = lane >> 4;
     const int c = c0 + 16 * w + l16;                   // this lane's key
     const bool valid = c < n_keys;
-    const size_t tokb = (size_t)bh * L;
+    const size_t tokb = (size_t)bh * L, tokb_lin = (size_t)(bh / a.G) * L, tokb_qk = a.qk_per_out_head ? tokb : tokb_lin;
     const float scale2 = a.scale * LOG2E;
 
     // the wavefront's rows of K and V (row of an invalid key: the tile's first, masked below)
     u32x4 kf[KS][NT], vf[KS][NT];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        const size_t off = (tokb + (valid ? c : c0)) * D + 32 * ks + 8 * lq;
+        const size_t off = (size_t)(valid ? c : c0) * D + 32 * ks + 8 * lq;
         Raw8<T> r;
-        r.load(a.K + off);
+        r.load(a.K + (OWN ? tokb_qk : tokb) * D + off);
         r.terms(kf[ks]);
-        r.load(a.V + off);
+        r.load(a.V + tokb * D + off);
         r.terms(vf[ks]);
     }
     f32x4 accK[MD], accV[MD];
@@ -427,7 +429,7 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
     float g = 0.f;
 
     // the queries that see the tile's first key, in tiles; the blocks of the tile take equal shares of them
-    const int i_first = OWN ? c0 : a.idx[tokb + c0] & ~63;
+    const int i_first = OWN ? c0 : a.idx[tokb_lin + c0] & ~63;
     const int n_tiles = OWN ? 1 : (L - i_first) / 64;
     const int i_lo = i_first + (int)((long long)n_tiles * seg / a.n_seg) * 64;
     const int i_hi = i_first + (int)((long long)n_tiles * (seg + 1) / a.n_seg) * 64;
@@ -439,13 +441,13 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
 #pragma unroll
         for (int i = 0; i < NPC; ++i) {
             const int e = tid + 256 * i, row = e / (D / 8), col = (e % (D / 8)) * 8;
-            rq[i].load(a.Q + (tokb + i0 + row) * D + col);
+            rq[i].load(a.Q + (tokb_qk + i0 + row) * D + col);
             ro[i].load(a.dO + (tokb + i0 + row) * D + col);
         }
         if (tid < 64) {
             rl = a.lse[tokb + i0 + tid] * LOG2E;
             rd = a.Dvec[tokb + i0 + tid];
-            if (!OWN) rc = a.vis[tokb + i0 + tid];
+            if (!OWN) rc = a.vis[tokb_lin + i0 + tid];
         }
     };
     // the next tile is fetched while this one is multiplied, except where the gradients' two registers per value do not
@@ -555,11 +557,12 @@ template <int D>
 __global__ __launch_bounds__(256) void softmax_bwd_dkv_combine_kernel(
     const float* __restrict__ dk_part, const float* __restrict__ dv_part, const float* __restrict__ g_part,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ n_s, float* __restrict__ dK, float* __restrict__ dV,
-    float* __restrict__ g_nla, int L, int n_seg, float scale, int accumulate) {
+    float* __restrict__ g_nla, int L, int G, int n_seg, float scale, int accumulate) {
     constexpr int TPK = D / 4;                 // threads per key
     const int bh = blockIdx.y, c = blockIdx.x * (256 / TPK) + threadIdx.x / TPK, col = (threadIdx.x % TPK) * 4;
-    if (c >= n_s[bh]) return;
+    if (c >= n_s[bh / G]) return;
     const size_t tokb = (size_t)bh * L;
+    const int t = idx[(size_t)(bh / G) * L + c];   // the token the key was gathered from
     float4 k = make_float4(0.f, 0.f, 0.f, 0.f), v = k;
     float g = 0.f;
     for (int s = 0; s < n_seg; ++s) {
@@ -570,7 +573,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_dkv_combine_kernel(
         v.x += b.x; v.y += b.y; v.z += b.z; v.w += b.w;
         g += g_part[row];
     }
-    const size_t dst = (tokb + idx[tokb + c]) * D + col;
+    const size_t dst = (tokb + t) * D + col;
     if (accumulate) {   // routing per chunk: the token's rows already hold its shares from inside its chunk
         const float4 k0 = *reinterpret_cast<const float4*>(dK + dst), v0 = *reinterpret_cast<const float4*>(dV + dst);
         *reinterpret_cast<float4*>(dK + dst) = make_float4(k0.x + scale * k.x, k0.y + scale * k.y, k0.z + scale * k.z, k0.w + scale * k.w);
@@ -579,7 +582,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_dkv_combine_kernel(
         *reinterpret_cast<float4*>(dK + dst) = make_float4(scale * k.x, scale * k.y, scale * k.z, scale * k.w);
         *reinterpret_cast<float4*>(dV + dst) = v;
     }
-    if (col == 0 && g_nla != nullptr) g_nla[tokb + idx[tokb + c]] = g;
+    if (col == 0 && g_nla != nullptr) g_nla[tokb + t] = g;
 }
 
 // Compacted rows a query sees: with routing per token the first cnt[t]; with routing per chunk those of earlier
@@ -634,13 +637,14 @@ static bool launch_dq_t(const FwdPlan& pl, const void* Q, const void* Kc, const 
     constexpr int lds = 2 * TermTile<D, terms_of<T>()>::BYTES;
     if (!lds_limit(kern, lds)) return false;
     const SmDqArgs<T, TO> a{(const T*)Q, (const T*)Kc, (const T*)Vc, (const T*)K, (const T*)V, (const TO*)dO, vis, O_nla, lse,
-                            Dvec, dQ, pl.L, pl.BH, pl.routing == NATS_ROUTE_CHUNK, pl.softmax_scale};
-    hipLaunchKernelGGL(kern, query_grid(pl.BH, pl.L), dim3(256), lds, st, a);
+                            Dvec, dQ, pl.L, pl.BHG, pl.routing == NATS_ROUTE_CHUNK, pl.G, pl.qk_per_out_head, pl.softmax_scale};
+    hipLaunchKernelGGL(kern, query_grid(pl.BHG, pl.L), dim3(256), lds, st, a);
     return true;
 }
 
-// dQ [B,H,L,d] f32 is written (not accumulated), with routing per chunk including the queries' own chunks; also
-// Dvec [B,H,L].  dO_f32: dO is fp32 whatever the tensors' type.
+// (In this and the launchers below dQ, dK, dV, Dvec, the cache, lse, O_nla and the scratch have pl.BHG heads.)
+// dQ [BHG,L,d] f32 is written (not accumulated), with routing per chunk including the queries' own chunks; also
+// Dvec [BHG,L].  dO_f32: dO is fp32 whatever the tensors' type.
 nats_status launch_softmax_bwd_dq(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* K, const void* V,
                                   const void* dO, bool dO_f32, const int32_t* vis, const float* O_nla, const float* lse,
                                   float* Dvec, float* dQ, hipStream_t st) {
@@ -663,8 +667,8 @@ static bool launch_dkv_t(const FwdPlan& pl, const void* Q, const void* K, const 
     if (!lds_limit(kern, lds)) return false;
     const int n_seg = OWN ? 1 : BWD_DKV_SEGMENTS;
     const SmDkvArgs<T, TO> a{(const T*)Q, (const T*)K, (const T*)V, (const TO*)dO, vis, idx, n_s, lse, Dvec, dk, dv, g, pl.L,
-                             pl.BH, n_seg, pl.softmax_scale};
-    hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)(pl.L / 64) * pl.BH * n_seg)), dim3(256), lds, st, a);
+                             pl.BHG, n_seg, pl.G, pl.qk_per_out_head, pl.softmax_scale};
+    hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)(pl.L / 64) * pl.BHG * n_seg)), dim3(256), lds, st, a);
     return true;
 }
 template <bool OWN>
@@ -678,8 +682,8 @@ static bool launch_dkv(const FwdPlan& pl, const void* Q, const void* K, const vo
 #undef NATS_SMK
 }
 
-// the rows idx[c] of dK, dV [B,H,L,d] f32 (and of g_nla [B,H,L], optional) are overwritten (routing per chunk: added to);
-// other rows are left alone.  dk_part, dv_part: BWD_DKV_SEGMENTS * BH * L * d floats, g_part: BWD_DKV_SEGMENTS * BH * L (scratch)
+// the rows idx[c] of dK, dV [BHG,L,d] f32 (and of g_nla [BHG,L], optional) are overwritten (routing per chunk: added to);
+// other rows are left alone.  dk_part, dv_part: BWD_DKV_SEGMENTS * BHG * L * d floats, g_part: BWD_DKV_SEGMENTS * BHG * L (scratch)
 nats_status launch_softmax_bwd_dkv(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* dO, bool dO_f32,
                                    const int32_t* vis, const int32_t* idx, const int32_t* n_s, const float* lse,
                                    const float* Dvec, float* dK, float* dV, float* g_nla, float* dk_part, float* dv_part,
@@ -691,13 +695,13 @@ nats_status launch_softmax_bwd_dkv(const FwdPlan& pl, const void* Q, const void*
     nats_status rc = check_launch("softmax_bwd_dkv");
     if (rc != NATS_OK) return rc;
     if (pl.d == 64) {
-        dim3 grid((pl.L + 15) / 16, pl.BH);   // 256 / (64 / 4) keys per block
+        dim3 grid((pl.L + 15) / 16, pl.BHG);   // 256 / (64 / 4) keys per block
         hipLaunchKernelGGL((softmax_bwd_dkv_combine_kernel<64>), grid, dim3(256), 0, st, dk_part, dv_part, g_part, idx, n_s,
-                           dK, dV, g_nla, pl.L, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
+                           dK, dV, g_nla, pl.L, pl.G, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
     } else {
-        dim3 grid((pl.L + 7) / 8, pl.BH);     // 256 / (128 / 4) keys per block
+        dim3 grid((pl.L + 7) / 8, pl.BHG);     // 256 / (128 / 4) keys per block
         hipLaunchKernelGGL((softmax_bwd_dkv_combine_kernel<128>), grid, dim3(256), 0, st, dk_part, dv_part, g_part, idx, n_s,
-                           dK, dV, g_nla, pl.L, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
+                           dK, dV, g_nla, pl.L, pl.G, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
     }
     return check_launch("softmax_bwd_dkv_combine");
 }
