@@ -527,7 +527,7 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
     // The kernels run one after the other on the caller's stream.  (The softmax branch depends on nothing
     // the preparation of the linear branch computes, but the preparation kernel fills every CU by itself:
     // beside it on a second stream the softmax branch only waited for free slots, and nothing was gained.)
-    if (!uses_chunk_path(pl)) {
+    if (!uses_chunk_path(pl) && !pl.fp32_chunks) {   // otherwise part of the first launch below
         ProfScope ps("scan_compact", stream);
         st = launch_scan_compact(pl, mask, Ks, V, cnt, idx, n_s, Kc, Vc, ex.Kc, ex.Vc, ex.cap, nullptr, stream);
     }
@@ -566,7 +566,8 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
             float* ck = reinterpret_cast<float*>(ws + pl.off_ck);
             {
                 ProfScope ps("gdn_bwd_prep", stream);
-                st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, false, stream);
+                st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, false, Ks, V, cnt, idx, n_s, Kc, Vc, ex.Kc, ex.Vc,
+                                         ex.cap, nullptr, stream);
                 if (st != NATS_OK) return st;
             }
             {   // the residuals go where the branch's rows will be
@@ -668,7 +669,20 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     // a merge that normalises them they are differentiated through, in fp32 accuracy.
     const bool mfma_stats = pl.dtype == NATS_BF16 && bp.merge_mode == 0;
     void* VhT = mfma_stats ? ws + bp.off_vht : nullptr;
-    {   // what the softmax branch's backward needs from its forward: the compacted cache, lse, the branch output
+    float* ops = reinterpret_cast<float*>(ws + bp.off_ops);
+    float* Uh = reinterpret_cast<float*>(ws + bp.off_uh);
+    float* dck = reinterpret_cast<float*>(ws + bp.off_dck);
+    float* dot = reinterpret_cast<float*>(ws + bp.off_dot);
+    const bool by_chunks = pl.math != NATS_MATH_FP32;   // the linear branch's backward by chunks of 64 tokens
+    // What the softmax branch's backward needs from its forward: the compacted cache, lse, the branch output.  The scan and
+    // compaction ride in the launch that makes the operands of the linear branch's chunks, where there is one.
+    const bool chunk_states = by_chunks || !chunk;
+    if (chunk_states) {
+        ProfScope ps("gdn_bwd_prep", stream);
+        st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, true, Ks, V, cnt, idx, n_s, Kc, Vc, nullptr, nullptr, 0, VhT,
+                                 stream);
+        if (st != NATS_OK) return st;
+    } else {
         ProfScope ps("scan_compact", stream);
         st = launch_scan_compact(pl, mask, Ks, V, cnt, idx, n_s, Kc, Vc, nullptr, nullptr, 0, VhT, stream);
         if (st != NATS_OK) return st;
@@ -682,17 +696,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         st = launch_softmax_terms_fwd(pl, Qs, Kc, Vc, Ks, V, cnt, nullptr, nullptr, nullptr, nullptr, O_nla, lse, stream);
         if (st != NATS_OK) return st;
     }
-    float* ops = reinterpret_cast<float*>(ws + bp.off_ops);
-    float* Uh = reinterpret_cast<float*>(ws + bp.off_uh);
-    float* dck = reinterpret_cast<float*>(ws + bp.off_dck);
-    float* dot = reinterpret_cast<float*>(ws + bp.off_dot);
-    const bool by_chunks = pl.math != NATS_MATH_FP32;   // the linear branch's backward by chunks of 64 tokens
-    if (by_chunks || !chunk) {   // the linear branch forwards once more by chunks, leaving the state at the start of every chunk
-        {
-            ProfScope ps("gdn_bwd_prep", stream);
-            st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, true, stream);
-            if (st != NATS_OK) return st;
-        }
+    if (chunk_states) {   // the linear branch forwards once more by chunks, leaving the state at the start of every chunk
         ProfScope ps("gdn_chunk_states", stream);
         st = launch_gdn_chunk_states(pl, K, V, ops, true, ex.initial_state, nullptr, ckpt, Uh, stream);
         if (st != NATS_OK) return st;

@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "nats_common.h"
+#include "scan_compact_block.h"
 #include "softmax_terms.h"
 
 namespace nats {
@@ -63,38 +64,76 @@ __device__ __forceinline__ double dpp_move_f64(double x) {
 }
 
 // ---- operands of a chunk ---------------------------------------------------------------------------------------------
-// One block per (chunk, batch*head).  Products in fp32 from the inputs as given (bf16 converts exactly); the inverse
-// by 16 x 16 blocks: forward substitution on the diagonal, matrix instructions below it.
+// One block per (chunk, batch*head).  K K^T and Q K^T from the inputs as given: bf16 tensors on the bf16 instruction (one
+// exact product per step, tiles of 17 KB: four blocks per CU; widened to fp32 in LDS, two blocks per CU, B 2, H 16,
+// L 8192, d 128 took 129 us, now 75 with the scan), fp32 tensors on the fp32 one.  The inverse by 16 x 16 blocks: forward substitution
+// on the diagonal, fp32 matrix instructions below it.
+// The grid starts with the blocks of the mask scan and compaction (as a launch of their own these few, latency-bound
+// blocks stood on the stream for 3 us at L 256, 6 at L 704, 14 at the size above).
+template <typename T>
+struct PrepArgs {
+    const T *Q, *K;
+    const float *alpha, *beta;
+    const uint8_t* mask;
+    ChunkOps o;
+    int L, BH, freeze_on_softmax, linear_op, chunk_mask;
+};
 template <typename T, int D>
-__global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__ Q, const T* __restrict__ K,
-                                                           const float* __restrict__ alpha, const float* __restrict__ beta,
-                                                           const uint8_t* __restrict__ mask, const ChunkOps o, const int L,
-                                                           const int BH, const int freeze_on_softmax, const int linear_op,
-                                                           const int chunk_mask) {
-    constexpr int KS = D + 4, E = Vec16<T>::N, NP = CB_C * D / E / 256;
-    extern __shared__ __align__(16) float cb_smem[];
-    float* Ks = cb_smem;
-    float* Qs = cb_smem + CB_C * KS;
+struct PrepLds {
+    static constexpr bool bf16 = sizeof(T) == 2;
+    static constexpr int KS = D + 4;                            // row stride of an fp32 tile
+    static constexpr int M_BYTES = CB_C * CB_MS * 4;            // T and At diag(b') take the tiles' places
+    static constexpr int TILE = bf16 ? TermTile<D, 1>::BYTES : CB_C * KS * 4;
+    static constexpr int REGION = TILE > M_BYTES ? TILE : M_BYTES;
+    static constexpr int bytes = 2 * REGION + CB_C * (8 + 4);
+    static_assert(bytes >= SCAN_LDS_INTS * 4, "the scan's blocks use the same bytes");
+};
+
+template <typename T, int D>
+__device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const int block, unsigned char* lds) {
+    using LY = PrepLds<T, D>;
+    constexpr int KS = LY::KS, E = Vec16<T>::N, NP = CB_C * D / E / 256;
+    const T* __restrict__ Q = a.Q;
+    const T* __restrict__ K = a.K;
+    const float* __restrict__ alpha = a.alpha;
+    const float* __restrict__ beta = a.beta;
+    const uint8_t* __restrict__ mask = a.mask;
+    const ChunkOps& o = a.o;
+    const int L = a.L, BH = a.BH, freeze_on_softmax = a.freeze_on_softmax, linear_op = a.linear_op, chunk_mask = a.chunk_mask;
+    float* Ks = reinterpret_cast<float*>(lds);
+    float* Qs = reinterpret_cast<float*>(lds + LY::REGION);
+    const TermTile<D, 1> Kt{reinterpret_cast<uint16_t*>(lds)}, Qt{reinterpret_cast<uint16_t*>(lds + LY::REGION)};
     float* As = Qs;                         // after the products: At diag(b'), [64][CB_MS]
     // log2 gamma: its prefix sums in double, so that a decay ratio gamma_r / gamma_i, the exponential of a difference of
     // two of them, keeps fp32 accuracy whatever stands in front of token i in the chunk (alphas near 0)
-    double* s_g = reinterpret_cast<double*>(cb_smem + 2 * CB_C * KS);
+    double* s_g = reinterpret_cast<double*>(lds + 2 * LY::REGION);
     float* s_bp = reinterpret_cast<float*>(s_g + CB_C);
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
     const int n_chunks = L / CB_C;
-    const int bh = blockIdx.x % BH, chunk = blockIdx.x / BH;
+    const int bh = block % BH, chunk = block / BH;
     const size_t gc = (size_t)bh * n_chunks + chunk, tok0 = (size_t)bh * L + (size_t)chunk * CB_C;
+    if constexpr (LY::bf16) {
+        u32x4 kr[NP], qr[NP];
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const int e = tid + 256 * i, row = e / (D / E), c = (e % (D / E)) * E;
-        float tmp[E];
-        Vec16<T>::load(K + (tok0 + row) * D + c, tmp);
+        for (int i = 0; i < NP; ++i) {
+            kr[i] = reinterpret_cast<const u32x4*>(K + tok0 * D)[tid + 256 * i];
+            qr[i] = reinterpret_cast<const u32x4*>(Q + tok0 * D)[tid + 256 * i];
+        }
 #pragma unroll
-        for (int j = 0; j < E; j += 4) *reinterpret_cast<float4*>(Ks + row * KS + c + j) = make_float4(tmp[j], tmp[j + 1], tmp[j + 2], tmp[j + 3]);
-        Vec16<T>::load(Q + (tok0 + row) * D + c, tmp);
+        for (int i = 0; i < NP; ++i) {
+            const int e = tid + 256 * i, row = e / (D / E), c = (e % (D / E)) * E;
+            const u32x4 k1[1] = {kr[i]}, q1[1] = {qr[i]};
+            Kt.put(row, c, k1);
+            Qt.put(row, c, q1);
+        }
+    } else {
 #pragma unroll
-        for (int j = 0; j < E; j += 4) *reinterpret_cast<float4*>(Qs + row * KS + c + j) = make_float4(tmp[j], tmp[j + 1], tmp[j + 2], tmp[j + 3]);
+        for (int i = 0; i < NP; ++i) {
+            const int e = tid + 256 * i, row = e / (D / E), c = (e % (D / E)) * E;
+            *reinterpret_cast<float4*>(Ks + row * KS + c) = ld4(reinterpret_cast<const float*>(K) + (tok0 + row) * D + c);
+            *reinterpret_cast<float4*>(Qs + row * KS + c) = ld4(reinterpret_cast<const float*>(Q) + (tok0 + row) * D + c);
+        }
     }
     if (w == 0) {
         // Routing per token: a softmax token writes nothing (b' = 0) and, in the variant without decay there, its
@@ -138,11 +177,24 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
         if (t < 10) {
             const int a = (0x3333222110 >> (4 * t)) & 15, b = (0x3210210100 >> (4 * t)) & 15;
             f32x4 accK = {0.f, 0.f, 0.f, 0.f}, accQ = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (LY::bf16) {
+                // (steps of 32 columns from zero, added by vector adds, which round to nearest)
+#pragma unroll
+                for (int ks = 0; ks < D / 32; ++ks) {
+                    u32x4 kb[1], ka[1], qa[1];
+                    Kt.rows(16 * b + l16, 32 * ks + 8 * lq, kb);
+                    Kt.rows(16 * a + l16, 32 * ks + 8 * lq, ka);
+                    Qt.rows(16 * a + l16, 32 * ks + 8 * lq, qa);
+                    accK += mfma_bf16(ka[0], kb[0], f32x4{0.f, 0.f, 0.f, 0.f});
+                    accQ += mfma_bf16(qa[0], kb[0], f32x4{0.f, 0.f, 0.f, 0.f});
+                }
+            } else {
 #pragma unroll 4
-            for (int kt = 0; kt < D / 16; ++kt) {
-                const float4 bk = ld4(Ks + (16 * b + l16) * KS + 16 * kt + 4 * lq);
-                accK = mac16(ld4(Ks + (16 * a + l16) * KS + 16 * kt + 4 * lq), bk, accK);
-                accQ = mac16(ld4(Qs + (16 * a + l16) * KS + 16 * kt + 4 * lq), bk, accQ);
+                for (int kt = 0; kt < D / 16; ++kt) {
+                    const float4 bk = ld4(Ks + (16 * b + l16) * KS + 16 * kt + 4 * lq);
+                    accK = mac16(ld4(Ks + (16 * a + l16) * KS + 16 * kt + 4 * lq), bk, accK);
+                    accQ = mac16(ld4(Qs + (16 * a + l16) * KS + 16 * kt + 4 * lq), bk, accQ);
+                }
             }
             const int i = 16 * b + l16;
             const double gi = s_g[i];
@@ -224,6 +276,18 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const T* __restrict__
         if ((c4 >> 4) <= (r >> 4)) t = ld4(Ts + r * CB_MS + c4);
         *reinterpret_cast<float4*>(Tmo + r * CB_C + c4) = t;
     }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const PrepArgs<T> a, const ScanArgs<T> sc, const int scan_segs,
+                                                           const int scan_blocks) {
+    static_assert(SCAN_THREADS == 256, "both kinds of block");
+    extern __shared__ __align__(16) float cb_smem[];
+    if ((int)blockIdx.x < scan_blocks) {
+        scan_compact_block<T>(sc, blockIdx.x % scan_segs, blockIdx.x / scan_segs, reinterpret_cast<int*>(cb_smem));
+        return;
+    }
+    gdn_bwd_prep_block<T, D>(a, blockIdx.x - scan_blocks, reinterpret_cast<unsigned char*>(cb_smem));
 }
 
 // ---- the states along the sequence -------------------------------------------------------------------------------------
@@ -631,9 +695,6 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
                 make_float4(Sacc[t][0], Sacc[t][1], Sacc[t][2], Sacc[t][3]);
     }
 }
-
-template <int D>
-constexpr size_t prep_lds_bytes() { return sizeof(float) * (2 * (size_t)CB_C * (D + 4) + 3 * CB_C); }
 
 // ---- the gradients of a chunk -------------------------------------------------------------------------------------------
 // One block per (chunk, batch*head), 4 wavefronts; wavefront w owns a quarter of the columns of dQ and dK (all 64 rows)
@@ -1164,28 +1225,36 @@ size_t chunk_ops_floats(const FwdPlan& pl, bool with_at) {
 }
 
 template <typename T, int D>
-static bool launch_prep_t(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
-                          const uint8_t* mask, const ChunkOps& o, hipStream_t st) {
+static bool launch_prep_t(const FwdPlan& pl, const PrepArgs<T>& a, const ScanArgs<T>& sc, hipStream_t st) {
     auto kern = gdn_bwd_prep_kernel<T, D>;
-    constexpr size_t lds = prep_lds_bytes<D>();
+    constexpr size_t lds = PrepLds<T, D>::bytes;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.BH * (pl.L / CB_C))), dim3(256), lds, st, (const T*)Q,
-                       (const T*)K, alpha, beta, mask, o, pl.L, pl.BH, pl.freeze_on_softmax, pl.linear_op,
-                       pl.routing == NATS_ROUTE_CHUNK);
+    const int scan_segs = (pl.L + SCAN_SEG - 1) / SCAN_SEG, scan_blocks = scan_segs * pl.BHG;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(scan_blocks + pl.BH * (pl.L / CB_C))), dim3(256), lds, st, a, sc, scan_segs,
+                       scan_blocks);
     return true;
 }
 
-// ops: chunk_ops_floats(pl) floats.  Either routing.
+// ops: chunk_ops_floats(pl) floats.  Either routing.  The same launch carries the mask scan and compaction (arguments as
+// launch_scan_compact; Ks: the softmax branch's keys).
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
-                                const uint8_t* mask, float* ops, bool with_at, hipStream_t st) {
-    const ChunkOps o = chunk_ops(pl, ops, with_at);
-    bool ok;
-    if (pl.dtype == NATS_BF16) ok = pl.d == 64 ? launch_prep_t<bf16_t, 64>(pl, Q, K, alpha, beta, mask, o, st)
-                                               : launch_prep_t<bf16_t, 128>(pl, Q, K, alpha, beta, mask, o, st);
-    else ok = pl.d == 64 ? launch_prep_t<float, 64>(pl, Q, K, alpha, beta, mask, o, st)
-                         : launch_prep_t<float, 128>(pl, Q, K, alpha, beta, mask, o, st);
-    if (!ok) { set_error("gdn_bwd_prep: the kernel's LDS size was refused"); return NATS_ERR_HIP; }
+                                const uint8_t* mask, float* ops, bool with_at, const void* Ks, const void* V, int32_t* cnt,
+                                int32_t* idx, int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user,
+                                void* VhT, hipStream_t st) {
+    const int by_chunk = pl.routing == NATS_ROUTE_CHUNK;
+    auto go = [&](auto t) {
+        using T = decltype(t);
+        const PrepArgs<T> a{(const T*)Q, (const T*)K, alpha, beta, mask, chunk_ops(pl, ops, with_at), pl.L, pl.BH,
+                            pl.freeze_on_softmax, pl.linear_op, by_chunk};
+        const ScanArgs<T> sc{mask, (const T*)Ks, (const T*)V, pl.L, pl.d, cnt, idx, n_s, (T*)Kc, (T*)Vc, (T*)Kc_user, (T*)Vc_user,
+                             cap_user, (half_t*)VhT, by_chunk ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head};
+        return pl.d == 64 ? launch_prep_t<T, 64>(pl, a, sc, st) : launch_prep_t<T, 128>(pl, a, sc, st);
+    };
+    if (!(pl.dtype == NATS_BF16 ? go(bf16_t{}) : go(float{}))) {
+        set_error("gdn_bwd_prep: the kernel's LDS size was refused");
+        return NATS_ERR_HIP;
+    }
     return check_launch("gdn_bwd_prep");
 }
 

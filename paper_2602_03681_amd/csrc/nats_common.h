@@ -280,7 +280,9 @@ nats_status launch_gdn_checkpoints(const FwdPlan& pl, const void* K, const void*
 // chunkwise backward of the linear branch (fp32 matrix instructions), routing per token
 size_t chunk_ops_floats(const FwdPlan& pl, bool with_at);
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
-                                const uint8_t* mask, float* ops, bool with_at, hipStream_t st);
+                                const uint8_t* mask, float* ops, bool with_at, const void* Ks, const void* V, int32_t* cnt,
+                                int32_t* idx, int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user,
+                                void* VhT, hipStream_t st);
 nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, bool with_at,
                                     const float* S_init, float* S_final, float* ck, float* Uh, hipStream_t st);
 nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
