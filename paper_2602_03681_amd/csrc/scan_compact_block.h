@@ -117,24 +117,38 @@ __device__ __forceinline__ void scan_compact_block(const ScanArgs<T>& a, const i
     const int lpr = d / EPL;                  // lanes per row (8..32, divides 256)
     const int rows_per_pass = SCAN_THREADS / lpr;
     const int part = tid % lpr;
-    for (int r = tid / lpr; r < seg_total; r += rows_per_pass) {
-        const int t = s_pos[r];
-        const int c = before + r;
-        const uint4 kv = *reinterpret_cast<const uint4*>(K + ((size_t)bk * L + t) * d + part * EPL);
-        const uint4 vv = *reinterpret_cast<const uint4*>(V + ((size_t)bo * L + t) * d + part * EPL);
-        const size_t dst = ((size_t)bo * L + c) * d + part * EPL;
-        *reinterpret_cast<uint4*>(Kc + dst) = kv;
-        *reinterpret_cast<uint4*>(Vc + dst) = vv;
-        if (Kc_user != nullptr && c < cap_user) {
-            const size_t du = ((size_t)bo * cap_user + c) * d + part * EPL;
-            *reinterpret_cast<uint4*>(Kc_user + du) = kv;
-            *reinterpret_cast<uint4*>(Vc_user + du) = vv;
-        }
-        if (VhT != nullptr) {   // fp16 copy, transposed inside tiles of 64 compacted rows: [tile][d][64]
-            const T* ve = reinterpret_cast<const T*>(&vv);
-            half_t* tile = VhT + ((size_t)bo * L + (size_t)(c >> 6) * 64) * d;
+    // GATHER rows per thread in flight: one row after the other, a pass is a round trip to memory, and a segment with a
+    // fifth of its tokens routed to the softmax branch is 13 passes at d = 128 (the launch it rides in, B 3, H 6, L 1216:
+    // 24.8 us one by one, 23.5 so).
+    constexpr int GATHER = 4;
+    for (int r0 = tid / lpr; r0 < seg_total; r0 += GATHER * rows_per_pass) {
+        uint4 kr[GATHER], vr[GATHER];
 #pragma unroll
-            for (int j = 0; j < EPL; ++j) tile[(size_t)(part * EPL + j) * 64 + vht_col(c)] = elem_to_half(ve[j]);
+        for (int u = 0; u < GATHER; ++u) {   // past the end: the last row once more, not stored
+            const int t = s_pos[min(r0 + u * rows_per_pass, seg_total - 1)];
+            kr[u] = *reinterpret_cast<const uint4*>(K + ((size_t)bk * L + t) * d + part * EPL);
+            vr[u] = *reinterpret_cast<const uint4*>(V + ((size_t)bo * L + t) * d + part * EPL);
+        }
+#pragma unroll
+        for (int u = 0; u < GATHER; ++u) {
+            const int r = r0 + u * rows_per_pass;
+            if (r >= seg_total) break;
+            const int c = before + r;
+            const uint4 kv = kr[u], vv = vr[u];
+            const size_t dst = ((size_t)bo * L + c) * d + part * EPL;
+            *reinterpret_cast<uint4*>(Kc + dst) = kv;
+            *reinterpret_cast<uint4*>(Vc + dst) = vv;
+            if (Kc_user != nullptr && c < cap_user) {
+                const size_t du = ((size_t)bo * cap_user + c) * d + part * EPL;
+                *reinterpret_cast<uint4*>(Kc_user + du) = kv;
+                *reinterpret_cast<uint4*>(Vc_user + du) = vv;
+            }
+            if (VhT != nullptr) {   // fp16 copy, transposed inside tiles of 64 compacted rows: [tile][d][64]
+                const T* ve = reinterpret_cast<const T*>(&vv);
+                half_t* tile = VhT + ((size_t)bo * L + (size_t)(c >> 6) * 64) * d;
+#pragma unroll
+                for (int j = 0; j < EPL; ++j) tile[(size_t)(part * EPL + j) * 64 + vht_col(c)] = elem_to_half(ve[j]);
+            }
         }
     }
     // the tail of the last V^T tile is multiplied by zero weights downstream: make it finite
