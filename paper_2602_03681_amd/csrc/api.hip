@@ -174,7 +174,7 @@ static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl, bo
     pl->off_kc = off;  off = align_up(off + n_out * pl->d * esz, 256);
     pl->off_vc = off;  off = align_up(off + n_out * pl->d * esz, 256);
     pl->off_ola = off; off = align_up(off + n_out * pl->d * 4, 256);
-    pl->off_tf = pl->off_p = pl->off_gamv = pl->off_kdv = pl->off_gam = pl->off_seg = pl->off_vht = pl->off_olah = 0;
+    pl->off_tf = pl->off_p = pl->off_gamv = pl->off_kdv = pl->off_gam = pl->off_seg = pl->off_vh = pl->off_olah = 0;
     pl->off_snap = pl->off_ops = pl->off_ck = 0;
     pl->fp32_chunks = !by_tokens && uses_fp32_chunks(*pl);
     pl->off_wout = off; off = align_up(off + 2 * n_out * 4, 256);   // weights of Eq. 21 when computed by Eq. 22
@@ -193,7 +193,7 @@ static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl, bo
         pl->off_gam = off;  off = align_up(off + (n_tok / pl->C) * 4, 256);
         // start state, zero-run end state and transposed transition of every segment
         pl->off_seg = off;  off = align_up(off + 3 * (size_t)pl->BHG * gdn_segments(*pl) * pl->d * pl->d * 4, 256);
-        pl->off_vht = off;  off = align_up(off + n_out * pl->d * 2, 256);   // fp16 V^T tiles of the softmax branch
+        pl->off_vh = off;  off = align_up(off + n_out * pl->d * 2, 256);   // fp16 rows of the compacted values
         pl->off_olah = off; off = align_up(off + n_out * pl->d * 2, 256);   // fp16 hand-off between the branches
     }
     pl->total = off;
@@ -205,7 +205,7 @@ static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl, bo
 // the reverse sweep and the partial sums of its blocks.
 struct BwdPlan {
     size_t off_onla, off_lse, off_dvec, off_ckpt, off_scratch, off_dqp, off_dkp, off_dap, off_dbp, off_skp, off_svp, off_sgp,
-        off_gnla, off_vis, off_dslap, off_ops, off_uh, off_dck, off_dot, off_vht, off_pdq, off_pdk, off_pda, off_pdb, off_pgn,
+        off_gnla, off_vis, off_dslap, off_ops, off_uh, off_dck, off_dot, off_vh, off_pdq, off_pdk, off_pda, off_pdb, off_pgn,
         off_psl, total;
     // head grouping member by member (G > 1): the pass runs once per member of the groups on `total` bytes; behind them,
     // one member's heads of V, dO, the initial state (gathered) and the member's gradients before they are added or
@@ -250,7 +250,7 @@ static void plan_bwd(const FwdPlan& pl, BwdPlan* bp) {
     bp->off_uh = off;      off = align_up(off + ch * n_out * pl.d * 4, 256);
     bp->off_dck = off;     off = align_up(off + ch * (1 - tk) * pl.BHG * (pl.L / 64) * pl.d * pl.d * 4, 256);
     bp->off_dot = off;     off = align_up(off + ch * (1 - tk) * pl.BHG * (pl.L / 64) * (pl.d / 4) * 4, 256);
-    bp->off_vht = off;     off = align_up(off + n_out * pl.d * 2, 256);   // fp16 V^T tiles of the compacted values (bf16 tensors)
+    bp->off_vh = off;     off = align_up(off + n_out * pl.d * 2, 256);   // fp16 rows of the compacted values (bf16 tensors)
     // head grouping in one pass: the output heads' shares of the gradients of what a group shares
     const size_t gr = pl.G > 1 ? 1 : 0;
     bp->off_pdq = off;     off = align_up(off + gr * n_out * pl.d * 4, 256);
@@ -539,7 +539,7 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
         float* kdv = reinterpret_cast<float*>(ws + pl.off_kdv);
         float* gamC = reinterpret_cast<float*>(ws + pl.off_gam);
         float* seg_ws = reinterpret_cast<float*>(ws + pl.off_seg);
-        void* VhT = ws + pl.off_vht;
+        void* Vh = ws + pl.off_vh;
         void* Oh = ws + pl.off_olah;   // fp16 hand-off between the two branches
         // The linear branch first, leaving its rows as fp16; the softmax kernel runs last and merges where its own
         // rows are in registers (the plain sum of Section 4.1 as well as Eq. 21, which needs whole rows of both
@@ -550,7 +550,7 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
             ProfScope ps("gdn_chunk_inv", stream);
             // (this launch also carries the blocks of the mask scan and compaction)
             st = launch_gdn_chunk_inv(pl, Q, K, alpha, beta, mask, TF, PF, gamv, kdv, gamC, Ks, V, cnt, idx, n_s, Kc, Vc,
-                                      ex.Kc, ex.Vc, ex.cap, VhT, stream);
+                                      ex.Kc, ex.Vc, ex.cap, Vh, stream);
         }
         if (st != NATS_OK) return st;
         st = launch_gdn_seg_scan(pl, Q, K, V, TF, PF, gamv, kdv, gamC, ex.initial_state, ex.final_state, seg_ws, Oh,
@@ -558,7 +558,7 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
         if (st != NATS_OK) return st;
         {
             ProfScope ps("flash_softmax", stream);
-            st = launch_flash_softmax(pl, Qs, Kc, VhT, Ks, V, cnt, Oh, ex.w_nla, ex.w_la, O, ex.O_nla, ex.lse, stream, W_fused);
+            st = launch_flash_softmax(pl, Qs, Kc, Vh, Ks, V, cnt, Oh, ex.w_nla, ex.w_la, O, ex.O_nla, ex.lse, stream, W_fused);
         }
     } else {
         if (pl.fp32_chunks) {
@@ -668,7 +668,7 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     // The softmax branch's forward: the plain sum needs its rows for D_i alone and takes the forward's own kernel; behind
     // a merge that normalises them they are differentiated through, in fp32 accuracy.
     const bool mfma_stats = pl.dtype == NATS_BF16 && bp.merge_mode == 0;
-    void* VhT = mfma_stats ? ws + bp.off_vht : nullptr;
+    void* Vh = mfma_stats ? ws + bp.off_vh : nullptr;
     float* ops = reinterpret_cast<float*>(ws + bp.off_ops);
     float* Uh = reinterpret_cast<float*>(ws + bp.off_uh);
     float* dck = reinterpret_cast<float*>(ws + bp.off_dck);
@@ -679,17 +679,17 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     const bool chunk_states = by_chunks || !chunk;
     if (chunk_states) {
         ProfScope ps("gdn_bwd_prep", stream);
-        st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, true, Ks, V, cnt, idx, n_s, Kc, Vc, nullptr, nullptr, 0, VhT,
+        st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, true, Ks, V, cnt, idx, n_s, Kc, Vc, nullptr, nullptr, 0, Vh,
                                  stream);
         if (st != NATS_OK) return st;
     } else {
         ProfScope ps("scan_compact", stream);
-        st = launch_scan_compact(pl, mask, Ks, V, cnt, idx, n_s, Kc, Vc, nullptr, nullptr, 0, VhT, stream);
+        st = launch_scan_compact(pl, mask, Ks, V, cnt, idx, n_s, Kc, Vc, nullptr, nullptr, 0, Vh, stream);
         if (st != NATS_OK) return st;
     }
     if (mfma_stats) {
         ProfScope ps("flash_softmax", stream);
-        st = launch_flash_softmax(pl, Qs, Kc, VhT, Ks, V, cnt, nullptr, nullptr, nullptr, nullptr, O_nla, lse, stream);
+        st = launch_flash_softmax(pl, Qs, Kc, Vh, Ks, V, cnt, nullptr, nullptr, nullptr, nullptr, O_nla, lse, stream);
         if (st != NATS_OK) return st;
     } else {
         ProfScope ps("softmax_terms_fwd", stream);

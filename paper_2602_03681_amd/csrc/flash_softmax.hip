@@ -8,11 +8,16 @@
 // output in registers.  Everything is computed transposed so that no operand has to be
 // re-laid out between the two products:
 //   S^T [key x query] = Kc Q^T     bf16 MFMA (inputs exact), A = K tile from LDS, B = Q held in registers
-//   O^T [d_v x query] += V^T P^T   fp16 MFMA, A = V^T tile from LDS (written transposed, fp16, by the
-//                                  compaction kernel), B = P^T straight from the S^T accumulators:
+//   O^T [d_v x query] += V^T P^T   fp16 MFMA, A = V^T from the V tile in LDS by transposing reads
+//                                  (ds_read_b64_tr_b16), B = P^T straight from the S^T accumulators:
 //                                  a result tile gives each lane 4 consecutive keys of one query, and two
-//                                  such tiles fill the 8 contraction slots of one lane (the V^T tile's
-//                                  columns are stored in that slot order).
+//                                  such tiles fill the 8 contraction slots of one lane (two reads, of 4 keys
+//                                  each, give the other operand in that slot order).
+// V comes as fp16 rows (the compaction's copy) and, from a chunk of the block's own queries, as bf16 rows.  (With V^T
+// tiles written by the compaction in scattered stores of 2 bytes, and a block's own chunks transposed by writes of
+// 2 bytes to LDS, a layer of B 4, H 6, G 2, L 4096, routing per chunk, took 239 us, this kernel 108 of them, now 213 and
+// 88; a prefill of 3 x 1216 tokens, a fifth of them softmax tokens, 85.4, now 74.3, the launch with the compaction in it
+// 23.5, now 13.0.)
 // A query is one MFMA column, so its max / sum live in the 4 lanes {l, l+16, l+32, l+48}:
 // two xor-shuffles per reduction.  P is rounded to fp16 (2^-12), not bf16: with few visible
 // keys a single p v term dominates and bf16's 2^-9 would exceed the parity bar.
@@ -29,7 +34,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int FL_THREADS = 256;
 constexpr int FL_NQ = 2;                 // 16-query MFMA columns per wavefront
-constexpr int FL_VAHEAD = 6;             // V^T fragment reads in flight ahead of their matrix instructions
+constexpr int FL_VAHEAD = 6;             // V^T fragments in flight ahead of their matrix instructions
 constexpr int FL_OCC = 2;                // blocks per CU the kernel is built for
 constexpr int FL_BM = 4 * 16 * FL_NQ;    // queries per block
 constexpr int FL_BN = 64;                // compacted keys per tile
@@ -67,7 +72,7 @@ __device__ __forceinline__ float quad_sum(float x) {
 // none of their code.
 template <int D, bool chunk_routing, bool STATS, bool MERGED>
 __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kc, const half_t* __restrict__ VhT,
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kc, const half_t* __restrict__ Vh,
     const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const int32_t* __restrict__ cnt, const half_t* __restrict__ O_la, const float* __restrict__ w_nla,
     const float* __restrict__ w_la, bf16_t* __restrict__ O,
@@ -76,13 +81,13 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     int heads_out) {
     const int combine_mode = MERGED ? combine_mode_arg : 0;
     constexpr int RS = D + LDS_PAD;      // K / Q tile rows (bf16 elements)
-    constexpr int TS = FL_BN + LDS_PAD;  // V^T tile rows (fp16 elements)
+    constexpr int VS = D + 16;           // V tile rows (fp16 elements): the transposing reads of 8 rows meet every bank once
     constexpr int OS = D + 4;            // output staging rows (fp32 elements)
     constexpr int KS_D = D / 32;
     constexpr int DT = D / 16;           // 16-row d_v tiles
-    // one LDS region, three tenants: the Q tile (prologue), the K and V^T tiles (main loop), the
+    // one LDS region, three tenants: the Q tile (prologue), the K and V tiles (main loop), the
     // per-wavefront output staging (epilogue)
-    constexpr int TILE_BYTES = FL_BN * RS * 2 + D * TS * 2;
+    constexpr int TILE_BYTES = FL_BN * (RS + VS) * 2;
     constexpr int Q_BYTES = FL_BM * RS * 2;
     constexpr int O_BYTES = 4 * 16 * OS * 4;
     constexpr int LDS_BYTES = TILE_BYTES > Q_BYTES ? (TILE_BYTES > O_BYTES ? TILE_BYTES : O_BYTES)
@@ -114,7 +119,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
 
     // ---- prologue: the block's Q rows, coalesced, through LDS into B-operand fragments ------------
     constexpr int NQP = FL_BM * D / 8 / FL_THREADS;   // 16-byte pieces per thread of the Q tile
-    constexpr int NKP = FL_BN * D / 8 / FL_THREADS;   // ... of a K tile and of a V^T tile
+    constexpr int NKP = FL_BN * D / 8 / FL_THREADS;   // ... of a K tile and of a V tile
     // Every global load of the prologue is issued before the first use of any of them, so that the
     // block pays one memory latency here, not one per dependent step: the per-query counts, the count
     // that bounds the block, the Q tile and key tile 0 (which exists for every sequence: the
@@ -135,10 +140,10 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         my_cnt[nq] = visible_rows(min(q0 + ql, L - 1));
     }
     const int n_hi = visible_rows(q_last);    // non-decreasing in t: bound for the whole block
-    u32x4 kreg[NKP], vreg[NKP];               // next K / V^T tile on its way from global memory to LDS
+    u32x4 kreg[NKP], vreg[NKP];               // next K / V tile on its way from global memory to LDS
     auto load_tile = [&](int kt) __attribute__((always_inline)) {
         const u32x4* Kt = reinterpret_cast<const u32x4*>(Kc + (tokbase + (size_t)kt * FL_BN) * D);
-        const u32x4* Vt = reinterpret_cast<const u32x4*>(VhT + (tokbase + (size_t)kt * FL_BN) * D);   // [D][64]
+        const u32x4* Vt = reinterpret_cast<const u32x4*>(Vh + (tokbase + (size_t)kt * FL_BN) * D);
 #pragma unroll
         for (int i = 0; i < NKP; ++i) {   // both tiles are contiguous in global memory
             kreg[i] = Kt[tid + FL_THREADS * i];
@@ -213,17 +218,11 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         const int dc = kt - n_tiles;
         __syncthreads();   // the previous tile (or the Q tile) is no longer read
 #pragma unroll
-        for (int i = 0; i < NKP; ++i) {   // registers -> LDS: K rows [key][d], V^T rows [d_v][key]
-            const int e = tid + FL_THREADS * i;
-            *reinterpret_cast<u32x4*>(Ks + (e / (D / 8)) * RS + (e % (D / 8)) * 8) = kreg[i];
-            if (!own) {
-                *reinterpret_cast<u32x4*>(Vs + (e >> 3) * TS + (e & 7) * 8) = vreg[i];
-            } else {   // a piece of row `key` of V: transposed here, columns in the order the compaction kernel uses
-                const int key = e / (D / 8), c8 = e % (D / 8);
-                const half8 hv = bf16x8_to_half8(vreg[i]);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) Vs[(c8 * 8 + j) * TS + vht_col(key)] = hv[j];
-            }
+        for (int i = 0; i < NKP; ++i) {   // registers -> LDS: rows [key][d] of K and V
+            const int e = tid + FL_THREADS * i, row = e / (D / 8), c = (e % (D / 8)) * 8;
+            *reinterpret_cast<u32x4*>(Ks + row * RS + c) = kreg[i];
+            if (own) vreg[i] = __builtin_bit_cast(u32x4, bf16x8_to_half8(vreg[i]));
+            *reinterpret_cast<u32x4*>(Vs + row * VS + c) = vreg[i];
         }
         __syncthreads();
         load_any(kt + 1 < n_all ? kt + 1 : kt);   // next tile in flight during this tile's products
@@ -339,8 +338,14 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         for (int t = 0; t < DT; ++t)
 #pragma unroll
             for (int s2 = 0; s2 < 2; ++s2) {
-                // the tile's columns were stored in contraction-slot order by the compaction kernel
-                const half8 fv = lds_read8(Vs + (16 * t + l16) * TS + 32 * s2 + 8 * lq);
+                // lane (l16, lq): column 16 t + l16, keys 32 s2 + 4 lq + j in slots j < 4, 16 further in the others (a
+                // group of 16 lanes names 4 rows x 16 columns and receives them transposed)
+                typedef short s16x4 __attribute__((ext_vector_type(4)));
+                typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+                const half_t* av = Vs + (32 * s2 + 4 * lq + (l16 >> 2)) * VS + 16 * t + 4 * (l16 & 3);
+                const half4 v_lo = __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)av));
+                const half4 v_hi = __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(av + 16 * VS)));
+                const half8 fv = __builtin_shufflevector(v_lo, v_hi, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
                 for (int nq = 0; nq < FL_NQ; ++nq) {
                     accO[nq][t] = mfma16(fv, pf[nq][s2], accO[nq][t]);
@@ -363,11 +368,11 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         // Issue order of this block: V^T fragments several reads ahead of the matrix instructions that take
         // them (the compiler's own order waits for every other read just before its use).
         if (!STATS) {
-            __builtin_amdgcn_sched_group_barrier(0x100, FL_VAHEAD, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2 * FL_VAHEAD, 0);
 #pragma unroll
             for (int i = 0; i < DT * 2; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, FL_NQ, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             }
         }
     }
@@ -588,7 +593,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
 }
 
 template <int D>
-static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const void* VhT, const void* K,
+static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vh, const void* K,
                       const void* V, const int32_t* cnt,
                       const void* O_la, const float* w_nla, const float* w_la, void* O,
                       float* O_nla_out, float* lse_out, const float* W_out, hipStream_t st) {
@@ -596,12 +601,12 @@ static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const vo
     if (O == nullptr) {   // the backward pass's call: branch output and log-sum-exp only
         if (pl.routing == NATS_ROUTE_CHUNK)
             hipLaunchKernelGGL((flash_softmax_kernel<D, true, true, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)VhT, (const bf16_t*)K, (const bf16_t*)V, cnt, nullptr,
+                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt, nullptr,
                                nullptr, nullptr, nullptr, O_nla_out, lse_out, pl.L, pl.softmax_scale, 0, pl.rms_eps, pl.BHG,
                                pl.G, pl.qk_per_out_head, pl.inner_chunk != 2, nullptr, 0, 1);
         else
             hipLaunchKernelGGL((flash_softmax_kernel<D, false, true, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)VhT, (const bf16_t*)K, (const bf16_t*)V, cnt, nullptr,
+                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt, nullptr,
                                nullptr, nullptr, nullptr, O_nla_out, lse_out, pl.L, pl.softmax_scale, 0, pl.rms_eps, pl.BHG,
                                pl.G, pl.qk_per_out_head, pl.inner_chunk != 2, nullptr, 0, 1);
         return;
@@ -609,13 +614,13 @@ static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const vo
     if (pl.combine_mode != 0) {   // Eq. 21, its ablation, Eq. 22: the instantiation with their code
         if (pl.routing == NATS_ROUTE_CHUNK)
             hipLaunchKernelGGL((flash_softmax_kernel<D, true, false, true>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)VhT, (const bf16_t*)K, (const bf16_t*)V, cnt,
+                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
                                (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
                                pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
                                W_out, pl.weight_act, pl.H * pl.G);
         else
             hipLaunchKernelGGL((flash_softmax_kernel<D, false, false, true>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)VhT, (const bf16_t*)K, (const bf16_t*)V, cnt,
+                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
                                (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
                                pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
                                W_out, pl.weight_act, pl.H * pl.G);
@@ -623,13 +628,13 @@ static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const vo
     }
     if (pl.routing == NATS_ROUTE_CHUNK)
         hipLaunchKernelGGL((flash_softmax_kernel<D, true, false, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                           (const bf16_t*)Kc, (const half_t*)VhT, (const bf16_t*)K, (const bf16_t*)V, cnt,
+                           (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
                            (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
                            pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
                            W_out, pl.weight_act, pl.H * pl.G);
     else
         hipLaunchKernelGGL((flash_softmax_kernel<D, false, false, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                           (const bf16_t*)Kc, (const half_t*)VhT, (const bf16_t*)K, (const bf16_t*)V, cnt,
+                           (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
                            (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
                            pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
                            W_out, pl.weight_act, pl.H * pl.G);
@@ -638,7 +643,7 @@ static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const vo
 // reads O_la (fp16, the linear branch's rows), merges, writes O.  O = NULL: no merge, O_nla_out and lse_out (both
 // required then) to fp32 accuracy.  W_out (or NULL): the merge weights made here from the kernel's queries by
 // Eq. 22 instead of read from w_nla, w_la; only with O_nla_out = NULL, and Q must be the tensor Eq. 22 reads.
-nats_status launch_flash_softmax(const FwdPlan& pl, const void* Q, const void* Kc, const void* VhT,
+nats_status launch_flash_softmax(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vh,
                                  const void* K, const void* V, const int32_t* cnt, const void* O_la, const float* w_nla,
                                  const float* w_la, void* O, float* O_nla_out, float* lse_out, hipStream_t st,
                                  const float* W_out) {
@@ -646,8 +651,8 @@ nats_status launch_flash_softmax(const FwdPlan& pl, const void* Q, const void* K
         set_error("flash_softmax: weights by Eq. 22 inside the kernel need the merge without the fp32 side output");
         return NATS_ERR_UNSUPPORTED;
     }
-    if (pl.d == 64) launch_fl<64>(pl, Q, Kc, VhT, K, V, cnt, O_la, w_nla, w_la, O, O_nla_out, lse_out, W_out, st);
-    else launch_fl<128>(pl, Q, Kc, VhT, K, V, cnt, O_la, w_nla, w_la, O, O_nla_out, lse_out, W_out, st);
+    if (pl.d == 64) launch_fl<64>(pl, Q, Kc, Vh, K, V, cnt, O_la, w_nla, w_la, O, O_nla_out, lse_out, W_out, st);
+    else launch_fl<128>(pl, Q, Kc, Vh, K, V, cnt, O_la, w_nla, w_la, O, O_nla_out, lse_out, W_out, st);
     return check_launch("flash_softmax");
 }
 

@@ -1241,14 +1241,14 @@ static bool launch_prep_t(const FwdPlan& pl, const PrepArgs<T>& a, const ScanArg
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
                                 const uint8_t* mask, float* ops, bool with_at, const void* Ks, const void* V, int32_t* cnt,
                                 int32_t* idx, int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user,
-                                void* VhT, hipStream_t st) {
+                                void* Vh, hipStream_t st) {
     const int by_chunk = pl.routing == NATS_ROUTE_CHUNK;
     auto go = [&](auto t) {
         using T = decltype(t);
         const PrepArgs<T> a{(const T*)Q, (const T*)K, alpha, beta, mask, chunk_ops(pl, ops, with_at), pl.L, pl.BH,
                             pl.freeze_on_softmax, pl.linear_op, by_chunk};
         const ScanArgs<T> sc{mask, (const T*)Ks, (const T*)V, pl.L, pl.d, cnt, idx, n_s, (T*)Kc, (T*)Vc, (T*)Kc_user, (T*)Vc_user,
-                             cap_user, (half_t*)VhT, by_chunk ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head};
+                             cap_user, (half_t*)Vh, by_chunk ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head};
         return pl.d == 64 ? launch_prep_t<T, 64>(pl, a, sc, st) : launch_prep_t<T, 128>(pl, a, sc, st);
     };
     if (!(pl.dtype == NATS_BF16 ? go(bf16_t{}) : go(float{}))) {

@@ -400,13 +400,13 @@ __global__ __launch_bounds__(INV_THREADS, INV_OCC) void gdn_chunk_inv_kernel(con
 nats_status launch_gdn_chunk_inv(const FwdPlan& pl, const void* Q, const void* K, const float* alpha,
                                  const float* beta, const uint8_t* mask, void* TF, void* PF, float* gamv,
                                  float* kdv, float* gamC, const void* K_sm, const void* V, int32_t* cnt, int32_t* idx,
-                                 int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user, void* VhT,
+                                 int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user, void* Vh,
                                  hipStream_t st) {
     const InvArgs a{(const bf16_t*)Q, (const bf16_t*)K, alpha, beta, mask, pl.L, pl.routing == NATS_ROUTE_CHUNK,
                     (half_t*)TF, (half_t*)PF, gamv, kdv, gamC, pl.BH, pl.linear_op, pl.freeze_on_softmax,
                     pl.inner_chunk == 1};
     const ScanArgs<bf16_t> sc{mask, (const bf16_t*)K_sm, (const bf16_t*)V, pl.L, pl.d, cnt, idx, n_s, (bf16_t*)Kc,
-                              (bf16_t*)Vc, (bf16_t*)Kc_user, (bf16_t*)Vc_user, cap_user, (half_t*)VhT,
+                              (bf16_t*)Vc, (bf16_t*)Kc_user, (bf16_t*)Vc_user, cap_user, (half_t*)Vh,
                               pl.routing == NATS_ROUTE_CHUNK ? 6 : 0, pl.G, pl.qk_per_out_head};   // (this path: routing chunks of 64)
     const int scan_segs = (pl.L + SCAN_SEG - 1) / SCAN_SEG, scan_blocks = scan_segs * pl.BHG;
     dim3 grid((unsigned)(scan_blocks + (pl.L / CH) * ((pl.BH + 7) & ~7)));

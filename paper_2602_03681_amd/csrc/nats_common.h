@@ -152,15 +152,6 @@ struct Vec16<bf16_t> {
     }
 };
 
-// Column of compacted row c inside its V^T tile of 64 keys.  Within each group of 32 keys the columns
-// are stored in the order in which the softmax kernel's second MFMA consumes them: a lane quad lq holds
-// keys {4 lq + j} of the first 16-key result tile and {16 + 4 lq + j} of the second in its 8
-// contraction slots, so those 8 keys are made contiguous (one 16-byte LDS read per fragment).
-__device__ __forceinline__ int vht_col(int c) {
-    const int k32 = c & 31;
-    return (c & 32) + 8 * ((k32 & 15) >> 2) + 4 * (k32 >> 4) + (k32 & 3);
-}
-
 // number of non-zero bytes in a 32-bit word
 __device__ __forceinline__ int nonzero_bytes(uint32_t w) {
     uint32_t t = ((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w;
@@ -213,7 +204,7 @@ struct FwdPlan {
     // workspace carve-up (byte offsets)
     size_t off_cnt, off_idx, off_ns, off_kc, off_vc, off_ola, total;
     // chunkwise (MFMA) linear branch: per-chunk operands
-    size_t off_tf, off_p, off_gamv, off_kdv, off_gam, off_seg, off_vht, off_olah, off_snap, off_wout;
+    size_t off_tf, off_p, off_gamv, off_kdv, off_gam, off_seg, off_vh, off_olah, off_snap, off_wout;
     // fp32 arithmetic, linear branch by chunks: operands and start state of every chunk
     int fp32_chunks;
     size_t off_ops, off_ck;
@@ -222,14 +213,14 @@ struct FwdPlan {
 // kernel launchers (one per .hip file); every pointer is a device pointer
 nats_status launch_scan_compact(const FwdPlan& pl, const uint8_t* mask, const void* K, const void* V,
                                 int32_t* cnt, int32_t* idx, int32_t* n_s, void* Kc, void* Vc,
-                                void* Kc_user, void* Vc_user, int cap_user, void* VhT, hipStream_t st);
+                                void* Kc_user, void* Vc_user, int cap_user, void* Vh, hipStream_t st);
 nats_status launch_gdn_recurrent(const FwdPlan& pl, const void* Q, const void* K, const void* V,
                                  const float* alpha, const float* beta, const uint8_t* mask,
                                  const float* S0, float* S_final, float* O_la, float* snap, hipStream_t st);
 nats_status launch_gdn_chunk_inv(const FwdPlan& pl, const void* Q, const void* K, const float* alpha,
                                  const float* beta, const uint8_t* mask, void* TF, void* PF, float* gamv,
                                  float* kdv, float* gamC, const void* K_sm, const void* V, int32_t* cnt, int32_t* idx,
-                                 int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user, void* VhT,
+                                 int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user, void* Vh,
                                  hipStream_t st);
 int gdn_segments(const FwdPlan& pl);   // segments per (batch, head) the chunkwise linear branch will use
 nats_status launch_gdn_seg_scan(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* TF,
@@ -239,7 +230,7 @@ nats_status launch_gdn_seg_scan(const FwdPlan& pl, const void* Q, const void* K,
 nats_status launch_softmax_terms_fwd(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* K,
                                      const void* V, const int32_t* cnt, const float* O_la, const float* w_nla,
                                      const float* w_la, void* O, float* O_nla_out, float* lse_out, hipStream_t st);
-nats_status launch_flash_softmax(const FwdPlan& pl, const void* Q, const void* Kc, const void* VhT,
+nats_status launch_flash_softmax(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vh,
                                  const void* K, const void* V,
                                  const int32_t* cnt, const void* O_la, const float* w_nla,
                                  const float* w_la, void* O, float* O_nla_out, float* lse_out, hipStream_t st,
@@ -282,7 +273,7 @@ size_t chunk_ops_floats(const FwdPlan& pl, bool with_at);
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
                                 const uint8_t* mask, float* ops, bool with_at, const void* Ks, const void* V, int32_t* cnt,
                                 int32_t* idx, int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user,
-                                void* VhT, hipStream_t st);
+                                void* Vh, hipStream_t st);
 nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void* V, float* ops, bool with_at,
                                     const float* S_init, float* S_final, float* ck, float* Uh, hipStream_t st);
 nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,

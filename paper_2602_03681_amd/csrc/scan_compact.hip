@@ -20,16 +20,16 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_compact_kernel(const ScanAr
 
 nats_status launch_scan_compact(const FwdPlan& pl, const uint8_t* mask, const void* K, const void* V,
                                 int32_t* cnt, int32_t* idx, int32_t* n_s, void* Kc, void* Vc,
-                                void* Kc_user, void* Vc_user, int cap_user, void* VhT, hipStream_t st) {
+                                void* Kc_user, void* Vc_user, int cap_user, void* Vh, hipStream_t st) {
     dim3 grid((pl.L + SCAN_SEG - 1) / SCAN_SEG, pl.BHG);
     if (pl.dtype == NATS_BF16) {
         const ScanArgs<bf16_t> a{mask, (const bf16_t*)K, (const bf16_t*)V, pl.L, pl.d, cnt, idx, n_s, (bf16_t*)Kc,
-                                 (bf16_t*)Vc, (bf16_t*)Kc_user, (bf16_t*)Vc_user, cap_user, (half_t*)VhT,
+                                 (bf16_t*)Vc, (bf16_t*)Kc_user, (bf16_t*)Vc_user, cap_user, (half_t*)Vh,
                                  pl.routing == NATS_ROUTE_CHUNK ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head};
         hipLaunchKernelGGL(scan_compact_kernel<bf16_t>, grid, dim3(SCAN_THREADS), 0, st, a);
     } else {
         const ScanArgs<float> a{mask, (const float*)K, (const float*)V, pl.L, pl.d, cnt, idx, n_s, (float*)Kc,
-                                (float*)Vc, (float*)Kc_user, (float*)Vc_user, cap_user, (half_t*)VhT,
+                                (float*)Vc, (float*)Kc_user, (float*)Vc_user, cap_user, (half_t*)Vh,
                                 pl.routing == NATS_ROUTE_CHUNK ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head};
         hipLaunchKernelGGL(scan_compact_kernel<float>, grid, dim3(SCAN_THREADS), 0, st, a);
     }

@@ -8,7 +8,7 @@
 
 namespace nats {
 
-// fp16 value of one stored element (the MFMA softmax kernel's V^T operand)
+// fp16 value of one stored element (the MFMA softmax kernel's copy of V)
 __device__ __forceinline__ half_t elem_to_half(bf16_t x) { return f32_to_half_sat(to_float(x)); }
 __device__ __forceinline__ half_t elem_to_half(float x) { return f32_to_half_sat(x); }
 
@@ -24,7 +24,7 @@ struct ScanArgs {
     int32_t *cnt, *idx, *n_s;
     T *Kc, *Vc, *Kc_user, *Vc_user;
     int cap_user;
-    half_t* VhT;
+    half_t* Vh;
     int chunk_mask;   // 0: one mask byte per token; otherwise log2 of the routing chunk (6 or 7): one byte per chunk
     int G, k_per_out_head;
 };
@@ -46,7 +46,7 @@ __device__ __forceinline__ void scan_compact_block(const ScanArgs<T>& a, const i
     T* __restrict__ Vc = a.Vc;
     T* __restrict__ Kc_user = a.Kc_user;
     T* __restrict__ Vc_user = a.Vc_user;
-    half_t* __restrict__ VhT = a.VhT;
+    half_t* __restrict__ Vh = a.Vh;
     int* s_wave = lds;                        // [SCAN_THREADS / 64]
     int* s_pos = lds + SCAN_THREADS / 64;     // [SCAN_SEG]
     // Head grouping (Section 4.3): G output heads share the mask of linear head bh.  Every output head gathers
@@ -118,8 +118,8 @@ __device__ __forceinline__ void scan_compact_block(const ScanArgs<T>& a, const i
     const int rows_per_pass = SCAN_THREADS / lpr;
     const int part = tid % lpr;
     // GATHER rows per thread in flight: one row after the other, a pass is a round trip to memory, and a segment with a
-    // fifth of its tokens routed to the softmax branch is 13 passes at d = 128 (the launch it rides in, B 3, H 6, L 1216:
-    // 24.8 us one by one, 23.5 so).
+    // fifth of its tokens routed to the softmax branch is 13 passes at d = 128 (the launch it rides in, B 3, H 6, L 1216,
+    // then with the scattered stores of a transposed copy of V: 24.8 us one by one, 23.5 so).
     constexpr int GATHER = 4;
     for (int r0 = tid / lpr; r0 < seg_total; r0 += GATHER * rows_per_pass) {
         uint4 kr[GATHER], vr[GATHER];
@@ -143,23 +143,28 @@ __device__ __forceinline__ void scan_compact_block(const ScanArgs<T>& a, const i
                 *reinterpret_cast<uint4*>(Kc_user + du) = kv;
                 *reinterpret_cast<uint4*>(Vc_user + du) = vv;
             }
-            if (VhT != nullptr) {   // fp16 copy, transposed inside tiles of 64 compacted rows: [tile][d][64]
+            if (Vh != nullptr) {   // fp16 copy for the softmax kernel on matrix instructions
                 const T* ve = reinterpret_cast<const T*>(&vv);
-                half_t* tile = VhT + ((size_t)bo * L + (size_t)(c >> 6) * 64) * d;
+                half_t* h = Vh + dst;
+                if constexpr (EPL == 8) {
+                    half8 x;
 #pragma unroll
-                for (int j = 0; j < EPL; ++j) tile[(size_t)(part * EPL + j) * 64 + vht_col(c)] = elem_to_half(ve[j]);
+                    for (int j = 0; j < 8; ++j) x[j] = elem_to_half(ve[j]);
+                    *reinterpret_cast<half8*>(h) = x;
+                } else {
+                    half4 x;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[j] = elem_to_half(ve[j]);
+                    *reinterpret_cast<half4*>(h) = x;
+                }
             }
         }
     }
-    // the tail of the last V^T tile is multiplied by zero weights downstream: make it finite
-    if (VhT != nullptr && seg0 + SCAN_SEG >= L) {
-        const int n_total = before + seg_total;
-        const int pad = ((n_total + 63) & ~63) - n_total;
-        half_t* tile = VhT + ((size_t)bo * L + (size_t)(n_total >> 6) * 64) * d;
-        for (int e = tid; e < pad * d; e += SCAN_THREADS) {
-            const int dv = e / pad, cc = (n_total & 63) + e % pad;
-            tile[(size_t)dv * 64 + vht_col(cc)] = (half_t)0.f;
-        }
+    // the rest of the last tile of 64 rows is multiplied by zero weights downstream: make it finite
+    if (Vh != nullptr && seg0 + SCAN_SEG >= L) {
+        const int n_total = before + seg_total, pad = ((n_total + 63) & ~63) - n_total;
+        half_t* rest = Vh + ((size_t)bo * L + n_total) * d;
+        for (int e = tid; e < pad * d / 8; e += SCAN_THREADS) reinterpret_cast<uint4*>(rest)[e] = make_uint4(0u, 0u, 0u, 0u);
     }
 }
 
