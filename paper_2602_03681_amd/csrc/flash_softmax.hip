@@ -3,7 +3,7 @@
 //   Eq. 12: query t sees exactly the first cnt[t] rows of the compacted key/value cache)
 //   O[t] = O_la[t] + o_nla[t]  (Section 4.1)   or   w_nla RMSNorm(o_nla[t]) + w_la RMSNorm(O_la[t])  (Eq. 21)
 //
-// Flash-style: a block owns FL_BM = 128 consecutive queries (4 wavefronts x 32), walks the
+// Flash-style: a block owns 128 consecutive queries (4 wavefronts x 32; 64 for small problems), walks the
 // key tiles of 64 compacted rows that its last query can see, and keeps running max / sum /
 // output in registers.  Everything is computed transposed so that no operand has to be
 // re-laid out between the two products:
@@ -25,6 +25,8 @@
 // MFMA-bound on its tiles: 4 d FLOP per visible (query, key) pair.
 #include <math.h>
 
+#include <type_traits>
+
 #include "mfma_util.h"
 #include "nats_common.h"
 
@@ -33,10 +35,12 @@ namespace nats {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int FL_THREADS = 256;
-constexpr int FL_NQ = 2;                 // 16-query MFMA columns per wavefront
 constexpr int FL_VAHEAD = 6;             // V^T fragments in flight ahead of their matrix instructions
-constexpr int FL_OCC = 2;                // blocks per CU the kernel is built for
-constexpr int FL_BM = 4 * 16 * FL_NQ;    // queries per block
+// 16-query MFMA columns per wavefront (NQ) and blocks per CU the kernel is built for: 2 and 2, or 1 and 3.  Two columns
+// share every read of a K or V^T fragment (B 2, H 16, L 8192: 64 us against 75; B 1, H 16, L 32768: 205 against 255).  Where
+// blocks of two columns would be less than a round of two per CU, blocks of one are twice as many and shorter
+// (B 3, H 6, L 1216, 240 blocks: 15.6 us against 13.2; B 4, H 8, L 2048, d 64, just a round: 10.0 and 9.8).
+constexpr int FL_ONE_ROUND = 512;
 constexpr int FL_BN = 64;                // compacted keys per tile
 
 __device__ __forceinline__ f32x4 mfma16_bf16(u32x4 a, u32x4 b, f32x4 c) {
@@ -70,8 +74,8 @@ __device__ __forceinline__ float quad_sum(float x) {
 // product (and their sum) as the sum of two fp16 terms, and only O_nla_out (fp32) and lse_out are written; no merge.
 // MERGED: the merges other than the plain sum (combine_mode 1, 2) and Eq. 22; the plain sum's instantiation carries
 // none of their code.
-template <int D, bool chunk_routing, bool STATS, bool MERGED>
-__global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
+template <int D, bool chunk_routing, bool STATS, bool MERGED, int NQ>
+__global__ __launch_bounds__(FL_THREADS, (NQ == 1 ? 3 : 2)) void flash_softmax_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kc, const half_t* __restrict__ Vh,
     const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const int32_t* __restrict__ cnt, const half_t* __restrict__ O_la, const float* __restrict__ w_nla,
@@ -80,6 +84,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     float eps, int BH, int G, int qk_per_out_head, int own_chunk, const float* __restrict__ W_out, int weight_act,
     int heads_out) {
     const int combine_mode = MERGED ? combine_mode_arg : 0;
+    constexpr int BM = 4 * 16 * NQ;      // queries per block
     constexpr int RS = D + LDS_PAD;      // K / Q tile rows (bf16 elements)
     constexpr int VS = D + 16;           // V tile rows (fp16 elements): the transposing reads of 8 rows meet every bank once
     constexpr int OS = D + 4;            // output staging rows (fp32 elements)
@@ -88,7 +93,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     // one LDS region, three tenants: the Q tile (prologue), the K and V tiles (main loop), the
     // per-wavefront output staging (epilogue)
     constexpr int TILE_BYTES = FL_BN * (RS + VS) * 2;
-    constexpr int Q_BYTES = FL_BM * RS * 2;
+    constexpr int Q_BYTES = BM * RS * 2;
     constexpr int O_BYTES = 4 * 16 * OS * 4;
     constexpr int LDS_BYTES = TILE_BYTES > Q_BYTES ? (TILE_BYTES > O_BYTES ? TILE_BYTES : O_BYTES)
                                                    : (Q_BYTES > O_BYTES ? Q_BYTES : O_BYTES);
@@ -111,20 +116,20 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     const int bh = chunk_routing ? blockIdx.x / n_tiles_g : blockIdx.x % bh8;
     const int tile = n_tiles_g - 1 - (chunk_routing ? blockIdx.x % n_tiles_g : blockIdx.x / bh8);
     if (bh >= BH) return;
-    const int q0 = tile * FL_BM;
+    const int q0 = tile * BM;
     const size_t tokbase = (size_t)bh * L;                 // bh counts output heads (BH of them)
     const size_t tokbase_lin = (size_t)(bh / G) * L;       // the linear head whose mask the group shares: cnt
     const size_t tokbase_qk = qk_per_out_head ? tokbase : tokbase_lin;   // queries and raw keys of the softmax branch
     const float scale2 = scale * 1.44269504088896341f;   // logits in base-2 units
 
     // ---- prologue: the block's Q rows, coalesced, through LDS into B-operand fragments ------------
-    constexpr int NQP = FL_BM * D / 8 / FL_THREADS;   // 16-byte pieces per thread of the Q tile
+    constexpr int NQP = BM * D / 8 / FL_THREADS;   // 16-byte pieces per thread of the Q tile
     constexpr int NKP = FL_BN * D / 8 / FL_THREADS;   // ... of a K tile and of a V tile
     // Every global load of the prologue is issued before the first use of any of them, so that the
     // block pays one memory latency here, not one per dependent step: the per-query counts, the count
     // that bounds the block, the Q tile and key tile 0 (which exists for every sequence: the
     // compacted buffers have capacity L >= 64 rows; its contents are not used if nothing is visible).
-    const int q_last = min(q0 + FL_BM, L) - 1;
+    const int q_last = min(q0 + BM, L) - 1;
     // Compacted rows visible to a query: routing per token, the first cnt[t]; routing per chunk, those of
     // earlier chunks, i.e. cnt at the last token before the query's chunk (the chunk's own tokens come
     // from K and V after the compacted tiles, see below).
@@ -133,10 +138,10 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         const int cs = t & ~(FL_BN - 1);
         return cs > 0 ? cnt[tokbase_lin + cs - 1] : 0;
     };
-    int my_cnt[FL_NQ];
+    int my_cnt[NQ];
 #pragma unroll
-    for (int nq = 0; nq < FL_NQ; ++nq) {
-        const int ql = (wave * FL_NQ + nq) * 16 + l16;
+    for (int nq = 0; nq < NQ; ++nq) {
+        const int ql = (wave * NQ + nq) * 16 + l16;
         my_cnt[nq] = visible_rows(min(q0 + ql, L - 1));
     }
     const int n_hi = visible_rows(q_last);    // non-decreasing in t: bound for the whole block
@@ -180,18 +185,18 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     // The tiles of this block in order: n_tiles compacted ones, then (routing per chunk) the chunks the
     // block's own queries lie in.  Tile i + 1 is loaded while tile i is used.
     // (own_chunk = 0: the variant in which only the linear operation computes the inner part of a chunk)
-    const int n_own = (chunk_routing && own_chunk) ? (min(q0 + FL_BM, L) - q0) / FL_BN : 0;
+    const int n_own = (chunk_routing && own_chunk) ? (min(q0 + BM, L) - q0) / FL_BN : 0;
     const int n_all = n_tiles + n_own;
     auto load_any = [&](int i) __attribute__((always_inline)) {
         if (i < n_tiles) load_tile(i); else load_own_chunk(i - n_tiles);
     };
     if (chunk_routing) load_any(0);   // which kind tile 0 is depends on the counts just read
     __syncthreads();
-    u32x4 qf[FL_NQ][KS_D];
+    u32x4 qf[NQ][KS_D];
     int wave_hi = 0, wave_lo = 0x7fffffff;   // most and fewest keys visible to a query of this wavefront
 #pragma unroll
-    for (int nq = 0; nq < FL_NQ; ++nq) {
-        const int ql = (wave * FL_NQ + nq) * 16 + l16;
+    for (int nq = 0; nq < NQ; ++nq) {
+        const int ql = (wave * NQ + nq) * 16 + l16;
         if (q0 + ql >= L) my_cnt[nq] = 0;   // rows past the end see nothing
 #pragma unroll
         for (int ks = 0; ks < KS_D; ++ks)
@@ -202,11 +207,11 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     wave_hi = wave_extreme_i32<true>(wave_hi);
     wave_lo = wave_extreme_i32<false>(wave_lo);
 
-    f32x4 accO[FL_NQ][DT];
-    float m_run[FL_NQ];
-    f32x4 accL[FL_NQ];   // running sum of the weights, the same value in every row
+    f32x4 accO[NQ][DT];
+    float m_run[NQ];
+    f32x4 accL[NQ];   // running sum of the weights, the same value in every row
 #pragma unroll
-    for (int nq = 0; nq < FL_NQ; ++nq) {
+    for (int nq = 0; nq < NQ; ++nq) {
         m_run[nq] = -INFINITY;
         accL[nq] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -227,28 +232,28 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         __syncthreads();
         load_any(kt + 1 < n_all ? kt + 1 : kt);   // next tile in flight during this tile's products
         // keys of this tile visible to each of this lane's queries (may be <= 0 or >= 64)
-        int vis[FL_NQ];
+        int vis[NQ];
         bool full_tile, skip;
         if (!own) {
 #pragma unroll
-            for (int nq = 0; nq < FL_NQ; ++nq) vis[nq] = my_cnt[nq] - kt * FL_BN;
+            for (int nq = 0; nq < NQ; ++nq) vis[nq] = my_cnt[nq] - kt * FL_BN;
             full_tile = (kt + 1) * FL_BN <= wave_lo;
             skip = kt * FL_BN >= wave_hi;     // nothing visible to this wavefront in this tile (uniform)
         } else {
 #pragma unroll
-            for (int nq = 0; nq < FL_NQ; ++nq) {   // causal inside the chunk, the token itself included
-                const int ql = (wave * FL_NQ + nq) * 16 + l16;
+            for (int nq = 0; nq < NQ; ++nq) {   // causal inside the chunk, the token itself included
+                const int ql = (wave * NQ + nq) * 16 + l16;
                 vis[nq] = (q0 + ql < L) ? ql - dc * FL_BN + 1 : 0;
             }
             full_tile = false;
-            skip = (wave * FL_NQ * 16) / FL_BN != dc;   // this wavefront's queries lie in another chunk (uniform)
+            skip = (wave * NQ * 16) / FL_BN != dc;   // this wavefront's queries lie in another chunk (uniform)
         }
         if (skip) continue;
 
-        // ---- S^T = K Q^T for 64 keys x 16*FL_NQ queries ------------------------------------------
-        f32x4 accS[FL_NQ][4];
+        // ---- S^T = K Q^T for 64 keys x 16*NQ queries ------------------------------------------
+        f32x4 accS[NQ][4];
 #pragma unroll
-        for (int nq = 0; nq < FL_NQ; ++nq)
+        for (int nq = 0; nq < NQ; ++nq)
 #pragma unroll
             for (int m = 0; m < 4; ++m) accS[nq][m] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -257,13 +262,13 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
             for (int m = 0; m < 4; ++m) {
                 const u32x4 fk = *reinterpret_cast<const u32x4*>(Ks + (16 * m + l16) * RS + 32 * ks + 8 * lq);
 #pragma unroll
-                for (int nq = 0; nq < FL_NQ; ++nq) accS[nq][m] = mfma16_bf16(fk, qf[nq][ks], accS[nq][m]);
+                for (int nq = 0; nq < NQ; ++nq) accS[nq][m] = mfma16_bf16(fk, qf[nq][ks], accS[nq][m]);
             }
         // issue order: K fragments several reads ahead of the matrix instructions that take them
         __builtin_amdgcn_sched_group_barrier(0x100, FL_VAHEAD, 0);
 #pragma unroll
         for (int i = 0; i < KS_D * 4; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, FL_NQ, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, NQ, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
 
@@ -274,9 +279,9 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         // below); the running maximum is raised only when the tile's maximum exceeds it by more than 2^8
         // (the weights then stay below 2^8, exact enough in fp16 and far from overflow), so rescaling of
         // the accumulators is rare and skipped by the whole wavefront.
-        half8 pf[FL_NQ][2], pr[FL_NQ][2];   // pr (STATS): what rounding to fp16 left of the weights
+        half8 pf[NQ][2], pr[NQ][2];   // pr (STATS): what rounding to fp16 left of the weights
 #pragma unroll
-        for (int nq = 0; nq < FL_NQ; ++nq) {
+        for (int nq = 0; nq < NQ; ++nq) {
             if (!full_tile) {
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
@@ -347,7 +352,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
                 const half4 v_hi = __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(av + 16 * VS)));
                 const half8 fv = __builtin_shufflevector(v_lo, v_hi, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
-                for (int nq = 0; nq < FL_NQ; ++nq) {
+                for (int nq = 0; nq < NQ; ++nq) {
                     accO[nq][t] = mfma16(fv, pf[nq][s2], accO[nq][t]);
                     if (STATS) accO[nq][t] = mfma16(fv, pr[nq][s2], accO[nq][t]);
                 }
@@ -360,7 +365,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
 #pragma unroll
             for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                for (int nq = 0; nq < FL_NQ; ++nq) {
+                for (int nq = 0; nq < NQ; ++nq) {
                     accL[nq] = mfma16(ones, pf[nq][s2], accL[nq]);
                     if (STATS) accL[nq] = mfma16(ones, pr[nq][s2], accL[nq]);
                 }
@@ -371,7 +376,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
             __builtin_amdgcn_sched_group_barrier(0x100, 2 * FL_VAHEAD, 0);
 #pragma unroll
             for (int i = 0; i < DT * 2; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, FL_NQ, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, NQ, 0);
                 __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             }
         }
@@ -387,22 +392,22 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         constexpr int HS = D + 8;                 // staged row, fp16 elements
         constexpr int LPR_H = D / 8;              // lanes per row
         constexpr int RPP_H = 64 / LPR_H;         // rows per pass
-        static_assert(4 * FL_NQ * 16 * HS * 2 <= LDS_BYTES, "fp16 output staging must fit the tile region");
-        half_t* Oh = reinterpret_cast<half_t*>(smem) + wave * (FL_NQ * 16 * HS);
+        static_assert(4 * NQ * 16 * HS * 2 <= LDS_BYTES, "fp16 output staging must fit the tile region");
+        half_t* Oh = reinterpret_cast<half_t*>(smem) + wave * (NQ * 16 * HS);
         // Eq. 22 here (W_out given: [heads_out][2][D] f32): the two logits of a query are dot products of its row with
         // the head's two weight vectors, and the query's row is still in this lane group's registers as the first
         // product's operand (lane (l16, lq) holds columns 32 ks + 8 lq .. + 7 of query l16): 8 D / 16 multiply-adds per
         // lane, a sum over the four lanes of the query, the activation; the weights go through LDS to the lanes that
         // merge the row.
-        __shared__ float s_w[MERGED ? 2 : 1][MERGED ? FL_BM : 1];
+        __shared__ float s_w[MERGED ? 2 : 1][MERGED ? BM : 1];
         const bool fused_w = MERGED && combine_mode != 0 && W_out != nullptr;
-        u32x4 la_rows[FL_NQ * 16 / RPP_H];   // the linear branch's rows (fp16), asked for up front (before the
+        u32x4 la_rows[NQ * 16 / RPP_H];   // the linear branch's rows (fp16), asked for up front (before the
         // weights' dot products below, which cover part of their latency)
-        float wn_row[FL_NQ * 16 / RPP_H], wl_row[FL_NQ * 16 / RPP_H];   // the rows' weights (Eq. 21 and its ablation)
+        float wn_row[NQ * 16 / RPP_H], wl_row[NQ * 16 / RPP_H];   // the rows' weights (Eq. 21 and its ablation)
         const float w_default = combine_mode == 1 ? 0.5f : 1.f;
 #pragma unroll
-        for (int pass = 0; pass < FL_NQ * 16 / RPP_H; ++pass) {
-            const int q = q0 + wave * FL_NQ * 16 + pass * RPP_H + lane / LPR_H;
+        for (int pass = 0; pass < NQ * 16 / RPP_H; ++pass) {
+            const int q = q0 + wave * NQ * 16 + pass * RPP_H + lane / LPR_H;
             const size_t tok = tokbase + (q < L ? q : 0);
             la_rows[pass] = *reinterpret_cast<const u32x4*>(O_la + tok * D + 8 * (lane % LPR_H));
             wn_row[pass] = (combine_mode != 0 && !fused_w && w_nla != nullptr) ? w_nla[tok] : w_default;
@@ -410,9 +415,9 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
         }
         if (fused_w) {
             const float* w0 = W_out + (size_t)(bh % heads_out) * 2 * D;
-            float lg[FL_NQ][2];
+            float lg[NQ][2];
 #pragma unroll
-            for (int nq = 0; nq < FL_NQ; ++nq) lg[nq][0] = lg[nq][1] = 0.f;
+            for (int nq = 0; nq < NQ; ++nq) lg[nq][0] = lg[nq][1] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KS_D; ++ks) {
                 float wv[2][8];
@@ -424,7 +429,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
                     wv[k][4] = y.x; wv[k][5] = y.y; wv[k][6] = y.z; wv[k][7] = y.w;
                 }
 #pragma unroll
-                for (int nq = 0; nq < FL_NQ; ++nq)
+                for (int nq = 0; nq < NQ; ++nq)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const float qa = __uint_as_float(qf[nq][ks][j] << 16), qb = __uint_as_float(qf[nq][ks][j] & 0xffff0000u);
@@ -433,7 +438,7 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
                     }
             }
 #pragma unroll
-            for (int nq = 0; nq < FL_NQ; ++nq) {
+            for (int nq = 0; nq < NQ; ++nq) {
                 const float a = quad_sum(lg[nq][0]), b = quad_sum(lg[nq][1]);
                 float wa, wb;
                 if (weight_act == 0) {          // Eq. 22: softmax over the two logits
@@ -450,14 +455,14 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
                     wb = b;
                 }
                 if (lq == 0) {
-                    s_w[0][(wave * FL_NQ + nq) * 16 + l16] = wa;
-                    s_w[1][(wave * FL_NQ + nq) * 16 + l16] = wb;
+                    s_w[0][(wave * NQ + nq) * 16 + l16] = wa;
+                    s_w[1][(wave * NQ + nq) * 16 + l16] = wb;
                 }
             }
         }
 #pragma unroll
-        for (int nq = 0; nq < FL_NQ; ++nq) {
-            const int q = q0 + (wave * FL_NQ + nq) * 16 + l16;
+        for (int nq = 0; nq < NQ; ++nq) {
+            const int q = q0 + (wave * NQ + nq) * 16 + l16;
             const float l = accL[nq][0];
             const float inv_l = l > 0.f ? 1.f / l : 0.f;
             if (lse_out != nullptr && lq == 0 && q < L)
@@ -469,18 +474,18 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
                                    accO[nq][t][3] * inv_l});
         }
         __builtin_amdgcn_wave_barrier();   // LDS operations of one wavefront complete in order
-        u32x4 rows[FL_NQ * 16 / RPP_H];
+        u32x4 rows[NQ * 16 / RPP_H];
 #pragma unroll
-        for (int pass = 0; pass < FL_NQ * 16 / RPP_H; ++pass) {
+        for (int pass = 0; pass < NQ * 16 / RPP_H; ++pass) {
             rows[pass] = *reinterpret_cast<const u32x4*>(Oh + (pass * RPP_H + lane / LPR_H) * HS + 8 * (lane % LPR_H));
             if (fused_w) {   // this wavefront's own queries: written above by this wavefront
-                wn_row[pass] = s_w[0][wave * FL_NQ * 16 + pass * RPP_H + lane / LPR_H];
-                wl_row[pass] = s_w[1][wave * FL_NQ * 16 + pass * RPP_H + lane / LPR_H];
+                wn_row[pass] = s_w[0][wave * NQ * 16 + pass * RPP_H + lane / LPR_H];
+                wl_row[pass] = s_w[1][wave * NQ * 16 + pass * RPP_H + lane / LPR_H];
             }
         }
 #pragma unroll
-        for (int pass = 0; pass < FL_NQ * 16 / RPP_H; ++pass) {
-            const int q = q0 + wave * FL_NQ * 16 + pass * RPP_H + lane / LPR_H;
+        for (int pass = 0; pass < NQ * 16 / RPP_H; ++pass) {
+            const int q = q0 + wave * NQ * 16 + pass * RPP_H + lane / LPR_H;
             const half8 a = __builtin_bit_cast(half8, rows[pass]), b = __builtin_bit_cast(half8, la_rows[pass]);
             float o[8];
             if (combine_mode == 0) {   // O = O_la + O_nla (Section 4.1), rounded to bf16 once
@@ -525,20 +530,20 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     constexpr int LPR = D / 4;            // lanes per output row (float4 each)
     constexpr int RPP = 64 / LPR;         // rows per pass of a wavefront
     float* Ow = Ot + wave * 16 * OS;
-    half4 lah_all[FL_NQ][16 / RPP];       // the linear branch's rows, all loads issued up front
+    half4 lah_all[NQ][16 / RPP];       // the linear branch's rows, all loads issued up front
 #pragma unroll
-    for (int nq = 0; nq < FL_NQ; ++nq)
+    for (int nq = 0; nq < NQ; ++nq)
 #pragma unroll
         for (int pass = 0; pass < 16 / RPP; ++pass) {
-            const int q = q0 + (wave * FL_NQ + nq) * 16 + pass * RPP + lane / LPR;
+            const int q = q0 + (wave * NQ + nq) * 16 + pass * RPP + lane / LPR;
             lah_all[nq][pass] = half4{0, 0, 0, 0};
             if (!STATS)
                 lah_all[nq][pass] =
                     *reinterpret_cast<const half4*>(O_la + (tokbase + (q < L ? q : 0)) * D + 4 * (lane % LPR));
         }
 #pragma unroll
-    for (int nq = 0; nq < FL_NQ; ++nq) {
-        const int qbase = q0 + (wave * FL_NQ + nq) * 16;
+    for (int nq = 0; nq < NQ; ++nq) {
+        const int qbase = q0 + (wave * NQ + nq) * 16;
         const float l = accL[nq][0];
         const float inv_l = l > 0.f ? 1.f / l : 0.f;
         if (lse_out != nullptr && lq == 0 && qbase + l16 < L)
@@ -592,52 +597,39 @@ __global__ __launch_bounds__(FL_THREADS, FL_OCC) void flash_softmax_kernel(
     }
 }
 
+template <int D, bool chunk_routing, bool STATS, bool MERGED>
+static void launch_fl_t(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vh, const void* K, const void* V,
+                        const int32_t* cnt, const void* O_la, const float* w_nla, const float* w_la, void* O,
+                        float* O_nla_out, float* lse_out, const float* W_out, hipStream_t st) {
+    auto go = [&](auto nq) {
+        constexpr int NQ = decltype(nq)::value, BM = 4 * 16 * NQ;
+        const dim3 grid((unsigned)(((pl.L + BM - 1) / BM) * ((pl.BHG + 7) & ~7)));
+        hipLaunchKernelGGL((flash_softmax_kernel<D, chunk_routing, STATS, MERGED, NQ>), grid, dim3(FL_THREADS), 0, st,
+                           (const bf16_t*)Q, (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
+                           (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L, pl.softmax_scale,
+                           pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2, W_out,
+                           pl.weight_act, pl.H * pl.G);
+    };
+    if (((pl.L + 127) / 128) * ((pl.BHG + 7) & ~7) < FL_ONE_ROUND) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 2>{});
+}
 template <int D>
-static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vh, const void* K,
-                      const void* V, const int32_t* cnt,
-                      const void* O_la, const float* w_nla, const float* w_la, void* O,
+static void launch_fl(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vh, const void* K, const void* V,
+                      const int32_t* cnt, const void* O_la, const float* w_nla, const float* w_la, void* O,
                       float* O_nla_out, float* lse_out, const float* W_out, hipStream_t st) {
-    dim3 grid((unsigned)(((pl.L + FL_BM - 1) / FL_BM) * ((pl.BHG + 7) & ~7)));
+    const bool chunk = pl.routing == NATS_ROUTE_CHUNK;
+#define NATS_FL(CH, ST, ME) launch_fl_t<D, CH, ST, ME>(pl, Q, Kc, Vh, K, V, cnt, O_la, w_nla, w_la, O, O_nla_out, lse_out, W_out, st)
     if (O == nullptr) {   // the backward pass's call: branch output and log-sum-exp only
-        if (pl.routing == NATS_ROUTE_CHUNK)
-            hipLaunchKernelGGL((flash_softmax_kernel<D, true, true, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt, nullptr,
-                               nullptr, nullptr, nullptr, O_nla_out, lse_out, pl.L, pl.softmax_scale, 0, pl.rms_eps, pl.BHG,
-                               pl.G, pl.qk_per_out_head, pl.inner_chunk != 2, nullptr, 0, 1);
-        else
-            hipLaunchKernelGGL((flash_softmax_kernel<D, false, true, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt, nullptr,
-                               nullptr, nullptr, nullptr, O_nla_out, lse_out, pl.L, pl.softmax_scale, 0, pl.rms_eps, pl.BHG,
-                               pl.G, pl.qk_per_out_head, pl.inner_chunk != 2, nullptr, 0, 1);
-        return;
+        if (chunk) NATS_FL(true, true, false);
+        else NATS_FL(false, true, false);
+    } else if (pl.combine_mode != 0) {   // Eq. 21, its ablation, Eq. 22: the instantiation with their code
+        if (chunk) NATS_FL(true, false, true);
+        else NATS_FL(false, false, true);
+    } else {
+        if (chunk) NATS_FL(true, false, false);
+        else NATS_FL(false, false, false);
     }
-    if (pl.combine_mode != 0) {   // Eq. 21, its ablation, Eq. 22: the instantiation with their code
-        if (pl.routing == NATS_ROUTE_CHUNK)
-            hipLaunchKernelGGL((flash_softmax_kernel<D, true, false, true>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
-                               (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
-                               pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
-                               W_out, pl.weight_act, pl.H * pl.G);
-        else
-            hipLaunchKernelGGL((flash_softmax_kernel<D, false, false, true>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                               (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
-                               (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
-                               pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
-                               W_out, pl.weight_act, pl.H * pl.G);
-        return;
-    }
-    if (pl.routing == NATS_ROUTE_CHUNK)
-        hipLaunchKernelGGL((flash_softmax_kernel<D, true, false, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                           (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
-                           (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
-                           pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
-                           W_out, pl.weight_act, pl.H * pl.G);
-    else
-        hipLaunchKernelGGL((flash_softmax_kernel<D, false, false, false>), grid, dim3(FL_THREADS), 0, st, (const bf16_t*)Q,
-                           (const bf16_t*)Kc, (const half_t*)Vh, (const bf16_t*)K, (const bf16_t*)V, cnt,
-                           (const half_t*)O_la, w_nla, w_la, (bf16_t*)O, O_nla_out, lse_out, pl.L,
-                           pl.softmax_scale, pl.combine_mode, pl.rms_eps, pl.BHG, pl.G, pl.qk_per_out_head, pl.inner_chunk != 2,
-                           W_out, pl.weight_act, pl.H * pl.G);
+#undef NATS_FL
 }
 
 // reads O_la (fp16, the linear branch's rows), merges, writes O.  O = NULL: no merge, O_nla_out and lse_out (both
