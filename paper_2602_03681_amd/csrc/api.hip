@@ -213,6 +213,7 @@ struct BwdPlan {
     int G;
     size_t off_gv, off_gdo, off_gdv, off_gdq, off_gdk, off_gda, off_gdb, off_gs0, off_gds0, off_ggn, off_ggl, off_gsn,
         off_gsl, off_gqn, off_gkn, off_gdqn, off_gdkn, total_grouped;
+    size_t reported;   // what the caller is told to bring: total_grouped or more
     // the merges of Eq. 21 and its ablation (merge_mode 1, 2; 0: the plain sum): the linear branch's output rows, the
     // two branches' gradients of their rows, the snapshot rows of the token-by-token forward (routing per chunk), a
     // member's weights and their gradients (head grouping), and, token by token, fp32 copies of bf16 tensors (the pass
@@ -320,6 +321,10 @@ static void plan_bwd_merge(const FwdPlan& pl, int G, BwdPlan* bp) {
 // than BWD_ONE_PASS_BYTES, and token by token, it is the plan of one member of the groups, B x H heads with pl->G = 1, and
 // bp->G = G.
 constexpr size_t BWD_ONE_PASS_BYTES = (size_t)16 << 30;
+// Member by member the workspace is the same for every group size.  Where the one pass over groups of 8 takes no more than
+// this, its size is what is reported for every G > 1 (at most four times what G = 2 needs), so that a small problem's buffer
+// still serves any group size; a call asks for what it needs itself.
+constexpr size_t BWD_ONE_SIZE_BYTES = (size_t)64 << 20;
 static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, BwdPlan* bp) {
     if (p == nullptr) { set_error("params is NULL"); return NATS_ERR_NULL; }
     nats_fwd_params one = *p;
@@ -347,7 +352,18 @@ static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, Bw
         if (fits) {
             plan_bwd(*pl, bp);
             if (bp->merge_mode != 0) plan_bwd_merge(*pl, 1, bp);
-            if (bp->total_grouped <= BWD_ONE_PASS_BYTES) return NATS_OK;
+            if (bp->total_grouped <= BWD_ONE_PASS_BYTES) {
+                bp->reported = bp->total_grouped;
+                FwdPlan pl8;
+                BwdPlan bp8 = *bp;
+                one.group = 8;
+                if (validate_fwd_params(&one, &pl8) == NATS_OK) {
+                    plan_bwd(pl8, &bp8);
+                    if (bp8.merge_mode != 0) plan_bwd_merge(pl8, 1, &bp8);
+                    if (bp8.total_grouped <= BWD_ONE_SIZE_BYTES) bp->reported = bp8.total_grouped;
+                }
+                return NATS_OK;
+            }
         }
         one.group = 1;
     }
@@ -361,6 +377,7 @@ static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, Bw
     plan_bwd(*pl, bp);
     if (G > 1) plan_bwd_group(*pl, G, bp);
     if (bp->merge_mode != 0) plan_bwd_merge(*pl, G, bp);
+    bp->reported = bp->total_grouped;
     return NATS_OK;
 }
 
@@ -604,7 +621,7 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p) {
     FwdPlan pl;
     BwdPlan bp;
     if (validate_bwd_params(p, &pl, &bp) != NATS_OK) return 0;
-    return bp.total_grouped;
+    return bp.reported;
 }
 
 // The backward pass on the plan's heads (pl.G > 1: all output heads of the groups).  ex by value: the optional outputs
