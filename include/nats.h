@@ -248,22 +248,21 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p);
  * softmax token get nothing from the linear branch and vice versa (Section 4.2).
  *   p->combine_mode 1 (Eq. 21) and 2 (Section 5, the ablation with one normalisation): the merge acts on the two
  *             branches' output rows, so its adjoint turns dO into one gradient per branch, and each branch then runs
- *             as for the plain sum.  The pass recomputes both branches' rows in fp32 (the linear branch's token by
- *             token), takes p->rms_eps and extra->w_nla, w_la, and returns extra->dw_nla, dw_la.  These per-branch
- *             gradients are fp32, so bf16 tensors are widened first and the whole pass runs on fp32 tensors
- *             (slower than combine_mode 0, and a workspace larger by the fp32 copies).
+ *             as for the plain sum.  The pass recomputes both branches' rows to fp32 accuracy, takes p->rms_eps and
+ *             extra->w_nla, w_la, and returns extra->dw_nla, dw_la.  The per-branch gradients are fp32 (more work per
+ *             product than combine_mode 0, and a workspace larger by both branches' rows and gradients; with
+ *             NATS_MATH_FP32 bf16 tensors are widened first, and it is larger by the fp32 copies).
  *   Q, K, V, alpha, beta, mask : as in the forward (either routing).
  *             With routing per chunk the function differentiated is the one the
  *             forward computes there: both operations compute every chunk's inner part, the masks act between
  *             chunks, a softmax chunk hands on (its decay) x (the state at its start).  Every sum is fp32 and the recurrence's adjoint is fp32 throughout.
  *             p->math: with NATS_MATH_AUTO the linear branch's adjoint runs by chunks of 64
- *             tokens on fp32 matrix instructions (the chunk form of Eq. 19 / 20 and its derivative; the states
+ *             tokens, in fp32 accuracy on matrix instructions (the chunk form of Eq. 19 / 20 and its derivative; the states
  *             at the chunk starts, then the state gradients behind every chunk, then all chunks in parallel);
  *             dalpha then comes through the logarithms of the decays and needs alpha > 0 (an alpha of exactly 0
  *             gets dalpha = 0).  NATS_MATH_FP32 takes the adjoint token by token (the workspace is larger).
- *             For bf16 tensors the softmax branch's dQ, dK, dV products run on the matrix cores: Q, K, V, dO
- *             enter exactly (they are bf16), the probabilities and dS enter as the sum of two fp16 terms,
- *             so the gradients keep fp32-level accuracy; for f32 tensors those products are fp32 too
+ *             Products run on the bf16 matrix instruction with operands as sums of bf16 terms: bf16 tensors are
+ *             one term, fp32 operands (f32 tensors, probabilities, dS, states) three, which is all of their bits
  *   dO      : in  [B,H,L,d] dtype p->dtype
  *   dQ, dK, dV : out [B,H,L,d] f32 (whatever p->dtype);  dalpha, dbeta : out [B,H,L] f32
  *   extra   : optional, may be NULL
@@ -272,7 +271,8 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p);
  *             V, dO, dV are [B,H*G,L,d] and initial_state, d_initial_state [B,H*G,d,d], head h*G + g the member g
  *             of linear head h as in the forward; Q, K, alpha, beta, mask and their gradients, g_nla, g_la and the
  *             score gradients stay [B,H,...]: a shared input's gradient is the sum over the G heads that read it.
- *             The pass runs once per member (G times the work and a workspace larger by one member's tensors)
+ *             The pass runs over all H*G heads at once (a workspace that grows with G); with NATS_MATH_FP32, and
+ *             where that workspace would exceed 16 GiB, once per member (larger by one member's tensors)
  *   workspace : at least nats_hybrid_attn_bwd_workspace_bytes(p); nothing is kept from the forward call, the
  *             backward recomputes what it needs (the state is checkpointed once per 64 tokens)
  * Sums over (batch, head)-internal blocks are taken in a fixed order: results are deterministic. */
