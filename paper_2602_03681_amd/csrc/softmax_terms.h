@@ -34,6 +34,13 @@ __device__ __forceinline__ f32x4 mfma_terms(const u32x4 (&a)[NA], const u32x4 (&
     return c;
 }
 
+// the terms of the negated numbers
+template <int N>
+__device__ __forceinline__ void negate(u32x4 (&t)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) t[i] ^= 0x80008000u;
+}
+
 // the upper halves of two floats side by side, a's in the low half
 __device__ __forceinline__ uint32_t high_halves(float a, float b) {
     return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);

@@ -24,7 +24,11 @@
 // over the tile's rows read it transposed (ds_read_b64_tr_b16), and P and dS go from the first product's result tiles
 // into the second product's operand in registers.  A tile's product starts from zero and is added to the running sum by
 // a vector add: the matrix instruction's own accumulation does not round to nearest, and over a long walk (a first token
-// seen by 8192 queries) its error showed (1.6e-4 of dV's RMS; 6e-5 this way).  No sum runs over blocks: results are deterministic.
+// seen by 8192 queries) its error showed (1.6e-4 of dV's RMS; 6e-5 this way).  It truncates towards minus infinity, and D,
+// which dP is taken from, is summed by rounding adds: g and the chunk scores, sums of dS over all queries in which dP and D
+// cancel, then collect that error with one sign (2e-6 .. 8e-6 of the chunk scores' norm at L 700 .. 1700, 64-bit arithmetic
+// as the measure).  So every other step of dP's contraction is taken with one operand negated and subtracted: the errors
+// have both signs and the scores are off by 3e-7 .. 1.1e-6, as with sums that round to nearest (4e-7 .. 1.8e-6).  No sum runs over blocks: results are deterministic.
 #include <math.h>
 
 #include "softmax_terms.h"
@@ -272,6 +276,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
         Raw8<TO> ro;
         ro.load(a.dO + off);
         ro.terms(of[ks]);
+        if (ks & 1) negate(of[ks]);
         float x[8];
         ro.floats(x);
         const float4 o0 = ld4(a.O_nla + off), o1 = ld4(a.O_nla + off + 4);
@@ -321,9 +326,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
         __syncthreads();
         if (it + 1 < n_all) fetch(it + 1);
         if (wave_extreme_i32<true>(mine) <= 0) continue;   // uniform
-        f32x4 s[4], dp[4];
+        f32x4 s[4], dp[4], dn[4];   // dn: the steps with the negated operand
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) { s[mt] = f32x4{0.f, 0.f, 0.f, 0.f}; dp[mt] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        for (int mt = 0; mt < 4; ++mt) s[mt] = dp[mt] = dn[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -332,8 +337,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
                 Kt.rows(16 * mt + l16, 32 * ks + 8 * lq, k);
                 Vt.rows(16 * mt + l16, 32 * ks + 8 * lq, v);
                 s[mt] = mfma_terms(k, qf[ks], s[mt]);
-                dp[mt] = mfma_terms(v, of[ks], dp[mt]);
+                if (ks & 1) dn[mt] = mfma_terms(v, of[ks], dn[mt]);
+                else dp[mt] = mfma_terms(v, of[ks], dp[mt]);
             }
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) dp[mt] -= dn[mt];
         u32x4 ds[2][N_TERMS];
 #pragma unroll
         for (int mp = 0; mp < 2; ++mp) {
@@ -422,6 +430,7 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
         r.terms(kf[ks]);
         r.load(a.V + tokb * D + off);
         r.terms(vf[ks]);
+        if (ks & 1) negate(vf[ks]);
     }
     f32x4 accK[MD], accV[MD];
 #pragma unroll
@@ -470,9 +479,9 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
         if (tid < 64) { s_lse2[tid] = rl; s_D[tid] = rd; s_vis[tid] = OWN ? c0 + tid + 1 : rc; }
         __syncthreads();
         if (AHEAD && i0 + 64 < i_hi) fetch(i0 + 64);
-        f32x4 s[4], dp[4];
+        f32x4 s[4], dp[4], dn[4];   // dn: the steps with the negated operand
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) { s[mt] = f32x4{0.f, 0.f, 0.f, 0.f}; dp[mt] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        for (int mt = 0; mt < 4; ++mt) s[mt] = dp[mt] = dn[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -481,8 +490,11 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
                 Qt.rows(16 * mt + l16, 32 * ks + 8 * lq, q);
                 Ot.rows(16 * mt + l16, 32 * ks + 8 * lq, o);
                 s[mt] = mfma_terms(q, kf[ks], s[mt]);   // rows: queries 16 mt + 4 lq + j, column: key l16
-                dp[mt] = mfma_terms(o, vf[ks], dp[mt]);
+                if (ks & 1) dn[mt] = mfma_terms(o, vf[ks], dn[mt]);
+                else dp[mt] = mfma_terms(o, vf[ks], dp[mt]);
             }
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) dp[mt] -= dn[mt];
         u32x4 p[2][N_TERMS], ds[2][N_TERMS];
 #pragma unroll
         for (int mp = 0; mp < 2; ++mp) {

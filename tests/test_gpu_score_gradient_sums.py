@@ -1,0 +1,50 @@
+"""Chunk score gradients of Eq. 16 against 64-bit arithmetic.  They are sums of dS = P (dP - D) over all queries of a head,
+and over the rows that a query sees dS sums to zero: an error of one sign in dP adds up over the queries while the sum itself
+does not grow.  (The bf16 matrix instruction truncates towards minus infinity as it accumulates, 1 part in 2^24 or so.)"""
+import pytest
+import torch
+
+import paper_2602_03681_amd as nats
+from paper_2602_03681_amd import binding as nb
+
+pytestmark = pytest.mark.gpu
+C = 64
+
+
+def _exact(Q, K, V, dO, mask, G):
+    """dscore_nla [B,H,L/C] of the plain sum, in 64 bits: the linear branch has no part in it."""
+    rep = lambda t: t.double().repeat_interleave(G, 1)
+    B, H, L, d = Q.shape
+    q, k, v, g, m = rep(Q), rep(K), V.double(), dO.double(), mask.bool().repeat_interleave(G, 1)
+    t = torch.arange(L, device=Q.device)
+    before = t[:, None] // C > t[None] // C
+    if mask.shape[2] == L:                                   # routing per token
+        see = (t[:, None] >= t[None]) & m[:, :, None]
+        own = torch.zeros_like(see)
+    else:
+        own = ((t[:, None] >= t[None]) & ~before).expand(B, H * G, L, L)
+        see = before & m.repeat_interleave(C, 2)[:, :, None]
+    s = (q @ k.transpose(2, 3).contiguous() / d ** 0.5).masked_fill(~(see | own), float("-inf"))
+    p = torch.nan_to_num(torch.softmax(s, -1))
+    dp = g @ v.transpose(2, 3).contiguous()
+    ds = p * (dp - (p * dp).sum(-1, keepdim=True)) * see
+    return ds.sum(2).view(B, H, G, L // C, C).sum((2, 4))
+
+
+@pytest.mark.parametrize("routing", [nb.NATS_ROUTE_TOKEN, nb.NATS_ROUTE_CHUNK])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,H,G,L,d", [(2, 2, 2, 768, 128), (3, 4, 1, 704, 64), (2, 2, 1, 1664, 128)])
+def test_distance_to_64_bits(B, H, G, L, d, dtype, routing):
+    gen = torch.Generator().manual_seed(L + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    unit = lambda *s: torch.nn.functional.normalize(rnd(*s), dim=-1).to(dtype).cuda()
+    Q, K, V, dO = unit(B, H, L, d), unit(B, H, L, d), rnd(B, H * G, L, d).to(dtype).cuda(), rnd(B, H * G, L, d).to(dtype).cuda()
+    alpha, beta = torch.sigmoid(2 + 0.5 * rnd(B, H, L)).cuda(), torch.sigmoid(rnd(B, H, L)).cuda()
+    n = L // C if routing == nb.NATS_ROUTE_CHUNK else L
+    mask = (torch.rand(B, H, n, generator=gen) < 0.1).to(torch.uint8).cuda()
+    mask[:, :, 0] = 1
+    got = nats.hybrid_attn_bwd(Q, K, V, alpha, beta, mask, dO, C, routing=routing, group=G, want=("dscore_nla",))["dscore_nla"]
+    ref = _exact(Q, K, V, dO, mask, G)
+    # a dS is some ten fp32 roundings of 2^-24 of P dP, and a sum over queries and keys that cancels to a third of the
+    # size its terms would give at random keeps that; measured 3e-7 .. 1.1e-6, with an error of one sign 2e-6 .. 8e-6
+    assert float((got - ref).norm() / ref.norm()) <= 1.5e-6
