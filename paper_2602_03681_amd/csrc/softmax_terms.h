@@ -1,9 +1,12 @@
 // Products to fp32 accuracy on the bf16 matrix instruction (internal header).
 //
-// An fp32 number is exactly the sum of three bf16 numbers: its 24 significant bits cut into 8 + 8 + 8.  A product of
+// An fp32 number is exactly the sum of three bf16 numbers, each the one before's remainder rounded to nearest.  A product of
 // two matrices is then the sum of products of their terms, each at the bf16 rate, 16 times the fp32 rate of
-// this chip: 3 products where one operand is bf16 already (exact up to the fp32 accumulation), 6 where neither is (the
-// three left out are below 2^-23 of the operands' product).  Against one fp32 matrix instruction that is 5 and 2.7
+// this chip: 3 products where one operand is bf16 already (exact up to the fp32 accumulation), 6 where neither is.  The
+// three left out are together at most 2^-23 of the operands' product (second terms reach 2^-8 of the power of two of the
+// number, third ones 2^-16) and have either sign.  (Cut off instead of rounded, the terms after the first reach 2^-7 and
+// 2^-15, all of the number's sign: up to 2^-21, a bias; the carried states of a 512-token recurrence were then 1.1e-7 off,
+// now 7e-8, as in a recurrence of fp32 multiply-adds.)  Against one fp32 matrix instruction that is 5 and 2.7
 // times the rate, and there are no fp16 range limits anywhere.
 #pragma once
 #include "mfma_util.h"
@@ -41,24 +44,25 @@ __device__ __forceinline__ void negate(u32x4 (&t)[N]) {
     for (int i = 0; i < N; ++i) t[i] ^= 0x80008000u;
 }
 
-// the upper halves of two floats side by side, a's in the low half
-__device__ __forceinline__ uint32_t high_halves(float a, float b) {
-    return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+// Two floats -> their bf16 terms, the first float's in the low halves.  Each term is rounded to nearest: what is left is exact in
+// fp32, at most half of the term's last place, and of either sign.
+__device__ __forceinline__ void split_pair(float x, float y, uint32_t (&t)[N_TERMS]) {
+#pragma unroll
+    for (int i = 0; i < N_TERMS; ++i) {
+        t[i] = pack_bf16x2(x, y);
+        if (i == N_TERMS - 1) break;
+        x -= __uint_as_float(t[i] << 16);
+        y -= __uint_as_float(t[i] & 0xffff0000u);
+    }
 }
 // 8 floats -> their bf16 terms
 __device__ __forceinline__ void split_terms(const float (&x)[8], u32x4 (&t)[N_TERMS]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float r[2], q[2];
+        uint32_t p[N_TERMS];
+        split_pair(x[2 * i], x[2 * i + 1], p);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const float v = x[2 * i + k];
-            r[k] = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);          // exact: 16 bits are left
-            q[k] = r[k] - __uint_as_float(__float_as_uint(r[k]) & 0xffff0000u);    // exact: 8 bits are left
-        }
-        t[0][i] = high_halves(x[2 * i], x[2 * i + 1]);
-        t[1][i] = high_halves(r[0], r[1]);
-        t[2][i] = high_halves(q[0], q[1]);
+        for (int n = 0; n < N_TERMS; ++n) t[n][i] = p[n];
     }
 }
 
@@ -99,15 +103,11 @@ struct Raw8 {
 
 // 4 floats -> their bf16 terms
 __device__ __forceinline__ void split_terms(const float (&x)[4], uint2 (&t)[N_TERMS]) {
-    float r[4], q[4];
+    uint32_t lo[N_TERMS], hi[N_TERMS];
+    split_pair(x[0], x[1], lo);
+    split_pair(x[2], x[3], hi);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        r[k] = x[k] - __uint_as_float(__float_as_uint(x[k]) & 0xffff0000u);
-        q[k] = r[k] - __uint_as_float(__float_as_uint(r[k]) & 0xffff0000u);
-    }
-    t[0] = make_uint2(high_halves(x[0], x[1]), high_halves(x[2], x[3]));
-    t[1] = make_uint2(high_halves(r[0], r[1]), high_halves(r[2], r[3]));
-    t[2] = make_uint2(high_halves(q[0], q[1]), high_halves(q[2], q[3]));
+    for (int n = 0; n < N_TERMS; ++n) t[n] = make_uint2(lo[n], hi[n]);
 }
 
 // A tile of 64 rows of D elements in LDS: one plane [64][D + LDS_PAD] of bf16 per term.  Operand of a product over the

@@ -1,0 +1,61 @@
+"""Distances of the fp32 calls from 64-bit arithmetic, as relative 2-norms over random inputs of the workloads' distributions:
+the bars are what fp32 multiply-adds one after the other give, not a tolerance for any fp32 program."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2602_03681_amd as nats
+from paper_2602_03681_amd import binding as nb
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(B, H, L, d, p, seed):
+    gen = torch.Generator().manual_seed(seed)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    unit = lambda *s: torch.nn.functional.normalize(rnd(*s), dim=-1)
+    x = dict(Q=unit(B, H, L, d), K=unit(B, H, L, d), V=rnd(B, H, L, d), alpha=torch.sigmoid(2 + 0.5 * rnd(B, H, L)),
+             beta=torch.sigmoid(rnd(B, H, L)), mask=(torch.rand(B, H, L, generator=gen) < p).to(torch.uint8))
+    return {k: v.cuda() for k, v in x.items()}
+
+
+def _recurrence(x):
+    """O_la [B,H,L,d] and the last state of Eq. 19 / 20, in 64 bits."""
+    q, k, v, a, b = (x[n].double() for n in ("Q", "K", "V", "alpha", "beta"))
+    b = b * (x["mask"] == 0)
+    B, H, L, d = q.shape
+    S = torch.zeros(B, H, d, d, dtype=torch.float64, device=q.device)
+    o = []
+    for t in range(L):
+        S = a[:, :, t, None, None] * S
+        S = S + (b[:, :, t, None] * (v[:, :, t] - (S @ k[:, :, t, :, None])[..., 0]))[..., None] * k[:, :, t, None, :]
+        o.append((S @ q[:, :, t, :, None])[..., 0])
+    return torch.stack(o, 2), S
+
+
+def _distance(got, ref):
+    return float((got.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_carried_state(d):
+    x = _inputs(2, 3, 512, d, 0.1, seed=40 + d)
+    got = nats.hybrid_attn_fwd_ex(*(x[n] for n in ("Q", "K", "V", "alpha", "beta", "mask")), 64, want=("final_state",))
+    # token by token, in fp32 multiply-adds, 7.0e-8 .. 8.5e-8; with a bias in the products 1.1e-7
+    assert _distance(got["final_state"], _recurrence(x)[1]) <= 9.5e-8
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_logits_of_one_sign(d):
+    """Every query sees the first token alone, so lse is its logit; all numbers positive, so nothing that a product leaves
+    out averages away."""
+    rng = np.random.default_rng(d)
+    x = _inputs(1, 2, 64, d, 0.0, seed=50 + d)
+    for n in ("Q", "K"):   # mantissas whose later bits are all ones: the largest remainders
+        bits = 0x3f800000 | rng.integers(0, 128, x[n].shape) << 16 | 0xffff
+        x[n] = torch.from_numpy(bits.astype(np.uint32).view(np.float32)).cuda()
+    x["mask"][:, :, 0] = 1
+    got = nats.hybrid_attn_fwd_ex(*(x[n] for n in ("Q", "K", "V", "alpha", "beta", "mask")), 64, want=("lse",))["lse"]
+    ref = (x["Q"].double() * x["K"].double()[:, :, :1]).sum(-1) / d ** 0.5
+    # d products added in fp32 and scaled: a few roundings of 2^-24
+    assert float(((got.double() - ref) / ref).abs().max()) <= 3e-7
