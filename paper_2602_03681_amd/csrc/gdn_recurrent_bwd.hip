@@ -548,6 +548,14 @@ nats_status launch_bwd_combine(const FwdPlan& pl, const float* dq_part, const fl
     return check_launch("bwd_combine");
 }
 
+// Sum over a chunk's 64 tokens (a wavefront), in lane 0.  In 64 bits: a score gradient is a difference of large terms, and the
+// rounding of their sum is not to be larger than that of the terms.
+__device__ __forceinline__ float chunk_sum(double x) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off);
+    return (float)x;
+}
+
 // Score gradients with routing per token (Section 4.2).  Eq. 17 for one token: the sum over the state's entries
 // of (gradient w.r.t. the state after the token's write) x (what the token wrote) = beta_t (r_t . dS_t k_t), which is
 // beta_t times the gradient of beta_t that the reverse sweep has already reduced; zero for softmax tokens.  Eq. 16
@@ -557,15 +565,15 @@ __global__ __launch_bounds__(64) void score_gradients_kernel(const float* __rest
                                                             float* __restrict__ g_la, float* __restrict__ dscore_nla,
                                                             float* __restrict__ dscore_la, int L) {
     const size_t t = (size_t)blockIdx.y * L + (size_t)blockIdx.x * 64 + threadIdx.x;
-    const float gl = mask[t] ? 0.f : beta[t] * dbeta[t];
-    if (g_la != nullptr) g_la[t] = gl;
+    const double gl = mask[t] ? 0. : (double)beta[t] * (double)dbeta[t];
+    if (g_la != nullptr) g_la[t] = (float)gl;
     const size_t c = (size_t)blockIdx.y * (L / 64) + blockIdx.x;
     if (dscore_la != nullptr) {
-        const float s = lane_group_sum<64>(gl);
+        const float s = chunk_sum(gl);
         if (threadIdx.x == 0) dscore_la[c] = s;
     }
     if (dscore_nla != nullptr) {
-        const float s = lane_group_sum<64>(g_nla[t]);
+        const float s = chunk_sum(g_nla[t]);
         if (threadIdx.x == 0) dscore_nla[c] = s;
     }
 }
@@ -587,7 +595,7 @@ __global__ __launch_bounds__(64) void score_gradients_chunk_kernel(const float* 
                                                                   size_t n_chunks_all) {
     const size_t c = (size_t)blockIdx.y * (L / 64) + blockIdx.x;
     if (dscore_nla != nullptr) {
-        const float s = lane_group_sum<64>(g_nla[(size_t)blockIdx.y * L + (size_t)blockIdx.x * 64 + threadIdx.x]);
+        const float s = chunk_sum(g_nla[(size_t)blockIdx.y * L + (size_t)blockIdx.x * 64 + threadIdx.x]);
         if (threadIdx.x == 0) dscore_nla[c] = s;
     }
     if (dscore_la != nullptr && ds_la_part != nullptr && threadIdx.x == 0) {

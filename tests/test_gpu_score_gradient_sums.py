@@ -48,3 +48,24 @@ def test_distance_to_64_bits(B, H, G, L, d, dtype, routing):
     # a dS is some ten fp32 roundings of 2^-24 of P dP, and a sum over queries and keys that cancels to a third of the
     # size its terms would give at random keeps that; measured 3e-7 .. 1.1e-6, with an error of one sign 2e-6 .. 8e-6
     assert float((got - ref).norm() / ref.norm()) <= 1.5e-6
+
+
+@pytest.mark.parametrize("routing", [nb.NATS_ROUTE_TOKEN, nb.NATS_ROUTE_CHUNK])
+@pytest.mark.parametrize("G", [1, 3])
+def test_a_chunk_score_is_rounded_once(G, routing):
+    """Eq. 16 and 17 as sums over a chunk of what the same call returns per token: one rounding, whatever cancels."""
+    B, H, L, d = 2, 3, 320, 64
+    gen = torch.Generator().manual_seed(7)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    unit = lambda: torch.nn.functional.normalize(rnd(B, H, L, d), dim=-1).cuda()
+    beta = torch.sigmoid(rnd(B, H, L)).cuda()
+    mask = (torch.rand(B, H, L // (C if routing else 1), generator=gen) < 0.3).to(torch.uint8).cuda()
+    want = ("g_nla", "dscore_nla") + (() if routing else ("dscore_la",))
+    r = nats.hybrid_attn_bwd(unit(), unit(), rnd(B, H * G, L, d).cuda(), torch.sigmoid(2 + rnd(B, H, L)).cuda(), beta, mask,
+                             rnd(B, H * G, L, d).cuda(), C, routing=routing, group=G, want=want)
+    sums = dict(dscore_nla=r["g_nla"].double())
+    if not routing:
+        sums["dscore_la"] = beta.double() * r["dbeta"].double() * (mask == 0)
+    for key, per_token in sums.items():
+        ref = per_token.view(B, H, L // C, C).sum(-1)
+        assert bool(((r[key].double() - ref).abs() <= 2.0 ** -24 * 1.001 * ref.abs()).all()), key
