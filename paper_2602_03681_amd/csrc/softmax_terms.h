@@ -37,6 +37,19 @@ __device__ __forceinline__ f32x4 mfma_terms(const u32x4 (&a)[NA], const u32x4 (&
     return c;
 }
 
+// The same with everything but the leading product in a sum of its own, to be added at the end: an accumulation rounds at the
+// size of what it adds onto, and of 6 instructions per step one then adds onto the large sum.
+template <int NA, int NB>
+__device__ __forceinline__ void mfma_terms(const u32x4 (&a)[NA], const u32x4 (&b)[NB], f32x4& lead, f32x4& rest) {
+#pragma unroll
+    for (int s = N_TERMS - 1; s > 0; --s)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int j = s - i;
+            if (j >= 0 && j < NB) rest = mfma_bf16(a[i], b[j], rest);
+        }
+    lead = mfma_bf16(a[0], b[0], lead);
+}
 // the terms of the negated numbers
 template <int N>
 __device__ __forceinline__ void negate(u32x4 (&t)[N]) {

@@ -37,6 +37,21 @@ namespace nats {
 
 constexpr float LOG2E = 1.44269504088896341f, LN2 = 0.69314718055994531f;
 
+// e^x for x <= 0 and a little above.  x is a logit minus the row's maximum or log-sum-exp, taken in one rounding: it is small
+// where the weight counts, so the factor's and the product's rounding are too.  (Logits, maxima and log-sum-exps in base 2
+// would save this multiplication and round each of them at their own size: queries and keys of RMS norm 2, logits of up
+// to 20, d 128: the branch's rows 7.5e-7 from 64 bits, dV 9e-7.)
+__device__ __forceinline__ float exp_of(float x) { return __builtin_amdgcn_exp2f(LOG2E * x); }
+
+// logits from the two sums of mfma_terms; bf16 tensors have one product and no rest
+template <int NT>
+__device__ __forceinline__ void add_rest(f32x4 (&s)[4], const f32x4 (&rest)[4]) {
+    if constexpr (NT > 1) {
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) s[mt] += rest[mt];
+    }
+}
+
 // Grid of the kernels whose blocks own queries: one-dimensional, tile-major over (batch, head) pairs padded to a multiple
 // of 8.  The last tiles, which see the most keys, are dispatched first, and the blocks of a pair land on the same XCD
 // and share its L2 for the compacted keys.
@@ -76,7 +91,6 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_fwd
     const size_t tokb = (size_t)bh * L, tokb_lin = (size_t)(bh / a.G) * L;
     const size_t tokb_qk = a.qk_per_out_head ? tokb : tokb_lin;
     const int t = q0 + 16 * w + l16;   // this lane's query
-    const float scale2 = a.scale * LOG2E;
 
     u32x4 qf[KS][NT];
 #pragma unroll
@@ -93,7 +107,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_fwd
     f32x4 acc[MD];
 #pragma unroll
     for (int md = 0; md < MD; ++md) acc[md] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;   // base-2 units; l_run: this lane's share of the sum
+    float m_run = -INFINITY, l_run = 0.f;   // l_run: this lane's share of the sum
 
     // tile it: compacted rows 64 it .. , then the chunk's own rows; fetched while the tile before it is multiplied
     Raw8<T> rk[NPC], rv[NPC];
@@ -131,17 +145,18 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_fwd
         __syncthreads();
         if (it + 1 < n_comp + n_own) fetch(it + 1);
         if (wave_extreme_i32<true>(mine) <= 0) continue;   // uniform: none of the wavefront's queries sees the tile
-        f32x4 s[4];
+        f32x4 s[4], sr[4];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) s[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < 4; ++mt) s[mt] = sr[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 u32x4 k[NT];
                 Kt.rows(16 * mt + l16, 32 * ks + 8 * lq, k);
-                s[mt] = mfma_terms(k, qf[ks], s[mt]);   // rows: keys 16 mt + 4 lq + j, column: query l16
+                mfma_terms(k, qf[ks], s[mt], sr[mt]);   // rows: keys 16 mt + 4 lq + j, column: query l16
             }
+        add_rest<NT>(s, sr);
         if (wave_extreme_i32<false>(mine) < 64) {   // uniform: some query does not see the whole tile
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt)
@@ -153,11 +168,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_fwd
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
             for (int j = 0; j < 4; ++j) tm = fmaxf(tm, s[mt][j]);
-        tm *= scale2;   // scale2 > 0
+        tm *= a.scale;   // > 0
         tm = fmaxf(tm, lane_xor16(tm, lane));
         tm = fmaxf(tm, lane_xor32(tm, lane));
         const float m_new = fmaxf(m_run, tm), m_use = m_new == -INFINITY ? 0.f : m_new;   // nothing visible yet: weights 0
-        const float corr = __builtin_amdgcn_exp2f(m_run - m_use);                          // 2^-inf = 0 on the first tile
+        const float corr = exp_of(m_run - m_use);   // exp(-inf) = 0 on the first tile
         m_run = m_new;
         float ps = 0.f;
         u32x4 p[2][N_TERMS];
@@ -166,7 +181,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_fwd
             float x[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                x[j] = __builtin_amdgcn_exp2f(fmaf(scale2, s[2 * mp + (j >> 2)][j & 3], -m_use));
+                x[j] = exp_of(fmaf(a.scale, s[2 * mp + (j >> 2)][j & 3], -m_use));
                 ps += x[j];
             }
             split_terms(x, p[mp]);
@@ -190,7 +205,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_fwd
     l_run += lane_xor32(l_run, lane);
     const float inv_l = l_run > 0.f ? 1.f / l_run : 0.f;
     const size_t row = tokb + t;
-    if (a.lse != nullptr && lq == 0) a.lse[row] = l_run > 0.f ? (m_run + __builtin_amdgcn_logf(l_run)) * LN2 : -INFINITY;
+    if (a.lse != nullptr && lq == 0) a.lse[row] = l_run > 0.f ? m_run + __builtin_amdgcn_logf(l_run) * LN2 : -INFINITY;
 #pragma unroll
     for (int md = 0; md < MD; ++md) {
         acc[md][0] *= inv_l; acc[md][1] *= inv_l; acc[md][2] *= inv_l; acc[md][3] *= inv_l;
@@ -263,7 +278,6 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, lq = lane >> 4;
     const size_t tokb = (size_t)bh * a.L, tokb_lin = (size_t)(bh / a.G) * a.L, tokb_qk = a.qk_per_out_head ? tokb : tokb_lin;
     const int t = q0 + 16 * w + l16;   // this lane's query
-    const float scale2 = a.scale * LOG2E;
 
     u32x4 qf[KS][NT], of[KS][NO];
     float Dq = 0.f;   // D = do . o: the query's row lies in its 4 lanes
@@ -285,7 +299,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
     Dq += lane_xor16(Dq, lane);
     Dq += lane_xor32(Dq, lane);
     if (lq == 0) a.Dvec[tokb + t] = Dq;
-    const float lse2 = a.lse[tokb + t] * LOG2E;
+    const float lse = a.lse[tokb + t];
     const int my_cnt = a.vis[tokb_lin + t], n_hi = a.vis[tokb_lin + q0 + 63];
     const int n_comp = (n_hi + 63) >> 6, n_all = n_comp + (a.own_chunk ? 1 : 0);
 
@@ -326,9 +340,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
         __syncthreads();
         if (it + 1 < n_all) fetch(it + 1);
         if (wave_extreme_i32<true>(mine) <= 0) continue;   // uniform
-        f32x4 s[4], dp[4], dn[4];   // dn: the steps with the negated operand
+        f32x4 s[4], sr[4], dp[4], dn[4];   // dn: the steps with the negated operand
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) s[mt] = dp[mt] = dn[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < 4; ++mt) s[mt] = sr[mt] = dp[mt] = dn[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -336,10 +350,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
                 u32x4 k[NT], v[NT];
                 Kt.rows(16 * mt + l16, 32 * ks + 8 * lq, k);
                 Vt.rows(16 * mt + l16, 32 * ks + 8 * lq, v);
-                s[mt] = mfma_terms(k, qf[ks], s[mt]);
+                mfma_terms(k, qf[ks], s[mt], sr[mt]);
                 if (ks & 1) dn[mt] = mfma_terms(v, of[ks], dn[mt]);
                 else dp[mt] = mfma_terms(v, of[ks], dp[mt]);
             }
+        add_rest<NT>(s, sr);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) dp[mt] -= dn[mt];
         u32x4 ds[2][N_TERMS];
@@ -349,7 +364,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_dq_
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int mt = 2 * mp + (j >> 2), key = 16 * mt + 4 * lq + (j & 3);
-                const float p = key < mine ? __builtin_amdgcn_exp2f(scale2 * s[mt][j & 3] - lse2) : 0.f;
+                const float p = key < mine ? exp_of(fmaf(a.scale, s[mt][j & 3], -lse)) : 0.f;
                 x[j] = p * (dp[mt][j & 3] - Dq);
             }
             split_terms(x, ds[mp]);
@@ -403,8 +418,8 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
     extern __shared__ __align__(16) unsigned char st_smem[];
     const typename LY::QTile Qt{reinterpret_cast<uint16_t*>(st_smem)};
     const typename LY::OTile Ot{reinterpret_cast<uint16_t*>(st_smem + LY::QTile::BYTES)};
-    float* s_lse2 = reinterpret_cast<float*>(st_smem + LY::QTile::BYTES + LY::OTile::BYTES);
-    float* s_D = s_lse2 + 64;
+    float* s_lse = reinterpret_cast<float*>(st_smem + LY::QTile::BYTES + LY::OTile::BYTES);
+    float* s_D = s_lse + 64;
     int* s_vis = reinterpret_cast<int*>(s_D + 64);
     // One-dimensional grid, the key tile slowest: the tiles that hold keys (the first ones) are dispatched first, the
     // heaviest of all (tile 0, seen by every query) at the very front; the empty ones follow and exit at once.  (With the
@@ -418,7 +433,6 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
     const int c = c0 + 16 * w + l16;                   // this lane's key
     const bool valid = c < n_keys;
     const size_t tokb = (size_t)bh * L, tokb_lin = (size_t)(bh / a.G) * L, tokb_qk = a.qk_per_out_head ? tokb : tokb_lin;
-    const float scale2 = a.scale * LOG2E;
 
     // the wavefront's rows of K and V (row of an invalid key: the tile's first, masked below)
     u32x4 kf[KS][NT], vf[KS][NT];
@@ -454,7 +468,7 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
             ro[i].load(a.dO + (tokb + i0 + row) * D + col);
         }
         if (tid < 64) {
-            rl = a.lse[tokb + i0 + tid] * LOG2E;
+            rl = a.lse[tokb + i0 + tid];
             rd = a.Dvec[tokb + i0 + tid];
             if (!OWN) rc = a.vis[tokb_lin + i0 + tid];
         }
@@ -476,12 +490,12 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
             ro[i].terms(y);
             Ot.put(row, col, y);
         }
-        if (tid < 64) { s_lse2[tid] = rl; s_D[tid] = rd; s_vis[tid] = OWN ? c0 + tid + 1 : rc; }
+        if (tid < 64) { s_lse[tid] = rl; s_D[tid] = rd; s_vis[tid] = OWN ? c0 + tid + 1 : rc; }
         __syncthreads();
         if (AHEAD && i0 + 64 < i_hi) fetch(i0 + 64);
-        f32x4 s[4], dp[4], dn[4];   // dn: the steps with the negated operand
+        f32x4 s[4], sr[4], dp[4], dn[4];   // dn: the steps with the negated operand
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) s[mt] = dp[mt] = dn[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < 4; ++mt) s[mt] = sr[mt] = dp[mt] = dn[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -489,10 +503,11 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
                 u32x4 q[NT], o[NO];
                 Qt.rows(16 * mt + l16, 32 * ks + 8 * lq, q);
                 Ot.rows(16 * mt + l16, 32 * ks + 8 * lq, o);
-                s[mt] = mfma_terms(q, kf[ks], s[mt]);   // rows: queries 16 mt + 4 lq + j, column: key l16
+                mfma_terms(q, kf[ks], s[mt], sr[mt]);   // rows: queries 16 mt + 4 lq + j, column: key l16
                 if (ks & 1) dn[mt] = mfma_terms(o, vf[ks], dn[mt]);
                 else dp[mt] = mfma_terms(o, vf[ks], dp[mt]);
             }
+        add_rest<NT>(s, sr);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) dp[mt] -= dn[mt];
         u32x4 p[2][N_TERMS], ds[2][N_TERMS];
@@ -502,14 +517,14 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int mt = 2 * mp + h;
-                const float4 l4 = *reinterpret_cast<const float4*>(s_lse2 + 16 * mt + 4 * lq);
+                const float4 l4 = *reinterpret_cast<const float4*>(s_lse + 16 * mt + 4 * lq);
                 const float4 d4 = *reinterpret_cast<const float4*>(s_D + 16 * mt + 4 * lq);
                 const int4 c4 = *reinterpret_cast<const int4*>(s_vis + 16 * mt + 4 * lq);
                 const float ls[4] = {l4.x, l4.y, l4.z, l4.w}, dd[4] = {d4.x, d4.y, d4.z, d4.w};
                 const int vs[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float pj = (valid && c < vs[j]) ? __builtin_amdgcn_exp2f(scale2 * s[mt][j] - ls[j]) : 0.f;
+                    const float pj = (valid && c < vs[j]) ? exp_of(fmaf(a.scale, s[mt][j], -ls[j])) : 0.f;
                     const float dj = pj * (dp[mt][j] - dd[j]);
                     g += dj;
                     x[4 * h + j] = pj;

@@ -59,3 +59,29 @@ def test_logits_of_one_sign(d):
     ref = (x["Q"].double() * x["K"].double()[:, :, :1]).sum(-1) / d ** 0.5
     # d products added in fp32 and scaled: a few roundings of 2^-24
     assert float(((got.double() - ref) / ref).abs().max()) <= 3e-7
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_softmax_branch_with_large_logits(d):
+    """Queries and keys of RMS norm 2, logits of up to 20: what rounds at the logits' size, not at that of their differences,
+    shows.  Every token is a softmax token, so dV is the branch's too."""
+    B, H, L = 1, 4, 512
+    x = _inputs(B, H, L, d, 1.1, seed=60 + d)
+    gen = torch.Generator().manual_seed(d)
+    rms = lambda t: 2 * t / t.pow(2).mean(-1, keepdim=True).sqrt()
+    q, k = (rms(torch.randn(B, H, L, d, generator=gen)).cuda() for _ in range(2))
+    dO = torch.randn(B, H, L, d, generator=gen).cuda()
+    args = [x[n] for n in ("Q", "K", "V", "alpha", "beta", "mask")]
+    got = nats.hybrid_attn_fwd_ex(*args, 64, Q_nla=q, K_nla=k, want=("O_nla", "lse"))
+    got.update(nats.hybrid_attn_bwd(*args, dO, 64, Q_nla=q, K_nla=k, want=("g_nla",)))
+    q, k, v, g = (t.double() for t in (q, k, x["V"], dO))
+    s = (q @ k.transpose(2, 3).contiguous() / d ** 0.5).masked_fill(~torch.ones(L, L, dtype=torch.bool, device="cuda").tril(), float("-inf"))
+    lse = torch.logsumexp(s, -1)
+    p = torch.exp(s - lse[..., None])
+    o = p @ v
+    ds = p * (g @ v.transpose(2, 3).contiguous() - (g * o).sum(-1, keepdim=True))
+    # fp32 multiply-adds and expf one after the other: 4.8e-7, 3.9e-8, 8.0e-7, 8.8e-7, 7.0e-7, 8.8e-7 at L 1024, d 128
+    for key, ref, bar in (("O_nla", o, 5e-7), ("lse", lse, 6e-8), ("dQ_nla", ds @ k / d ** 0.5, 8e-7),
+                          ("dK_nla", ds.transpose(2, 3).contiguous() @ q / d ** 0.5, 8.8e-7),
+                          ("dV", p.transpose(2, 3).contiguous() @ g, 7e-7), ("g_nla", ds.sum(2), 8.8e-7)):
+        assert _distance(got[key], ref) <= bar, key
