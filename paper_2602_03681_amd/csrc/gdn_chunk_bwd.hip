@@ -54,6 +54,14 @@ __device__ __forceinline__ void unpack16(const u32x4 w, float (&out)[4], float) 
     for (int q = 0; q < 4; ++q) out[q] = __uint_as_float(w[q]);
 }
 
+// c + the product over 16 contraction indices, its four instructions from zero and added pairwise
+__device__ __forceinline__ f32x4 add16(const float4 a, const float4 b, const f32x4 c) {
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 x = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, zero, 0, 0, 0) + __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, zero, 0, 0, 0);
+    const f32x4 y = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, zero, 0, 0, 0) + __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, zero, 0, 0, 0);
+    return c + (x + y);
+}
+
 // x of the lane that the DPP control names (rows of the mask only; 0 where there is no source), both halves of a double
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_move_f64(double x) {
@@ -189,11 +197,27 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
                     accQ += mfma_bf16(qa[0], kb[0], f32x4{0.f, 0.f, 0.f, 0.f});
                 }
             } else {
+                // The forward adds the instructions' results up pairwise.  In fp32 a sum of D products in a row is 1.9e-7 off
+                // (half of the numbers q . k are small against their partial sums), and O_la with it: 2.0e-7 of its norm from
+                // 64 bits, now 1.1e-7, as token by token (B 1, H 2, L 256, d 64: 1 us of 33).  The backward pass keeps the
+                // running sum: behind Eq. 21 a row of O_la that is nearly zero, its q . k by chance nearly zero, is divided
+                // by its norm, and whichever last bits it has are the gradient's.
+                f32x4 sumK[2] = {accK, accK}, sumQ[2] = {accQ, accQ};
 #pragma unroll 4
                 for (int kt = 0; kt < D / 16; ++kt) {
                     const float4 bk = ld4(Ks + (16 * b + l16) * KS + 16 * kt + 4 * lq);
-                    accK = mac16(ld4(Ks + (16 * a + l16) * KS + 16 * kt + 4 * lq), bk, accK);
-                    accQ = mac16(ld4(Qs + (16 * a + l16) * KS + 16 * kt + 4 * lq), bk, accQ);
+                    const float4 ak = ld4(Ks + (16 * a + l16) * KS + 16 * kt + 4 * lq), aq = ld4(Qs + (16 * a + l16) * KS + 16 * kt + 4 * lq);
+                    if (keep_at) {
+                        accK = mac16(ak, bk, accK);
+                        accQ = mac16(aq, bk, accQ);
+                    } else {
+                        sumK[kt & 1] = add16(ak, bk, sumK[kt & 1]);
+                        sumQ[kt & 1] = add16(aq, bk, sumQ[kt & 1]);
+                    }
+                }
+                if (!keep_at) {
+                    accK = sumK[0] + sumK[1];
+                    accQ = sumQ[0] + sumQ[1];
                 }
             }
             const int i = 16 * b + l16;
@@ -1121,12 +1145,17 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
 // O_la may be Uh itself: a wavefront has read all it needs of it before it writes, and both are its own columns.
 // Head grouping: BH counts output heads, Q and the operands are those of linear head bh / G.  inner: 0 leaves P U out
 // (the ablation whose linear branch reads the carried state only).
-template <typename T, int D>
+// FWD: 16 contraction indices at a time from zero, added up (see the operands' kernel); otherwise running sums.
+template <typename T, int D, bool FWD>
 __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict__ Q, const ChunkOps o,
                                                            const float* __restrict__ ck, const float* Uh,
                                                            float* O_la, const int L, const int BH, const int G,
                                                            const int inner, const float la_scale) {
     constexpr int KS = D + 4, MS = CB_MS, VW = D / 4, VT = VW / 16;   // value columns per wavefront, in tiles of 16
+    auto mac = [](const float4 a, const float4 b, const f32x4 c) {
+        if constexpr (FWD) return c + mac16(a, b, f32x4{0.f, 0.f, 0.f, 0.f});
+        else return mac16(a, b, c);
+    };
     __shared__ __align__(16) float Qs[CB_C * KS];
     __shared__ __align__(16) float Ps[CB_C * MS];
     __shared__ float s_gam[CB_C];
@@ -1168,7 +1197,7 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
         for (int tt = 0; tt < 4; ++tt) {
             const float4 a = ld4(Qs + (16 * tt + l16) * KS + 16 * kt + 4 * lq);
 #pragma unroll
-            for (int vt = 0; vt < VT; ++vt) acc[tt][vt] = mac16(a, b[vt], acc[tt][vt]);
+            for (int vt = 0; vt < VT; ++vt) acc[tt][vt] = mac(a, b[vt], acc[tt][vt]);
         }
     }
     // rows scaled by gamma (a lane holds tokens 16 tt + 4 lq + j of value column l16)
@@ -1193,7 +1222,7 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
         for (int tt = tb; tt < 4; ++tt) {
             const float4 a = ld4(Ps + (16 * tt + l16) * MS + 16 * tb + 4 * lq);
 #pragma unroll
-            for (int vt = 0; vt < VT; ++vt) acc[tt][vt] = mac16(a, b[vt], acc[tt][vt]);
+            for (int vt = 0; vt < VT; ++vt) acc[tt][vt] = mac(a, b[vt], acc[tt][vt]);
         }
     }
 #pragma unroll
@@ -1292,23 +1321,23 @@ nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void
 }
 
 // O_la [BHG][L][d] f32 from ops (after launch_gdn_bwd_prep), ck and Uh (after launch_gdn_chunk_states; O_la may be Uh).
-template <typename T>
+template <typename T, int D, bool FWD>
 static void launch_out_t(const FwdPlan& pl, const void* Q, const ChunkOps& o, const float* ck, const float* Uh, float* O_la,
                          hipStream_t st) {
-    const dim3 grid((unsigned)(pl.BHG * (pl.L / CB_C)));
-    const int inner = pl.inner_chunk != 1;
-    if (pl.d == 64)
-        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 64>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Uh, O_la, pl.L, pl.BHG,
-                           pl.G, inner, pl.la_scale);
-    else
-        hipLaunchKernelGGL((gdn_chunk_out_kernel<T, 128>), grid, dim3(256), 0, st, (const T*)Q, o, ck, Uh, O_la, pl.L, pl.BHG,
-                           pl.G, inner, pl.la_scale);
+    hipLaunchKernelGGL((gdn_chunk_out_kernel<T, D, FWD>), dim3((unsigned)(pl.BHG * (pl.L / CB_C))), dim3(256), 0, st, (const T*)Q,
+                       o, ck, Uh, O_la, pl.L, pl.BHG, pl.G, pl.inner_chunk != 1, pl.la_scale);
+}
+template <typename T>
+static void launch_out_d(const FwdPlan& pl, const void* Q, const ChunkOps& o, const float* ck, const float* Uh, float* O_la,
+                         bool fwd, hipStream_t st) {
+    if (pl.d == 64) (fwd ? launch_out_t<T, 64, true> : launch_out_t<T, 64, false>)(pl, Q, o, ck, Uh, O_la, st);
+    else (fwd ? launch_out_t<T, 128, true> : launch_out_t<T, 128, false>)(pl, Q, o, ck, Uh, O_la, st);
 }
 nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Uh,
                                  float* O_la, hipStream_t st) {
     const ChunkOps o = chunk_ops(pl, ops, with_at);
-    if (pl.dtype == NATS_BF16) launch_out_t<bf16_t>(pl, Q, o, ck, Uh, O_la, st);
-    else launch_out_t<float>(pl, Q, o, ck, Uh, O_la, st);
+    if (pl.dtype == NATS_BF16) launch_out_d<bf16_t>(pl, Q, o, ck, Uh, O_la, !with_at, st);
+    else launch_out_d<float>(pl, Q, o, ck, Uh, O_la, !with_at, st);
     return check_launch("gdn_chunk_out");
 }
 
