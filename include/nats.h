@@ -182,7 +182,8 @@ size_t nats_hybrid_attn_fwd_workspace_bytes(const nats_fwd_params* p);
  * rounded to fp16 on their way into a product.  Magnitudes up to 65504 are represented; anything
  * beyond saturates at +-65504 (the hardware's fp16 clamp is on, no infinity or NaN arises) and no
  * status reports it.  alpha is clamped below at 1e-30 per token.  The fp32 path (NATS_F32 tensors,
- * or math = NATS_MATH_F32) has neither limit.
+ * or math = NATS_MATH_FP32) has neither limit; a NaN, an infinity or an alpha outside (0,1] acts from its token on, as in
+ * the recurrence (a head that does not come out finite by chunks is done once more token by token).
  * Returns NATS_OK once everything is enqueued. */
 nats_status nats_hybrid_attn_fwd(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
                                  const float* alpha, const float* beta, const uint8_t* mask, void* O,

@@ -175,13 +175,15 @@ static nats_status validate_fwd_params(const nats_fwd_params* p, FwdPlan* pl, bo
     pl->off_vc = off;  off = align_up(off + n_out * pl->d * esz, 256);
     pl->off_ola = off; off = align_up(off + n_out * pl->d * 4, 256);
     pl->off_tf = pl->off_p = pl->off_gamv = pl->off_kdv = pl->off_gam = pl->off_seg = pl->off_vh = pl->off_olah = 0;
-    pl->off_snap = pl->off_ops = pl->off_ck = 0;
+    pl->off_snap = pl->off_ops = pl->off_ck = pl->off_redo = 0;
     pl->fp32_chunks = !by_tokens && uses_fp32_chunks(*pl);
     pl->off_wout = off; off = align_up(off + 2 * n_out * 4, 256);   // weights of Eq. 21 when computed by Eq. 22
     if (pl->fp32_chunks) {
         pl->off_ops = off; off = align_up(off + chunk_ops_floats(*pl, false) * 4, 256);
         pl->off_ck = off;  off = align_up(off + (size_t)pl->BHG * (pl->L / 64) * pl->d * pl->d * 4, 256);
-    } else if (!uses_chunk_path(*pl) && pl->routing == NATS_ROUTE_CHUNK) {   // chunk-start state of the fp32 recurrence
+        pl->off_redo = off; off = align_up(off + (size_t)pl->BHG * (pl->L / 64) * 4, 256);
+    }
+    if (!uses_chunk_path(*pl) && pl->routing == NATS_ROUTE_CHUNK) {   // chunk-start state of the fp32 recurrence
         pl->off_snap = off; off = align_up(off + (size_t)pl->BHG * pl->d * pl->d * 4, 256);
     }
     if (uses_chunk_path(*pl)) {   // per-chunk operands of the chunkwise linear branch
@@ -578,9 +580,11 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
             st = launch_flash_softmax(pl, Qs, Kc, Vh, Ks, V, cnt, Oh, ex.w_nla, ex.w_la, O, ex.O_nla, ex.lse, stream, W_fused);
         }
     } else {
+        const int32_t* redo = nullptr;
         if (pl.fp32_chunks) {
             float* ops = reinterpret_cast<float*>(ws + pl.off_ops);
             float* ck = reinterpret_cast<float*>(ws + pl.off_ck);
+            int32_t* marks = reinterpret_cast<int32_t*>(ws + pl.off_redo);
             {
                 ProfScope ps("gdn_bwd_prep", stream);
                 st = launch_gdn_bwd_prep(pl, Q, K, alpha, beta, mask, ops, false, Ks, V, cnt, idx, n_s, Kc, Vc, ex.Kc, ex.Vc,
@@ -593,12 +597,15 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
                 if (st != NATS_OK) return st;
             }
             ProfScope ps("gdn_chunk_out", stream);
-            st = launch_gdn_chunk_out(pl, Q, ops, false, ck, O_la, O_la, stream);
-        } else {
+            st = launch_gdn_chunk_out(pl, Q, ops, false, ck, O_la, O_la, marks, stream);
+            if (st != NATS_OK) return st;
+            redo = marks;
+        }
+        {   // all heads, or those whose chunks were not finite
             ProfScope ps("gdn_recurrent", stream);
             st = launch_gdn_recurrent(pl, Q, K, V, alpha, beta, mask, ex.initial_state, ex.final_state, O_la,
                                       pl.routing == NATS_ROUTE_CHUNK ? reinterpret_cast<float*>(ws + pl.off_snap) : nullptr,
-                                      stream);
+                                      redo, stream);
         }
         if (st != NATS_OK) return st;
         ProfScope ps("softmax_terms_fwd", stream);
@@ -731,12 +738,12 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         float* O_la = reinterpret_cast<float*>(ws + bp.off_mola);
         if (by_chunks || !chunk) {
             ProfScope ps("gdn_chunk_out", stream);
-            st = launch_gdn_chunk_out(pl, Q, ops, true, ckpt, Uh, O_la, stream);
+            st = launch_gdn_chunk_out(pl, Q, ops, true, ckpt, Uh, O_la, nullptr, stream);
             if (st != NATS_OK) return st;
         } else {
             ProfScope ps("gdn_recurrent", stream);
             st = launch_gdn_recurrent(pl, Q, K, V, alpha, beta, mask, ex.initial_state, nullptr, O_la,
-                                      reinterpret_cast<float*>(ws + bp.off_msnap), stream);
+                                      reinterpret_cast<float*>(ws + bp.off_msnap), nullptr, stream);
             if (st != NATS_OK) return st;
         }
         ProfScope ps("merge_bwd", stream);

@@ -151,7 +151,10 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
         const bool soft = !chunk_mask && mask[tok0 + lane] != 0;
         const bool soft_chunk = chunk_mask && mask[gc] != 0;
         const float a = (freeze_on_softmax && soft) ? 1.f : alpha[tok0 + lane];
-        double gd = (double)__builtin_amdgcn_logf(fmaxf(a, 1e-37f));   // log2; inclusive scan over the 64 lanes
+        // An alpha of (nearly) 0 counts as 1e-37.  In the forward one that is no decay at all, negative or NaN, makes NaN here
+        // and so in the rows behind it: their head is then done token by token (gdn_chunk_out_kernel).
+        const float ac = o.At != nullptr ? fmaxf(a, 1e-37f) : (a >= 0.f && a < 1e-37f) ? 1e-37f : a;
+        double gd = (double)__builtin_amdgcn_logf(ac);   // log2; inclusive scan over the 64 lanes
         gd += dpp_move_f64<0x111, 0xF>(gd);
         gd += dpp_move_f64<0x112, 0xF>(gd);
         gd += dpp_move_f64<0x114, 0xF>(gd);
@@ -1142,6 +1145,11 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
 // quarter of the value columns for all 64 tokens, so every element of S0 and U is read once per block, straight
 // from memory as the right operand; Q and P, which every wavefront reads whole, go through LDS (P with its columns times
 // b': P U = P diag(b') Uh).
+// FWD, redo: whether the chunk made anything that is not finite, redo[chunk].  A product over a chunk or a half of it takes in,
+// with weight 0, tokens that a row does not see, and 0 x NaN is NaN: where a NaN or an infinity comes in (from the tensors, the
+// gates or an overflow), rows before it are lost too, in this chunk.  The recurrence token by token has no such products; the
+// launch behind this one redoes every head with a chunk marked here (gdn_recurrent.hip).  Whatever is not finite in a token's
+// Uh meets the diagonal of P and is seen in that token's row; without the inner part Uh itself is looked at.
 // O_la may be Uh itself: a wavefront has read all it needs of it before it writes, and both are its own columns.
 // Head grouping: BH counts output heads, Q and the operands are those of linear head bh / G.  inner: 0 leaves P U out
 // (the ablation whose linear branch reads the carried state only).
@@ -1150,7 +1158,7 @@ template <typename T, int D, bool FWD>
 __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict__ Q, const ChunkOps o,
                                                            const float* __restrict__ ck, const float* Uh,
                                                            float* O_la, const int L, const int BH, const int G,
-                                                           const int inner, const float la_scale) {
+                                                           const int inner, const float la_scale, int32_t* redo) {
     constexpr int KS = D + 4, MS = CB_MS, VW = D / 4, VT = VW / 16;   // value columns per wavefront, in tiles of 16
     auto mac = [](const float4 a, const float4 b, const f32x4 c) {
         if constexpr (FWD) return c + mac16(a, b, f32x4{0.f, 0.f, 0.f, 0.f});
@@ -1166,6 +1174,8 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
     const size_t gc = (size_t)bh * n_chunks + chunk, tok0 = (size_t)bh * L + (size_t)chunk * CB_C;
     const size_t gl = (size_t)(bh / G) * n_chunks + chunk, tokl = (size_t)(bh / G) * L + (size_t)chunk * CB_C;
     constexpr int E = Vec16<T>::N;
+    float seen = 0.f;   // stays 0 while all that it is shown is finite
+    auto look = [&](float x) { if constexpr (FWD) seen = fmaf(x, 0.f, seen); };
     for (int e = tid; e < CB_C * D / E; e += 256) {
         const int row = e / (D / E), c = (e % (D / E)) * E;
         float tmp[E];
@@ -1177,7 +1187,9 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
     for (int e = tid; e < CB_C * CB_C / 4; e += 256) {
         const int row = e / 16, c4 = (e % 16) * 4;
         const float4 p = ld4(o.Pm + gl * (CB_C * CB_C) + row * CB_C + c4), b = ld4(o.bp + tokl + c4);
-        *reinterpret_cast<float4*>(Ps + row * MS + c4) = make_float4(p.x * b.x, p.y * b.y, p.z * b.z, p.w * b.w);
+        const float4 pb = make_float4(p.x * b.x, p.y * b.y, p.z * b.z, p.w * b.w);
+        look(pb.x); look(pb.y); look(pb.z); look(pb.w);
+        *reinterpret_cast<float4*>(Ps + row * MS + c4) = pb;
     }
     if (tid < CB_C) s_gam[tid] = o.gam[tokl + tid];
     __syncthreads();
@@ -1211,13 +1223,18 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
             for (int j = 0; j < 4; ++j) acc[tt][vt][j] *= g[j];
     }
     // + P U: A = P[token][i], B = U[i = 16 tb + 4 lq + j][v]; P is lower triangular: tiles tb <= tt
-    if (inner)
+    if (inner || FWD)
 #pragma unroll
     for (int tb = 0; tb < 4; ++tb) {
         float4 b[VT];
 #pragma unroll
         for (int vt = 0; vt < VT; ++vt)
             b[vt] = ld4col(Uh + (tok0 + 16 * tb + 4 * lq) * D + VW * w + 16 * vt + l16, D);
+        if (!inner) {
+#pragma unroll
+            for (int vt = 0; vt < VT; ++vt) { look(b[vt].x); look(b[vt].y); look(b[vt].z); look(b[vt].w); }
+            continue;
+        }
 #pragma unroll
         for (int tt = tb; tt < 4; ++tt) {
             const float4 a = ld4(Ps + (16 * tt + l16) * MS + 16 * tb + 4 * lq);
@@ -1230,8 +1247,15 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
 #pragma unroll
         for (int vt = 0; vt < VT; ++vt)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                O_la[(tok0 + 16 * tt + 4 * lq + j) * D + VW * w + 16 * vt + l16] = la_scale * acc[tt][vt][j];
+            for (int j = 0; j < 4; ++j) {
+                const float x = la_scale * acc[tt][vt][j];
+                look(x);
+                O_la[(tok0 + 16 * tt + 4 * lq + j) * D + VW * w + 16 * vt + l16] = x;
+            }
+    if constexpr (FWD) {
+        const int any = __syncthreads_or(seen != 0.f);   // NaN by now: unequal to everything
+        if (tid == 0) redo[gc] = any;
+    }
 }
 
 // with_at: room for At as well (the backward pass; the forward does without)
@@ -1321,23 +1345,25 @@ nats_status launch_gdn_chunk_states(const FwdPlan& pl, const void* K, const void
 }
 
 // O_la [BHG][L][d] f32 from ops (after launch_gdn_bwd_prep), ck and Uh (after launch_gdn_chunk_states; O_la may be Uh).
+// redo: the forward's marks of chunks that are not finite, [BHG][L/64], for launch_gdn_recurrent; NULL in the backward pass.
 template <typename T, int D, bool FWD>
 static void launch_out_t(const FwdPlan& pl, const void* Q, const ChunkOps& o, const float* ck, const float* Uh, float* O_la,
-                         hipStream_t st) {
+                         int32_t* redo, hipStream_t st) {
     hipLaunchKernelGGL((gdn_chunk_out_kernel<T, D, FWD>), dim3((unsigned)(pl.BHG * (pl.L / CB_C))), dim3(256), 0, st, (const T*)Q,
-                       o, ck, Uh, O_la, pl.L, pl.BHG, pl.G, pl.inner_chunk != 1, pl.la_scale);
+                       o, ck, Uh, O_la, pl.L, pl.BHG, pl.G, pl.inner_chunk != 1, pl.la_scale, redo);
 }
 template <typename T>
 static void launch_out_d(const FwdPlan& pl, const void* Q, const ChunkOps& o, const float* ck, const float* Uh, float* O_la,
-                         bool fwd, hipStream_t st) {
-    if (pl.d == 64) (fwd ? launch_out_t<T, 64, true> : launch_out_t<T, 64, false>)(pl, Q, o, ck, Uh, O_la, st);
-    else (fwd ? launch_out_t<T, 128, true> : launch_out_t<T, 128, false>)(pl, Q, o, ck, Uh, O_la, st);
+                         int32_t* redo, hipStream_t st) {
+    const bool fwd = redo != nullptr;
+    if (pl.d == 64) (fwd ? launch_out_t<T, 64, true> : launch_out_t<T, 64, false>)(pl, Q, o, ck, Uh, O_la, redo, st);
+    else (fwd ? launch_out_t<T, 128, true> : launch_out_t<T, 128, false>)(pl, Q, o, ck, Uh, O_la, redo, st);
 }
 nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Uh,
-                                 float* O_la, hipStream_t st) {
+                                 float* O_la, int32_t* redo, hipStream_t st) {
     const ChunkOps o = chunk_ops(pl, ops, with_at);
-    if (pl.dtype == NATS_BF16) launch_out_d<bf16_t>(pl, Q, o, ck, Uh, O_la, !with_at, st);
-    else launch_out_d<float>(pl, Q, o, ck, Uh, O_la, !with_at, st);
+    if (pl.dtype == NATS_BF16) launch_out_d<bf16_t>(pl, Q, o, ck, Uh, O_la, redo, st);
+    else launch_out_d<float>(pl, Q, o, ck, Uh, O_la, redo, st);
     return check_launch("gdn_chunk_out");
 }
 

@@ -7,8 +7,9 @@
 // two shuffles); k_t, q_t, alpha_t, beta_t are the same for all rows and are staged through
 // LDS a tile of tokens at a time (broadcast reads).
 //
-// Taken in fp32 arithmetic where the chunk form (gdn_chunk_bwd.hip) is not: routing chunks of 128 tokens, and problems
-// whose state per chunk of 64 tokens would not fit the memory at hand.  Latency-bound: 0.37 us per token, the chain of
+// Taken in fp32 arithmetic where the chunk form (gdn_chunk_bwd.hip) is not: routing chunks of 128 tokens, problems
+// whose state per chunk of 64 tokens would not fit the memory at hand, and, behind the chunk form, the heads that it marked
+// as not finite (without a mark the launch is 2 us).  Latency-bound: 0.37 us per token, the chain of
 // two dot products over a row's lanes (6 d FLOP per row-token on the vector units).
 #include "nats_common.h"
 
@@ -24,7 +25,7 @@ __global__ __launch_bounds__(REC_THREADS) void gdn_recurrent_kernel(
     const float* __restrict__ alpha, const float* __restrict__ beta, const uint8_t* __restrict__ mask,
     const float* __restrict__ S0, float* __restrict__ S_final, float* __restrict__ O_la,
     float* __restrict__ snap, int L, float la_scale, int linear_op, int freeze_on_softmax, int G,
-    int no_inner_output, int RC) {
+    int no_inner_output, int RC, const int32_t* __restrict__ redo) {
     constexpr int DP = D / 4;       // columns of a row per lane
     constexpr int DPP = DP + 4;     // padded quarter stride: the four quarters land in different banks
     __shared__ __align__(16) float s_k[REC_TT][4 * DPP];
@@ -35,6 +36,11 @@ __global__ __launch_bounds__(REC_THREADS) void gdn_recurrent_kernel(
     const int bh = blockIdx.y;
     const int tid = threadIdx.x, r = tid >> 2, part = tid & 3;
     const int row = blockIdx.x * REC_ROWS + r;  // d_v index of this lane's row
+    if (redo != nullptr) {   // behind the chunk form: only heads in which a chunk came out with something not finite
+        int any = 0;
+        for (int i = tid; i < L / 64; i += REC_THREADS) any |= redo[(size_t)bh * (L / 64) + i];
+        if (!__syncthreads_or(any)) return;
+    }
     // bh counts output heads: the G heads of a group are row blocks of one wide state, fed by their own value
     // columns and by the queries, keys, gates and mask of linear head bh / G (Section 4.3)
     const size_t base = (size_t)bh * L, lin = (size_t)(bh / G) * L;
@@ -172,25 +178,26 @@ __global__ __launch_bounds__(REC_THREADS) void gdn_recurrent_kernel(
 template <typename T>
 static void launch_rec(const FwdPlan& pl, const void* Q, const void* K, const void* V, const float* alpha,
                        const float* beta, const uint8_t* mask, const float* S0, float* S_final,
-                       float* O_la, float* snap, hipStream_t st) {
+                       float* O_la, float* snap, const int32_t* redo, hipStream_t st) {
     dim3 grid(pl.d / REC_ROWS, pl.BHG);
     if (pl.d == 64)
         hipLaunchKernelGGL((gdn_recurrent_kernel<T, 64>), grid, dim3(REC_THREADS), 0, st, (const T*)Q,
                            (const T*)K, (const T*)V, alpha, beta, mask, S0, S_final, O_la, snap, pl.L, pl.la_scale,
-                           pl.linear_op, pl.freeze_on_softmax, pl.G, pl.inner_chunk == 1, pl.RC);
+                           pl.linear_op, pl.freeze_on_softmax, pl.G, pl.inner_chunk == 1, pl.RC, redo);
     else
         hipLaunchKernelGGL((gdn_recurrent_kernel<T, 128>), grid, dim3(REC_THREADS), 0, st, (const T*)Q,
                            (const T*)K, (const T*)V, alpha, beta, mask, S0, S_final, O_la, snap, pl.L, pl.la_scale,
-                           pl.linear_op, pl.freeze_on_softmax, pl.G, pl.inner_chunk == 1, pl.RC);
+                           pl.linear_op, pl.freeze_on_softmax, pl.G, pl.inner_chunk == 1, pl.RC, redo);
 }
 
 nats_status launch_gdn_recurrent(const FwdPlan& pl, const void* Q, const void* K, const void* V,
                                  const float* alpha, const float* beta, const uint8_t* mask,
-                                 const float* S0, float* S_final, float* O_la, float* snap, hipStream_t st) {
+                                 const float* S0, float* S_final, float* O_la, float* snap, const int32_t* redo,
+                                 hipStream_t st) {
     if (pl.dtype == NATS_BF16)
-        launch_rec<bf16_t>(pl, Q, K, V, alpha, beta, mask, S0, S_final, O_la, snap, st);
+        launch_rec<bf16_t>(pl, Q, K, V, alpha, beta, mask, S0, S_final, O_la, snap, redo, st);
     else
-        launch_rec<float>(pl, Q, K, V, alpha, beta, mask, S0, S_final, O_la, snap, st);
+        launch_rec<float>(pl, Q, K, V, alpha, beta, mask, S0, S_final, O_la, snap, redo, st);
     return check_launch("gdn_recurrent");
 }
 

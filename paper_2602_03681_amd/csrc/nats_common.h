@@ -205,9 +205,9 @@ struct FwdPlan {
     size_t off_cnt, off_idx, off_ns, off_kc, off_vc, off_ola, total;
     // chunkwise (MFMA) linear branch: per-chunk operands
     size_t off_tf, off_p, off_gamv, off_kdv, off_gam, off_seg, off_vh, off_olah, off_snap, off_wout;
-    // fp32 arithmetic, linear branch by chunks: operands and start state of every chunk
+    // fp32 arithmetic, linear branch by chunks: operands and start state of every chunk, marks of those that are not finite
     int fp32_chunks;
-    size_t off_ops, off_ck;
+    size_t off_ops, off_ck, off_redo;
 };
 
 // kernel launchers (one per .hip file); every pointer is a device pointer
@@ -216,7 +216,8 @@ nats_status launch_scan_compact(const FwdPlan& pl, const uint8_t* mask, const vo
                                 void* Kc_user, void* Vc_user, int cap_user, void* Vh, hipStream_t st);
 nats_status launch_gdn_recurrent(const FwdPlan& pl, const void* Q, const void* K, const void* V,
                                  const float* alpha, const float* beta, const uint8_t* mask,
-                                 const float* S0, float* S_final, float* O_la, float* snap, hipStream_t st);
+                                 const float* S0, float* S_final, float* O_la, float* snap, const int32_t* redo,
+                                 hipStream_t st);   // redo: NULL, or [BHG][L/64]: only heads with a mark are done
 nats_status launch_gdn_chunk_inv(const FwdPlan& pl, const void* Q, const void* K, const float* alpha,
                                  const float* beta, const uint8_t* mask, void* TF, void* PF, float* gamv,
                                  float* kdv, float* gamC, const void* K_sm, const void* V, int32_t* cnt, int32_t* idx,
@@ -302,7 +303,7 @@ nats_status launch_merge_bwd(const FwdPlan& pl, int mode, float eps, const float
                              const void* dO, const float* w_nla, const float* w_la, float* dO_la, float* dO_nla,
                              float* dw_nla, float* dw_la, hipStream_t st);
 nats_status launch_gdn_chunk_out(const FwdPlan& pl, const void* Q, float* ops, bool with_at, const float* ck, const float* Uh,
-                                 float* O_la, hipStream_t st);
+                                 float* O_la, int32_t* redo, hipStream_t st);
 nats_status launch_widen_bf16(const void* src, float* dst, size_t n, hipStream_t st);
 nats_status launch_score_gradients_chunk(const FwdPlan& pl, const float* g_nla, const float* ds_la_part, float* dscore_nla,
                                          float* dscore_la, hipStream_t st);   // ds_la_part NULL: dscore_la is left as it is
