@@ -203,6 +203,54 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void softmax_terms_fwd
     // ---- epilogue: normalise, optional branch outputs, merge, store; the query's row lies in its 4 lanes
     l_run += lane_xor16(l_run, lane);
     l_run += lane_xor32(l_run, lane);
+    // A weight 0 times a NaN or an infinity in a row of V that the query does not see is NaN (and an infinity's second term is one
+    // by itself).  So a wavefront with a query that did not come out finite walks its queries' own rows once more, one row at a
+    // time on the vector units, and what came out that way stands for those queries.
+    float seen = 0.f * l_run;   // stays 0 while all is finite
+#pragma unroll
+    for (int md = 0; md < MD; ++md)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) seen = fmaf(acc[md][j], 0.f, seen);
+    seen += lane_xor16(seen, lane);
+    seen += lane_xor32(seen, lane);
+    if (__any(seen != 0.f)) {
+        f32x4 acc2[MD];
+#pragma unroll
+        for (int md = 0; md < MD; ++md) acc2[md] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float m = -INFINITY, l = 0.f;
+        const T* qr = a.Q + (tokb_qk + t) * D + 4 * lq;
+        auto walk = [&](const T* kb, const T* vb, int n) {   // the query sees the first n rows
+            const int n_max = wave_extreme_i32<true>(n);     // all lanes stay: the sums below run across them
+#pragma unroll 1
+            for (int c = 0; c < n_max; ++c) {
+                const T *kr = kb + (size_t)c * D + 4 * lq, *vr = vb + (size_t)c * D + 4 * lq;
+                float dot = 0.f;
+#pragma unroll
+                for (int md = 0; md < MD; ++md)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) dot = fmaf(to_float(qr[16 * md + j]), to_float(kr[16 * md + j]), dot);
+                dot += lane_xor16(dot, lane);
+                dot += lane_xor32(dot, lane);
+                if (c >= n) continue;
+                const float sc = a.scale * dot, m_new = fmaxf(m, sc), m_use = m_new == -INFINITY ? 0.f : m_new;
+                const float corr = exp_of(m - m_use), pw = exp_of(sc - m_use);
+                m = m_new;
+                l = l * corr + pw;
+#pragma unroll
+                for (int md = 0; md < MD; ++md)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc2[md][j] = fmaf(pw, to_float(vr[16 * md + j]), acc2[md][j] * corr);
+            }
+        };
+        walk(a.Kc + tokb * D, a.Vc + tokb * D, my_cnt);
+        if (n_own > 0) walk(a.K + (tokb_qk + cs) * D, a.V + (tokb + cs) * D, t + 1 - cs);
+        if (seen != 0.f) {
+            m_run = m;
+            l_run = l;
+#pragma unroll
+            for (int md = 0; md < MD; ++md) acc[md] = acc2[md];
+        }
+    }
     const float inv_l = l_run > 0.f ? 1.f / l_run : 0.f;
     const size_t row = tokb + t;
     if (a.lse != nullptr && lq == 0) a.lse[row] = l_run > 0.f ? m_run + __builtin_amdgcn_logf(l_run) * LN2 : -INFINITY;

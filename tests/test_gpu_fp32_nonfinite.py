@@ -17,7 +17,7 @@ NAMES = ("Q", "K", "V", "alpha", "beta", "mask")
 def _run(x, routing=nb.NATS_ROUTE_TOKEN, dtype="f32", **kw):
     g = to_dev(x, dtype)
     r = nats.hybrid_attn_fwd_ex(*(g[k] for k in NAMES), 64, math=nb.NATS_MATH_FP32, routing=routing,
-                                want=("O_la", "O_nla", "final_state"), **kw)
+                                want=("O_la", "O_nla", "lse", "final_state"), **kw)
     torch.cuda.synchronize()
     return {k: host(v) for k, v in r.items()}
 
@@ -108,3 +108,27 @@ def test_inner_part_left_out():
     _same(got["final_state"][0, 1], want)
     _same(got["O_la"][0, 1], clean["O_la"][0, 1])
     assert np.array_equal(got["final_state"][0, 0], clean["final_state"][0, 0])
+
+
+@pytest.mark.parametrize("routing", [nb.NATS_ROUTE_TOKEN, nb.NATS_ROUTE_CHUNK])
+@pytest.mark.parametrize("what,value", [("V", np.nan), ("V", np.inf), ("V", -np.inf), ("K", np.nan), ("Q", np.nan)])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_softmax_branch_takes_it_from_its_token_on(dtype, d, what, value, routing):
+    x = make_fwd_inputs(1, 3, 320, d, dtype, 0.2, seed=550)
+    kw, t = {}, 212
+    if routing == nb.NATS_ROUTE_CHUNK:
+        x["mask"] = make_chunk_mask(1, 3, 5, 0.5, seed=4)
+        x["mask"][0, 1] = (1, 0, 0, 1, 0)
+        kw = dict(chunk_routing=64)
+    else:
+        x["mask"][0, :, t] = 1
+    clean = _run(x, routing, dtype)
+    x[what] = x[what].copy()
+    x[what][0, 1, t, 5] = value
+    got = _run(x, routing, dtype)
+    with np.errstate(all="ignore"):
+        ref = oracle_fwd(x, want=("O_nla", "lse"), **kw)
+    assert not np.isfinite(got["O_nla"][0, 1, t:]).all()
+    for key in ("O_nla", "lse"):
+        _same(got[key][0, 1], ref[key][0, 1])
+        assert np.array_equal(got[key][0, 0], clean[key][0, 0]) and np.array_equal(got[key][0, 2], clean[key][0, 2])
