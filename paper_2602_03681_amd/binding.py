@@ -163,6 +163,12 @@ def _require(t: Optional[torch.Tensor], name: str, shape: Sequence[int], dtype: 
         raise ValueError(f"{name} must be contiguous {dtype} of shape {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
 
 
+def _require_workspace(t: Optional[torch.Tensor]):
+    """Its elements are counted as bytes: uint8, or wider ones counted short."""
+    if t is not None and not (t.is_cuda and t.is_contiguous()):
+        raise ValueError("workspace must be a contiguous GPU tensor")
+
+
 def _stream_ptr() -> ctypes.c_void_p:
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
@@ -218,6 +224,7 @@ def hybrid_attn_fwd_ex(Q, K, V, alpha, beta, mask, C: int = 64, *, softmax_scale
     dev = Q.device
     O = torch.empty_like(V) if out is None else out
     _require(O, "out", (B, HG, L, d), dt)
+    _require_workspace(workspace)
     want = set(want)
     unknown = want - set(_EX_OUTPUTS)
     if unknown:
@@ -269,6 +276,7 @@ def hybrid_attn_fwd(Q, K, V, alpha, beta, mask, C: int = 64, *, softmax_scale: f
         workspace = torch.empty(max(fwd_workspace_bytes(params), 16), dtype=torch.uint8, device=Q.device)
     O = torch.empty_like(Q) if out is None else out
     _require(O, "out", (B, H, L, d), dt)
+    _require_workspace(workspace)
     _check(lib.nats_hybrid_attn_fwd(ctypes.byref(params), _ptr(Q), _ptr(K), _ptr(V), _ptr(alpha), _ptr(beta),
                                     _ptr(mask), _ptr(O), _ptr(workspace), workspace.numel(), _stream_ptr()))
     return O
@@ -338,6 +346,7 @@ def hybrid_attn_bwd(Q, K, V, alpha, beta, mask, dO, C: int = 64, *, softmax_scal
         _check(lib.nats_hybrid_attn_bwd(ctypes.byref(params), *([None] * 12), None, None, 0, None))
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
+    _require_workspace(workspace)
     dev = Q.device
     res = {k: torch.empty((B, H, L, d), dtype=torch.float32, device=dev) for k in ("dQ", "dK")}
     res["dV"] = torch.empty((B, H * G, L, d), dtype=torch.float32, device=dev)
@@ -399,6 +408,7 @@ def hybrid_attn_decode(state, k_cache, v_cache, cache_len, q, k, v, alpha, beta,
     _require(o, "out", (B, H, d), dt)
     _require(q_nla, "q_nla", (B, H, d), dt)
     _require(k_nla, "k_nla", (B, H, d), dt)
+    _require_workspace(workspace)
     params = DecParams(B, H, d, cap, _dtype_code(k_cache), softmax_scale, la_scale, combine_mode, rms_eps, linear_op,
                        int(freeze_on_softmax), q_nla.data_ptr() if q_nla is not None else None,
                        k_nla.data_ptr() if k_nla is not None else None,

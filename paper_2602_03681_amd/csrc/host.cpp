@@ -98,6 +98,7 @@ PyObject* guarded(F&& f) {
 void set_workspace(nats_dec_params& p, PyObject* given, at::Tensor& own, const at::Tensor& like) {
     if (given != Py_None) {
         const at::Tensor& t = tensor(given);
+        if (!t.is_cuda() || t.layout() != at::kStrided || !t.is_contiguous()) throw NotTaken();
         p.workspace = t.data_ptr();
         p.workspace_bytes = (size_t)t.numel();
     } else if (wants_workspace((int64_t)p.B * p.H, p.d, p.cap)) {
