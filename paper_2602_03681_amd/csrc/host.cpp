@@ -15,6 +15,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <initializer_list>
@@ -82,19 +83,20 @@ PyObject* status(nats_status st, const at::Tensor& out) {
     return THPVariable_Wrap(out);
 }
 
+// NotTaken: None; any other C++ exception as torch raises it (an allocation that fails: torch.cuda.OutOfMemoryError)
 template <typename F>
 PyObject* guarded(F&& f) {
+    HANDLE_TH_ERRORS
     try {
         return f();
     } catch (const NotTaken&) {
         Py_RETURN_NONE;
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
     }
+    END_HANDLE_TH_ERRORS
 }
 
-// the workspace of a step: the caller's, or one made for the call (kept by the tensor until the call has been enqueued)
+// The workspace of a step: the caller's, or one made for the call (kept by the tensor until the call has been enqueued) where
+// memory is left for it; the step also runs without.
 void set_workspace(nats_dec_params& p, PyObject* given, at::Tensor& own, const at::Tensor& like) {
     if (given != Py_None) {
         const at::Tensor& t = tensor(given);
@@ -102,9 +104,14 @@ void set_workspace(nats_dec_params& p, PyObject* given, at::Tensor& own, const a
         p.workspace = t.data_ptr();
         p.workspace_bytes = (size_t)t.numel();
     } else if (wants_workspace((int64_t)p.B * p.H, p.d, p.cap)) {
-        p.workspace_bytes = (size_t)small_parts_bytes((int64_t)p.B * p.H, p.d, p.cap);
-        own = at::empty({(int64_t)p.workspace_bytes}, like.options().dtype(at::kByte));
+        const int64_t bytes = small_parts_bytes((int64_t)p.B * p.H, p.d, p.cap);
+        try {
+            own = at::empty({bytes}, like.options().dtype(at::kByte));
+        } catch (const c10::OutOfMemoryError&) {
+            return;
+        }
         p.workspace = own.data_ptr();
+        p.workspace_bytes = (size_t)bytes;
     }
 }
 
