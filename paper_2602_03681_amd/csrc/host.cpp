@@ -95,6 +95,16 @@ PyObject* guarded(F&& f) {
     END_HANDLE_TH_ERRORS
 }
 
+// The library's launches without the interpreter lock, as a ctypes call makes them: a launch waits where the stream's queue
+// is full, and other threads go on meanwhile.
+template <typename F>
+nats_status unlocked(F&& f) {
+    PyThreadState* const state = PyEval_SaveThread();
+    const nats_status st = f();   // (a C entry: throws nothing)
+    PyEval_RestoreThread(state);
+    return st;
+}
+
 // The workspace of a step: the caller's, or one made for the call (kept by the tensor until the call has been enqueued) where
 // memory is left for it; the step also runs without.
 void set_workspace(nats_dec_params& p, PyObject* given, at::Tensor& own, const at::Tensor& like) {
@@ -156,9 +166,12 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
         void* op = pointer(out, dt, {B, H, d});
         at::Tensor own;
         set_workspace(p, a[16], own, q);
-        return status(nats_hybrid_attn_decode(&p, (float*)state, kcache, vcache, (int32_t*)len, qp, kp, vp, (const float*)alpha,
-                                              (const float*)beta, (const uint8_t*)mask, (const float*)wn, (const float*)wl, op,
-                                              (int32_t*)err, current_stream()), out);
+        void* const stream = current_stream();
+        return status(unlocked([&] {
+            return nats_hybrid_attn_decode(&p, (float*)state, kcache, vcache, (int32_t*)len, qp, kp, vp, (const float*)alpha,
+                                           (const float*)beta, (const uint8_t*)mask, (const float*)wn, (const float*)wl, op,
+                                           (int32_t*)err, stream);
+        }), out);
     });
 }
 
@@ -200,8 +213,11 @@ PyObject* decode_chunk(PyObject*, PyObject* const* a, Py_ssize_t n) {
         void* op = pointer(out, dt, {B, H, d});
         at::Tensor own;
         set_workspace(p, Py_None, own, q);
-        return status(nats_hybrid_attn_decode_chunk(&p, &s, qp, kp, vp, (const float*)alpha, (const float*)beta,
-                                                    (const float*)wn, (const float*)wl, op, (int32_t*)err, current_stream()), out);
+        void* const stream = current_stream();
+        return status(unlocked([&] {
+            return nats_hybrid_attn_decode_chunk(&p, &s, qp, kp, vp, (const float*)alpha, (const float*)beta, (const float*)wn,
+                                                 (const float*)wl, op, (int32_t*)err, stream);
+        }), out);
     });
 }
 

@@ -1,4 +1,7 @@
-"""The host side of the per-token calls: how it behaves out of memory, under capture and beside threads."""
+"""The host side of the per-token calls: how it behaves out of memory and beside threads."""
+import threading
+import time
+
 import pytest
 import torch
 
@@ -56,3 +59,35 @@ def test_a_step_without_memory_for_a_workspace_runs_without(no_memory):
     nats.hybrid_attn_decode(*(x[k] for k in NAMES), out=out)
     torch.cuda.synchronize()
     assert float((out.float() - want.float()).abs().max()) <= 2.0 ** -7 * float(want.float().abs().max())
+
+
+def test_other_threads_run_while_a_launch_waits():
+    """Behind a kernel of a second the stream's queue fills up and a launch waits for room."""
+    x = _step(1, 2, 64, 96)
+    out = torch.empty_like(x["q"])
+    run = lambda: nats.hybrid_attn_decode(*(x[k] for k in NAMES), out=out)
+    run()
+    torch.cuda._sleep(1000)
+    torch.cuda.synchronize()
+    gaps, stop = [0.0], threading.Event()
+
+    def ticks():
+        last = time.perf_counter()
+        while not stop.is_set():
+            time.sleep(0.001)
+            now = time.perf_counter()
+            gaps[0] = max(gaps[0], now - last)
+            last = now
+    other = threading.Thread(target=ticks)
+    other.start()
+    longest = 0.0
+    t0 = time.perf_counter()
+    torch.cuda._sleep(2_000_000_000)             # about a second
+    while time.perf_counter() - t0 < 0.5 and longest < 0.2:
+        t1 = time.perf_counter()
+        run()
+        longest = max(longest, time.perf_counter() - t1)
+    stop.set()
+    other.join()
+    torch.cuda.synchronize()
+    assert gaps[0] <= 0.1 or gaps[0] < longest / 2, (gaps[0], longest)
