@@ -9,7 +9,8 @@
 //   None                an argument is not what this path takes (a wrong shape, a CPU tensor, a subclass, ...): the Python
 //                       function then runs its own checks, which name what is wrong.
 // A workspace that the caller did not give is allocated for the call where the step gains by it (see wants_workspace),
-// from torch's caching allocator like the output: ordered on the current stream, and part of a graph under capture.
+// from torch's caching allocator like the output, ordered on the current stream; not while the stream is being captured, where
+// torch may have no pool to take it from.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -64,6 +65,14 @@ int dtype_code(at::ScalarType dt) {
 
 void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
+// (an error, as for the null stream beside a capture of another one, counts as capturing)
+bool capturing() {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c10::hip::getCurrentHIPStream().stream(), &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Whether a step without a workspace of the caller's gets one: with few (batch, head) pairs one block per pair leaves the
 // chip idle.  Measured (bf16, us per step, one block against blocks of 64 rows and a second kernel):
 //   d 128, 16 pairs: 64 rows 6.5 / 6.3, 256 rows 8.0 / 6.6, 1000 rows 13.0 / 7.2, 2048 rows 19.6 / 9.0;
@@ -113,7 +122,7 @@ void set_workspace(nats_dec_params& p, PyObject* given, at::Tensor& own, const a
         if (!t.is_cuda() || t.layout() != at::kStrided || !t.is_contiguous()) throw NotTaken();
         p.workspace = t.data_ptr();
         p.workspace_bytes = (size_t)t.numel();
-    } else if (wants_workspace((int64_t)p.B * p.H, p.d, p.cap)) {
+    } else if (wants_workspace((int64_t)p.B * p.H, p.d, p.cap) && !capturing()) {
         const int64_t bytes = small_parts_bytes((int64_t)p.B * p.H, p.d, p.cap);
         try {
             own = at::empty({bytes}, like.options().dtype(at::kByte));

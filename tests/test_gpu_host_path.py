@@ -1,4 +1,5 @@
-"""The host side of the per-token calls: how it behaves out of memory and beside threads."""
+"""The host side of the per-token calls: how it behaves out of memory, under capture and beside threads."""
+import ctypes
 import threading
 import time
 
@@ -91,3 +92,46 @@ def test_other_threads_run_while_a_launch_waits():
     other.join()
     torch.cuda.synchronize()
     assert gaps[0] <= 0.1 or gaps[0] < longest / 2, (gaps[0], longest)
+
+
+def _hip():
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    return ctypes.CDLL(path)
+
+
+@pytest.mark.parametrize("chunked", [False, True])
+def test_a_captured_step_allocates_nothing(chunked):
+    """A capture outside torch's own graphs has no pool for what torch allocates meanwhile: with an output given, a step makes
+    no allocation there, and the graph computes what the eager call does."""
+    B, H, d, cap = 1, 16, 128, 512
+    x, hip = _step(B, H, d, cap, length=300), _hip()
+    st = dict(state_start=torch.empty_like(x["state"]), chunk_decay=torch.ones(B, H, device="cuda"),
+              chunk_pos=torch.zeros(B, H, dtype=torch.int32, device="cuda"), **{k: x[k] for k in NAMES[:4]})
+    out, first = torch.empty_like(x["q"]), {k: v.clone() for k, v in dict(x, **st).items()}
+    if chunked:
+        run = lambda: nats.hybrid_attn_decode_chunk(st, *(x[k] for k in NAMES[4:9]), out=out)
+    else:
+        run = lambda: nats.hybrid_attn_decode(*(x[k] for k in NAMES), out=out)
+    run()
+    want = out.clone()
+    s, graph, exe = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        handle = ctypes.c_void_p(s.cuda_stream)
+        assert hip.hipStreamBeginCapture(handle, 2) == 0        # relaxed
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        run()
+        made = torch.cuda.memory_stats()["allocation.all.allocated"] - before
+        assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert made == 0
+    assert hip.hipGraphInstantiate(ctypes.byref(exe), graph, None, None, ctypes.c_size_t(0)) == 0
+    for _ in range(3):
+        for k, v in dict(x, **st).items():
+            v.copy_(first[k])
+        out.zero_()
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(exe, handle) == 0
+        torch.cuda.synchronize()
+        assert float((out.float() - want.float()).abs().max()) <= 2.0 ** -7 * float(want.float().abs().max())
+    hip.hipGraphExecDestroy(exe)
+    hip.hipGraphDestroy(graph)
