@@ -175,8 +175,10 @@ size_t nats_hybrid_attn_fwd_workspace_bytes(const nats_fwd_params* p);
  *   mask    : in  [B,H,L] u8 (routing = NATS_ROUTE_TOKEN) or [B,H,L/C] u8 (NATS_ROUTE_CHUNK), non-zero =
  *             softmax token / chunk (Eq. 12-13)
  *   O       : out [B,H,L,d] dtype p->dtype
- *   workspace, workspace_bytes : device scratch of at least *_workspace_bytes(p); contents
- *             are undefined afterwards; two calls in flight must not share it.
+ *   workspace, workspace_bytes : device scratch of *_workspace_bytes(p) or more; contents
+ *             are undefined afterwards; two calls in flight must not share it.  In fp32 arithmetic the largest part of it
+ *             is a state per chunk of 64 tokens; one smaller by 256 bytes or more, down to what the error then names,
+ *             is taken too, and the linear branch runs token by token on it.
  * Value range of the bf16 path: its products take fp16 operands (fp32 sums, fp32 carried state), so
  * V, the carried state, the rows V - S k that the delta rule writes and both branches' output rows are
  * rounded to fp16 on their way into a product.  Magnitudes up to 65504 are represented; anything

@@ -621,6 +621,10 @@ nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, con
     FwdPlan pl;
     const nats_status st = validate_fwd_params(p, &pl);
     if (st != NATS_OK) return st;
+    // fp32 arithmetic on a workspace without room for a state per chunk: token by token, which needs none.  (A size that only
+    // rounding keeps from the reported one, its parts lie at multiples of 256 bytes, is refused: a mistake that would cost
+    // several times the time and no error.)
+    if (pl.fp32_chunks && workspace_bytes + 256 <= pl.total) (void)validate_fwd_params(p, &pl, true);
     return run_fwd(pl, Q, K, V, alpha, beta, mask, O, extra, workspace, workspace_bytes, hip_stream);
 }
 
