@@ -274,8 +274,9 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p);
  *             V, dO, dV are [B,H*G,L,d] and initial_state, d_initial_state [B,H*G,d,d], head h*G + g the member g
  *             of linear head h as in the forward; Q, K, alpha, beta, mask and their gradients, g_nla, g_la and the
  *             score gradients stay [B,H,...]: a shared input's gradient is the sum over the G heads that read it.
- *             The pass runs over all H*G heads at once (a workspace that grows with G); with NATS_MATH_FP32, and
- *             where that workspace would exceed 16 GiB, once per member (larger by one member's tensors)
+ *             The pass runs once per member (a workspace larger by one member's tensors, whatever G), or, given G times
+ *             the reported workspace, over all H*G heads at once, which is faster (not with NATS_MATH_FP32, nor where
+ *             that pass would use more than 16 GiB)
  *   workspace : at least nats_hybrid_attn_bwd_workspace_bytes(p); nothing is kept from the forward call, the
  *             backward recomputes what it needs (the state is checkpointed once per 64 tokens)
  * Sums over (batch, head)-internal blocks are taken in a fixed order: results are deterministic. */

@@ -306,6 +306,20 @@ def hybrid_attn_fwd_noalloc(Q, K, V, alpha, beta, mask, out, C: int = 64, *, sof
     return out
 
 
+_ONE_PASS_BYTES = 16 << 30   # the library's own limit for the pass over all heads of the groups
+
+
+def _bwd_workspace(need: int, G: int, device) -> torch.Tensor:
+    """G times what is needed lets the backward pass run over all heads of the groups at once; where that much cannot be
+    had, it runs member by member."""
+    if G > 1 and need * G <= _ONE_PASS_BYTES:
+        try:
+            return torch.empty(need * G, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    return torch.empty(need, dtype=torch.uint8, device=device)
+
+
 def hybrid_attn_bwd(Q, K, V, alpha, beta, mask, dO, C: int = 64, *, softmax_scale: float = 0.0, la_scale: float = 0.0,
                     linear_op: int = NATS_LINEAR_GDN, freeze_on_softmax: bool = False, initial_state=None,
                     want=(), workspace=None, routing: int = NATS_ROUTE_TOKEN,
@@ -345,7 +359,7 @@ def hybrid_attn_bwd(Q, K, V, alpha, beta, mask, dO, C: int = 64, *, softmax_scal
     if need == 0:   # let the library say what is wrong with the parameters
         _check(lib.nats_hybrid_attn_bwd(ctypes.byref(params), *([None] * 12), None, None, 0, None))
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
+        workspace = _bwd_workspace(need, G if math == NATS_MATH_AUTO else 1, Q.device)
     _require_workspace(workspace)
     dev = Q.device
     res = {k: torch.empty((B, H, L, d), dtype=torch.float32, device=dev) for k in ("dQ", "dK")}

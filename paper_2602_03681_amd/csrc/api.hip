@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -215,7 +216,6 @@ struct BwdPlan {
     int G;
     size_t off_gv, off_gdo, off_gdv, off_gdq, off_gdk, off_gda, off_gdb, off_gs0, off_gds0, off_ggn, off_ggl, off_gsn,
         off_gsl, off_gqn, off_gkn, off_gdqn, off_gdkn, total_grouped;
-    size_t reported;   // what the caller is told to bring: total_grouped or more
     // the merges of Eq. 21 and its ablation (merge_mode 1, 2; 0: the plain sum): the linear branch's output rows, the
     // two branches' gradients of their rows, the snapshot rows of the token-by-token forward (routing per chunk), a
     // member's weights and their gradients (head grouping), and, token by token, fp32 copies of bf16 tensors (the pass
@@ -319,15 +319,12 @@ static void plan_bwd_merge(const FwdPlan& pl, int G, BwdPlan* bp) {
 // pl: the plan of the pass itself.  With head grouping (p->group = G > 1) that is the plan of all output heads (pl->G = G,
 // bp->G = 1): the kernels by chunks find the shared inputs of an output head by its index, its shares of their gradients
 // are added up behind them (a training step of B 4, H 6, G 2, L 4096, d 128: 2377 us member by member, with copies of each
-// member's rows and launches of 192 blocks, 2146 in one pass).  Where that pass would take more
-// than BWD_ONE_PASS_BYTES, and token by token, it is the plan of one member of the groups, B x H heads with pl->G = 1, and
-// bp->G = G.
+// member's rows and launches of 192 blocks, 2146 in one pass).  Where the caller's workspace has no room for that, where that
+// pass would take more than BWD_ONE_PASS_BYTES, and token by token, it is the plan of one member of the groups, B x H heads
+// with pl->G = 1, and bp->G = G: that is the size reported, the same for every group size, and G times it always has room
+// for the one pass (each of whose buffers is a member's at most G times over).
 constexpr size_t BWD_ONE_PASS_BYTES = (size_t)16 << 30;
-// Member by member the workspace is the same for every group size.  Where the one pass over groups of 8 takes no more than
-// this, its size is what is reported for every G > 1 (at most four times what G = 2 needs), so that a small problem's buffer
-// still serves any group size; a call asks for what it needs itself.
-constexpr size_t BWD_ONE_SIZE_BYTES = (size_t)64 << 20;
-static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, BwdPlan* bp) {
+static nats_status validate_bwd_params(const nats_fwd_params* p, size_t workspace_bytes, FwdPlan* pl, BwdPlan* bp) {
     if (p == nullptr) { set_error("params is NULL"); return NATS_ERR_NULL; }
     nats_fwd_params one = *p;
     const int G = p->group > 1 ? p->group : 1;
@@ -354,18 +351,7 @@ static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, Bw
         if (fits) {
             plan_bwd(*pl, bp);
             if (bp->merge_mode != 0) plan_bwd_merge(*pl, 1, bp);
-            if (bp->total_grouped <= BWD_ONE_PASS_BYTES) {
-                bp->reported = bp->total_grouped;
-                FwdPlan pl8;
-                BwdPlan bp8 = *bp;
-                one.group = 8;
-                if (validate_fwd_params(&one, &pl8) == NATS_OK) {
-                    plan_bwd(pl8, &bp8);
-                    if (bp8.merge_mode != 0) plan_bwd_merge(pl8, 1, &bp8);
-                    if (bp8.total_grouped <= BWD_ONE_SIZE_BYTES) bp->reported = bp8.total_grouped;
-                }
-                return NATS_OK;
-            }
+            if (bp->total_grouped <= std::min(workspace_bytes, BWD_ONE_PASS_BYTES)) return NATS_OK;
         }
         one.group = 1;
     }
@@ -379,7 +365,6 @@ static nats_status validate_bwd_params(const nats_fwd_params* p, FwdPlan* pl, Bw
     plan_bwd(*pl, bp);
     if (G > 1) plan_bwd_group(*pl, G, bp);
     if (bp->merge_mode != 0) plan_bwd_merge(*pl, G, bp);
-    bp->reported = bp->total_grouped;
     return NATS_OK;
 }
 
@@ -631,8 +616,8 @@ nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, con
 size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p) {
     FwdPlan pl;
     BwdPlan bp;
-    if (validate_bwd_params(p, &pl, &bp) != NATS_OK) return 0;
-    return bp.reported;
+    if (validate_bwd_params(p, 0, &pl, &bp) != NATS_OK) return 0;
+    return bp.total_grouped;
 }
 
 // The backward pass on the plan's heads (pl.G > 1: all output heads of the groups).  ex by value: the optional outputs
@@ -840,7 +825,7 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
                                  void* hip_stream) {
     FwdPlan pl;
     BwdPlan bp;
-    nats_status st = validate_bwd_params(p, &pl, &bp);
+    nats_status st = validate_bwd_params(p, workspace != nullptr ? workspace_bytes : 0, &pl, &bp);
     if (st != NATS_OK) return st;
     if (!Q || !K || !V || !alpha || !beta || !mask || !dO || !dQ || !dK || !dV || !dalpha || !dbeta) {
         set_error("Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha and dbeta must all be non-NULL");

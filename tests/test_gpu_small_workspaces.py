@@ -1,4 +1,6 @@
 """Calls on a workspace smaller than the reported one that they still take: the same results by the way that needs less."""
+import ctypes
+
 import pytest
 import torch
 
@@ -27,3 +29,32 @@ def test_fp32_forward_token_by_token(dtype):
     assert rel_err(host(r["O_la"]), ref["O_la"]) <= 1e-5 and rel_err(host(r["final_state"]), ref["S"]) <= 1e-5
     with pytest.raises(nb.NatsError, match="needed"):
         nats.hybrid_attn_fwd_ex(*args, 64, math=nb.NATS_MATH_FP32, workspace=ws[:n - 1])
+
+
+@pytest.mark.parametrize("own_qk", [False, True])
+@pytest.mark.parametrize("routing", [nb.NATS_ROUTE_TOKEN, nb.NATS_ROUTE_CHUNK])
+@pytest.mark.parametrize("dtype,d,G,mode", [("f32", 64, 3, 1), ("bf16", 128, 2, 1), ("bf16", 64, 4, 0)])
+def test_grouped_backward_member_by_member(dtype, d, G, mode, routing, own_qk):
+    B, H, L = 2, 2, 192
+    g = to_dev(make_fwd_inputs(B, H, L, d, dtype, 0.3, seed=78 + G), dtype)
+    gen = torch.Generator().manual_seed(G)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    heads = lambda: rnd(B, H * G, L, d).to(g["Q"].dtype).cuda()
+    mask = g["mask"][:, :, ::64].contiguous() if routing else g["mask"]
+    kw = dict(group=G, routing=routing, combine_mode=mode, want=("d_initial_state", "g_nla", "dscore_nla", "dscore_la"),
+              initial_state=(0.1 * rnd(B, H * G, d, d)).cuda())
+    if mode: kw.update(w_nla=torch.rand(B, H * G, L, generator=gen).cuda(), w_la=torch.rand(B, H * G, L, generator=gen).cuda())
+    if own_qk: kw.update({k: torch.nn.functional.normalize(heads().float(), dim=-1).to(g["Q"].dtype) for k in ("Q_nla", "K_nla")})
+    args = (g["Q"], g["K"], heads(), g["alpha"], g["beta"], mask, heads())
+    code = nb.NATS_F32 if dtype == "f32" else nb.NATS_BF16
+    p = nb.make_fwd_params(B, H, L, d, 64, code, routing=routing, combine_mode=mode, group=G)
+    n = int(nb.load_library().nats_hybrid_attn_bwd_workspace_bytes(ctypes.byref(p)))
+    ws = torch.full((n * G + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    by_member = nats.hybrid_attn_bwd(*args, workspace=ws[:n], **kw)
+    assert bool((ws[n:] == 0xA5).all())
+    at_once = nats.hybrid_attn_bwd(*args, workspace=ws[:n * G], **kw)
+    assert bool((ws[n * G:] == 0xA5).all())
+    for key, got in by_member.items():     # the order of the sums over the members differs, and their rounding
+        terms = 64 * G * 2.0 ** -23 * float(at_once["g_nla"].abs().max()) if key == "dscore_nla" else 0.0   # (that cancel)
+        ref = host(at_once[key])
+        assert abs(host(got) - ref).max() <= 1.5e-6 * (ref ** 2).mean() ** 0.5 + terms, key

@@ -34,3 +34,16 @@ def test_fp32_forward_takes_a_workspace_without_states(lib, B, H, L, d, dtype, m
     reported = nb.fwd_workspace_bytes(p)
     small = needed(lambda n: lib.nats_hybrid_attn_fwd(ctypes.byref(p), *([FAKE] * 7), FAKE, n, None))
     assert small == sizes(B, H, L, d, dtype) < reported
+
+
+@pytest.mark.parametrize("dtype", [nb.NATS_F32, nb.NATS_BF16])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("B,H,L,d", [(1, 2, 64, 64), (2, 4, 4096, 128)])
+def test_grouped_backward_reports_one_size(lib, B, H, L, d, mode, dtype):
+    """Member by member, which is what is reported, the size is the same for every group, and that size is taken."""
+    size = {}
+    for G in (1, 2, 3, 8):
+        p = nb.make_fwd_params(B, H, L, d, 64, dtype, group=G, combine_mode=mode)
+        size[G] = lib.nats_hybrid_attn_bwd_workspace_bytes(ctypes.byref(p))
+        assert needed(lambda n: lib.nats_hybrid_attn_bwd(ctypes.byref(p), *([FAKE] * 12), None, FAKE, n, None)) == size[G]
+    assert size[1] < size[2] == size[3] == size[8] < 2 * size[1]
