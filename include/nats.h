@@ -262,8 +262,8 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p);
  *             p->math: with NATS_MATH_AUTO the linear branch's adjoint runs by chunks of 64
  *             tokens, in fp32 accuracy on matrix instructions (the chunk form of Eq. 19 / 20 and its derivative; the states
  *             at the chunk starts, then the state gradients behind every chunk, then all chunks in parallel);
- *             dalpha then comes through the logarithms of the decays and needs alpha > 0 (an alpha of exactly 0
- *             gets dalpha = 0).  NATS_MATH_FP32 takes the adjoint token by token (the workspace is larger).
+ *             dalpha then comes through the logarithms of the decays: an alpha below 1e-37 counts as that and gets
+ *             dalpha = 0, and dalpha's rounding grows as 1 / alpha.  NATS_MATH_FP32 takes the adjoint token by token (the workspace is larger).
  *             Products run on the bf16 matrix instruction with operands as sums of bf16 terms: bf16 tensors are
  *             one term, fp32 operands (f32 tensors, probabilities, dS, states) three, which is all of their bits
  *   dO      : in  [B,H,L,d] dtype p->dtype

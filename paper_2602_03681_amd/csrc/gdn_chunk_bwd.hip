@@ -37,8 +37,10 @@ constexpr int CB_C = 64;          // chunk
 constexpr int CB_MS = CB_C + 4;   // row stride (floats) of a 64 x 64 operand in LDS
 constexpr int CB_NV = 16;         // value columns per block of the sequential kernels
 
-struct ChunkOps {   // per chunk: Tm, At, Pm [64][64] f32 row-major;  per token: g2 (log2 of gamma), gam, kd, bp;  per chunk: gamC
-    float *Tm, *At, *Pm, *g2, *gam, *kd, *bp, *gamC;
+// per chunk: Tm, At, Pm [64][64] f32 row-major;  per token: gam, kd, bp;  per chunk: gamC;  for the gradients, per token:
+// log2 of gamma as the sum of two floats, g2 and g2l
+struct ChunkOps {
+    float *Tm, *At, *Pm, *g2, *g2l, *gam, *kd, *bp, *gamC;
 };
 
 // a 16-byte word of T as it came from memory -> floats (8 for bf16, 4 for fp32)
@@ -168,7 +170,10 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
         const float bp = soft ? 0.f : beta[tok0 + lane];
         s_g[lane] = gd;
         s_bp[lane] = bp;
-        o.g2[tok0 + lane] = g;
+        if (o.At != nullptr) {
+            o.g2[tok0 + lane] = g;
+            o.g2l[tok0 + lane] = (float)(gd - (double)g);
+        }
         o.gam[tok0 + lane] = gam;
         o.kd[tok0 + lane] = soft_chunk ? 0.f : __builtin_amdgcn_exp2f((float)(gC - gd));
         o.bp[tok0 + lane] = bp;
@@ -756,7 +761,7 @@ struct GradLds {
     static constexpr int last = o_a + CB_C * CB_MS * 4;
     static constexpr int first = RTile::BYTES + (terms_of<TO>() == 1 ? TermTile<D, 1>::BYTES : 0);
     static constexpr int o_small = first > last ? first : last;
-    static constexpr int bytes = o_small + (4 + 8 + 8) * CB_C * 4 + 4 * 4;
+    static constexpr int bytes = o_small + (5 + 8 + 8) * CB_C * 4 + 4 * 4;
     static constexpr int blocks = 2 * bytes <= 160 * 1024 ? 2 : 1;   // per CU
 };
 
@@ -776,7 +781,8 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
     float* s_gam = s_g2 + CB_C;
     float* s_kd = s_gam + CB_C;
     float* s_bp = s_kd + CB_C;
-    float* rs = s_bp + CB_C;                   // [4 column tiles][64 rows]: row sums of dAt . At + dP . P per tile
+    float* s_g2l = s_bp + CB_C;
+    float* rs = s_g2l + CB_C;                  // [4 column tiles][64 rows]: row sums of dAt . At + dP . P per tile
     float* cs = rs + 4 * CB_C;                 // [4 row tiles][64 columns]: column sums of the same without the factor b'
     float* gk = cs + 4 * CB_C;                 // [4 wavefronts][64]: the state terms of d ln gamma, per wavefront's columns
     float* gu = gk + 4 * CB_C;                 // ...: kd K . (Uh dS1), likewise
@@ -830,6 +836,7 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
     Raw8<float> Rr[NPC];
     // one of g2, gam, kd, b' of the chunk's tokens
     const float gate_in = (w == 0 ? a.o.g2 : w == 1 ? a.o.gam : w == 2 ? a.o.kd : a.o.bp)[tokl + lane];
+    const float g2l_in = w == 0 ? a.o.g2l[tokl + lane] : 0.f;
 #pragma unroll
     for (int p = 0; p < NPC; ++p) dOr[p].load(a.dO + tok0 * D + 8 * (tid + 256 * p));
 #pragma unroll
@@ -841,6 +848,7 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
     put_rows(Ot, dOr);
     if (together) put_rows(Rt, Rr);
     s_g2[tid] = gate_in;   // s_g2, s_gam, s_kd, s_bp lie one behind the other
+    if (w == 0) s_g2l[lane] = g2l_in;
     for (int e = tid; e < 8 * CB_C; e += 256) rs[e] = 0.f;   // rs and cs
     __syncthreads();
     f32x4 Gdq[4][NCT], Gdk[4][NCT], Gu[4][NCT];
@@ -941,12 +949,14 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
                 accA = mfma_terms(r, u, accA);
             }
             const int i = 16 * tb + l16;
-            const float gi = s_g2[i], bi = s_bp[i];
+            const float gi = s_g2[i], gil = s_g2l[i], bi = s_bp[i];
             float csum = 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 16 * ta + 4 * lq + j;
-                const float G = __builtin_amdgcn_exp2f(s_g2[r] - gi);
+                // as the operands' kernel has it: behind alphas near 0 log2 gamma reaches thousands, and a float of that
+                // size holds no more than three digits of a ratio
+                const float G = __builtin_amdgcn_exp2f((s_g2[r] - gi) + (s_g2l[r] - gil));
                 const float dp = (i <= r) ? a.la_scale * accP[j] : 0.f, da = (i < r) ? -delta * accA[j] : 0.f;   // no At without the delta rule
                 const float e = da * atv[j] + dp * pmv[j];   // dP = dO' U^T, dAt = - dR U^T: these times b'_i
                 const float rsum = lane_group_sum<16>(bi * e);
@@ -1132,7 +1142,9 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
         dl += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dl), 0x143, 0xC, 0xF, false));
         const size_t t = tok0 + r, tl = tokl + r;
         const bool frozen = a.freeze_on_softmax && !a.chunk_mask && a.mask[tl] != 0;   // its alpha counted as 1
-        a.dalpha[t] = frozen ? 0.f : dl / fmaxf(a.alpha[tl], 1e-30f);
+        // (an alpha below 1e-37 counted as that, whatever it was; what dl carries of the rounding of its sums would be all there is)
+        const float al = a.alpha[tl];
+        a.dalpha[t] = frozen || al < 1e-37f ? 0.f : dl / al;
         a.dbeta[t] = !a.chunk_mask && a.mask[tl] != 0 ? 0.f : db;   // routing per token: a softmax token does not write
         if (a.g_nla != nullptr) a.g_nla[t] = 0.f;
     }
@@ -1266,7 +1278,8 @@ static ChunkOps chunk_ops(const FwdPlan& pl, float* base, bool with_at = true) {
     o.At = with_at ? o.Tm + n_ch * CB_C * CB_C : nullptr;
     o.Pm = o.Tm + (with_at ? 2 : 1) * n_ch * CB_C * CB_C;
     o.g2 = o.Pm + n_ch * CB_C * CB_C;
-    o.gam = o.g2 + n_tok;
+    o.g2l = o.g2 + (with_at ? n_tok : 0);
+    o.gam = o.g2l + (with_at ? n_tok : 0);
     o.kd = o.gam + n_tok;
     o.bp = o.kd + n_tok;
     o.gamC = o.bp + n_tok;
@@ -1274,7 +1287,7 @@ static ChunkOps chunk_ops(const FwdPlan& pl, float* base, bool with_at = true) {
 }
 size_t chunk_ops_floats(const FwdPlan& pl, bool with_at) {
     const size_t n_tok = (size_t)pl.BH * pl.L, n_ch = n_tok / CB_C;
-    return (with_at ? 3 : 2) * n_ch * CB_C * CB_C + 4 * n_tok + align_up(n_ch, 64);
+    return (with_at ? 3 : 2) * n_ch * CB_C * CB_C + (with_at ? 5 : 3) * n_tok + align_up(n_ch, 64);
 }
 
 template <typename T, int D>
