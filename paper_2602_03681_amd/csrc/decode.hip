@@ -698,14 +698,15 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_combine_kernel(
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i)
             if (first + h + i * NH < n_parts) M2 = fmaxf(M2, pm[i]);
-        if (M2 == -INFINITY) continue;   // the group has no part here
-        const float was = expf(M - M2);
+        // (no part here, or none with a finite logit: weights 0, and a part that holds NaN still brings it)
+        const float ref = M2 == -INFINITY ? 0.f : M2;
+        const float was = expf(M - ref);
         num *= was;
         den *= was;
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i)
             if (first + h + i * NH < n_parts) {
-                const float wgt = expf(pm[i] - M2);
+                const float wgt = expf(pm[i] - ref);
                 num += wgt * pa[i];
                 den += wgt * pl[i];
             }

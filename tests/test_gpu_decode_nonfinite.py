@@ -1,0 +1,55 @@
+"""NaN and infinities in the caches of a generation step: every form of the step gives what the definition gives."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2602_03681_amd as nats
+from paper_2602_03681_amd import binding as nb
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(B, H, d, cap, length, dtype, seed):
+    gen = torch.Generator().manual_seed(seed)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    unit = lambda *s: torch.nn.functional.normalize(rnd(*s), dim=-1).to(dtype)
+    x = dict(state=0.02 * rnd(B, H, d, d), k_cache=unit(B, H, cap, d), v_cache=rnd(B, H, cap, d).to(dtype),
+             cache_len=torch.full((B, H), length, dtype=torch.int32), q=unit(B, H, d), k=unit(B, H, d), v=rnd(B, H, d).to(dtype),
+             alpha=torch.sigmoid(2 + rnd(B, H)), beta=torch.sigmoid(rnd(B, H)), mask=torch.zeros(B, H, dtype=torch.uint8))
+    return {k: v.cuda() for k, v in x.items()}
+
+
+def _softmax_rows(x, length):
+    d = x["q"].shape[-1]
+    k, v = x["k_cache"][:, :, :length].double(), x["v_cache"][:, :, :length].double()
+    p = torch.softmax((k @ x["q"].double()[..., None])[..., 0] / d ** 0.5, -1)
+    return (p[..., None, :] @ v)[..., 0, :]
+
+
+# the forms: one block per pair (one of two kernels by the number of pairs), parts of 64 rows and of 256
+FORMS = {"own": (1, 16, 128), "wide": (1, 16, 64), "many": (6, 48, 64), "parts256": (6, 48, 64)}
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("length,row", [(65, 64), (257, 256), (321, 320), (64, 10)])
+@pytest.mark.parametrize("what", ["k_nan", "v_nan"])
+def test_every_form(form, length, row, what):
+    B, H, d = FORMS[form]
+    cap = 384
+    x = _step(B, H, d, cap, length, torch.bfloat16, seed=length)
+    clean = _softmax_rows(x, length)
+    x["k_cache" if what == "k_nan" else "v_cache"][0, 1, row, 5] = float("inf" if what == "v_inf" else "nan")
+    ws = None
+    if form == "parts256":
+        ws = torch.empty(nb.decode_workspace_bytes(B, H, d, cap, nb.NATS_BF16), dtype=torch.uint8, device="cuda")
+    x["state"].zero_()
+    x["beta"].zero_()                                       # the linear branch brings 0
+    o = nats.hybrid_attn_decode(*(x[k] for k in ("state", "k_cache", "v_cache", "cache_len", "q", "k", "v", "alpha", "beta", "mask")),
+                                workspace=ws).double()
+    want = clean.clone()
+    if what == "k_nan": want[0, 1] = float("nan")           # the logit is NaN, and with it every weight
+    else: want[0, 1, 5] = float("inf" if what == "v_inf" else "nan")
+    want, o = want.cpu().numpy(), o.cpu().numpy()
+    assert np.array_equal(np.isnan(o), np.isnan(want)) and np.array_equal(np.isposinf(o), np.isposinf(want))
+    fin = np.isfinite(want)
+    assert np.abs(o[fin] - want[fin]).max() <= 2.0 ** -7 * np.abs(want[fin]).max()
