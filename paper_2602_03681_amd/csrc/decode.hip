@@ -599,6 +599,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_split_kernel(
         for (int j = 0; j < EPL; ++j) acc[j] *= corr;
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
+            if (c0 + u * NSG >= c_hi) continue;   // (a repeated row's weight is 0, but 0 x infinity is NaN)
             const float pw = __builtin_amdgcn_exp2f((sc[u] - m_new) * 1.44269504088896341f);
             l_run += pw;
             float vf[EPL];

@@ -32,7 +32,7 @@ FORMS = {"own": (1, 16, 128), "wide": (1, 16, 64), "many": (6, 48, 64), "parts25
 
 @pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("length,row", [(65, 64), (257, 256), (321, 320), (64, 10)])
-@pytest.mark.parametrize("what", ["k_nan", "v_nan"])
+@pytest.mark.parametrize("what", ["k_nan", "v_nan", "v_inf"])
 def test_every_form(form, length, row, what):
     B, H, d = FORMS[form]
     cap = 384
