@@ -794,8 +794,8 @@ __global__ __launch_bounds__(FIX_THREADS) void gdn_seg_fix_kernel(float* __restr
 //   L 8192, d 128 401 against 390, B 1, H 2, L 512, d 64 29.8 against 24.9.  Three, of 4 or 5 chunks, are not ahead of one
 //   either (19 chunks 66.5 / 65.7); four are from 16 chunks on (B 3, H 6, L 1216 60.0 / 65.7, B 1, H 4, L 1024 49.0 / 52.8).
 // * The fix-up is a chain over the segments, about 1.4 us each, against two passes of 3.5 us per chunk of a segment: the
-//   sum is least near n^2 = 5 chunks.  n^2 <= 4 chunks: L 16384, one head, 64 / 32 segments 203.5 / 154.6; L 8192, 4 heads,
-//   32 / 20 110.1 / 104.1; L 4096, 8 heads, 16 / 20 73.4 / 72.7.
+//   sum is least near n^2 = 5 chunks.  n^2 <= 4 chunks: L 16384, one head, 64 / 32 segments 203.5 / 154.6 (the rule: 32);
+//   L 8192, 4 heads, 32 / 20 110.1 / 104.1 (the rule: 22); L 4096, 8 heads, 16 / 20 73.4 / 72.7 (the rule: 16, 4 chunks each).
 int gdn_segments(const FwdPlan& pl) {
     const int n_chunks = pl.L / SC;
     int n = pl.gdn_segments > 0 ? pl.gdn_segments : std::max(1, 256 / pl.BHG);

@@ -1,5 +1,5 @@
-"""The automatic number of segments of the linear branch's chunk recurrence, at the sizes where the rule changes: the final
-state agrees with one segment's to fp32 rounding (the fix-up's products carry 22 bits and more), the rows to fp16 hand-off."""
+"""The automatic number of segments of the linear branch's chunk recurrence where it is more than one (the rule itself:
+test_segment_rule.py): state and rows agree with those of one segment, to the fp16 operands and hand-off of both."""
 import pytest
 import torch
 
@@ -7,12 +7,14 @@ import paper_2602_03681_amd as nats
 from nats_inputs import make_fwd_inputs
 
 from gpu_util import host, rel_err, to_dev
+from test_segment_rule import segments
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("H,L,d", [(2, 960, 128), (2, 1024, 128), (2, 64, 64), (1, 4096, 64), (1, 8192, 128), (128, 1024, 64)])
+@pytest.mark.parametrize("H,L,d", [(2, 1024, 128), (3, 1216, 128), (1, 1280, 64), (85, 1024, 64), (1, 4096, 64), (1, 8192, 128)])
 def test_automatic_segments(H, L, d):
+    assert segments(H, L, d) > 1
     g = to_dev(make_fwd_inputs(1, H, L, d, "bf16", 0.05, seed=1300 + L), "bf16")
     x = tuple(g[k] for k in ("Q", "K", "V", "alpha", "beta", "mask"))
     auto, one = (nats.hybrid_attn_fwd_ex(*x, 64, gdn_segments=n, want=("final_state", "O_la")) for n in (0, 1))
