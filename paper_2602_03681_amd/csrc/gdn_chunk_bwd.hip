@@ -99,7 +99,8 @@ struct PrepLds {
     static_assert(bytes >= SCAN_LDS_INTS * 4, "the scan's blocks use the same bytes");
 };
 
-template <typename T, int D>
+// FWD: for the forward (o.At and the gradients' logarithms are not asked for)
+template <typename T, int D, bool FWD>
 __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const int block, unsigned char* lds) {
     using LY = PrepLds<T, D>;
     constexpr int KS = LY::KS, E = Vec16<T>::N, NP = CB_C * D / E / 256;
@@ -155,7 +156,7 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
         const float a = (freeze_on_softmax && soft) ? 1.f : alpha[tok0 + lane];
         // An alpha of (nearly) 0 counts as 1e-37.  In the forward one that is no decay at all, negative or NaN, makes NaN here
         // and so in the rows behind it: their head is then done token by token (gdn_chunk_out_kernel).
-        const float ac = o.At != nullptr ? fmaxf(a, 1e-37f) : (a >= 0.f && a < 1e-37f) ? 1e-37f : a;
+        const float ac = !FWD ? fmaxf(a, 1e-37f) : (a >= 0.f && a < 1e-37f) ? 1e-37f : a;
         double gd = (double)__builtin_amdgcn_logf(ac);   // log2; inclusive scan over the 64 lanes
         gd += dpp_move_f64<0x111, 0xF>(gd);
         gd += dpp_move_f64<0x112, 0xF>(gd);
@@ -170,7 +171,7 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
         const float bp = soft ? 0.f : beta[tok0 + lane];
         s_g[lane] = gd;
         s_bp[lane] = bp;
-        if (o.At != nullptr) {
+        if (!FWD) {
             o.g2[tok0 + lane] = g;
             o.g2l[tok0 + lane] = (float)(gd - (double)g);
         }
@@ -181,8 +182,7 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
     }
     __syncthreads();
     // the 10 lower tiles (a, b), b <= a, of K K^T and Q K^T: tile t of the list to wavefront t % 4
-    const bool keep_at = o.At != nullptr;   // the forward has no use for it
-    float* Ato = o.At + (keep_at ? gc * (CB_C * CB_C) : 0);
+    float* Ato = FWD ? nullptr : o.At + gc * (CB_C * CB_C);
     float* Pmo = o.Pm + gc * (CB_C * CB_C);
     float* Tmo = o.Tm + gc * (CB_C * CB_C);
     f32x4 keepA[3];
@@ -207,7 +207,7 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
             } else {
                 // The forward adds the instructions' results up pairwise.  In fp32 a sum of D products in a row is 1.9e-7 off
                 // (half of the numbers q . k are small against their partial sums), and O_la with it: 2.0e-7 of its norm from
-                // 64 bits, now 1.1e-7, as token by token (B 1, H 2, L 256, d 64: 1 us of 33).  The backward pass keeps the
+                // 64 bits, now 1.1e-7, as token by token (B 1, H 2, L 256, d 64: this kernel 8.6 -> 10.9 us).  The backward pass keeps the
                 // running sum: behind Eq. 21 a row of O_la that is nearly zero, its q . k by chance nearly zero, is divided
                 // by its norm, and whichever last bits it has are the gradient's.
                 f32x4 sumK[2] = {accK, accK}, sumQ[2] = {accQ, accQ};
@@ -215,15 +215,15 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
                 for (int kt = 0; kt < D / 16; ++kt) {
                     const float4 bk = ld4(Ks + (16 * b + l16) * KS + 16 * kt + 4 * lq);
                     const float4 ak = ld4(Ks + (16 * a + l16) * KS + 16 * kt + 4 * lq), aq = ld4(Qs + (16 * a + l16) * KS + 16 * kt + 4 * lq);
-                    if (keep_at) {
-                        accK = mac16(ak, bk, accK);
-                        accQ = mac16(aq, bk, accQ);
-                    } else {
+                    if constexpr (FWD) {
                         sumK[kt & 1] = add16(ak, bk, sumK[kt & 1]);
                         sumQ[kt & 1] = add16(aq, bk, sumQ[kt & 1]);
+                    } else {
+                        accK = mac16(ak, bk, accK);
+                        accQ = mac16(aq, bk, accQ);
                     }
                 }
-                if (!keep_at) {
+                if constexpr (FWD) {
                     accK = sumK[0] + sumK[1];
                     accQ = sumQ[0] + sumQ[1];
                 }
@@ -235,7 +235,7 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
                 const int r = 16 * a + 4 * lq + j;
                 const float G = __builtin_amdgcn_exp2f((float)(s_g[r] - gi));
                 const float at = (i < r && linear_op == 0) ? G * accK[j] : 0.f;
-                if (keep_at) Ato[r * CB_C + i] = at;
+                if (!FWD) Ato[r * CB_C + i] = at;
                 Pmo[r * CB_C + i] = (i <= r) ? G * accQ[j] : 0.f;
                 keepA[s][j] = at * s_bp[i];
             }
@@ -247,7 +247,7 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int off = (16 * a + 4 * lq + j) * CB_C + 16 * b + l16;
-            if (keep_at) Ato[off] = 0.f;
+            if (!FWD) Ato[off] = 0.f;
             Pmo[off] = 0.f;
         }
     }
@@ -310,7 +310,7 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
     }
 }
 
-template <typename T, int D>
+template <typename T, int D, bool FWD>
 __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const PrepArgs<T> a, const ScanArgs<T> sc, const int scan_segs,
                                                            const int scan_blocks) {
     static_assert(SCAN_THREADS == 256, "both kinds of block");
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const PrepArgs<T> a, 
         scan_compact_block<T>(sc, blockIdx.x % scan_segs, blockIdx.x / scan_segs, reinterpret_cast<int*>(cb_smem));
         return;
     }
-    gdn_bwd_prep_block<T, D>(a, blockIdx.x - scan_blocks, reinterpret_cast<unsigned char*>(cb_smem));
+    gdn_bwd_prep_block<T, D, FWD>(a, blockIdx.x - scan_blocks, reinterpret_cast<unsigned char*>(cb_smem));
 }
 
 // ---- the states along the sequence -------------------------------------------------------------------------------------
@@ -1235,24 +1235,26 @@ __global__ __launch_bounds__(256) void gdn_chunk_out_kernel(const T* __restrict_
             for (int j = 0; j < 4; ++j) acc[tt][vt][j] *= g[j];
     }
     // + P U: A = P[token][i], B = U[i = 16 tb + 4 lq + j][v]; P is lower triangular: tiles tb <= tt
-    if (inner || FWD)
+    if (inner) {
 #pragma unroll
-    for (int tb = 0; tb < 4; ++tb) {
-        float4 b[VT];
+        for (int tb = 0; tb < 4; ++tb) {
+            float4 b[VT];
 #pragma unroll
-        for (int vt = 0; vt < VT; ++vt)
-            b[vt] = ld4col(Uh + (tok0 + 16 * tb + 4 * lq) * D + VW * w + 16 * vt + l16, D);
-        if (!inner) {
+            for (int vt = 0; vt < VT; ++vt)
+                b[vt] = ld4col(Uh + (tok0 + 16 * tb + 4 * lq) * D + VW * w + 16 * vt + l16, D);
 #pragma unroll
-            for (int vt = 0; vt < VT; ++vt) { look(b[vt].x); look(b[vt].y); look(b[vt].z); look(b[vt].w); }
-            continue;
+            for (int tt = tb; tt < 4; ++tt) {
+                const float4 a = ld4(Ps + (16 * tt + l16) * MS + 16 * tb + 4 * lq);
+#pragma unroll
+                for (int vt = 0; vt < VT; ++vt) acc[tt][vt] = mac(a, b[vt], acc[tt][vt]);
+            }
         }
-#pragma unroll
-        for (int tt = tb; tt < 4; ++tt) {
-            const float4 a = ld4(Ps + (16 * tt + l16) * MS + 16 * tb + 4 * lq);
-#pragma unroll
-            for (int vt = 0; vt < VT; ++vt) acc[tt][vt] = mac(a, b[vt], acc[tt][vt]);
-        }
+    } else if constexpr (FWD) {
+        for (int tb = 0; tb < 4; ++tb)
+            for (int vt = 0; vt < VT; ++vt) {
+                const float4 b = ld4col(Uh + (tok0 + 16 * tb + 4 * lq) * D + VW * w + 16 * vt + l16, D);
+                look(b.x); look(b.y); look(b.z); look(b.w);
+            }
     }
 #pragma unroll
     for (int tt = 0; tt < 4; ++tt)
@@ -1290,9 +1292,9 @@ size_t chunk_ops_floats(const FwdPlan& pl, bool with_at) {
     return (with_at ? 3 : 2) * n_ch * CB_C * CB_C + (with_at ? 5 : 3) * n_tok + align_up(n_ch, 64);
 }
 
-template <typename T, int D>
+template <typename T, int D, bool FWD>
 static bool launch_prep_t(const FwdPlan& pl, const PrepArgs<T>& a, const ScanArgs<T>& sc, hipStream_t st) {
-    auto kern = gdn_bwd_prep_kernel<T, D>;
+    auto kern = gdn_bwd_prep_kernel<T, D, FWD>;
     constexpr size_t lds = PrepLds<T, D>::bytes;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
@@ -1315,7 +1317,8 @@ nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K,
                             pl.freeze_on_softmax, pl.linear_op, by_chunk};
         const ScanArgs<T> sc{mask, (const T*)Ks, (const T*)V, pl.L, pl.d, cnt, idx, n_s, (T*)Kc, (T*)Vc, (T*)Kc_user, (T*)Vc_user,
                              cap_user, (half_t*)Vh, by_chunk ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head};
-        return pl.d == 64 ? launch_prep_t<T, 64>(pl, a, sc, st) : launch_prep_t<T, 128>(pl, a, sc, st);
+        if (pl.d == 64) return with_at ? launch_prep_t<T, 64, false>(pl, a, sc, st) : launch_prep_t<T, 64, true>(pl, a, sc, st);
+        return with_at ? launch_prep_t<T, 128, false>(pl, a, sc, st) : launch_prep_t<T, 128, true>(pl, a, sc, st);
     };
     if (!(pl.dtype == NATS_BF16 ? go(bf16_t{}) : go(float{}))) {
         set_error("gdn_bwd_prep: the kernel's LDS size was refused");
