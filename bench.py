@@ -36,7 +36,7 @@ def kernel_work(name, cfg, sum_cnt):
     if name == "scan_compact":      # mask in, cnt + idx out, gathered K/V rows in and out
         n_soft = int(round(cfg.p_softmax * n_tok))
         return "hbm", n_tok * (1 + 4) + n_soft * (4 + 4 * d * esz)
-    if name == "gdn_recurrent":     # per row-token: decay d, S.k 2d, rank-1 2d, S.q 2d (fp32 VALU)
+    if name == "gdn_recurrent":     # (token by token) per row-token: decay d, S.k 2d, rank-1 2d, S.q 2d (fp32 VALU)
         return "alu_f32", n_tok * d * (7 * d)
     if name == "softmax_terms_fwd": # QK^T and PV: 4 d FLOP per visible (query, key) pair
         return "mfma", 4 * d * sum_cnt
@@ -179,11 +179,13 @@ def bench_backward(args):
 
 def measure_backward(steps_in, warmup_in, routing_name="token", by_tokens=False, combine_mode=0, preheat_ms=200.0):
     """Backward pass on workload 2's shapes (bf16 tensors, fp32 gradients): a step is one nats_hybrid_attn_bwd call.
-    The linear branch's adjoint runs by chunks on fp32 matrix instructions (operands per chunk, states forwards,
-    state gradients backwards, then every chunk's gradients); the softmax branch's products run on fp16 / bf16 matrix
-    instructions with two-term fp16 weights.  Roofline: fp32 matrix peak for the chunk kernels, counted per chunk of
-    64 tokens with triangular products at 10 of 16 tiles.  combine_mode 1, 2: the backward through the merge of Eq. 21
-    (its single-normalisation ablation), which widens the tensors and runs the fp32 kernels."""
+    The linear branch's adjoint runs by chunks (operands per chunk, states forwards, state gradients backwards, then
+    every chunk's gradients), the softmax branch's by key tiles, all on the bf16 matrix instruction with fp32 operands as
+    sums of three bf16 terms.  Roofline: the peak of the instruction that a kernel's products run on, against the
+    method's own products (each counted once, however many term products it takes), per chunk of 64 tokens with
+    triangular products at 10 of 16 tiles.  combine_mode 1, 2: the backward through the merge of Eq. 21 (its
+    single-normalisation ablation), with fp32 gradients of the branches' rows beside the bf16 tensors; by_tokens: the
+    linear adjoint token by token in fp32 (behind a merge on tensors widened to fp32)."""
     import torch
 
     import paper_2602_03681_amd as nats
@@ -232,7 +234,7 @@ def measure_backward(steps_in, warmup_in, routing_name="token", by_tokens=False,
     sq, st = 2.0 * 64 * d * d, 2.0 * 64 * 64 * d   # a [64 x d] . [d x d] product, a [64 x 64] . [64 x d] one
     flops = {   # per chunk
         "gdn_bwd_prep": 2 * tri * st,                       # K K^T, Q K^T
-        "gdn_chunk_states": 2 * sq + 2 * tri * st,          # K S^T, the state update; T and At products
+        "gdn_chunk_states": 2 * sq + tri * st,              # K S^T, the state update; the product with T
         "gdn_chunk_state_grads": 3 * sq + 2 * tri * st,     # K dS^T, two state updates; P^T and T^T products
         "gdn_chunk_grads": 3 * sq + 4 * tri * st + st,      # dO' S0, dR S0, U dS1; dP, dAt, (dP.G) K, (dP.G)^T Q; symmetric . K
         "gdn_chunk_out": sq + tri * st,                     # Q S0^T, P U (the branch's rows for the merge's adjoint)
@@ -244,17 +246,20 @@ def measure_backward(steps_in, warmup_in, routing_name="token", by_tokens=False,
     for k, f in flops.items():
         if k in kern:
             ach = f * n_chunks / (kern[k]["avg_ms"] * 1e-3) / 1e12
-            roofs[k] = {"bound": "alu" if k == "gdn_recurrent_bwd" else "mfma", "achieved": round(ach, 3), "peak": 157.3,
-                        "unit": "TFLOP/s", "frac": round(ach / 157.3, 5), "avg_kernel_ms": round(kern[k]["avg_ms"], 4)}
+            # fp32 vector and matrix instructions have one peak, the bf16 matrix instruction another
+            peak = PEAK["alu_f32" if k in ("gdn_recurrent_bwd", "gdn_chunk_out") else "mfma"][0]
+            roofs[k] = {"bound": "alu" if k == "gdn_recurrent_bwd" else "mfma", "achieved": round(ach, 3), "peak": peak,
+                        "unit": "TFLOP/s", "frac": round(ach / peak, 5), "avg_kernel_ms": round(kern[k]["avg_ms"], 4)}
     lead = max(roofs, key=lambda k: roofs[k]["avg_kernel_ms"])
     out = {"metric": "hybrid_attn_bwd_tokens_per_s", "value": round(cfg.B * cfg.L / (ms * 1e-3), 1), "unit": "tokens/s",
            "n_gpus": 1, "steps": steps, "warmup": warmup_in, "ms_per_step": round(ms, 4), "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
            "config": {"workload": "backward of cfg2_headline_bf16" + (", routing per chunk" if routing_name == "chunk" else "")
                                   + " (bf16 tensors, fp32 gradients; linear branch "
-                                  + ("token by token in fp32" if by_tokens else "by chunks on fp32 MFMA")
-                                  + (", softmax-branch products on MFMA with two-term fp16 weights)" if combine_mode == 0 else
-                                     f", through the merge combine_mode {combine_mode}: tensors widened, fp32 kernels)")},
+                                  + ("token by token in fp32" if by_tokens else "by chunks")
+                                  + ", products on bf16 MFMA, fp32 operands as three bf16 terms"
+                                  + (")" if combine_mode == 0 else f"; through the merge, combine_mode {combine_mode}"
+                                     + (", tensors widened to fp32)" if by_tokens else ")"))},
            "kernels_ms": {k: round(v["avg_ms"], 4) for k, v in kern.items()}, "dominant": dom,
            "roofline": dict(kernel=lead, traffic=None, **roofs[lead]), "kernel_rooflines": roofs,
            "cpu_baseline": None}

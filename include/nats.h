@@ -51,9 +51,9 @@ typedef enum nats_dtype { NATS_F32 = 0, NATS_BF16 = 1 } nats_dtype;
 /* Arithmetic used inside the kernels.
  *   NATS_MATH_AUTO : f32 tensors -> fp32 kernels; bf16 tensors -> chunkwise bf16 MFMA kernels
  *                    with fp32 state and accumulation.
- *   NATS_MATH_FP32 : fp32 arithmetic for either tensor dtype (the forward's linear branch by chunks on
- *                    fp32 matrix instructions, token by token where a state per chunk would not fit);
- *                    slower, used for tight-tolerance work. */
+ *   NATS_MATH_FP32 : fp32 arithmetic for either tensor dtype (the forward's linear branch by chunks, token by
+ *                    token where a state per chunk would not fit; products on fp32 matrix instructions, or on the
+ *                    bf16 one with operands as sums of three bf16 terms); slower, used for tight-tolerance work. */
 typedef enum nats_math { NATS_MATH_AUTO = 0, NATS_MATH_FP32 = 1 } nats_math;
 
 /* ------------------------------------------------------------------------- *
@@ -258,7 +258,7 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p);
  *   Q, K, V, alpha, beta, mask : as in the forward (either routing).
  *             With routing per chunk the function differentiated is the one the
  *             forward computes there: both operations compute every chunk's inner part, the masks act between
- *             chunks, a softmax chunk hands on (its decay) x (the state at its start).  Every sum is fp32 and the recurrence's adjoint is fp32 throughout.
+ *             chunks, a softmax chunk hands on (its decay) x (the state at its start).  Every sum is fp32.
  *             p->math: with NATS_MATH_AUTO the linear branch's adjoint runs by chunks of 64
  *             tokens, in fp32 accuracy on matrix instructions (the chunk form of Eq. 19 / 20 and its derivative; the states
  *             at the chunk starts, then the state gradients behind every chunk, then all chunks in parallel);

@@ -79,11 +79,10 @@ static bool uses_chunk_path(const FwdPlan& pl) {
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// fp32 arithmetic: the linear branch by chunks of 64 tokens on fp32 matrix instructions (the kernels the backward pass
-// makes its states with) unless a routing decision spans two chunks, or the start states of all chunks (d^2 floats
+// fp32 arithmetic: the linear branch by chunks of 64 tokens (the kernels the backward pass makes its states with) unless a routing decision spans two chunks, or the start states of all chunks (d^2 floats
 // per chunk and output head) would take more than FP32_CHUNK_BYTES: then token by token, which needs none.  At every size
 // that fits the chunk form is the shorter chain (a step per 64 tokens instead of one per token): the linear branch of B 1,
-// H 2, L 256, d 64 takes 24 us (three launches) instead of 95, of B 2, H 3, L 704 38 instead of 266.
+// H 2, L 256, d 64 takes 28 us (four launches) instead of 96, of B 2, H 3, L 704 42 instead of 262.
 constexpr size_t FP32_CHUNK_BYTES = (size_t)16 << 30;
 static bool uses_fp32_chunks(const FwdPlan& pl) {
     return !uses_chunk_path(pl) && !(pl.routing == NATS_ROUTE_CHUNK && pl.RC != 64) &&
@@ -587,7 +586,7 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
             redo = marks;
         }
         {   // all heads, or those whose chunks were not finite
-            ProfScope ps("gdn_recurrent", stream);
+            ProfScope ps(redo != nullptr ? "gdn_redo" : "gdn_recurrent", stream);
             st = launch_gdn_recurrent(pl, Q, K, V, alpha, beta, mask, ex.initial_state, ex.final_state, O_la,
                                       pl.routing == NATS_ROUTE_CHUNK ? reinterpret_cast<float*>(ws + pl.off_snap) : nullptr,
                                       redo, stream);

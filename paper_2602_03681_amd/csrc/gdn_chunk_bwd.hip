@@ -205,11 +205,11 @@ __device__ __forceinline__ void gdn_bwd_prep_block(const PrepArgs<T>& a, const i
                     accQ += mfma_bf16(qa[0], kb[0], f32x4{0.f, 0.f, 0.f, 0.f});
                 }
             } else {
-                // The forward adds the instructions' results up pairwise.  In fp32 a sum of D products in a row is 1.9e-7 off
-                // (half of the numbers q . k are small against their partial sums), and O_la with it: 2.0e-7 of its norm from
-                // 64 bits, now 1.1e-7, as token by token (B 1, H 2, L 256, d 64: this kernel 8.6 -> 10.9 us).  The backward pass keeps the
-                // running sum: behind Eq. 21 a row of O_la that is nearly zero, its q . k by chance nearly zero, is divided
-                // by its norm, and whichever last bits it has are the gradient's.
+                // The forward adds the instructions' results up pairwise: with q . k and k . k as one running sum of D products
+                // O_la was 2.0e-7 of its norm from 64 bits, now 1.14e-7 (token by token 1.07e-7; B 1, H 2, L 256, d 64: this
+                // kernel 8.6 -> 10.9 us).  The backward pass keeps the running sum: behind Eq. 21 a row of O_la that is
+                // nearly zero, its q . k by chance nearly zero, is divided by its norm, and whichever last bits it has are
+                // the gradient's.
                 f32x4 sumK[2] = {accK, accK}, sumQ[2] = {accQ, accQ};
 #pragma unroll 4
                 for (int kt = 0; kt < D / 16; ++kt) {
@@ -360,7 +360,7 @@ struct SeqArgs {
 // What leaves the chain for other kernels: U is not stored (b' Uh where it is needed), dbeta and the residuals' part of it
 // come from sums the gradient kernel has anyway, and the states are stored by the moving wavefronts, in whole rows, from
 // the terms they lie in.  On fp32 instructions, with all of that in the chain, at B 2, H 16, L 8192, d 128 bf16: forwards
-// 398 us (3.1 us per chunk), backwards 560; now 225 and 353.  Still a chain of latencies: 393 MB written and 100-300 MB
+// 398 us (3.1 us per chunk), backwards 560; now 245 and 360.  Still a chain of latencies: 393 MB written and 100-300 MB
 // read from HBM would take 100-140 us.
 template <typename T, typename TX, int D, int DIR>
 struct SeqLds {

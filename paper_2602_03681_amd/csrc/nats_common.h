@@ -255,7 +255,7 @@ nats_status launch_decode_commit(const nats_dec_params& p, float* state, const f
                                  const float* chunk_decay, int32_t* chunk_pos, int32_t* cache_len,
                                  const uint8_t* mask_c, int32_t* err_flags, hipStream_t st);
 
-// ---- backward pass (fp32 arithmetic) ----
+// ---- backward pass (gradients to fp32 accuracy) ----
 nats_status launch_softmax_bwd_dq(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* K, const void* V,
                                   const void* dO, bool dO_f32, const int32_t* vis, const float* O_nla, const float* lse,
                                   float* Dvec, float* dQ, hipStream_t st);
@@ -269,7 +269,7 @@ nats_status launch_gdn_recurrent_bwd(const FwdPlan& pl, const void* Q, const voi
                                      float* dbeta_part, float* dV, float* dS0, float* ds_la_part, hipStream_t st);
 nats_status launch_gdn_checkpoints(const FwdPlan& pl, const void* K, const void* V, const float* alpha, const float* beta,
                                    const uint8_t* mask, const float* S0, float* ckpt, hipStream_t st);
-// chunkwise backward of the linear branch (fp32 matrix instructions), routing per token
+// the linear branch by chunks, to fp32 accuracy: the backward pass, and the forward in fp32 arithmetic (with_at false)
 size_t chunk_ops_floats(const FwdPlan& pl, bool with_at);
 nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K, const float* alpha, const float* beta,
                                 const uint8_t* mask, float* ops, bool with_at, const void* Ks, const void* V, int32_t* cnt,

@@ -13,7 +13,7 @@
 // All products run on the bf16 matrix instruction with operands as sums of bf16 terms (softmax_terms.h): bf16 tensors
 // are one term, fp32 tensors, the weights P, dS and fp32 gradients of the output rows three.  The kernels before this
 // took the products of fp32 tensors on the vector units: at B 4, H 6, L 4096, d 128, routing per chunk, fp32, the branch's
-// rows 740 -> 210 us, dQ 665 -> 250, dK / dV over the compacted keys 775 -> 270, inside the chunks 483 -> 116.  For bf16
+// rows 710 -> 206 us, dQ 640 -> 271, dK / dV over the compacted keys 790 -> 314, inside the chunks 483 -> 114.  For bf16
 // tensors they took two fp16 terms of P and dS (22 of 24 bits, and the range of fp16), with transposed fp16 copies of
 // the tiles written to LDS: at B 2, H 16, L 8192, d 128 dQ 170 -> 146 us, dK / dV 185 -> 182.  What bounds them: per tile
 // and wavefront about as much vector work (masks, exponentials, splitting) as matrix work, and as many LDS reads (every

@@ -24,7 +24,8 @@ def test_decays_down_to_zero(dtype, d, routing):
     dO = make_grad_output(B, H, L, d, dtype, seed=610)
     if routing == nb.NATS_ROUTE_CHUNK:
         x["mask"] = make_chunk_mask(B, H, L // 64, 0.4, seed=5)
-        ref = nbw.hybrid_bwd_chunk_routed(x["Q"], x["K"], x["V"], x["alpha"], x["beta"], x["mask"], 64, dO)
+        with np.errstate(all="ignore"):      # its dalpha at 0
+            ref = nbw.hybrid_bwd_chunk_routed(x["Q"], x["K"], x["V"], x["alpha"], x["beta"], x["mask"], 64, dO)
     else:
         ref = nbw.hybrid_bwd(x["Q"], x["K"], x["V"], x["alpha"], x["beta"], x["mask"], dO)
     g = to_dev(x, dtype)

@@ -88,3 +88,19 @@ def test_softmax_branch_with_large_logits(d):
                           ("dK_nla", ds.transpose(2, 3).contiguous() @ q / d ** 0.5, 8.8e-7),
                           ("dV", p.transpose(2, 3).contiguous() @ g, 7e-7), ("g_nla", ds.sum(2), 8.8e-7)):
         assert _distance(got[key], ref) <= bar, key
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [64, 128])
+def test_gradients_of_the_plain_sum(d, dtype):
+    from oracle import nats_oracle_bwd as nbw
+    x = _inputs(1, 3, 320, d, 0.1, seed=70 + d)
+    for n in ("Q", "K", "V"):
+        x[n] = x[n].to(dtype)
+    dO = torch.randn(1, 3, 320, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()
+    args = [x[n] for n in ("Q", "K", "V", "alpha", "beta", "mask")]
+    got = nats.hybrid_attn_bwd(*args, dO, 64)
+    ref = nbw.hybrid_bwd(*(t.float().cpu().numpy() if t.is_floating_point() else t.cpu().numpy() for t in args), dO.float().cpu().numpy())
+    # over 40 drawn calls, fp32 multiply-adds and fp32 matrix instructions: at most 3.2e-7, 3.7e-7, 3.8e-7, 7.0e-7, 4.0e-7
+    for key, bar in (("dQ", 3.2e-7), ("dK", 3.7e-7), ("dV", 3.8e-7), ("dalpha", 7e-7), ("dbeta", 4e-7)):
+        assert _distance(got[key].cpu(), torch.from_numpy(np.asarray(ref[key], np.float64))) <= bar, key
