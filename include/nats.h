@@ -205,7 +205,7 @@ nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, con
  * process ends.  The call allocates nothing and frees nothing (no hipMalloc, no allocating library routine); its
  * first call on a device looks up the buffer's address (no stream operation).  Problems whose
  * nats_hybrid_attn_fwd_workspace_bytes() exceeds NATS_NOALLOC_SCRATCH_BYTES return NATS_ERR_WORKSPACE and
- * launch nothing.  Every call on a GPU shares that GPU's buffer: calls that overlap in time on one GPU (two
+ * launch nothing (in fp32 arithmetic: whose workspace without states per chunk does; see nats_hybrid_attn_fwd).  Every call on a GPU shares that GPU's buffer: calls that overlap in time on one GPU (two
  * streams, two threads) race; calls ordered on one stream do not.  The buffer keeps the last call's contents;
  * no kernel needs it cleared.  Arguments and result as nats_hybrid_attn_fwd. */
 #define NATS_NOALLOC_SCRATCH_BYTES (32u << 20)
