@@ -58,3 +58,16 @@ def test_grouped_backward_member_by_member(dtype, d, G, mode, routing, own_qk):
         terms = 64 * G * 2.0 ** -23 * float(at_once["g_nla"].abs().max()) if key == "dscore_nla" else 0.0   # (that cancel)
         ref = host(at_once[key])
         assert abs(host(got) - ref).max() <= 1.5e-6 * (ref ** 2).mean() ** 0.5 + terms, key
+
+
+def test_the_workspace_a_grouped_call_brings_itself():
+    """room for the pass over all heads at once, which one launch tells apart: a sum over the groups, and no copies of rows"""
+    g = to_dev(make_fwd_inputs(1, 2, 128, 64, "bf16", 0.3, seed=79), "bf16")
+    for G in (2, 5, 8):
+        gen = torch.Generator().manual_seed(G)
+        V, dO = (torch.randn(1, 2 * G, 128, 64, generator=gen).bfloat16().cuda() for _ in range(2))
+        nb.profile_begin(256)
+        nats.hybrid_attn_bwd(g["Q"], g["K"], V, g["alpha"], g["beta"], g["mask"], dO, group=G)
+        torch.cuda.synchronize()
+        kernels = nb.profile_end(32)
+        assert kernels["sum_groups"]["launches"] == 1 and kernels["gdn_chunk_grads"]["launches"] == 1
