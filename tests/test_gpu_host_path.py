@@ -91,7 +91,8 @@ def test_other_threads_run_while_a_launch_waits():
     stop.set()
     other.join()
     torch.cuda.synchronize()
-    assert gaps[0] <= 0.1 or gaps[0] < longest / 2, (gaps[0], longest)
+    # (where the queue had room for all of it, nothing was seen)
+    assert longest < 0.2 or gaps[0] < longest / 2, (gaps[0], longest)
 
 
 def _hip():
