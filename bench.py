@@ -21,7 +21,7 @@ if ROOT not in sys.path:
 PEAK = {"hbm": (8000.0, "GB/s"), "mfma": (2500.0, "TFLOP/s"), "alu_f32": (157.3, "TFLOP/s")}
 
 # the launches that together are the linear branch's segmented scan (recurrence, output and merge)
-SEG_SCAN = ("gdn_seg_pass1", "gdn_seg_fix", "gdn_seg_pass2")
+SEG_SCAN = ("gdn_seg_pass1", "gdn_seg_fix", "gdn_seg_pass2", "gdn_slice_scan")
 
 
 def kernel_work(name, cfg, sum_cnt):

@@ -28,9 +28,10 @@
 // inversion kernel).  No barrier and no LDS round trip stands inside the chain.
 //   The four STAGING wavefronts prepare what all d_v slices share, one chunk ahead, in a double-buffered LDS
 // set: the K and Q tiles (contiguous loads, converted to fp16 once, columns permuted into the slot order above),
-// T'', P and the gates.  (K^T scaled by kd, the operand of the state update, is made by the state wavefronts
+// T'', P and the gates.  (K^T, the operand of the state update, is made by the state wavefronts
 // from the K tile, a (contraction step, column half) share each: a product with a 0/1 selector hands a row-major
-// fragment back in the accumulator layout, exactly.)  They also store the output rows (fp16; the
+// fragment back in the accumulator layout, exactly.  kd rides on U: one rounding to fp16 where kd K and U were two, and the
+// state a fifth nearer to 64 bits.)  They also store the output rows (fp16; the
 // softmax kernel, which runs afterwards, merges the two branches), which the state wavefronts leave in an LDS
 // tile (computed transposed, S0 Q^T and U^T P^T, so that a lane holds four consecutive d_v of a token): whole
 // rows of 2 d bytes go out.
@@ -51,7 +52,7 @@ constexpr int SC = 64;           // chunk size
 template <int D>
 struct SegLds {
     static constexpr int SS = D + LDS_PAD;     // halves per row of the K, Q tiles [64][SS] and of the output tile
-    static constexpr int TS = SC + LDS_PAD;    // halves per row of Kd^T [d_k][TS]
+    static constexpr int TS = SC + LDS_PAD;    // halves per row of K^T [d_k][TS]
     // one operand set (halves)
     static constexpr int o_Kt = 0;
     static constexpr int o_Qt = o_Kt + SC * SS;
@@ -60,7 +61,7 @@ struct SegLds {
     static constexpr int o_G = o_P + TRI_FRAG_HALFS;   // fp32: gam[64], gam_C at [64], kd[64] from [68]
     static constexpr int G_KD = 68;
     static constexpr int SET = o_G + 2 * 132;          // 132 floats
-    static constexpr int o_Kd = 2 * SET;               // Kd^T [d_k][TS]: written and read inside one step
+    static constexpr int o_Kd = 2 * SET;               // K^T [d_k][TS]: written and read inside one step
     static constexpr int o_Out = o_Kd + D * TS;        // output tile [64][SS], fp16
     static constexpr int n_half = o_Out + SC * SS;
     static constexpr int bytes = n_half * 2;
@@ -69,7 +70,7 @@ struct SegLds {
 };
 
 // LDS of a block that runs the two output-free roles of a segment side by side (no Q, P, output tile): two operand
-// sets, and Kd^T per group and chunk parity, so that one barrier per chunk is enough.
+// sets, and K^T per group and chunk parity, so that one barrier per chunk is enough.
 template <int D>
 struct PairLds {
     static constexpr int SS = SegLds<D>::SS, TS = SegLds<D>::TS;
@@ -78,7 +79,7 @@ struct PairLds {
     static constexpr int o_G = o_T + TRI_FRAG_HALFS;
     static constexpr int G_KD = 68;
     static constexpr int SET = o_G + 2 * 132;
-    static constexpr int o_Kd = 2 * SET;               // Kd^T [group][chunk parity][d_k][TS]
+    static constexpr int o_Kd = 2 * SET;               // K^T [group][chunk parity][d_k][TS]
     static constexpr int n_half = o_Kd + 4 * D * TS;
     static constexpr int o_Qt = 0, o_P = 0, o_Out = 0; // not present
     static_assert(n_half <= SegLds<D>::n_half, "inside the kernel's LDS");
@@ -106,32 +107,6 @@ struct SegArgs {
     float la_scale;
 };
 
-// 8 consecutive bf16 -> 8 fp16.  Truncating conversion: a bf16 value has 8 significant bits, so it is exact
-// inside the fp16 range, and beyond the range it saturates instead of overflowing to infinity.
-__device__ __forceinline__ half8 cvt_bf16x8(u32x4 u) {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    half8 h;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const h2 p = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(u[i] << 16),
-                                                                       __uint_as_float(u[i] & 0xffff0000u)));
-        h[2 * i] = p[0];
-        h[2 * i + 1] = p[1];
-    }
-    return h;
-}
-
-// two accumulator tiles (rows 4 lq + j of each) -> the 8 contraction slots of one operand fragment
-__device__ __forceinline__ half8 pack_tiles(f32x4 lo, f32x4 hi) {
-    half8 h;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        h[j] = (half_t)lo[j];
-        h[4 + j] = (half_t)hi[j];
-    }
-    return h;
-}
-
 // ------------------------------------------------------------------------------------------------------------
 // STATE wavefronts.  ROLE and F32OUT are compile-time: the chunk loop is straight-line code.
 // Index conventions of a lane (l16 = lane % 16, lq = lane / 16):
@@ -142,9 +117,9 @@ __device__ __forceinline__ half8 pack_tiles(f32x4 lo, f32x4 hi) {
 // PAIR: the block runs the two output-free roles of a segment side by side, wavefronts 0-3 one, 4-7 the other, and
 // has no staging group: the 512 threads bring in the operand set themselves (K tile, T'', gates: 2-3 loads of 16
 // bytes per thread and chunk, asked for two chunks ahead at the top of a step and written into the set of the
-// next chunk at the top of the following step).  Kd^T (one for both groups at d = 128, each group's own at
+// next chunk at the top of the following step).  K^T (one for both groups at d = 128, each group's own at
 // d = 64) has a buffer per chunk parity:
-// with the sets and Kd^T both double-buffered the barrier in the middle of a step is the only one (what a
+// with the sets and K^T both double-buffered the barrier in the middle of a step is the only one (what a
 // wavefront writes before it in step c + 1 was last read before that barrier in step c, or in step c - 1).
 template <int D, int ROLE, bool F32OUT>
 __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int bh, const int seg, half_t* lds) {
@@ -220,11 +195,11 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
     };
     const float gated_off = a.gated ? 0.f : 1.f;   // without the delta rule the state does not enter R
     half_t* OutT = lds + Lds::o_Out;
-    // Kd^T[d_k][token slots] = kd_tok K[tok][d_k] is made here too, from the K tile: a product with a 0/1 selector
+    // K^T[d_k][token slots] is made here too, from the K tile: a product with a 0/1 selector
     // hands 16 d_k columns of a token tile's K fragment back as an accumulator tile (rows tok 4 lq + j, col d_k),
-    // exactly; those are 4 consecutive slots of a Kd^T row.  The (contraction step, column half) pairs are dealt
+    // exactly; those are 4 consecutive slots of a K^T row.  The (contraction step, column half) pairs are dealt
     // to the four wavefronts: d = 128: step = wavefront, both halves; d = 64: step = wavefront % 2, half = wavefront / 2.
-    // In a paired block at d = 128 the two groups make one Kd^T together: step = wavefront, half = group.
+    // In a paired block at d = 128 the two groups make one K^T together: step = wavefront, half = group.
     constexpr bool SHARE_KD = PAIR && KS_D == 4;
     constexpr int NTR = SHARE_KD ? 1 : KS_D / 2;    // pairs per wavefront and token tile
     const int tr_ks = KS_D == 4 ? wave : (wave & 1);
@@ -306,7 +281,7 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
         f32x4 accO[NVT][4];
         half8 rfrag[2][NVT];      // R[token slots][v = l16]: B operand of T'' R
         // Without outputs there are registers to spare: the K fragments of the next token tile are read while the
-        // current tile's products run (the write of Kd^T below keeps the compiler from moving those reads up by
+        // current tile's products run (the write of K^T below keeps the compiler from moving those reads up by
         // itself: it cannot tell the two LDS regions apart).
         half8 kf_next[KS_D], kt_next;
         if (!HAS_OUT) {
@@ -353,14 +328,10 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
                         accR[t2][vt] = mfma16(kf[ks], sfrag[vt][ks], accR[t2][vt]);                 // rows tok, col v
                         if (HAS_OUT) accO[vt][tt] = mfma16(sfrag[vt][ks], qf[ks], accO[vt][tt]);   // rows v, col tok
                     }
-                {   // this wavefront's share of Kd^T for token tile tt
-                    const float4 k4 = *reinterpret_cast<const float4*>(Gt + Lds::G_KD + 16 * tt + 4 * lq);
-                    const float kk[4] = {k4.x, k4.y, k4.z, k4.w};
+                {   // this wavefront's share of K^T for token tile tt
 #pragma unroll
                     for (int i = 0; i < NTR; ++i) {
-                        f32x4 t = mfma16(kt, iselp[i], f32x4{0.f, 0.f, 0.f, 0.f});   // col d_k = 32 tr_ks + 16 hf + l16
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) t[j] *= kk[j];
+                        const f32x4 t = mfma16(kt, iselp[i], f32x4{0.f, 0.f, 0.f, 0.f});   // col d_k = 32 tr_ks + 16 hf + l16
                         *reinterpret_cast<half4*>(Kd + (32 * tr_ks + 16 * tr_hf[i] + l16) * TS + 32 * kp + 8 * lq + 4 * t2) =
                             to_half4_hw(t);
                     }
@@ -380,7 +351,8 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
         }
 
         // ---- U = T'' R (T'' lower triangular: token tiles 0, 1 need the first contraction step only) ----
-        half8 ufrag[2][NVT];      // U[token slots][v = l16]: B operand of Kd^T U, A operand of U^T P^T
+        half8 ufrag[2][NVT];      // U[token slots][v = l16]: A operand of U^T P^T
+        half8 kufrag[2][NVT];     // kd U: B operand of K^T (kd U)
 #pragma unroll
         for (int kp = 0; kp < 2; ++kp) {
             f32x4 accU[2][NVT];
@@ -397,9 +369,21 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
                 }
             }
 #pragma unroll
-            for (int vt = 0; vt < NVT; ++vt) ufrag[kp][vt] = pack_tiles(accU[0][vt], accU[1][vt]);
+            for (int vt = 0; vt < NVT; ++vt) {
+                if (HAS_OUT) ufrag[kp][vt] = pack_tiles(accU[0][vt], accU[1][vt]);
+#pragma unroll
+                for (int t2 = 0; t2 < 2; ++t2) {
+                    const float4 k4 = *reinterpret_cast<const float4*>(Gt + Lds::G_KD + 16 * (2 * kp + t2) + 4 * lq);
+                    accU[t2][vt][0] *= k4.x;
+                    accU[t2][vt][1] *= k4.y;
+                    accU[t2][vt][2] *= k4.z;
+                    accU[t2][vt][3] *= k4.w;
+                }
+                kufrag[kp][vt] = pack_tiles(accU[0][vt], accU[1][vt]);
+            }
         }
 
+        if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0);   // (reads moved up across this line cost 16 registers that are not there)
         // ---- output rows: gam (S0 Q^T) + U^T P^T, into the LDS tile (la_scale rides on the gate and on P) ----
         if (HAS_OUT) {
 #pragma unroll
@@ -418,7 +402,7 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
             }
         }
         const float gC = Gt[64];   // (read before the barrier: in a paired block the set may be rewritten after it)
-        __syncthreads();   // the staging group has taken the previous chunk's rows out of the output tile; Kd^T complete
+        __syncthreads();   // the staging group has taken the previous chunk's rows out of the output tile; K^T complete
         if (HAS_OUT) {
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt)
@@ -432,7 +416,7 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
                 }
         }
 
-        // ---- S1^T = gam_C S0^T + Kd^T U, and its operand form for the next chunk ----
+        // ---- S1^T = gam_C S0^T + K^T (kd U), and its operand form for the next chunk ----
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
             half8 af[2];
@@ -443,7 +427,7 @@ __device__ __forceinline__ void seg_state_waves(const SegArgs<D>& a, const int b
 #pragma unroll
                 for (int j = 0; j < 4; ++j) accS[dt][vt][j] *= gC;
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) accS[dt][vt] = mfma16(af[ks], ufrag[ks][vt], accS[dt][vt]);   // rows d_k, col v
+                for (int ks = 0; ks < 2; ++ks) accS[dt][vt] = mfma16(af[ks], kufrag[ks][vt], accS[dt][vt]);   // rows d_k, col v
             }
         }
 #pragma unroll
@@ -623,7 +607,9 @@ __device__ __forceinline__ void seg_staging_waves(const SegArgs<D>& a, const int
 }
 
 template <int D, bool F32OUT>
-__global__ __launch_bounds__(SEG_THREADS) void gdn_seg_scan_kernel(const SegArgs<D> a) {
+// (the LDS allows one block per CU: without the bound the compiler schedules the d = 64 kernel for four wavefronts per SIMD, with too few
+// reads in flight; B 1, H 16, L 8192 82.5 us for the whole forward, 86.3 without)
+__global__ __launch_bounds__(SEG_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void gdn_seg_scan_kernel(const SegArgs<D> a) {
     extern __shared__ __align__(16) unsigned char seg_smem[];
     half_t* lds = reinterpret_cast<half_t*>(seg_smem);
     fp16_saturate_on();   // conversions to fp16 clamp to the fp16 range (see to_half4_hw)
@@ -787,9 +773,10 @@ __global__ __launch_bounds__(FIX_THREADS) void gdn_seg_fix_kernel(float* __restr
     if (sg <= last) step(sg, fa, fb);
 }
 
-// number of segments a (batch, head) is cut into: enough blocks to fill the chip, at least 4 chunks each
+// number of segments a (batch, head) is cut into: enough blocks to fill the chip, at least 4 chunks each.  If automatic, the number
+// that the workspace has room for: seg_form() may take fewer, or none.
 //
-// Automatic, beside that: (us of a whole forward, p 0.05)
+// Automatic, beside that: (us of a whole forward in segments, p 0.05)
 // * Two segments run one behind the other (the second waits for the first's end state) and never beat one: B 2, H 16,
 //   L 8192, d 128 401 against 390, B 1, H 2, L 512, d 64 29.8 against 24.9.  Three, of 4 or 5 chunks, are not ahead of one
 //   either (19 chunks 66.5 / 65.7); four are from 16 chunks on (B 3, H 6, L 1216 60.0 / 65.7, B 1, H 4, L 1024 49.0 / 52.8).
@@ -803,6 +790,41 @@ int gdn_segments(const FwdPlan& pl) {
     if (pl.gdn_segments > 0) return n;
     while (n * n > 4 * n_chunks) --n;
     return n_chunks < 16 || n == 2 ? 1 : n;
+}
+
+// The form of an automatic call: in segments (ns = 0, n_seg of them, at most as many as the workspace has room for) or in one pass
+// with ns slices of 16 value columns per block (gdn_slice_scan.hip), whichever is expected to take less, in us:
+// * one pass: a step per chunk, 1.1 with one slice per block and 1.42 with two (d = 64: 0.87, 1.0);
+// * segments: two passes of a step per chunk of a segment, 3.1 (d = 64: 2.05 and 0.1 per head on an XCD), 1.4 (0.55) per segment
+//   for the fix-up and 4 for two more launches.
+// A CU takes one block at a time and the blocks of a head are dealt to one of the eight XCDs, 32 CUs each: more blocks than that on
+// the fullest XCD are another round (18 heads in 12 segments: 33 on two of the XCDs, L 3072, d 128 107.9 us for the whole
+// forward, 84.8 in one pass).  Measured, whole forwards, p 0.05, in segments / in one pass: d 128, 2 heads, L 512 34.2 / 24.9, L 2048
+// 55.9 / 50.0, L 3072 64.7 / 69.2; 18 heads, L 1024 54.5 / 38.7; 32 heads, L 2048 76.0 / 65.2, L 4096 117.0 / 117.4, L 6144
+// 160.7 / 172.8; 48 heads (two slices), L 1024 66.3 / 46.7, L 4096 158.8 / 151.6, L 6144 229 / 241; d 64, 8 heads, L 1536 34.8 /
+// 31.8, L 3072 39.7 / 49.6; 32 heads, L 2048 49.0 / 46.7, L 3072 62.8 / 66.5.
+struct SegForm {
+    int n_seg, ns;
+};
+static SegForm seg_form(const FwdPlan& pl) {
+    const int n_chunks = pl.L / SC, cap = gdn_segments(pl);
+    if (pl.gdn_segments > 0) return {cap, 0};
+    const int heads = (pl.BH + 7) / 8 * pl.G;   // on the fullest XCD
+    auto rounds = [](int blocks) { return (blocks + 31) / 32; };
+    const bool narrow = pl.d == 64;
+    const float seg_step = narrow ? 2.05f + 0.1f * heads : 3.1f, fix = narrow ? 0.55f : 1.4f;
+    SegForm best{1, 0};
+    float least = rounds(heads) * n_chunks * seg_step;
+    for (int g = 3; g <= cap; ++g) {
+        const float t = 2 * rounds(heads * (g - 1)) * ((n_chunks + g - 1) / g) * seg_step + fix * g + 4.f;
+        if (t < least) least = t, best = {g, 0};
+    }
+    for (int ns = 1; ns <= 2; ++ns) {
+        const float step = narrow ? (ns == 1 ? 0.87f : 1.0f) : (ns == 1 ? 1.1f : 1.42f);
+        const float t = rounds(heads * (pl.d / 16 / ns)) * n_chunks * step;
+        if (t < least) least = t, best = {1, ns};
+    }
+    return best;
 }
 
 template <int D, bool F32OUT>
@@ -819,7 +841,6 @@ static nats_status launch_seg_k(const FwdPlan& pl, SegArgs<D> a, hipStream_t st)
         attr_done[dev] = true;
     }
     const int n_chunks = pl.L / SC;
-    a.n_seg = gdn_segments(pl);
     a.seg_len = (n_chunks + a.n_seg - 1) / a.n_seg;
     a.n_seg = (n_chunks + a.seg_len - 1) / a.seg_len;   // no empty segment
     const int bh8 = 8 * ((pl.BH + 7) / 8) * pl.G;   // linear heads padded to the XCD count, times the group size
@@ -857,17 +878,20 @@ nats_status launch_gdn_seg_scan(const FwdPlan& pl, const void* Q, const void* K,
                                 const void* PF, const float* gamv, const float* kdv, const float* gamC,
                                 const float* S0, float* S_final, float* seg_ws, void* O_la_h, float* O_la_f32,
                                 hipStream_t st) {
+    const SegForm form = seg_form(pl);
+    if (form.ns > 0)
+        return launch_gdn_slice_scan(pl, form.ns, Q, K, V, TF, PF, gamv, kdv, gamC, S0, S_final, O_la_h, O_la_f32, st);
     const size_t per = (size_t)pl.BHG * gdn_segments(pl) * pl.d * pl.d;
     if (pl.d == 64) {
         SegArgs<64> a{(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const half_t*)TF, (const half_t*)PF,
                       gamv, kdv, gamC, S0, S_final, seg_ws, seg_ws + per, seg_ws + 2 * per, (half_t*)O_la_h,
-                      O_la_f32, pl.L, pl.BHG, 0, 0, 0,
+                      O_la_f32, pl.L, pl.BHG, form.n_seg, 0, 0,
                       pl.linear_op == NATS_LINEAR_GATED, pl.G, pl.la_scale};
         return launch_seg_t<64>(pl, a, st);
     }
     SegArgs<128> a{(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const half_t*)TF, (const half_t*)PF,
                    gamv, kdv, gamC, S0, S_final, seg_ws, seg_ws + per, seg_ws + 2 * per, (half_t*)O_la_h,
-                   O_la_f32, pl.L, pl.BHG, 0, 0, 0,
+                   O_la_f32, pl.L, pl.BHG, form.n_seg, 0, 0,
                    pl.linear_op == NATS_LINEAR_GATED, pl.G, pl.la_scale};
     return launch_seg_t<128>(pl, a, st);
 }

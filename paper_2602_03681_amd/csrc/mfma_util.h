@@ -68,6 +68,32 @@ __device__ __forceinline__ half4 to_half4_hw(f32x4 v) {
     return h;
 }
 
+// 8 consecutive bf16 -> 8 fp16.  Truncating conversion: a bf16 value has 8 significant bits, so it is exact
+// inside the fp16 range, and beyond the range it saturates instead of overflowing to infinity.
+__device__ __forceinline__ half8 cvt_bf16x8(u32x4 u) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    half8 h;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const h2 p = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(u[i] << 16),
+                                                                       __uint_as_float(u[i] & 0xffff0000u)));
+        h[2 * i] = p[0];
+        h[2 * i + 1] = p[1];
+    }
+    return h;
+}
+
+// two accumulator tiles (rows 4 lq + j of each) -> the 8 contraction slots of one operand fragment
+__device__ __forceinline__ half8 pack_tiles(f32x4 lo, f32x4 hi) {
+    half8 h;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        h[j] = (half_t)lo[j];
+        h[4 + j] = (half_t)hi[j];
+    }
+    return h;
+}
+
 // ---- fp32 matrix instruction v_mfma_f32_16x16x4_f32: out[m][n] += sum_kk A[m][kk] B[kk][n]; lane (l16, lq) gives
 // A[m = l16][kk = lq], B[kk = lq][n = l16] and holds out[m = 4 lq + j][n = l16], j = 0..3.  mac16 contracts over 16
 // indices in four instructions, instruction j over the indices 4 lq + j: a lane's A operands are then four

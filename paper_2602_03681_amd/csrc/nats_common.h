@@ -228,6 +228,9 @@ nats_status launch_gdn_seg_scan(const FwdPlan& pl, const void* Q, const void* K,
                                 const void* PF, const float* gamv, const float* kdv, const float* gamC,
                                 const float* S0, float* S_final, float* seg_ws, void* O_la_h, float* O_la_f32,
                                 hipStream_t st);
+nats_status launch_gdn_slice_scan(const FwdPlan& pl, int ns, const void* Q, const void* K, const void* V, const void* TF,
+                                  const void* PF, const float* gamv, const float* kdv, const float* gamC, const float* S0,
+                                  float* S_final, void* O_la_h, float* O_la_f32, hipStream_t st);
 nats_status launch_softmax_terms_fwd(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* K,
                                      const void* V, const int32_t* cnt, const float* O_la, const float* w_nla,
                                      const float* w_la, void* O, float* O_nla_out, float* lse_out, hipStream_t st);
