@@ -286,6 +286,15 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
                                  const nats_bwd_extra* extra, void* workspace, size_t workspace_bytes,
                                  void* hip_stream);
 
+/* The same for bf16 tensors (p->dtype NATS_BF16), with the gradients of Q, K and V rounded to bf16 (to nearest, from the same fp32
+ * sums) in dQ_bf16, dK_bf16 [B,H,L,d] and dV_bf16 [B,H*G,L,d].  dQ, dK, dV are scratch of the same sizes as above, whose contents
+ * are undefined afterwards: where the pass can, it writes the rounded gradients from the sums instead of them. */
+nats_status nats_hybrid_attn_bwd_bf16(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                                      const float* alpha, const float* beta, const uint8_t* mask, const void* dO,
+                                      float* dQ, float* dK, float* dV, float* dalpha, float* dbeta,
+                                      const nats_bwd_extra* extra, void* dQ_bf16, void* dK_bf16, void* dV_bf16, void* workspace,
+                                      size_t workspace_bytes, void* hip_stream);
+
 /* ------------------------------------------------------------------------- *
  * Single-token decode (Section 4.1, per-token generation, with per-token routing)
  * ------------------------------------------------------------------------- */

@@ -41,7 +41,8 @@ class _HybridAttn(torch.autograd.Function):
                                softmax_scale=o["softmax_scale"], la_scale=o["la_scale"], linear_op=o["linear_op"],
                                freeze_on_softmax=o["freeze_on_softmax"], initial_state=initial_state, want=tuple(want),
                                routing=o["routing"], group=o["group"], Q_nla=Q_nla, K_nla=K_nla,
-                               combine_mode=o["combine_mode"], rms_eps=o["rms_eps"], w_nla=w_nla, w_la=w_la)
+                               combine_mode=o["combine_mode"], rms_eps=o["rms_eps"], w_nla=w_nla, w_la=w_la,
+                               grads_bf16=Q.dtype == torch.bfloat16)
 
         def g(key, like, wanted):
             return r[key].to(like.dtype) if (wanted and like is not None and key in r) else None

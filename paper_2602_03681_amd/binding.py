@@ -75,7 +75,8 @@ EXPORTS = ("nats_hybrid_attn_fwd_workspace_bytes", "nats_hybrid_attn_fwd", "nats
            "nats_hybrid_attn_decode", "nats_last_error", "nats_abi_version", "nats_profile_begin",
            "nats_profile_end", "nats_probe_mfma", "nats_hybrid_attn_decode_chunk",
            "nats_hybrid_attn_decode_commit", "nats_merge_weights", "nats_route_chunks",
-           "nats_hybrid_attn_bwd_workspace_bytes", "nats_hybrid_attn_bwd", "nats_hybrid_attn_fwd_noalloc",
+           "nats_hybrid_attn_bwd_workspace_bytes", "nats_hybrid_attn_bwd", "nats_hybrid_attn_bwd_bf16",
+           "nats_hybrid_attn_fwd_noalloc",
            "nats_hybrid_attn_decode_workspace_bytes", "nats_merge_weights_from_x")
 
 
@@ -124,6 +125,9 @@ def load_library():
     lib.nats_hybrid_attn_bwd.restype = ctypes.c_int
     lib.nats_hybrid_attn_bwd.argtypes = ([ctypes.POINTER(FwdParams)] + [vp] * 12 + [ctypes.POINTER(BwdExtra), vp,
                                           ctypes.c_size_t, vp])
+    lib.nats_hybrid_attn_bwd_bf16.restype = ctypes.c_int
+    lib.nats_hybrid_attn_bwd_bf16.argtypes = ([ctypes.POINTER(FwdParams)] + [vp] * 12 + [ctypes.POINTER(BwdExtra)] + [vp] * 4
+                                              + [ctypes.c_size_t, vp])
     lib.nats_last_error.restype = ctypes.c_char_p
     lib.nats_abi_version.restype = ctypes.c_int
     lib.nats_probe_mfma.restype = ctypes.c_double
@@ -326,14 +330,15 @@ def hybrid_attn_bwd(Q, K, V, alpha, beta, mask, dO, C: int = 64, *, softmax_scal
                     linear_op: int = NATS_LINEAR_GDN, freeze_on_softmax: bool = False, initial_state=None,
                     want=(), workspace=None, routing: int = NATS_ROUTE_TOKEN,
                     math: int = NATS_MATH_AUTO, group: int = 1, Q_nla=None, K_nla=None, combine_mode: int = 0,
-                    rms_eps: float = 0.0, w_nla=None, w_la=None) -> Dict[str, torch.Tensor]:
+                    rms_eps: float = 0.0, w_nla=None, w_la=None, grads_bf16: bool = False) -> Dict[str, torch.Tensor]:
     """nats_hybrid_attn_bwd: gradients of O = O_la + O_nla given dO.  Returns dQ, dK, dV [B,H,L,d] f32, dalpha,
     dbeta [B,H,L] f32 and, if named in `want`, d_initial_state [B,H,d,d], g_nla, g_la [B,H,L] (routing per token),
     dscore_nla, dscore_la [B,H,L/C] (Eq. 16, Eq. 17).  math = NATS_MATH_FP32: the linear branch's adjoint token by
     token instead of by chunks.  group = G > 1 (head grouping): V, dO, dV [B,H*G,L,d], the states [B,H*G,d,d].
     Q_nla, K_nla [B,H*G,L,d] (both or neither): the softmax branch's own queries and keys; their gradients come back
     as dQ_nla, dK_nla, and dQ, dK are then the linear branch's alone.  combine_mode 1, 2 (Eq. 21 and its ablation
-    with one normalisation) with the weights w_nla, w_la [B,H*G,L] f32 (or None): also returns dw_nla, dw_la."""
+    with one normalisation) with the weights w_nla, w_la [B,H*G,L] f32 (or None): also returns dw_nla, dw_la.  grads_bf16
+    (bf16 tensors): dQ, dK, dV come back rounded to bf16 (nats_hybrid_attn_bwd_bf16)."""
     lib = load_library()
     B, H, L, d = Q.shape
     dt = Q.dtype
@@ -385,10 +390,15 @@ def hybrid_attn_bwd(Q, K, V, alpha, beta, mask, dO, C: int = 64, *, softmax_scal
                      K_nla.data_ptr() if K_nla is not None else None, g("dQ_nla"), g("dK_nla"),
                      w_nla.data_ptr() if w_nla is not None else None, w_la.data_ptr() if w_la is not None else None,
                      g("dw_nla"), g("dw_la"))
-    _check(lib.nats_hybrid_attn_bwd(ctypes.byref(params), _ptr(Q), _ptr(K), _ptr(V), _ptr(alpha), _ptr(beta), _ptr(mask),
-                                    _ptr(dO), _ptr(res["dQ"]), _ptr(res["dK"]), _ptr(res["dV"]), _ptr(res["dalpha"]),
-                                    _ptr(res["dbeta"]), ctypes.byref(extra), _ptr(workspace), workspace.numel(),
-                                    _stream_ptr()))
+    call = [ctypes.byref(params), _ptr(Q), _ptr(K), _ptr(V), _ptr(alpha), _ptr(beta), _ptr(mask), _ptr(dO), _ptr(res["dQ"]),
+            _ptr(res["dK"]), _ptr(res["dV"]), _ptr(res["dalpha"]), _ptr(res["dbeta"]), ctypes.byref(extra)]
+    if grads_bf16:
+        rounded = {k: torch.empty_like(res[k], dtype=torch.bfloat16) for k in ("dQ", "dK", "dV")}
+        _check(lib.nats_hybrid_attn_bwd_bf16(*call, *(_ptr(t) for t in rounded.values()), _ptr(workspace), workspace.numel(),
+                                             _stream_ptr()))
+        res.update(rounded)
+    else:
+        _check(lib.nats_hybrid_attn_bwd(*call, _ptr(workspace), workspace.numel(), _stream_ptr()))
     return res
 
 

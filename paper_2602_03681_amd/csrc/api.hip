@@ -620,11 +620,11 @@ size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p) {
 }
 
 // The backward pass on the plan's heads (pl.G > 1: all output heads of the groups).  ex by value: the optional outputs
-// may be redirected.
+// may be redirected.  rounded: dQ, dK, dV go there as bf16 as well (the float ones are then scratch).
 static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q, const void* K, const void* V,
                             const float* alpha, const float* beta, const uint8_t* mask, const void* dO, float* dQ,
                             float* dK, float* dV, float* dalpha, float* dbeta, nats_bwd_extra ex, char* ws,
-                            hipStream_t stream) {
+                            const RoundedGrads& rounded, hipStream_t stream) {
     nats_status st = NATS_OK;
     int32_t* cnt = reinterpret_cast<int32_t*>(ws + pl.off_cnt);
     int32_t* idx = reinterpret_cast<int32_t*>(ws + pl.off_idx);
@@ -763,16 +763,23 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         if (st == NATS_OK) st = launch_zero_f32(dKs, n_qk, stream);
         if (st != NATS_OK) return st;
     }
+    RoundedGrads direct;
     if (by_chunks) {
         {   // backwards along the sequence: the state gradient behind every chunk, dV
             ProfScope ps("gdn_chunk_state_grads", stream);
             st = launch_gdn_chunk_state_grads(pl, Q, K, dO_l, dO_f32, ops, ckpt, dck, dot, dV, ex.d_initial_state, stream);
             if (st != NATS_OK) return st;
         }
-        // dQ += linear share; dK, dalpha, dbeta = linear share; g_nla cleared
+        // dQ += linear share; dK, dalpha, dbeta = linear share; g_nla cleared.  Rounded results leave the kernels that write an
+        // element for the last time: dQ this one; dK and dV this one and the one that writes the softmax tokens' rows, where
+        // these are not added to.
+        if (!grouped && !own_qk && pl.dtype == NATS_BF16) {
+            direct.dQ = rounded.dQ;
+            if (!chunk) direct = rounded;
+        }
         ProfScope ps("gdn_chunk_grads", stream);
         st = launch_gdn_chunk_grads(pl, Q, K, dO_l, dO_f32, alpha, mask, ops, ckpt, dck, Uh, dV, dot, dQ, dK, dalpha, dbeta, ex.g_nla,
-                                    dsl, stream);
+                                    dsl, direct, stream);
         if (st != NATS_OK) return st;
     } else {
         {
@@ -795,18 +802,27 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
         ProfScope ps("softmax_bwd_dkv", stream);
         st = launch_softmax_bwd_dkv(pl, Qs, Kc, Vc, dO_s, dO_f32, vis, idx, n_s, lse, Dvec, dKs, dV, ex.g_nla,
                                     reinterpret_cast<float*>(ws + bp.off_skp), reinterpret_cast<float*>(ws + bp.off_svp),
-                                    reinterpret_cast<float*>(ws + bp.off_sgp), stream);
+                                    reinterpret_cast<float*>(ws + bp.off_sgp), RoundedGrads{nullptr, direct.dK, direct.dV}, stream);
         if (st != NATS_OK) return st;
     }
     if (grouped) {
         ProfScope ps("sum_groups", stream);
         const size_t row = (size_t)pl.L;
-        const GroupSum sums[] = {{dQ, dQ_sum, row * pl.d}, {dK, dK_sum, row * pl.d}, {dalpha, dalpha_sum, row},
+        const GroupSum sums[] = {{dQ, dQ_sum, row * pl.d, rounded.dQ}, {dK, dK_sum, row * pl.d, rounded.dK}, {dalpha, dalpha_sum, row},
                                  {dbeta, dbeta_sum, row}, {ex.g_nla, g_nla_sum, row}, {dsl, dsl_sum, row / 64}};
         st = launch_sum_groups(pl.BH, pl.G, sums, 6, stream);
         if (st != NATS_OK) return st;
         dbeta = dbeta_sum;
         ex.g_nla = g_nla_sum;
+        direct.dQ = rounded.dQ;
+        direct.dK = rounded.dK;
+    }
+    {   // what none of these has rounded
+        const Rounding left[] = {{dQ, direct.dQ ? nullptr : rounded.dQ, n_qk}, {dK, direct.dK ? nullptr : rounded.dK, n_qk},
+                                 {dV, direct.dV ? nullptr : rounded.dV, n_qk}};
+        ProfScope ps("round_bf16", stream);
+        st = launch_round_bf16(left, 3, stream);
+        if (st != NATS_OK) return st;
     }
     if (ex.g_la != nullptr || ex.dscore_nla != nullptr || ex.dscore_la != nullptr) {   // Eq. 16, Eq. 17
         ProfScope ps("score_gradients", stream);
@@ -817,11 +833,11 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
 }
 
 
-nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
-                                 const float* alpha, const float* beta, const uint8_t* mask, const void* dO,
-                                 float* dQ, float* dK, float* dV, float* dalpha, float* dbeta,
-                                 const nats_bwd_extra* extra, void* workspace, size_t workspace_bytes,
-                                 void* hip_stream) {
+static nats_status run_bwd(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                           const float* alpha, const float* beta, const uint8_t* mask, const void* dO,
+                           float* dQ, float* dK, float* dV, float* dalpha, float* dbeta,
+                           const nats_bwd_extra* extra, const RoundedGrads& rounded, void* workspace, size_t workspace_bytes,
+                           void* hip_stream) {
     FwdPlan pl;
     BwdPlan bp;
     nats_status st = validate_bwd_params(p, workspace != nullptr ? workspace_bytes : 0, &pl, &bp);
@@ -848,12 +864,12 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
     }
     const void* ptrs[] = {Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha, dbeta, workspace, ex.initial_state,
                           ex.d_initial_state, ex.g_nla, ex.g_la, ex.dscore_nla, ex.dscore_la, ex.Q_nla, ex.K_nla,
-                          ex.dQ_nla, ex.dK_nla, ex.w_nla, ex.w_la, ex.dw_nla, ex.dw_la};
+                          ex.dQ_nla, ex.dK_nla, ex.w_nla, ex.w_la, ex.dw_nla, ex.dw_la, rounded.dQ, rounded.dK, rounded.dV};
     for (const void* ptr : ptrs)
         if (ptr != nullptr && !aligned16(ptr)) { set_error("pointer %p is not 16-byte aligned", ptr); return NATS_ERR_ALIGN; }
-    const void* outs[] = {dQ, dK, dV, dalpha, dbeta};
+    const void* outs[] = {dQ, dK, dV, dalpha, dbeta, rounded.dQ, rounded.dK, rounded.dV};
     for (const void* o : outs)
-        if (o == Q || o == K || o == V || o == dO || o == alpha || o == beta) {
+        if (o != nullptr && (o == Q || o == K || o == V || o == dO || o == alpha || o == beta)) {
             set_error("a gradient output must not alias an input");
             return NATS_ERR_SHAPE;
         }
@@ -875,7 +891,7 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
         }
     }
     pl.qk_per_out_head = pl.G > 1 && ex.Q_nla != nullptr;
-    if (bp.G == 1) return bwd_core(pl, bp, Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha, dbeta, ex, ws, stream);
+    if (bp.G == 1) return bwd_core(pl, bp, Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha, dbeta, ex, ws, rounded, stream);
 
     // Head grouping (Section 4.3) member by member: member g of every group, i.e. the output heads bh G + g, is a problem of B x H heads
     // with the linear heads' Q, K, alpha, beta and mask.  Its V, dO and initial state are gathered, the pass runs on
@@ -941,7 +957,7 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
         float* dKg = first ? dK : reinterpret_cast<float*>(ws + bp.off_gdk);
         float* dag = first ? dalpha : reinterpret_cast<float*>(ws + bp.off_gda);
         float* dbg = first ? dbeta : reinterpret_cast<float*>(ws + bp.off_gdb);
-        st = bwd_core(pl, bp, Q, K, Vg, alpha, beta, mask, dOg, dQg, dKg, dVg, dag, dbg, e1, ws, stream);
+        st = bwd_core(pl, bp, Q, K, Vg, alpha, beta, mask, dOg, dQg, dKg, dVg, dag, dbg, e1, ws, RoundedGrads(), stream);
         if (st != NATS_OK) return st;
         st = launch_copy_rows(dVg, row * 4, dV + g * row, G * row * 4, row * 4, pl.BH, stream);
         if (st != NATS_OK) return st;
@@ -973,7 +989,31 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
             if (st != NATS_OK) return st;
         }
     }
-    return st;
+    const Rounding all[] = {{dQ, rounded.dQ, nd}, {dK, rounded.dK, nd}, {dV, rounded.dV, nd * G}};
+    return launch_round_bf16(all, 3, stream);
+}
+
+nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                                 const float* alpha, const float* beta, const uint8_t* mask, const void* dO,
+                                 float* dQ, float* dK, float* dV, float* dalpha, float* dbeta,
+                                 const nats_bwd_extra* extra, void* workspace, size_t workspace_bytes,
+                                 void* hip_stream) {
+    return run_bwd(p, Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha, dbeta, extra, RoundedGrads(), workspace, workspace_bytes,
+                   hip_stream);
+}
+
+nats_status nats_hybrid_attn_bwd_bf16(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                                      const float* alpha, const float* beta, const uint8_t* mask, const void* dO,
+                                      float* dQ, float* dK, float* dV, float* dalpha, float* dbeta,
+                                      const nats_bwd_extra* extra, void* dQ_bf16, void* dK_bf16, void* dV_bf16, void* workspace,
+                                      size_t workspace_bytes, void* hip_stream) {
+    if (p != nullptr && p->dtype != NATS_BF16) { set_error("gradients rounded to bf16 go with bf16 tensors"); return NATS_ERR_DTYPE; }
+    if (!dQ_bf16 || !dK_bf16 || !dV_bf16) { set_error("dQ_bf16, dK_bf16 and dV_bf16 must all be non-NULL"); return NATS_ERR_NULL; }
+    RoundedGrads rounded;
+    rounded.dQ = dQ_bf16;
+    rounded.dK = dK_bf16;
+    rounded.dV = dV_bf16;
+    return run_bwd(p, Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha, dbeta, extra, rounded, workspace, workspace_bytes, hip_stream);
 }
 
 nats_status nats_hybrid_attn_fwd(const nats_fwd_params* p, const void* Q, const void* K, const void* V,

@@ -728,6 +728,9 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
     }
 }
 
+__device__ __forceinline__ void store_rounded(bf16_t* p, const float (&x)[2]) { *reinterpret_cast<uint32_t*>(p) = pack_bf16x2(x[0], x[1]); }
+__device__ __forceinline__ void store_rounded(bf16_t* p, const float (&x)[1]) { p->bits = (uint16_t)pack_bf16x2(x[0], 0.f); }
+
 // ---- the gradients of a chunk -------------------------------------------------------------------------------------------
 // One block per (chunk, batch*head), 4 wavefronts; wavefront w owns a quarter of the columns of dQ and dK (all 64 rows)
 // and of the three products with the states that feed them.  Every element of S0 and dS1 is then the operand of one
@@ -748,6 +751,7 @@ struct GradArgs {
     const float *ck, *dck, *Uh, *dR, *dot;
     float *dQ, *dK, *dalpha, *dbeta, *g_nla;
     float* dscore_la;   // optional, routing per chunk: Eq. 17 per chunk
+    bf16_t *dQb, *dKb, *dVb;   // ROUNDED: the results rounded to bf16 instead (dKb, dVb optional; dQ then holds the softmax branch's share)
     int L, BH, G;       // BH: output heads; the G of a group share Q, K, alpha, the mask and the operands
     float la_scale;
     int delta, freeze_on_softmax, chunk_mask;
@@ -765,7 +769,10 @@ struct GradLds {
     static constexpr int blocks = 2 * bytes <= 160 * 1024 ? 2 : 1;   // per CU
 };
 
-template <typename T, typename TO, int D>
+// ROUNDED: dQ (and, where nothing is added to them later but whole rows, dK and dV) go out as bf16, for a caller whose tensors are:
+// a cast behind the pass reads the fp32 gradient once more and writes it a second time (three of 134 MB at the size
+// above: 109 us).
+template <typename T, typename TO, int D, bool ROUNDED>
 __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_grads_kernel(const GradArgs<T, TO> a) {
     using LY = GradLds<T, TO, D>;
     constexpr int NT = terms_of<T>(), NO = terms_of<TO>(), NCT = D / 64, KS = D / 32, MS = CB_MS, NPC = D / 32;
@@ -846,6 +853,14 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
     // ---- stage 1: dO S0 and dR S0, with dO and dR in LDS together where dO is one term ------------------------------
     constexpr bool together = NO == 1;
     put_rows(Ot, dOr);
+    if (ROUNDED && a.dVb != nullptr) {   // dV = dR
+#pragma unroll
+        for (int p = 0; p < NPC; ++p) {
+            float x[8];
+            Rr[p].floats(x);
+            Vec16<bf16_t>::store(a.dVb + tok0 * D + 8 * (tid + 256 * p), x);
+        }
+    }
     if (together) put_rows(Rt, Rr);
     s_g2[tid] = gate_in;   // s_g2, s_gam, s_kd, s_bp lie one behind the other
     if (w == 0) s_g2l[lane] = g2l_in;
@@ -1110,9 +1125,22 @@ __global__ __launch_bounds__(256, (GradLds<T, TO, D>::blocks)) void gdn_chunk_gr
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const size_t off = (tok0 + 16 * ta + 4 * lq + j) * D + col0;
+            if constexpr (ROUNDED) {
+                float q[NCT], k[NCT];
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    q[ct] = oldq[ta][j][ct] + dQa[ta][ct][j];
+                    k[ct] = dKa[ta][ct][j];
+                }
+                store_rounded(a.dQb + off, q);
+                if (a.dKb != nullptr) {
+                    store_rounded(a.dKb + off, k);
+                    continue;
+                }
+            }
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
-                a.dQ[off + ct] = oldq[ta][j][ct] + dQa[ta][ct][j];
+                if (!ROUNDED) a.dQ[off + ct] = oldq[ta][j][ct] + dQa[ta][ct][j];
                 a.dK[off + ct] = dKa[ta][ct][j];
             }
         }
@@ -1402,7 +1430,10 @@ nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const
 
 template <typename T, typename TO, int D>
 static bool launch_grads_t(const FwdPlan& pl, const GradArgs<T, TO>& a, hipStream_t st) {
-    auto kern = gdn_chunk_grads_kernel<T, TO, D>;
+    auto kern = gdn_chunk_grads_kernel<T, TO, D, false>;
+    if constexpr (sizeof(T) == 2) {
+        if (a.dQb != nullptr) kern = gdn_chunk_grads_kernel<T, TO, D, true>;
+    }
     constexpr size_t lds = GradLds<T, TO, D>::bytes;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
@@ -1412,15 +1443,18 @@ static bool launch_grads_t(const FwdPlan& pl, const GradArgs<T, TO>& a, hipStrea
 
 // dQ += the linear branch's share; dK, dalpha, dbeta = it; g_nla (optional) cleared.  ck, dck: the states and state
 // gradients per chunk; Uh, dR (= the linear branch's dV) [BHG][L][d], and so everything written; dot as launch_gdn_chunk_state_grads left it.  dO_f32: dO is fp32 whatever the tensors' type.
+// rounded (bf16 tensors): dQ goes there instead, and dK and dV (= dR) where given
 nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
                                    const float* alpha, const uint8_t* mask, float* ops, const float* ck, const float* dck,
                                    const float* Uh, const float* dR, const float* dot, float* dQ, float* dK,
-                                   float* dalpha, float* dbeta, float* g_nla, float* dscore_la, hipStream_t st) {
+                                   float* dalpha, float* dbeta, float* g_nla, float* dscore_la, const RoundedGrads& rounded,
+                                   hipStream_t st) {
     auto go = [&](auto t, auto to) {
         using T = decltype(t);
         using TO = decltype(to);
         const GradArgs<T, TO> a{(const T*)Q, (const T*)K, (const TO*)dO, chunk_ops(pl, ops), alpha, mask, ck, dck,
-                                Uh, dR, dot, dQ, dK, dalpha, dbeta, g_nla, dscore_la, pl.L, pl.BHG, pl.G, pl.la_scale,
+                                Uh, dR, dot, dQ, dK, dalpha, dbeta, g_nla, dscore_la, (bf16_t*)rounded.dQ, (bf16_t*)rounded.dK,
+                                (bf16_t*)rounded.dV, pl.L, pl.BHG, pl.G, pl.la_scale,
                                 pl.linear_op == 0, pl.freeze_on_softmax, pl.routing == NATS_ROUTE_CHUNK};
         return pl.d == 64 ? launch_grads_t<T, TO, 64>(pl, a, st) : launch_grads_t<T, TO, 128>(pl, a, st);
     };

@@ -53,7 +53,8 @@ __global__ __launch_bounds__(HG_THREADS) void sum_groups_kernel(const GroupSums 
                 const float4 y = p[g * row];
                 x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
             }
-            reinterpret_cast<float4*>(s.sum)[e] = x;
+            if (s.rounded != nullptr) reinterpret_cast<uint2*>(s.rounded)[e] = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
+            else reinterpret_cast<float4*>(s.sum)[e] = x;
         }
     } else {   // a row per chunk, of any number of chunks
         const size_t n = s.row * a.BH;
@@ -63,6 +64,19 @@ __global__ __launch_bounds__(HG_THREADS) void sum_groups_kernel(const GroupSums 
             for (int g = 1; g < a.G; ++g) x += p[g * s.row];
             s.sum[e] = x;
         }
+    }
+}
+
+constexpr int MAX_ROUNDINGS = 3;
+struct Roundings {
+    Rounding r[MAX_ROUNDINGS];
+};
+__global__ __launch_bounds__(HG_THREADS) void round_bf16_kernel(const Roundings a) {
+    const Rounding r = a.r[blockIdx.y];
+    const size_t n = r.n / 4;
+    for (size_t e = (size_t)blockIdx.x * HG_THREADS + threadIdx.x; e < n; e += (size_t)gridDim.x * HG_THREADS) {
+        const float4 x = reinterpret_cast<const float4*>(r.src)[e];
+        reinterpret_cast<uint2*>(r.dst)[e] = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
     }
 }
 
@@ -123,6 +137,21 @@ nats_status launch_sum_groups(int BH, int G, const GroupSum* sums, int n, hipStr
     if (m == 0 || most == 0) return NATS_OK;
     hipLaunchKernelGGL(sum_groups_kernel, dim3(hg_grid(most * BH / 4), m), dim3(HG_THREADS), 0, st, a);
     return check_launch("sum_groups");
+}
+
+nats_status launch_round_bf16(const Rounding* r, int n, hipStream_t st) {
+    Roundings a;
+    int m = 0;
+    size_t most = 0;
+    for (int i = 0; i < n; ++i) {
+        if (r[i].dst == nullptr || r[i].n == 0) continue;
+        if (m == MAX_ROUNDINGS || r[i].n % 4 != 0) { set_error("round_bf16: too many arrays, or not of a multiple of four"); return NATS_ERR_SHAPE; }
+        a.r[m++] = r[i];
+        if (r[i].n > most) most = r[i].n;
+    }
+    if (m == 0) return NATS_OK;
+    hipLaunchKernelGGL(round_bf16_kernel, dim3(hg_grid(most / 4), m), dim3(HG_THREADS), 0, st, a);
+    return check_launch("round_bf16");
 }
 
 nats_status launch_zero_f32(float* dst, size_t n, hipStream_t st) {

@@ -259,13 +259,17 @@ nats_status launch_decode_commit(const nats_dec_params& p, float* state, const f
                                  const uint8_t* mask_c, int32_t* err_flags, hipStream_t st);
 
 // ---- backward pass (gradients to fp32 accuracy) ----
+// where the gradients of Q, K, V go rounded to bf16, each optional
+struct RoundedGrads {
+    void *dQ = nullptr, *dK = nullptr, *dV = nullptr;
+};
 nats_status launch_softmax_bwd_dq(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* K, const void* V,
                                   const void* dO, bool dO_f32, const int32_t* vis, const float* O_nla, const float* lse,
                                   float* Dvec, float* dQ, hipStream_t st);
 nats_status launch_softmax_bwd_dkv(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* dO, bool dO_f32,
                                    const int32_t* vis, const int32_t* idx, const int32_t* n_s, const float* lse,
                                    const float* Dvec, float* dK, float* dV, float* g_nla, float* dk_part, float* dv_part,
-                                   float* g_part, hipStream_t st);
+                                   float* g_part, const RoundedGrads& rounded, hipStream_t st);
 nats_status launch_gdn_recurrent_bwd(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* dO,
                                      const float* alpha, const float* beta, const uint8_t* mask, const float* ckpt,
                                      float* scratch, float* dq_part, float* dk_part, float* dalpha_part,
@@ -286,17 +290,27 @@ nats_status launch_gdn_chunk_state_grads(const FwdPlan& pl, const void* Q, const
 nats_status launch_gdn_chunk_grads(const FwdPlan& pl, const void* Q, const void* K, const void* dO, bool dO_f32,
                                    const float* alpha, const uint8_t* mask, float* ops, const float* ck, const float* dck,
                                    const float* Uh, const float* dR, const float* dot, float* dQ, float* dK,
-                                   float* dalpha, float* dbeta, float* g_nla, float* dscore_la, hipStream_t st);
+                                   float* dalpha, float* dbeta, float* g_nla, float* dscore_la, const RoundedGrads& rounded,
+                                   hipStream_t st);
 nats_status launch_visible_rows(const FwdPlan& pl, const int32_t* cnt, int32_t* vis, hipStream_t st);
 nats_status launch_softmax_bwd_own_chunk(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* dO,
                                          bool dO_f32, const float* lse, const float* Dvec, float* dK, float* dV, hipStream_t st);
 // head grouping in the backward pass (head_group.hip)
-// part: [BH G][row] -> sum: [BH][row], the G shares of a group in order (NULL sum: skipped); row in floats
+// part: [BH G][row] -> sum: [BH][row], the G shares of a group in order (NULL sum: skipped); row in floats.  rounded: where
+// the sum goes as bf16 instead (rows of a multiple of four)
 struct GroupSum {
     const float* part;
     float* sum;
     size_t row;
+    void* rounded = nullptr;
 };
+// up to three fp32 arrays -> bf16, in one launch (n a multiple of 4, 16-byte aligned)
+struct Rounding {
+    const float* src;
+    void* dst;
+    size_t n;
+};
+nats_status launch_round_bf16(const Rounding* r, int n, hipStream_t st);
 nats_status launch_sum_groups(int BH, int G, const GroupSum* sums, int n, hipStream_t st);
 nats_status launch_copy_rows(const void* src, size_t src_stride_bytes, void* dst, size_t dst_stride_bytes,
                              size_t row_bytes, size_t n_rows, hipStream_t st);

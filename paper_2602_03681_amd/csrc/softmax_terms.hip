@@ -628,11 +628,13 @@ __global__ __launch_bounds__(256, (DkvLds<T, TO, D>::blocks)) void softmax_terms
 
 // Adds the segments' shares of a compacted key up, in order, and writes the rows of dK, dV (and g_nla) of the
 // token the key was gathered from (its linear-branch gradient is zero).  One thread per key and 4 columns.
+// dKb, dVb (both or neither; not with accumulate): the rows go there as bf16 instead.
 template <int D>
 __global__ __launch_bounds__(256) void softmax_bwd_dkv_combine_kernel(
     const float* __restrict__ dk_part, const float* __restrict__ dv_part, const float* __restrict__ g_part,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ n_s, float* __restrict__ dK, float* __restrict__ dV,
-    float* __restrict__ g_nla, int L, int G, int n_seg, float scale, int accumulate) {
+    float* __restrict__ g_nla, bf16_t* __restrict__ dKb, bf16_t* __restrict__ dVb, int L, int G, int n_seg, float scale,
+    int accumulate) {
     constexpr int TPK = D / 4;                 // threads per key
     const int bh = blockIdx.y, c = blockIdx.x * (256 / TPK) + threadIdx.x / TPK, col = (threadIdx.x % TPK) * 4;
     if (c >= n_s[bh / G]) return;
@@ -649,7 +651,10 @@ __global__ __launch_bounds__(256) void softmax_bwd_dkv_combine_kernel(
         g += g_part[row];
     }
     const size_t dst = (tokb + t) * D + col;
-    if (accumulate) {   // routing per chunk: the token's rows already hold its shares from inside its chunk
+    if (dKb != nullptr) {
+        *reinterpret_cast<uint2*>(dKb + dst) = make_uint2(pack_bf16x2(scale * k.x, scale * k.y), pack_bf16x2(scale * k.z, scale * k.w));
+        *reinterpret_cast<uint2*>(dVb + dst) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+    } else if (accumulate) {   // routing per chunk: the token's rows already hold its shares from inside its chunk
         const float4 k0 = *reinterpret_cast<const float4*>(dK + dst), v0 = *reinterpret_cast<const float4*>(dV + dst);
         *reinterpret_cast<float4*>(dK + dst) = make_float4(k0.x + scale * k.x, k0.y + scale * k.y, k0.z + scale * k.z, k0.w + scale * k.w);
         *reinterpret_cast<float4*>(dV + dst) = make_float4(v0.x + v.x, v0.y + v.y, v0.z + v.z, v0.w + v.w);
@@ -758,11 +763,11 @@ static bool launch_dkv(const FwdPlan& pl, const void* Q, const void* K, const vo
 }
 
 // the rows idx[c] of dK, dV [BHG,L,d] f32 (and of g_nla [BHG,L], optional) are overwritten (routing per chunk: added to);
-// other rows are left alone.  dk_part, dv_part: BWD_DKV_SEGMENTS * BHG * L * d floats, g_part: BWD_DKV_SEGMENTS * BHG * L (scratch)
+// other rows are left alone.  rounded (dK and dV, or neither; routing per token): they go there instead.  dk_part, dv_part: BWD_DKV_SEGMENTS * BHG * L * d floats, g_part: BWD_DKV_SEGMENTS * BHG * L (scratch)
 nats_status launch_softmax_bwd_dkv(const FwdPlan& pl, const void* Q, const void* Kc, const void* Vc, const void* dO, bool dO_f32,
                                    const int32_t* vis, const int32_t* idx, const int32_t* n_s, const float* lse,
                                    const float* Dvec, float* dK, float* dV, float* g_nla, float* dk_part, float* dv_part,
-                                   float* g_part, hipStream_t st) {
+                                   float* g_part, const RoundedGrads& rounded, hipStream_t st) {
     if (!launch_dkv<false>(pl, Q, Kc, Vc, dO, dO_f32, vis, idx, n_s, lse, Dvec, dk_part, dv_part, g_part, st)) {
         set_error("softmax_bwd_dkv: the kernel's LDS size was refused");
         return NATS_ERR_HIP;
@@ -772,11 +777,11 @@ nats_status launch_softmax_bwd_dkv(const FwdPlan& pl, const void* Q, const void*
     if (pl.d == 64) {
         dim3 grid((pl.L + 15) / 16, pl.BHG);   // 256 / (64 / 4) keys per block
         hipLaunchKernelGGL((softmax_bwd_dkv_combine_kernel<64>), grid, dim3(256), 0, st, dk_part, dv_part, g_part, idx, n_s,
-                           dK, dV, g_nla, pl.L, pl.G, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
+                           dK, dV, g_nla, (bf16_t*)rounded.dK, (bf16_t*)rounded.dV, pl.L, pl.G, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
     } else {
         dim3 grid((pl.L + 7) / 8, pl.BHG);     // 256 / (128 / 4) keys per block
         hipLaunchKernelGGL((softmax_bwd_dkv_combine_kernel<128>), grid, dim3(256), 0, st, dk_part, dv_part, g_part, idx, n_s,
-                           dK, dV, g_nla, pl.L, pl.G, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
+                           dK, dV, g_nla, (bf16_t*)rounded.dK, (bf16_t*)rounded.dV, pl.L, pl.G, BWD_DKV_SEGMENTS, pl.softmax_scale, pl.routing == NATS_ROUTE_CHUNK);
     }
     return check_launch("softmax_bwd_dkv_combine");
 }
