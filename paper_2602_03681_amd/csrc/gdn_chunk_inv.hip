@@ -53,7 +53,7 @@ __device__ __forceinline__ int tri_tile(int a, int b) { return ((a * (a + 1)) / 
 // LDS plan (bytes): the K tile (fp16 [64][d+8]) is dead once A and P are complete, and T takes its place.
 template <int D>
 struct InvLds {
-    static constexpr int RS = D + LDS_PAD;
+    static constexpr int RS = D + 8;   // (with LDS_PAD five blocks do not fit a CU)
     static constexpr int tri_bytes = N_TRI * AT_TILE * 4;
     static constexpr int k_bytes = CH * RS * 2;
     static constexpr int r1_bytes = k_bytes > tri_bytes ? k_bytes : tri_bytes;
