@@ -21,7 +21,7 @@
 // Four kinds of kernel: the operands of every chunk (parallel over chunks), the states at the chunk starts (forwards
 // along the sequence), the state gradients (backwards along it), and the gradients of every chunk from those
 // (parallel over chunks).  Columns of V (rows of the state) never mix along the sequence, so the two sequential
-// kernels split every (batch, head) into slices of 16 value columns, one block each.
+// kernels split every (batch, head) into slices of 16 value columns, one or two per block.
 //
 // The operands' and the output's products run on v_mfma_f32_16x16x4_f32 through mac16 (sixteen contraction indices in four
 // instructions), everything else on the bf16 instruction with operands as sums of bf16 terms (softmax_terms.h).
@@ -35,7 +35,7 @@ namespace nats {
 
 constexpr int CB_C = 64;          // chunk
 constexpr int CB_MS = CB_C + 4;   // row stride (floats) of a 64 x 64 operand in LDS
-constexpr int CB_NV = 16;         // value columns per block of the sequential kernels
+constexpr int CB_NV = 16;         // value columns per slice of the sequential kernels
 
 // per chunk: Tm, At, Pm [64][64] f32 row-major;  per token: gam, kd, bp;  per chunk: gamC;  for the gradients, per token:
 // log2 of gamma as the sum of two floats, g2 and g2l
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(256) void gdn_bwd_prep_kernel(const PrepArgs<T> a, 
 }
 
 // ---- the states along the sequence -------------------------------------------------------------------------------------
-// DIR 0: forwards, the state S^T [d_k][16] of the block's 16 value columns; leaves S0 of every chunk (ck) and Uh.
+// DIR 0: forwards, the state S^T [d_k][16] of a slice's 16 value columns; leaves S0 of every chunk (ck) and Uh.
 // DIR 1: backwards, the gradient of that state; leaves dS1 of every chunk (ck), <dS1, S0>, dV and the gradient of the
 // initial state.  Wavefront w owns the chunk's tokens 16 w .. 16 w + 15 in everything that is one
 // row per token, and D / 64 of the state's 16 x 16 tiles.
@@ -344,7 +344,7 @@ struct SeqArgs {
     int delta;                     // 1: delta rule; 0: gated linear attention
 };
 
-// Eight wavefronts: four compute (as above), four only move the next chunks' operands from global memory to LDS and cut
+// Eight wavefronts per slice: four compute (as above), four only move the next chunks' operands from global memory to LDS and cut
 // them into bf16 terms (softmax_terms.h), the products' operands: bf16 tensors are one term, everything else three.  A
 // burst of loads of this size keeps a wavefront at the issue of its memory instructions for about as long as a whole
 // phase of the chunk's products takes, and there is one block per CU with nothing else to fill the time: so the
@@ -362,7 +362,11 @@ struct SeqArgs {
 // the terms they lie in.  On fp32 instructions, with all of that in the chain, at B 2, H 16, L 8192, d 128 bf16: forwards
 // 398 us (3.1 us per chunk), backwards 560; now 245 and 360.  Still a chain of latencies: 393 MB written and 100-300 MB
 // read from HBM would take 100-140 us.
-template <typename T, typename TX, int D, int DIR>
+// NSL 2: two slices per block, with what they share (K, Q, T, P, the vectors) moved once, by all eight moving wavefronts, and two
+// chains on every SIMD, each in the gaps of the other.  In DIR 1 P and T then take turns in one place (T, cut into terms
+// beforehand, is written while K S^T is multiplied) and K has one.  A chunk takes 1.3 (DIR 0) and 1.45 times as long as with one slice,
+// which pays where one slice per block makes a second round of blocks: see launch_seq_t.
+template <typename T, typename TX, int D, int DIR, int NSL>
 struct SeqLds {
     static constexpr int NT = terms_of<T>(), NX = DIR ? terms_of<TX>() : 1;
     using KTile = TermTile<D, NT>;                    // K; (DIR 1) Q
@@ -370,44 +374,47 @@ struct SeqLds {
     using STile = TermTile<D, N_TERMS, CB_NV>;        // the state
     using BTile = TermTile<64, N_TERMS, CB_NV>;       // 16 value columns of a chunk's tokens
     using XTile = TermTile<64, NX, CB_NV>;            // ... of dO as given
-    static constexpr int V_BYTES = ((DIR ? 0 : CB_NV * CB_MS) + 256) * 4;   // gam, kd, bp [64], gamC; (DIR 0) V [16 v][CB_MS]
+    static constexpr int V_BYTES = ((DIR ? 0 : NSL * CB_NV * CB_MS) + 256) * 4;   // gam, kd, bp [64], gamC; (DIR 0) V [16 v][CB_MS]
     static constexpr int n_b = DIR ? 3 : 2;           // DIR 0: R, kd U;  DIR 1: b' dU, -diag(gamma) dR, diag(gamma) dO'
     static constexpr bool turns = DIR == 1 && NT > 1 && D == 128;
-    static constexpr int fixed = (DIR && !turns ? 2 : 1) * MTile::BYTES + 2 * V_BYTES + STile::BYTES + n_b * BTile::BYTES +
-                                 (DIR ? (turns ? 0 : KTile::BYTES) + XTile::BYTES : 0);
+    static constexpr bool m_one = turns || (DIR == 1 && NSL > 1);
+    static constexpr int fixed = (DIR && !m_one ? 2 : 1) * MTile::BYTES + 2 * V_BYTES + NSL * (STile::BYTES + n_b * BTile::BYTES) +
+                                 (DIR ? (turns ? 0 : KTile::BYTES) + NSL * XTile::BYTES : 0);
     static constexpr bool k_one = turns || fixed + 2 * KTile::BYTES > 160 * 1024;
     static constexpr int o_k = 0;
     static constexpr int o_m1 = o_k + (k_one ? 1 : 2) * KTile::BYTES;
-    static constexpr int o_m2 = DIR && !turns ? o_m1 + MTile::BYTES : o_m1;
+    static constexpr int o_m2 = DIR && !m_one ? o_m1 + MTile::BYTES : o_m1;
     static constexpr int o_v = o_m2 + MTile::BYTES;
     static constexpr int o_s = o_v + 2 * V_BYTES;
-    static constexpr int o_b = o_s + STile::BYTES;
-    static constexpr int o_x = o_b + n_b * BTile::BYTES;
-    static constexpr int o_q = turns ? o_k : o_x + XTile::BYTES;
+    static constexpr int o_b = o_s + NSL * STile::BYTES;
+    static constexpr int o_x = o_b + NSL * n_b * BTile::BYTES;
+    static constexpr int o_q = turns ? o_k : o_x + NSL * XTile::BYTES;
     static constexpr int bytes = o_k + fixed + (k_one ? 1 : 2) * KTile::BYTES;
-    static constexpr int sets = NT > 1 && D == 128 ? 1 : 2;
+    static constexpr int sets = (NT > 1 && D == 128) || (DIR == 1 && NSL > 1) ? 1 : 2;
 };
 
-template <typename T, typename TX, int D, int DIR>
-__global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX> a) {
-    using LY = SeqLds<T, TX, D, DIR>;
-    constexpr int NT = LY::NT, NX = LY::NX, KT = D / 64, MS = CB_MS, NPC = 64 * D / 8 / 256, NS = LY::sets;
+template <typename T, typename TX, int D, int DIR, int NSL>
+__global__ __launch_bounds__(512 * NSL) void gdn_chunk_seq_kernel(const SeqArgs<T, TX> a) {
+    using LY = SeqLds<T, TX, D, DIR, NSL>;
+    constexpr int NT = LY::NT, NX = LY::NX, KT = D / 64, MS = CB_MS, NS = LY::sets;
+    constexpr int LT = 256 * NSL, NPC = 64 * D / 8 / LT, NPM = 64 * 64 / 8 / LT;   // threads that move; 8-element pieces of K and of T per thread
     extern __shared__ __align__(16) float cb_smem[];
     unsigned char* lds = reinterpret_cast<unsigned char*>(cb_smem);
     auto at = [&](int off) { return reinterpret_cast<uint16_t*>(lds + off); };
     auto Kt = [&](int i) { return typename LY::KTile{at(LY::o_k + (LY::k_one ? 0 : i) * LY::KTile::BYTES)}; };
     const typename LY::MTile Tt{at(LY::o_m1)}, Pt{at(LY::o_m2)};
     auto Gf = [&](int i) { return reinterpret_cast<float*>(lds + LY::o_v + i * LY::V_BYTES); };   // gam, kd, bp, gamC
-    auto Xf = [&](int i) { return Gf(i) + 256; };                                                 // DIR 0: V [16 v][MS]
-    const typename LY::STile St{at(LY::o_s)};
-    const typename LY::BTile B0{at(LY::o_b)}, B1{at(LY::o_b + LY::BTile::BYTES)}, B2{at(LY::o_b + 2 * LY::BTile::BYTES)};
-    const typename LY::KTile Qt{at(LY::o_q)};   // DIR 1
-    const typename LY::XTile Xt{at(LY::o_x)};   // DIR 1
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool loader = wave >= 4;
-    const int w = wave & 3, lt = tid & 255;
+    const bool loader = wave >= 4 * NSL;
+    const int w = wave & 3, lt = tid % LT, sl = NSL > 1 ? (wave >> 2) & (NSL - 1) : 0;   // sl: the wavefront's slice
     const int l16 = lane & 15, lq = lane >> 4;
-    const int bh = blockIdx.x % a.BH, slice = blockIdx.x / a.BH, v0 = CB_NV * slice;
+    const int bh = blockIdx.x % a.BH, slice = NSL * (blockIdx.x / a.BH) + sl, v0 = CB_NV * slice;
+    auto Xf = [&](int i) { return Gf(i) + 256 + sl * CB_NV * MS; };                               // DIR 0: V [16 v][MS]
+    const typename LY::STile St{at(LY::o_s + sl * LY::STile::BYTES)};
+    auto Bt = [&](int i) { return typename LY::BTile{at(LY::o_b + (sl * LY::n_b + i) * LY::BTile::BYTES)}; };
+    const typename LY::BTile B0 = Bt(0), B1 = Bt(1), B2 = Bt(2);
+    const typename LY::KTile Qt{at(LY::o_q)};                              // DIR 1
+    const typename LY::XTile Xt{at(LY::o_x + sl * LY::XTile::BYTES)};      // DIR 1
     const int lin = bh / a.G;   // linear head
     const int L = a.L, n_chunks = L / CB_C;
     const float delta = a.delta ? 1.f : 0.f;
@@ -418,7 +425,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
     if (loader) {
         struct Set {
             Raw8<T> k[NPC], q[DIR ? NPC : 1];
-            Raw8<float> m1[2], m2[DIR ? 2 : 1];
+            Raw8<float> m1[NPM], m2[DIR ? NPM : 1];
             float4 gate4, g4;
             TX x[4];
             float gC;
@@ -429,12 +436,12 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
         auto fetch_k = [&](Set& s, int i) {
             const size_t tok0 = (size_t)lin * L + (size_t)chunk_at(i) * CB_C;
 #pragma unroll
-            for (int p = 0; p < NPC; ++p) s.k[p].load(a.K + tok0 * D + 8 * (lt + 256 * p));   // a chunk's rows are contiguous
+            for (int p = 0; p < NPC; ++p) s.k[p].load(a.K + tok0 * D + 8 * (lt + LT * p));   // a chunk's rows are contiguous
         };
-        auto fetch_m = [&](Raw8<float> (&m)[2], const float* M, int i) {
+        auto fetch_m = [&](Raw8<float> (&m)[NPM], const float* M, int i) {
             M += ((size_t)lin * n_chunks + chunk_at(i)) * (CB_C * CB_C);
 #pragma unroll
-            for (int p = 0; p < 2; ++p) m[p].load(M + 8 * (lt + 256 * p));
+            for (int p = 0; p < NPM; ++p) m[p].load(M + 8 * (lt + LT * p));
         };
         auto fetch = [&](Set& s, int i) {   // all but K where it has one place and T where it takes turns
             const int c = chunk_at(i);
@@ -442,7 +449,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
             if (!LY::k_one) fetch_k(s, i);
             if (DIR) {
 #pragma unroll
-                for (int p = 0; p < NPC; ++p) s.q[p].load(a.Q + tok0 * D + 8 * (lt + 256 * p));
+                for (int p = 0; p < NPC; ++p) s.q[p].load(a.Q + tok0 * D + 8 * (lt + LT * p));
             }
             if (lt < 48) s.gate4 = ld4((lt < 16 ? a.o.gam : lt < 32 ? a.o.kd : a.o.bp) + tok0 + 4 * (lt & 15));
             if (lt == 48) s.gC = a.o.gamC[gc];
@@ -451,12 +458,12 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
 #pragma unroll
             for (int j = 0; j < 4; ++j) s.x[j] = a.X[(t4 + j) * D + v0 + l16];
             if constexpr (DIR) fetch_m(s.m2, a.o.Pm, i);
-            if (!LY::turns) fetch_m(s.m1, a.o.Tm, i);
+            if (!LY::m_one) fetch_m(s.m1, a.o.Tm, i);
         };
         auto put_k = [&](const typename LY::KTile& dst, const auto& r) {
 #pragma unroll
             for (int p = 0; p < NPC; ++p) {
-                const int e = 8 * (lt + 256 * p);
+                const int e = 8 * (lt + LT * p);
                 u32x4 t[NT];
                 r[p].terms(t);
                 dst.put(e / D, e % D, t);
@@ -464,8 +471,8 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
         };
         auto put_m = [&](const typename LY::MTile& dst, const auto& r) {
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int e = 8 * (lt + 256 * p);
+            for (int p = 0; p < NPM; ++p) {
+                const int e = 8 * (lt + LT * p);
                 u32x4 t[N_TERMS];
                 r[p].terms(t);
                 dst.put(e / 64, e % 64, t);
@@ -480,8 +487,8 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
                     make_float4(to_float(s.x[0]), to_float(s.x[1]), to_float(s.x[2]), to_float(s.x[3]));
         };
         // the state of chunk ci, in whole rows: 8 columns per thread, put together from their terms
-        const int sv = lt / (D / 8), sk = 8 * (lt % (D / 8));
-        const bool has_state = lt < CB_NV * D / 8;   // uniform
+        const int ls = lt & 255, sv = ls / (D / 8), sk = 8 * (ls % (D / 8));
+        const bool has_state = ls < CB_NV * D / 8;   // uniform
         auto state_at = [&](int i) { return (((size_t)bh * n_chunks + chunk_at(i)) * D + v0 + (has_state ? sv : 0)) * D + sk; };
         Raw8<float> s0[DIR ? NS : 1];                // DIR 1: the same elements of S0
         auto store_state = [&](const Raw8<float>& s0r, int ci) {
@@ -528,7 +535,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
         for (int i = 0; i < NS; ++i) {
             fetch(set[i], i);
             if (LY::k_one) fetch_k(set[i], i);
-            if (LY::turns) fetch_m(set[i].m1, a.o.Tm, i);
+            if (LY::m_one) fetch_m(set[i].m1, a.o.Tm, i);
             if constexpr (DIR == 1) s0[i].load(a.S0 + state_at(i));
         }
         put_k(LY::turns ? Qt : Kt(0), LY::turns ? set[0].q : set[0].k);
@@ -537,7 +544,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
             put_first(set[0]);
             put_m(Pt, set[0].m2);
         }
-        if (!LY::turns) put_m(Tt, set[0].m1);
+        if (!LY::m_one) put_m(Tt, set[0].m1);
         fetch(set[0], NS);
         if (LY::k_one && !LY::turns) fetch_k(set[0], NS);
         __syncthreads();
@@ -552,7 +559,22 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
             } else {
                 store_state(s0[0], ci);
             }
+            u32x4 tm[LY::m_one && !LY::turns ? NPM : 1][N_TERMS];
+            if constexpr (LY::m_one && !LY::turns) {   // chunk ci's T, cut here so that only its writes stand between two barriers
+                auto& m = set[(S + NS - 1) % NS].m1;
+#pragma unroll
+                for (int p = 0; p < NPM; ++p) m[p].terms(tm[p]);
+                fetch_m(m, a.o.Tm, ci + NS);
+            }
             __syncthreads();
+            if constexpr (LY::m_one && !LY::turns) {   // in P's place
+#pragma unroll
+                for (int p = 0; p < NPM; ++p) {
+                    const int e = 8 * (lt + LT * p);
+                    Tt.put(e / 64, e % 64, tm[p]);
+                }
+                __syncthreads();
+            }
             if (LY::turns) {   // chunk ci's K in Q's place, T in P's
                 put_k(Kt(0), s.k);
                 put_m(Tt, s.m1);
@@ -563,10 +585,10 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
             if constexpr (DIR == 1) put_first(s);
             put_vectors(s, nb);
             if (!LY::k_one) put_k(Kt(nb), s.k);
-            if constexpr (DIR == 1 && !LY::turns) put_m(Pt, s.m2);
+            if constexpr (DIR == 1 && !LY::m_one) put_m(Pt, s.m2);
             __syncthreads();
             if (LY::turns) __syncthreads();
-            if constexpr (LY::turns) put_m(Pt, s.m2);
+            if constexpr (LY::m_one) put_m(Pt, s.m2);
             else put_m(Tt, s.m1);
             if (!LY::turns) fetch(s, ci + 1 + NS);
             __syncthreads();
@@ -652,6 +674,9 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
             beside();
             __syncthreads();
             __syncthreads();   // K and T take Q's and P's places
+        } else if (LY::m_one) {
+            beside();
+            __syncthreads();   // T takes P's place
         }
         // ---- 1: the state seen by the wavefront's tokens: K_w S^T --------------------------------------------
         {
@@ -670,7 +695,7 @@ __global__ __launch_bounds__(512) void gdn_chunk_seq_kernel(const SeqArgs<T, TX>
 #pragma unroll
                 for (int j = 0; j < 4; ++j) y[j] = xv[j] - delta * gg[j] * acc0[j];
             } else {   // dU = P^T dO' + diag(kd) K dS1^T
-                if (!LY::turns) beside();
+                if (!LY::m_one) beside();
 #pragma unroll
                 for (int j = 0; j < 4; ++j) y[j] = bb[j] * (kk[j] * acc0[j] + a.la_scale * accP[j]);
             }
@@ -1355,15 +1380,27 @@ nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K,
     return check_launch("gdn_bwd_prep");
 }
 
-template <typename T, typename TX, int D, int DIR>
-static bool launch_seq_t(const SeqArgs<T, TX>& a, hipStream_t st) {
-    auto kern = gdn_chunk_seq_kernel<T, TX, D, DIR>;
-    constexpr size_t lds = SeqLds<T, TX, D, DIR>::bytes;
+template <typename T, typename TX, int D, int DIR, int NSL>
+static bool launch_seq_s(const SeqArgs<T, TX>& a, hipStream_t st) {
+    auto kern = gdn_chunk_seq_kernel<T, TX, D, DIR, NSL>;
+    constexpr size_t lds = SeqLds<T, TX, D, DIR, NSL>::bytes;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * (D / CB_NV))), dim3(512), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * (D / CB_NV / NSL))), dim3(512 * NSL), lds, st, a);
     return true;
+}
+template <typename T, typename TX, int D, int DIR>
+static bool launch_seq_t(const SeqArgs<T, TX>& a, hipStream_t st) {
+    // A block takes a CU to itself.  One slice per block up to one block per CU; beyond, where it would take another round, two (n
+    // against n / 2 blocks, never as many rounds).  Forwards / backwards in us, one slice -> two, d 128: 36 heads, L 2048
+    // 105 / 172 -> 75 / 128; 48 heads, L 4096 237 / 381 -> 167 / 278; 80 heads, L 2048 172 / 278 -> 149 / 257; 128 heads, L 2048
+    // 249 / 402 -> 175 / 293; d 64: 72 heads, L 2048 87 / 132 -> 60 / 98; 256 heads, L 2048 331 / 521 -> 189 / 278.  (32 heads,
+    // L 2048, one round either way: 63 / 95 with one.)  fp32 tensors, three terms each, leave no room for a second slice.
+    if constexpr (sizeof(T) == 2) {
+        if (a.BH * (D / CB_NV) > 256) return launch_seq_s<T, TX, D, DIR, 2>(a, st);
+    }
+    return launch_seq_s<T, TX, D, DIR, 1>(a, st);
 }
 template <int DIR, typename T, typename TX>
 static bool launch_seq_d(const FwdPlan& pl, const SeqArgs<T, TX>& a, hipStream_t st) {
