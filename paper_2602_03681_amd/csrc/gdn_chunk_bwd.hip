@@ -344,7 +344,7 @@ struct SeqArgs {
     int delta;                     // 1: delta rule; 0: gated linear attention
 };
 
-// Eight wavefronts per slice: four compute (as above), four only move the next chunks' operands from global memory to LDS and cut
+// Eight wavefronts per slice (fp32 tensors: twelve): four compute (as above), four only move the next chunks' operands from global memory to LDS and cut
 // them into bf16 terms (softmax_terms.h), the products' operands: bf16 tensors are one term, everything else three.  A
 // burst of loads of this size keeps a wavefront at the issue of its memory instructions for about as long as a whole
 // phase of the chunk's products takes, and there is one block per CU with nothing else to fill the time: so the
@@ -362,6 +362,9 @@ struct SeqArgs {
 // the terms they lie in.  On fp32 instructions, with all of that in the chain, at B 2, H 16, L 8192, d 128 bf16: forwards
 // 398 us (3.1 us per chunk), backwards 560; now 245 and 360.  Still a chain of latencies: 393 MB written and 100-300 MB
 // read from HBM would take 100-140 us.
+// With fp32 tensors, whose K and Q are cut into three terms too, eight wavefronts move for one slice: forwards / backwards in us with
+// four -> eight, d 64: 6 heads, L 704 19.0 / 35.2 -> 17.9 / 30.4; 64 heads, L 2048 61 / 111 -> 60 / 104; d 128: 8 heads, L 2048
+// 83.6 / 141 -> 69.7 / 115; 32 heads, L 2048 95 / 159 -> 89 / 144.  (bf16, 32 heads, L 8192, d 128: 243 / 362 -> 258 / 368.)
 // NSL 2: two slices per block, with what they share (K, Q, T, P, the vectors) moved once, by all eight moving wavefronts, and two
 // chains on every SIMD, each in the gaps of the other.  In DIR 1 P and T then take turns in one place (T, cut into terms
 // beforehand, is written while K S^T is multiplied) and K has one.  A chunk takes 1.3 (DIR 0) and 1.45 times as long as with one slice,
@@ -390,14 +393,15 @@ struct SeqLds {
     static constexpr int o_x = o_b + NSL * n_b * BTile::BYTES;
     static constexpr int o_q = turns ? o_k : o_x + NSL * XTile::BYTES;
     static constexpr int bytes = o_k + fixed + (k_one ? 1 : 2) * KTile::BYTES;
+    static constexpr int move = NSL > 1 || NT > 1 ? 512 : 256;   // threads that move
     static constexpr int sets = (NT > 1 && D == 128) || (DIR == 1 && NSL > 1) ? 1 : 2;
 };
 
 template <typename T, typename TX, int D, int DIR, int NSL>
-__global__ __launch_bounds__(512 * NSL) void gdn_chunk_seq_kernel(const SeqArgs<T, TX> a) {
+__global__ __launch_bounds__((256 * NSL + SeqLds<T, TX, D, DIR, NSL>::move)) void gdn_chunk_seq_kernel(const SeqArgs<T, TX> a) {
     using LY = SeqLds<T, TX, D, DIR, NSL>;
     constexpr int NT = LY::NT, NX = LY::NX, KT = D / 64, MS = CB_MS, NS = LY::sets;
-    constexpr int LT = 256 * NSL, NPC = 64 * D / 8 / LT, NPM = 64 * 64 / 8 / LT;   // threads that move; 8-element pieces of K and of T per thread
+    constexpr int LT = LY::move, NPC = 64 * D / 8 / LT, NPM = 64 * 64 / 8 / LT;   // threads that move; 8-element pieces of K and of T per thread
     extern __shared__ __align__(16) float cb_smem[];
     unsigned char* lds = reinterpret_cast<unsigned char*>(cb_smem);
     auto at = [&](int off) { return reinterpret_cast<uint16_t*>(lds + off); };
@@ -406,7 +410,7 @@ __global__ __launch_bounds__(512 * NSL) void gdn_chunk_seq_kernel(const SeqArgs<
     auto Gf = [&](int i) { return reinterpret_cast<float*>(lds + LY::o_v + i * LY::V_BYTES); };   // gam, kd, bp, gamC
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool loader = wave >= 4 * NSL;
-    const int w = wave & 3, lt = tid % LT, sl = NSL > 1 ? (wave >> 2) & (NSL - 1) : 0;   // sl: the wavefront's slice
+    const int w = wave & 3, lt = (LT > 256 * NSL ? tid - 256 * NSL : tid) & (LT - 1), sl = NSL > 1 ? (wave >> 2) & (NSL - 1) : 0;   // sl: the wavefront's slice
     const int l16 = lane & 15, lq = lane >> 4;
     const int bh = blockIdx.x % a.BH, slice = NSL * (blockIdx.x / a.BH) + sl, v0 = CB_NV * slice;
     auto Xf = [&](int i) { return Gf(i) + 256 + sl * CB_NV * MS; };                               // DIR 0: V [16 v][MS]
@@ -478,17 +482,18 @@ __global__ __launch_bounds__(512 * NSL) void gdn_chunk_seq_kernel(const SeqArgs<
                 dst.put(e / 64, e % 64, t);
             }
         };
+        const int ls = lt & 255, sv = ls / (D / 8), sk = 8 * (ls % (D / 8));
+        const bool half = LT > 256 * NSL && wave >= 8;   // twice the wavefronts per slice: half of them store the state, the others cut X
+        const bool has_state = !half && ls < CB_NV * D / 8, has_x = LT == 256 * NSL || half;   // uniform
         auto put_vectors = [&](const Set& s, int nb) {
             float* Gt = Gf(nb);
             if (lt < 48) *reinterpret_cast<float4*>(Gt + 4 * lt) = s.gate4;
             if (lt == 48) Gt[3 * CB_C] = s.gC;
-            if (DIR == 0)
+            if (DIR == 0 && has_x)
                 *reinterpret_cast<float4*>(Xf(nb) + l16 * MS + 16 * w + 4 * lq) =
                     make_float4(to_float(s.x[0]), to_float(s.x[1]), to_float(s.x[2]), to_float(s.x[3]));
         };
         // the state of chunk ci, in whole rows: 8 columns per thread, put together from their terms
-        const int ls = lt & 255, sv = ls / (D / 8), sk = 8 * (ls % (D / 8));
-        const bool has_state = ls < CB_NV * D / 8;   // uniform
         auto state_at = [&](int i) { return (((size_t)bh * n_chunks + chunk_at(i)) * D + v0 + (has_state ? sv : 0)) * D + sk; };
         Raw8<float> s0[DIR ? NS : 1];                // DIR 1: the same elements of S0
         auto store_state = [&](const Raw8<float>& s0r, int ci) {
@@ -515,6 +520,7 @@ __global__ __launch_bounds__(512 * NSL) void gdn_chunk_seq_kernel(const SeqArgs<
         };
         auto put_first = [&](const Set& s) {   // DIR 1: what the first phase alone reads
             if (!LY::turns) put_k(Qt, s.q);
+            if (!has_x) return;
             const float gg[4] = {s.g4.x, s.g4.y, s.g4.z, s.g4.w};
             float x[4], y[4];
 #pragma unroll
@@ -1387,7 +1393,7 @@ static bool launch_seq_s(const SeqArgs<T, TX>& a, hipStream_t st) {
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) return false;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * (D / CB_NV / NSL))), dim3(512 * NSL), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * (D / CB_NV / NSL))), dim3(256 * NSL + SeqLds<T, TX, D, DIR, NSL>::move), lds, st, a);
     return true;
 }
 template <typename T, typename TX, int D, int DIR>
