@@ -198,6 +198,12 @@ nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, con
                                     const float* alpha, const float* beta, const uint8_t* mask, void* O,
                                     const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
                                     void* hip_stream);
+/* Same, and every row of extra->Kc, Vc up to cap is written: those behind a head's softmax tokens are zeros (the call
+ * above leaves them as they are). */
+nats_status nats_hybrid_attn_fwd_ex_clear(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                                          const float* alpha, const float* beta, const uint8_t* mask, void* O,
+                                          const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
+                                          void* hip_stream);
 
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): nats_hybrid_attn_fwd with the workspace taken from a buffer of NATS_NOALLOC_SCRATCH_BYTES that is

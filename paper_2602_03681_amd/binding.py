@@ -71,7 +71,7 @@ class DecParams(ctypes.Structure):
                 ("workspace", ctypes.c_void_p), ("workspace_bytes", ctypes.c_size_t)]
 
 
-EXPORTS = ("nats_hybrid_attn_fwd_workspace_bytes", "nats_hybrid_attn_fwd", "nats_hybrid_attn_fwd_ex",
+EXPORTS = ("nats_hybrid_attn_fwd_workspace_bytes", "nats_hybrid_attn_fwd", "nats_hybrid_attn_fwd_ex", "nats_hybrid_attn_fwd_ex_clear",
            "nats_hybrid_attn_decode", "nats_last_error", "nats_abi_version", "nats_profile_begin",
            "nats_profile_end", "nats_probe_mfma", "nats_hybrid_attn_decode_chunk",
            "nats_hybrid_attn_decode_commit", "nats_merge_weights", "nats_route_chunks",
@@ -106,6 +106,8 @@ def load_library():
     lib.nats_hybrid_attn_fwd_ex.restype = ctypes.c_int
     lib.nats_hybrid_attn_fwd_ex.argtypes = ([ctypes.POINTER(FwdParams)] + [vp] * 7
                                             + [ctypes.POINTER(FwdExtra), vp, ctypes.c_size_t, vp])
+    lib.nats_hybrid_attn_fwd_ex_clear.restype = ctypes.c_int
+    lib.nats_hybrid_attn_fwd_ex_clear.argtypes = lib.nats_hybrid_attn_fwd_ex.argtypes
     lib.nats_hybrid_attn_decode.restype = ctypes.c_int
     lib.nats_hybrid_attn_decode.argtypes = [ctypes.POINTER(DecParams)] + [vp] * 15
     lib.nats_hybrid_attn_decode_chunk.restype = ctypes.c_int
@@ -239,8 +241,8 @@ def hybrid_attn_fwd_ex(Q, K, V, alpha, beta, mask, C: int = 64, *, softmax_scale
     res: Dict[str, torch.Tensor] = {"O": O}
     if "final_state" in want: res["final_state"] = torch.empty((B, HG, d, d), dtype=torch.float32, device=dev)
     if "Kc" in want:
-        res["Kc"] = torch.zeros((B, HG, cap, d), dtype=dt, device=dev)
-        res["Vc"] = torch.zeros((B, HG, cap, d), dtype=dt, device=dev)
+        res["Kc"] = torch.empty((B, HG, cap, d), dtype=dt, device=dev)
+        res["Vc"] = torch.empty((B, HG, cap, d), dtype=dt, device=dev)
     if "n_s" in want: res["n_s"] = torch.empty((B, H), dtype=torch.int32, device=dev)
     if "idx" in want: res["idx"] = torch.full((B, H, L), -1, dtype=torch.int32, device=dev)
     if "cnt" in want: res["cnt"] = torch.empty((B, H, L), dtype=torch.int32, device=dev)
@@ -254,9 +256,10 @@ def hybrid_attn_fwd_ex(Q, K, V, alpha, beta, mask, C: int = 64, *, softmax_scale
                      g("final_state"), g("Kc"), g("Vc"), cap if "Kc" in want else 0, g("n_s"), g("idx"),
                      g("cnt"), g("O_la"), g("O_nla"), g("lse"), W_out.data_ptr() if W_out is not None else None,
                      Q_nla.data_ptr() if Q_nla is not None else None, K_nla.data_ptr() if K_nla is not None else None)
-    _check(lib.nats_hybrid_attn_fwd_ex(ctypes.byref(params), _ptr(Q), _ptr(K), _ptr(V), _ptr(alpha), _ptr(beta),
-                                       _ptr(mask), _ptr(O), ctypes.byref(extra), _ptr(workspace),
-                                       workspace.numel(), _stream_ptr()))
+    # with Kc, Vc: rows behind a head's softmax tokens come back as zeros
+    call = lib.nats_hybrid_attn_fwd_ex_clear if "Kc" in want else lib.nats_hybrid_attn_fwd_ex
+    _check(call(ctypes.byref(params), _ptr(Q), _ptr(K), _ptr(V), _ptr(alpha), _ptr(beta), _ptr(mask), _ptr(O),
+                ctypes.byref(extra), _ptr(workspace), workspace.numel(), _stream_ptr()))
     return res
 
 

@@ -598,10 +598,9 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
     return st;
 }
 
-nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
-                                    const float* alpha, const float* beta, const uint8_t* mask, void* O,
-                                    const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
-                                    void* hip_stream) {
+static nats_status run_fwd_ex(const nats_fwd_params* p, const void* Q, const void* K, const void* V, const float* alpha, const float* beta,
+                              const uint8_t* mask, void* O, const nats_fwd_extra* extra, bool zero_rest, void* workspace,
+                              size_t workspace_bytes, void* hip_stream) {
     FwdPlan pl;
     const nats_status st = validate_fwd_params(p, &pl);
     if (st != NATS_OK) return st;
@@ -609,7 +608,22 @@ nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, con
     // rounding keeps from the reported one, its parts lie at multiples of 256 bytes, is refused: a mistake that would cost
     // several times the time and no error.)
     if (pl.fp32_chunks && workspace_bytes + 256 <= pl.total) (void)validate_fwd_params(p, &pl, true);
+    pl.zero_rest = zero_rest;
     return run_fwd(pl, Q, K, V, alpha, beta, mask, O, extra, workspace, workspace_bytes, hip_stream);
+}
+
+nats_status nats_hybrid_attn_fwd_ex(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                                    const float* alpha, const float* beta, const uint8_t* mask, void* O,
+                                    const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
+                                    void* hip_stream) {
+    return run_fwd_ex(p, Q, K, V, alpha, beta, mask, O, extra, false, workspace, workspace_bytes, hip_stream);
+}
+
+nats_status nats_hybrid_attn_fwd_ex_clear(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
+                                          const float* alpha, const float* beta, const uint8_t* mask, void* O,
+                                          const nats_fwd_extra* extra, void* workspace, size_t workspace_bytes,
+                                          void* hip_stream) {
+    return run_fwd_ex(p, Q, K, V, alpha, beta, mask, O, extra, true, workspace, workspace_bytes, hip_stream);
 }
 
 size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p) {

@@ -1375,7 +1375,7 @@ nats_status launch_gdn_bwd_prep(const FwdPlan& pl, const void* Q, const void* K,
         const PrepArgs<T> a{(const T*)Q, (const T*)K, alpha, beta, mask, chunk_ops(pl, ops, with_at), pl.L, pl.BH,
                             pl.freeze_on_softmax, pl.linear_op, by_chunk};
         const ScanArgs<T> sc{mask, (const T*)Ks, (const T*)V, pl.L, pl.d, cnt, idx, n_s, (T*)Kc, (T*)Vc, (T*)Kc_user, (T*)Vc_user,
-                             cap_user, (half_t*)Vh, by_chunk ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head};
+                             cap_user, (half_t*)Vh, by_chunk ? (pl.RC == 128 ? 7 : 6) : 0, pl.G, pl.qk_per_out_head, pl.zero_rest};
         if (pl.d == 64) return with_at ? launch_prep_t<T, 64, false>(pl, a, sc, st) : launch_prep_t<T, 64, true>(pl, a, sc, st);
         return with_at ? launch_prep_t<T, 128, false>(pl, a, sc, st) : launch_prep_t<T, 128, true>(pl, a, sc, st);
     };

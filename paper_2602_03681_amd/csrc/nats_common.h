@@ -192,6 +192,7 @@ struct FwdPlan {
     // Q, K, alpha, beta, mask).  BHG = BH * G output heads; qk_per_out_head: the softmax branch's queries and keys
     // are given per output head (otherwise it uses the linear head's)
     int G, BHG, qk_per_out_head;
+    int zero_rest = 0; // clear the rows of the caller's Kc, Vc behind a head's compacted ones
     int inner_chunk;   // routing per chunk: 0 both operations compute a chunk's inner part, 1 softmax attention only, 2 the linear operation only
     int dtype;
     int math;
