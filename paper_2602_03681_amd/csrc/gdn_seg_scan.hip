@@ -795,15 +795,19 @@ int gdn_segments(const FwdPlan& pl) {
 
 // The form of an automatic call: in segments (ns = 0, n_seg of them, at most as many as the workspace has room for) or in one pass
 // with ns slices of 16 value columns per block (gdn_slice_scan.hip), whichever is expected to take less, in us:
-// * one pass: a step per chunk, 1.1 with one slice per block and 1.42 with two (d = 64: 0.87, 1.0);
-// * segments: two passes of a step per chunk of a segment, 3.1 (d = 64: 2.05 and 0.1 per head on an XCD), 1.4 (0.55) per segment
-//   for the fix-up and 4 for two more launches.
+// * one pass: a step per chunk, 1.1 with one slice per block and 1.42 with two (d = 64: 0.87, 1.0), and 2.7 (3.7) before the
+//   first step of every round;
+// * one segment: a step per chunk, 2.3 and 0.035 per head on an XCD (1.2, 0.022), and 2.7 (4.6);
+// * more segments: two passes of a step per chunk of a segment, 3.1 (2.05 and 0.1 per head on an XCD), 1.4 (0.55) per segment
+//   for the fix-up, 4 for two more launches, and 2.7 (3.7).
 // A CU takes one block at a time and the blocks of a head are dealt to one of the eight XCDs, 32 CUs each: more blocks than that on
 // the fullest XCD are another round (18 heads in 12 segments: 33 on two of the XCDs, L 3072, d 128 107.9 us for the whole
 // forward, 84.8 in one pass).  Measured, whole forwards, p 0.05, in segments / in one pass: d 128, 2 heads, L 512 34.2 / 24.9, L 2048
 // 55.9 / 50.0, L 3072 64.7 / 69.2; 18 heads, L 1024 54.5 / 38.7; 32 heads, L 2048 76.0 / 65.2, L 4096 117.0 / 117.4, L 6144
 // 160.7 / 172.8; 48 heads (two slices), L 1024 66.3 / 46.7, L 4096 158.8 / 151.6, L 6144 229 / 241; d 64, 8 heads, L 1536 34.8 /
-// 31.8, L 3072 39.7 / 49.6; 32 heads, L 2048 49.0 / 46.7, L 3072 62.8 / 66.5.
+// 31.8, L 3072 39.7 / 49.6; 32 heads, L 2048 49.0 / 46.7, L 3072 62.8 / 66.5.  Slices in two rounds lose to one segment at every length: d 128,
+// 120 heads, L 256 30.8 / 33.6, L 2048 136 / 138; 96 heads, L 512 45.5 / 48.3, L 4096 285 / 312; d 64, 136 heads, L 256 25.3 / 28.2,
+// L 2048 104 / 116.  80 heads, L 1024, d 128 take one segment (75.1; three 86.4, two slices 77.4), L 2048 three (132.9; 134.0, 134.7).
 struct SegForm {
     int n_seg, ns;
 };
@@ -814,15 +818,16 @@ static SegForm seg_form(const FwdPlan& pl) {
     auto rounds = [](int blocks) { return (blocks + 31) / 32; };
     const bool narrow = pl.d == 64;
     const float seg_step = narrow ? 2.05f + 0.1f * heads : 3.1f, fix = narrow ? 0.55f : 1.4f;
+    const float start = narrow ? 3.7f : 2.7f;
     SegForm best{1, 0};
-    float least = rounds(heads) * n_chunks * seg_step;
+    float least = rounds(heads) * (narrow ? n_chunks * (1.2f + 0.022f * heads) + 4.6f : n_chunks * (2.3f + 0.035f * heads) + start);
     for (int g = 3; g <= cap; ++g) {
-        const float t = 2 * rounds(heads * (g - 1)) * ((n_chunks + g - 1) / g) * seg_step + fix * g + 4.f;
+        const float t = 2 * rounds(heads * (g - 1)) * ((n_chunks + g - 1) / g) * seg_step + fix * g + 4.f + start;
         if (t < least) least = t, best = {g, 0};
     }
     for (int ns = 1; ns <= 2; ++ns) {
         const float step = narrow ? (ns == 1 ? 0.87f : 1.0f) : (ns == 1 ? 1.1f : 1.42f);
-        const float t = rounds(heads * (pl.d / 16 / ns)) * n_chunks * step;
+        const float t = rounds(heads * (pl.d / 16 / ns)) * (n_chunks * step + start);
         if (t < least) least = t, best = {1, ns};
     }
     return best;
