@@ -360,7 +360,7 @@ struct SeqArgs {
 // What leaves the chain for other kernels: U is not stored (b' Uh where it is needed), dbeta and the residuals' part of it
 // come from sums the gradient kernel has anyway, and the states are stored by the moving wavefronts, in whole rows, from
 // the terms they lie in.  On fp32 instructions, with all of that in the chain, at B 2, H 16, L 8192, d 128 bf16: forwards
-// 398 us (3.1 us per chunk), backwards 560; now 245 and 360.  Still a chain of latencies: 393 MB written and 100-300 MB
+// 398 us (3.1 us per chunk), backwards 560; now 243 and 357.  Still a chain of latencies: 393 MB written and 100-300 MB
 // read from HBM would take 100-140 us.
 // With fp32 tensors, whose K and Q are cut into three terms too, eight wavefronts move for one slice: forwards / backwards in us with
 // four -> eight, d 64: 6 heads, L 704 19.0 / 35.2 -> 17.9 / 30.4; 64 heads, L 2048 61 / 111 -> 60 / 104; d 128: 8 heads, L 2048
@@ -372,11 +372,15 @@ struct SeqArgs {
 template <typename T, typename TX, int D, int DIR, int NSL>
 struct SeqLds {
     static constexpr int NT = terms_of<T>(), NX = DIR ? terms_of<TX>() : 1;
-    using KTile = TermTile<D, NT>;                    // K; (DIR 1) Q
-    using MTile = TermTile<64, N_TERMS>;              // T; (DIR 1) P
-    using STile = TermTile<D, N_TERMS, CB_NV>;        // the state
-    using BTile = TermTile<64, N_TERMS, CB_NV>;       // 16 value columns of a chunk's tokens
-    using XTile = TermTile<64, NX, CB_NV>;            // ... of dO as given
+    // Rows of 64: 8 elements longer, not LDS_PAD = 16, but for fp32 tensors and for DIR 0 at d = 128.  16 -> 8 in us: d 64, 3 heads, L 5376
+    // forwards 102 -> 96.5, backwards 156 -> 153.5; d 128, 48 heads, L 4096 backwards 262 -> 250; the others 243 -> 248 (32 heads,
+    // L 8192, d 128 forwards), 18.0 -> 18.4 and 30.2 -> 30.9 (6 heads, L 704, d 64 fp32).
+    static constexpr int P64 = NT > 1 || (DIR == 0 && D == 128) ? LDS_PAD : 8, PD = D == 64 ? P64 : LDS_PAD;
+    using KTile = TermTile<D, NT, 64, PD>;                 // K; (DIR 1) Q
+    using MTile = TermTile<64, N_TERMS, 64, P64>;          // T; (DIR 1) P
+    using STile = TermTile<D, N_TERMS, CB_NV, PD>;         // the state
+    using BTile = TermTile<64, N_TERMS, CB_NV, P64>;       // 16 value columns of a chunk's tokens
+    using XTile = TermTile<64, NX, CB_NV, P64>;            // ... of dO as given
     static constexpr int V_BYTES = ((DIR ? 0 : NSL * CB_NV * CB_MS) + 256) * 4;   // gam, kd, bp [64], gamC; (DIR 0) V [16 v][CB_MS]
     static constexpr int n_b = DIR ? 3 : 2;           // DIR 0: R, kd U;  DIR 1: b' dU, -diag(gamma) dR, diag(gamma) dO'
     static constexpr bool turns = DIR == 1 && NT > 1 && D == 128;

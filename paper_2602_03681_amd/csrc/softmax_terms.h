@@ -123,12 +123,12 @@ __device__ __forceinline__ void split_terms(const float (&x)[4], uint2 (&t)[N_TE
     for (int n = 0; n < N_TERMS; ++n) t[n] = make_uint2(lo[n], hi[n]);
 }
 
-// A tile of 64 rows of D elements in LDS: one plane [64][D + LDS_PAD] of bf16 per term.  Operand of a product over the
+// A tile of 64 rows of D elements in LDS: one plane [64][D + PAD] of bf16 per term.  Operand of a product over the
 // columns: 16-byte reads along a row (rows()).  Operand of a product over the rows: the transposing read of gfx950
 // (cols()), so that no transposed copy is made.
-template <int D, int N, int ROWS = 64>
+template <int D, int N, int ROWS = 64, int PAD = LDS_PAD>
 struct TermTile {
-    static constexpr int RS = D + LDS_PAD, PLANE = ROWS * RS, BYTES = N * PLANE * 2;
+    static constexpr int RS = D + PAD, PLANE = ROWS * RS, BYTES = N * PLANE * 2;
     using Terms = u32x4[N];
     uint16_t* p;
     __device__ __forceinline__ void put(int row, int col, const u32x4 (&t)[N]) const {
