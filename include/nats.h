@@ -110,7 +110,8 @@ typedef struct nats_fwd_params {
     int32_t gdn_segments;  /* bf16 path: segments the sequence of every (batch, head) is cut into, which then
                               run side by side (the recurrence over chunks is affine in the state, so the
                               segments' start states are composed afterwards); 0 chooses automatically
-                              (about 256 / (B*H), at least 4 chunks per segment).  The result does not depend
+                              (about 256 / (B*H), at least 4 chunks per segment; for few chunks one pass with
+                              the value columns split over blocks instead).  The result does not depend
                               on it beyond rounding                                                          */
     int32_t group;         /* head grouping (Section 4.3; the appendix's model sizes use 2 and 3): G = group
                               softmax heads share the mask of one linear head, 0 counts as 1, at most 8.

@@ -51,8 +51,8 @@ constexpr int SC = 64;           // chunk size
 
 template <int D>
 struct SegLds {
-    static constexpr int SS = D + 8;           // (16 more halves per row, as elsewhere: the same within 0.5 %)
-                                               // halves per row of the K, Q tiles [64][SS] and of the output tile
+    static constexpr int SS = D + 8;           // halves per row of the K, Q tiles [64][SS] and of the output tile
+                                               // (D + 16: the same within 0.5 %)
     static constexpr int TS = SC + 8;          // halves per row of K^T [d_k][TS]
     // one operand set (halves)
     static constexpr int o_Kt = 0;

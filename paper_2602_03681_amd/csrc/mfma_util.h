@@ -120,7 +120,8 @@ __device__ __forceinline__ float4 ldbcol(const uint16_t* p, int rs) {
 }
 
 // 16-bit elements added to every LDS row of 64 or 128: rows 8 x odd banks apart.  A wavefront's 16-byte read of 16 rows takes 5.6
-// cycles of the CU's LDS port at 288 bytes per row and 8.0 at 272 (8 elements), transposing reads 5.8 and 5.9.
+// cycles of the CU's LDS port at 288 bytes per row and 8.0 at 272 (8 elements), transposing reads 5.8 and 5.9.  (Rows of 64 in the
+// kernels along the sequence: some are faster with 8, see SeqLds.)
 constexpr int LDS_PAD = 16;
 
 }  // namespace nats
