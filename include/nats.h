@@ -295,7 +295,8 @@ nats_status nats_hybrid_attn_bwd(const nats_fwd_params* p, const void* Q, const 
 
 /* The same for bf16 tensors (p->dtype NATS_BF16), with the gradients of Q, K and V rounded to bf16 (to nearest, from the same fp32
  * sums) in dQ_bf16, dK_bf16 [B,H,L,d] and dV_bf16 [B,H*G,L,d].  dQ, dK, dV are scratch of the same sizes as above, whose contents
- * are undefined afterwards: where the pass can, it writes the rounded gradients from the sums instead of them. */
+ * are undefined afterwards: where the pass can, it writes the rounded gradients from the sums instead of them.  None of these six
+ * may share memory with another of them, with any other array of the call or with the workspace (NATS_ERR_SHAPE). */
 nats_status nats_hybrid_attn_bwd_bf16(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
                                       const float* alpha, const float* beta, const uint8_t* mask, const void* dO,
                                       float* dQ, float* dK, float* dV, float* dalpha, float* dbeta,

@@ -847,6 +847,41 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
 }
 
 
+// With rounded gradients (nats_hybrid_attn_bwd_bf16): the fp32 gradients are read after rows of the rounded ones are written, by other
+// blocks, so none of the six may share memory with another, with any other array of the call or with the workspace.
+static nats_status check_rounded_apart(const FwdPlan& pl, int G, const RoundedGrads& rounded, const void* Q, const void* K, const void* V,
+                                       const float* alpha, const float* beta, const uint8_t* mask, const void* dO, const float* dQ,
+                                       const float* dK, const float* dV, const float* dalpha, const float* dbeta, const nats_bwd_extra& ex,
+                                       const void* workspace, size_t workspace_bytes) {
+    const size_t tok = (size_t)pl.BH * pl.L, qk = tok * pl.d, v = qk * G, states = (size_t)pl.BH * G * pl.d * pl.d, chunks = tok / 64;
+    struct Span {
+        const char* name;
+        const void* p;
+        size_t n;
+    };
+    const Span spans[] = {
+        {"dQ_bf16", rounded.dQ, 2 * qk}, {"dK_bf16", rounded.dK, 2 * qk}, {"dV_bf16", rounded.dV, 2 * v},
+        {"dQ", dQ, 4 * qk}, {"dK", dK, 4 * qk}, {"dV", dV, 4 * v},
+        {"Q", Q, 2 * qk}, {"K", K, 2 * qk}, {"V", V, 2 * v}, {"dO", dO, 2 * v}, {"alpha", alpha, 4 * tok}, {"beta", beta, 4 * tok},
+        {"mask", mask, pl.routing == NATS_ROUTE_CHUNK ? tok / pl.RC : tok}, {"dalpha", dalpha, 4 * tok}, {"dbeta", dbeta, 4 * tok},
+        {"initial_state", ex.initial_state, 4 * states}, {"d_initial_state", ex.d_initial_state, 4 * states},
+        {"g_nla", ex.g_nla, 4 * tok}, {"g_la", ex.g_la, 4 * tok}, {"dscore_nla", ex.dscore_nla, 4 * chunks}, {"dscore_la", ex.dscore_la, 4 * chunks},
+        {"Q_nla", ex.Q_nla, 2 * v}, {"K_nla", ex.K_nla, 2 * v}, {"dQ_nla", ex.dQ_nla, 4 * v}, {"dK_nla", ex.dK_nla, 4 * v},
+        {"w_nla", ex.w_nla, 4 * tok * G}, {"w_la", ex.w_la, 4 * tok * G}, {"dw_nla", ex.dw_nla, 4 * tok * G}, {"dw_la", ex.dw_la, 4 * tok * G},
+        {"the workspace", workspace, workspace_bytes}};
+    const int n = (int)(sizeof(spans) / sizeof(spans[0]));
+    for (int i = 0; i < 6; ++i)
+        for (int j = i + 1; j < n; ++j) {
+            const Span &a = spans[i], &b = spans[j];
+            const uintptr_t pa = (uintptr_t)a.p, pb = (uintptr_t)b.p;
+            if (b.p != nullptr && (pa < pb ? pb - pa < a.n : pa - pb < b.n)) {
+                set_error("%s must not share memory with %s", a.name, b.name);
+                return NATS_ERR_SHAPE;
+            }
+        }
+    return NATS_OK;
+}
+
 static nats_status run_bwd(const nats_fwd_params* p, const void* Q, const void* K, const void* V,
                            const float* alpha, const float* beta, const uint8_t* mask, const void* dO,
                            float* dQ, float* dK, float* dV, float* dalpha, float* dbeta,
@@ -887,6 +922,11 @@ static nats_status run_bwd(const nats_fwd_params* p, const void* Q, const void* 
             set_error("a gradient output must not alias an input");
             return NATS_ERR_SHAPE;
         }
+    if (rounded.dQ != nullptr) {
+        st = check_rounded_apart(pl, p->group > 1 ? p->group : 1, rounded, Q, K, V, alpha, beta, mask, dO, dQ, dK, dV, dalpha, dbeta, ex,
+                                 workspace, workspace_bytes);
+        if (st != NATS_OK) return st;
+    }
 
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     char* ws = static_cast<char*>(workspace);
