@@ -834,7 +834,6 @@ static nats_status bwd_core(const FwdPlan& pl, const BwdPlan& bp, const void* Q,
     {   // what none of these has rounded
         const Rounding left[] = {{dQ, direct.dQ ? nullptr : rounded.dQ, n_qk}, {dK, direct.dK ? nullptr : rounded.dK, n_qk},
                                  {dV, direct.dV ? nullptr : rounded.dV, n_qk}};
-        ProfScope ps("round_bf16", stream);
         st = launch_round_bf16(left, 3, stream);
         if (st != NATS_OK) return st;
     }

@@ -150,6 +150,7 @@ nats_status launch_round_bf16(const Rounding* r, int n, hipStream_t st) {
         if (r[i].n > most) most = r[i].n;
     }
     if (m == 0) return NATS_OK;
+    ProfScope ps("round_bf16", st);
     hipLaunchKernelGGL(round_bf16_kernel, dim3(hg_grid(most / 4), m), dim3(HG_THREADS), 0, st, a);
     return check_launch("round_bf16");
 }
