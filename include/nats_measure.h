@@ -32,6 +32,11 @@ int nats_profile_end(char* names, float* total_ms, int32_t* launches, int max_ke
  * or a negative value on error (see nats_last_error). */
 double nats_probe_mfma(int iters, float* out, size_t out_floats, void* hip_stream);
 
+/* The form in which a forward call with these parameters runs the chunkwise linear branch (nats.h, gdn_segments), decided on the
+ * host from the sizes alone: *segments side by side, or in one pass with *slices (1 or 2) of 16 value columns per block and
+ * *segments = 1.  *slices = 0: in segments.  Both 0: the call does not take that path (fp32 arithmetic). */
+nats_status nats_linear_scan_form(const nats_fwd_params* p, int32_t* segments, int32_t* slices);
+
 #ifdef __cplusplus
 }
 #endif

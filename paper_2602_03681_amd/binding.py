@@ -73,8 +73,8 @@ class DecParams(ctypes.Structure):
 
 EXPORTS = ("nats_hybrid_attn_fwd_workspace_bytes", "nats_hybrid_attn_fwd", "nats_hybrid_attn_fwd_ex", "nats_hybrid_attn_fwd_ex_clear",
            "nats_hybrid_attn_decode", "nats_last_error", "nats_abi_version", "nats_profile_begin",
-           "nats_profile_end", "nats_probe_mfma", "nats_hybrid_attn_decode_chunk",
-           "nats_hybrid_attn_decode_commit", "nats_merge_weights", "nats_route_chunks",
+           "nats_profile_end", "nats_probe_mfma", "nats_linear_scan_form",
+           "nats_hybrid_attn_decode_chunk", "nats_hybrid_attn_decode_commit", "nats_merge_weights", "nats_route_chunks",
            "nats_hybrid_attn_bwd_workspace_bytes", "nats_hybrid_attn_bwd", "nats_hybrid_attn_bwd_bf16",
            "nats_hybrid_attn_fwd_noalloc",
            "nats_hybrid_attn_decode_workspace_bytes", "nats_merge_weights_from_x")
@@ -134,6 +134,8 @@ def load_library():
     lib.nats_abi_version.restype = ctypes.c_int
     lib.nats_probe_mfma.restype = ctypes.c_double
     lib.nats_probe_mfma.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    lib.nats_linear_scan_form.restype = ctypes.c_int
+    lib.nats_linear_scan_form.argtypes = [ctypes.POINTER(FwdParams)] + [ctypes.POINTER(ctypes.c_int32)] * 2
     lib.nats_profile_begin.restype = ctypes.c_int
     lib.nats_profile_begin.argtypes = [ctypes.c_int]
     lib.nats_profile_end.restype = ctypes.c_int
@@ -552,6 +554,13 @@ def hybrid_attn_decode_commit(st, mask_c, *, freeze_on_softmax: bool = False, er
     params = DecParams(B, H, d, cap, _dtype_code(st["k_cache"]), 0.0, 0.0, 0, 0.0, 0, int(freeze_on_softmax))
     _check(lib.nats_hybrid_attn_decode_commit(ctypes.byref(params), ctypes.byref(cs), _ptr(mask_c), _ptr(err_flags),
                                               _stream_ptr()))
+
+
+def linear_scan_form(params: FwdParams):
+    """nats_linear_scan_form -> (segments, slices): the form of the chunkwise linear branch that a call takes."""
+    n = ctypes.c_int32(), ctypes.c_int32()
+    _check(load_library().nats_linear_scan_form(ctypes.byref(params), *(ctypes.byref(x) for x in n)))
+    return n[0].value, n[1].value
 
 
 def profile_begin(max_records: int = 4096) -> None:

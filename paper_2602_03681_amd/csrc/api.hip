@@ -626,6 +626,17 @@ nats_status nats_hybrid_attn_fwd_ex_clear(const nats_fwd_params* p, const void* 
     return run_fwd_ex(p, Q, K, V, alpha, beta, mask, O, extra, true, workspace, workspace_bytes, hip_stream);
 }
 
+nats_status nats_linear_scan_form(const nats_fwd_params* p, int32_t* segments, int32_t* slices) {
+    if (segments == nullptr || slices == nullptr) { set_error("segments and slices must be non-NULL"); return NATS_ERR_NULL; }
+    FwdPlan pl;
+    const nats_status st = validate_fwd_params(p, &pl);
+    if (st != NATS_OK) return st;
+    const ScanForm form = uses_chunk_path(pl) ? gdn_scan_form(pl) : ScanForm{0, 0};
+    *segments = form.n_seg;
+    *slices = form.ns;
+    return NATS_OK;
+}
+
 size_t nats_hybrid_attn_bwd_workspace_bytes(const nats_fwd_params* p) {
     FwdPlan pl;
     BwdPlan bp;

@@ -808,10 +808,7 @@ int gdn_segments(const FwdPlan& pl) {
 // 31.8, L 3072 39.7 / 49.6; 32 heads, L 2048 49.0 / 46.7, L 3072 62.8 / 66.5.  Slices in two rounds lose to one segment at every length: d 128,
 // 120 heads, L 256 30.8 / 33.6, L 2048 136 / 138; 96 heads, L 512 45.5 / 48.3, L 4096 285 / 312; d 64, 136 heads, L 256 25.3 / 28.2,
 // L 2048 104 / 116.  80 heads, L 1024, d 128 take one segment (75.1; three 86.4, two slices 77.4), L 2048 three (132.9; 134.0, 134.7).
-struct SegForm {
-    int n_seg, ns;
-};
-static SegForm seg_form(const FwdPlan& pl) {
+static ScanForm seg_form(const FwdPlan& pl) {
     const int n_chunks = pl.L / SC, cap = gdn_segments(pl);
     if (pl.gdn_segments > 0) return {cap, 0};
     const int heads = (pl.BH + 7) / 8 * pl.G;   // on the fullest XCD
@@ -819,7 +816,7 @@ static SegForm seg_form(const FwdPlan& pl) {
     const bool narrow = pl.d == 64;
     const float seg_step = narrow ? 2.05f + 0.1f * heads : 3.1f, fix = narrow ? 0.55f : 1.4f;
     const float start = narrow ? 3.7f : 2.7f;
-    SegForm best{1, 0};
+    ScanForm best{1, 0};
     float least = rounds(heads) * (narrow ? n_chunks * (1.2f + 0.022f * heads) + 4.6f : n_chunks * (2.3f + 0.035f * heads) + start);
     for (int g = 3; g <= cap; ++g) {
         const float t = 2 * rounds(heads * (g - 1)) * ((n_chunks + g - 1) / g) * seg_step + fix * g + 4.f + start;
@@ -831,6 +828,13 @@ static SegForm seg_form(const FwdPlan& pl) {
         if (t < least) least = t, best = {1, ns};
     }
     return best;
+}
+
+ScanForm gdn_scan_form(const FwdPlan& pl) {
+    ScanForm form = seg_form(pl);
+    const int n_chunks = pl.L / SC, seg_len = (n_chunks + form.n_seg - 1) / form.n_seg;
+    form.n_seg = (n_chunks + seg_len - 1) / seg_len;   // no empty segment
+    return form;
 }
 
 template <int D, bool F32OUT>
@@ -848,7 +852,6 @@ static nats_status launch_seg_k(const FwdPlan& pl, SegArgs<D> a, hipStream_t st)
     }
     const int n_chunks = pl.L / SC;
     a.seg_len = (n_chunks + a.n_seg - 1) / a.n_seg;
-    a.n_seg = (n_chunks + a.seg_len - 1) / a.seg_len;   // no empty segment
     const int bh8 = 8 * ((pl.BH + 7) / 8) * pl.G;   // linear heads padded to the XCD count, times the group size
     const int n_mid = a.n_seg > 2 ? a.n_seg - 2 : 0;
     {
@@ -884,7 +887,7 @@ nats_status launch_gdn_seg_scan(const FwdPlan& pl, const void* Q, const void* K,
                                 const void* PF, const float* gamv, const float* kdv, const float* gamC,
                                 const float* S0, float* S_final, float* seg_ws, void* O_la_h, float* O_la_f32,
                                 hipStream_t st) {
-    const SegForm form = seg_form(pl);
+    const ScanForm form = gdn_scan_form(pl);
     if (form.ns > 0)
         return launch_gdn_slice_scan(pl, form.ns, Q, K, V, TF, PF, gamv, kdv, gamC, S0, S_final, O_la_h, O_la_f32, st);
     const size_t per = (size_t)pl.BHG * gdn_segments(pl) * pl.d * pl.d;

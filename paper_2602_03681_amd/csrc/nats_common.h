@@ -224,7 +224,12 @@ nats_status launch_gdn_chunk_inv(const FwdPlan& pl, const void* Q, const void* K
                                  float* kdv, float* gamC, const void* K_sm, const void* V, int32_t* cnt, int32_t* idx,
                                  int32_t* n_s, void* Kc, void* Vc, void* Kc_user, void* Vc_user, int cap_user, void* Vh,
                                  hipStream_t st);
-int gdn_segments(const FwdPlan& pl);   // segments per (batch, head) the chunkwise linear branch will use
+int gdn_segments(const FwdPlan& pl);   // segments per (batch, head) that the workspace of the chunkwise linear branch has room for
+// ... and the form that it takes: n_seg segments, or (ns 1 or 2) one pass with ns slices of 16 value columns per block
+struct ScanForm {
+    int n_seg, ns;
+};
+ScanForm gdn_scan_form(const FwdPlan& pl);
 nats_status launch_gdn_seg_scan(const FwdPlan& pl, const void* Q, const void* K, const void* V, const void* TF,
                                 const void* PF, const float* gamv, const float* kdv, const float* gamC,
                                 const float* S0, float* S_final, float* seg_ws, void* O_la_h, float* O_la_f32,

@@ -3,6 +3,7 @@ import numpy as np
 import torch
 
 from oracle import c_oracle
+from paper_2602_03681_amd import binding as nb
 
 TOL = {"f32": 1e-4, "bf16": 2e-2}   # max|err| / RMS(oracle), the bar the build is held to
 
@@ -51,6 +52,14 @@ def stored(dtype):
 
 def host(t):
     return t.detach().float().cpu().numpy() if t.is_floating_point() else t.detach().cpu().numpy()
+
+
+def launched(call):
+    """(what the call returns, the names of the kernels that it launched)"""
+    nb.profile_begin(256)
+    r = call()
+    torch.cuda.synchronize()
+    return r, set(nb.profile_end(32))
 
 
 def oracle_fwd(x, **kw):

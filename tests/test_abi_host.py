@@ -42,7 +42,7 @@ def test_abi_version(lib):
     # 110: p->math selects the form of the backward's linear adjoint, C = 128 with routing per chunk; 111: the backward
     # pass takes p->group; 112: nats_bwd_extra gained Q_nla, K_nla, dQ_nla, dK_nla;
     # 113: the backward takes combine_mode 1 and 2 (nats_bwd_extra gained w_nla, w_la, dw_nla, dw_la);
-    # 114: nats_hybrid_attn_fwd_ex_clear, nats_hybrid_attn_bwd_bf16
+    # 114: nats_hybrid_attn_fwd_ex_clear, nats_hybrid_attn_bwd_bf16, nats_linear_scan_form
 
 
 def good_params(**over):

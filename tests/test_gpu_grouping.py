@@ -104,15 +104,16 @@ def test_grouped_bf16_tensors_in_fp32_arithmetic():
     check(r, run_oracle(x, G, False, 0, True), x, G, "bf16", True)
 
 
+@pytest.mark.parametrize("n_seg", [0, 8])
 @pytest.mark.parametrize("G", [2, 3])
-def test_grouped_equals_repeated_heads_at_size(G):
-    """Several segments, several query tiles, odd head counts: the grouped call against the C oracle on H G heads
+def test_grouped_equals_repeated_heads_at_size(G, n_seg):
+    """One pass (the call's choice) and several segments, several query tiles, odd head counts: the grouped call against the C oracle on H G heads
     with the linear head's inputs repeated (what the grouping is defined to equal)."""
     B, H, L, d = 2, 3, 2048, 128
     x = grouped_inputs(B, H, G, L, d, "bf16", 0.06, 500 + G, False, False)
     g = to_dev({k: x[k] for k in ("Q", "K", "V", "alpha", "beta", "mask")}, "bf16")
     r = nats.hybrid_attn_fwd_ex(g["Q"], g["K"], g["V"], g["alpha"], g["beta"], g["mask"], 64, group=G,
-                                want=("O_la", "O_nla", "final_state"))
+                                want=("O_la", "O_nla", "final_state"), gdn_segments=n_seg)
     torch.cuda.synchronize()
     rep = lambda a: np.repeat(a, G, axis=1)
     ref = c_oracle.fwd(rep(x["Q"]), rep(x["K"]), x["V"], rep(x["alpha"]), rep(x["beta"]), rep(x["mask"]),

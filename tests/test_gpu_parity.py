@@ -331,9 +331,8 @@ def test_merge_weight_activations(act):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_more_pairs_than_the_chip_has_cus(d):
-    """B*H = 80: the recurrence kernel's grid (320 blocks) exceeds the CU count, so it runs without its prefetch
-    helper blocks and in more than one wave of blocks; the padded pair count of the one-dimensional grids
-    (80 is a multiple of 8, 75 below is not) changes nothing."""
+    """B*H = 80: 320 or 640 slices of 16 value columns, more than there are CUs (d = 64: two slices per block; d = 128: one
+    segment); the padded pair count of the one-dimensional grids (80 is a multiple of 8, 75 below is not) changes nothing."""
     for B, H in ((5, 16), (5, 15)):
         x = make_fwd_inputs(B, H, 256, d, "bf16", 0.1, seed=95 + H)
         r = run_ex(x, "bf16", want=("final_state", "n_s"))
@@ -355,42 +354,44 @@ def test_one_chunk_and_long_thin_shapes_bf16():
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_every_chunk_count_up_to_nine_bf16(d):
-    """1..9 chunks: the scan's staging wavefronts walk a segment's chunks two to a loop trip with an odd one behind,
-    one chunk ahead of the state wavefronts and with a clamped index at the end; with the automatic segment count
-    these lengths give segments of one to nine chunks (1 .. 7 chunks: one segment; 8, 9: two), with a given
-    initial state."""
+    """1..9 chunks: the staging wavefronts of either form of the scan walk the chunks two or three to a loop trip with the rest
+    behind, ahead of the others and with a clamped index at the end; as the call chooses (one pass) and as one segment, with a
+    given initial state."""
     for n_chunks in range(1, 10):
         L = 64 * n_chunks
         x = make_fwd_inputs(1, 3, L, d, "bf16", 0.1, seed=500 + 10 * n_chunks + d)
         S0 = (0.1 * np.random.default_rng(n_chunks).standard_normal((1, 3, d, d))).astype(np.float32)
-        r = run_ex(x, "bf16", want=("final_state",), initial_state=S0)
         ref = oracle_fwd(x, S0=S0, want=("S",))
-        assert rel_err(host(r["O"]), ref["O"], "bf16") <= TOL["bf16"], (L, d)
-        assert rel_err(host(r["final_state"]), ref["S"]) <= TOL["bf16"], (L, d)
+        for n_seg in (0, 1):
+            r = run_ex(x, "bf16", want=("final_state",), initial_state=S0, gdn_segments=n_seg)
+            assert rel_err(host(r["O"]), ref["O"], "bf16") <= TOL["bf16"], (L, d, n_seg)
+            assert rel_err(host(r["final_state"]), ref["S"]) <= TOL["bf16"], (L, d, n_seg)
 
 
 def test_pair_counts_between_powers_of_two_bf16():
-    """B*H = 40, 48, 56 at 16 chunks: pair counts between the powers of two, four segments each (the automatic
-    count, about 256 / (B*H), is capped at a quarter of the chunks): 200 to 280 blocks in the first pass."""
+    """B*H = 40, 48, 56 at 16 chunks: pair counts between the powers of two, in one pass (two slices per block, as the call
+    chooses) and in four segments each: 120 to 168 blocks in the first pass."""
     for B, H in ((5, 8), (6, 8), (7, 8)):
         x = make_fwd_inputs(B, H, 1024, 128, "bf16", 0.05, seed=600 + B)
-        r = run_ex(x, "bf16", want=("final_state",))
         ref = oracle_fwd(x, want=("S",))
-        assert rel_err(host(r["O"]), ref["O"], "bf16") <= TOL["bf16"], (B, H)
-        assert rel_err(host(r["final_state"]), ref["S"]) <= TOL["bf16"], (B, H)
+        for n_seg in (0, 4):
+            r = run_ex(x, "bf16", want=("final_state",), gdn_segments=n_seg)
+            assert rel_err(host(r["O"]), ref["O"], "bf16") <= TOL["bf16"], (B, H, n_seg)
+            assert rel_err(host(r["final_state"]), ref["S"]) <= TOL["bf16"], (B, H, n_seg)
 
 
 # ---------------------------------------------------------------------------------------------
 # value ranges of the bf16 path (its intermediates are fp16: accepted range stated in nats.h)
 # ---------------------------------------------------------------------------------------------
-def test_large_values_and_large_initial_state_bf16():
+@pytest.mark.parametrize("n_seg", [0, 4])   # one pass, as the call chooses; segments
+def test_large_values_and_large_initial_state_bf16(n_seg):
     """|V| up to about 1000 and an initial state of the same size: inside the stated range of the bf16 path
     (every intermediate below 65504), the bar holds as for unit-size values; both branches are linear in V."""
     d = 128
     x = make_fwd_inputs(1, 3, 1024, d, "bf16", 0.1, seed=701)
     x["V"] = (x["V"] * 256.0).astype(np.float32)            # still bf16 values: a power of two
     S0 = (200.0 * np.random.default_rng(702).standard_normal((1, 3, d, d))).astype(np.float32)
-    r = run_ex(x, "bf16", want=("final_state", "O_la", "O_nla"), initial_state=S0)
+    r = run_ex(x, "bf16", want=("final_state", "O_la", "O_nla"), initial_state=S0, gdn_segments=n_seg)
     ref = oracle_fwd(x, S0=S0)
     report("large V, large S0: O", host(r["O"]), ref["O"])
     assert rel_err(host(r["O"]), ref["O"], "bf16") <= TOL["bf16"]
@@ -460,11 +461,12 @@ def test_segment_count_does_not_change_the_result_beyond_rounding_bf16():
         assert np.abs(a - b).max() <= 2e-3 * np.sqrt(np.mean(b * b)), n_seg
 
 
-def test_values_beyond_the_fp16_range_saturate_bf16():
+@pytest.mark.parametrize("n_seg", [0, 1, 2])
+def test_values_beyond_the_fp16_range_saturate_bf16(n_seg):
     """|V| around 2^20: the linear branch's fp16 intermediates leave the stated range.  They saturate (the result
     is then inaccurate, as nats.h says) but nothing turns into inf or NaN."""
     x = make_fwd_inputs(1, 2, 512, 128, "bf16", 0.1, seed=730)
     x["V"] = (x["V"] * 2.0 ** 20).astype(np.float32)
-    r = run_ex(x, "bf16", want=("final_state", "O_la"))
+    r = run_ex(x, "bf16", want=("final_state", "O_la"), gdn_segments=n_seg)
     assert np.isfinite(host(r["O"])).all() and np.isfinite(host(r["O_la"])).all()
     assert np.isfinite(host(r["final_state"])).all()

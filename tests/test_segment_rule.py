@@ -1,5 +1,6 @@
-"""The automatic number of segments of the bf16 forward's linear branch, read off the workspace that a call reports (three
-states per segment and output head), on both sides of every line of the rule."""
+"""The number of segments that the workspace of the bf16 forward's linear branch has room for where the call chooses, read off the size
+that a call reports (three states per segment and output head), on both sides of every line of the rule.  It is the most that a call
+takes: how many it does take, or whether it runs in one pass instead, is test_scan_form.py's."""
 import pytest
 
 from paper_2602_03681_amd import binding as nb
