@@ -795,8 +795,8 @@ int gdn_segments(const FwdPlan& pl) {
 
 // The form of an automatic call: in segments (ns = 0, n_seg of them, at most as many as the workspace has room for) or in one pass
 // with ns slices of 16 value columns per block (gdn_slice_scan.hip), whichever is expected to take less, in us:
-// * one pass: a step per chunk, 1.1 with one slice per block and 1.42 with two (d = 64: 0.87, 1.0), and 2.7 (3.7) before the
-//   first step of every round;
+// * one pass, where its blocks are one round: a step per chunk, 1.1 with one slice per block and 1.42 with two (d = 64: 0.87, 1.0),
+//   and 2.7 (3.7) before the first step;
 // * one segment: a step per chunk, 2.3 and 0.035 per head on an XCD (1.2, 0.022), and 2.7 (4.6);
 // * more segments: two passes of a step per chunk of a segment, 3.1 (2.05 and 0.1 per head on an XCD), 1.4 (0.55) per segment
 //   for the fix-up, 4 for two more launches, and 2.7 (3.7).
@@ -805,9 +805,10 @@ int gdn_segments(const FwdPlan& pl) {
 // forward, 84.8 in one pass).  Measured, whole forwards, p 0.05, in segments / in one pass: d 128, 2 heads, L 512 34.2 / 24.9, L 2048
 // 55.9 / 50.0, L 3072 64.7 / 69.2; 18 heads, L 1024 54.5 / 38.7; 32 heads, L 2048 76.0 / 65.2, L 4096 117.0 / 117.4, L 6144
 // 160.7 / 172.8; 48 heads (two slices), L 1024 66.3 / 46.7, L 4096 158.8 / 151.6, L 6144 229 / 241; d 64, 8 heads, L 1536 34.8 /
-// 31.8, L 3072 39.7 / 49.6; 32 heads, L 2048 49.0 / 46.7, L 3072 62.8 / 66.5.  Slices in two rounds lose to one segment at every length: d 128,
-// 120 heads, L 256 30.8 / 33.6, L 2048 136 / 138; 96 heads, L 512 45.5 / 48.3, L 4096 285 / 312; d 64, 136 heads, L 256 25.3 / 28.2,
-// L 2048 104 / 116.  80 heads, L 1024, d 128 take one segment (75.1; three 86.4, two slices 77.4), L 2048 three (132.9; 134.0, 134.7).
+// 31.8, L 3072 39.7 / 49.6; 32 heads, L 2048 49.0 / 46.7, L 3072 62.8 / 66.5.  Slices in two rounds and more lose to one segment: d 128,
+// 120 heads, L 256 30.8 / 33.6, L 2048 136 / 138; 96 heads, L 512 45.5 / 48.3, L 4096 285 / 312; 128 heads, L 8704 749 / 831; 576 heads,
+// L 2048 724 / 839; d 64, 136 heads, L 256 25.3 / 28.2, L 2048 104 / 116; 320 heads, L 2048 254 / 256, L 8192 1084 / 1078; 512 heads, L 2048
+// 371 / 388.  80 heads, L 1024, d 128 take one segment (75.1; three 86.4, two slices 77.4), L 2048 three (132.9; 134.0, 134.7).
 static ScanForm seg_form(const FwdPlan& pl) {
     const int n_chunks = pl.L / SC, cap = gdn_segments(pl);
     if (pl.gdn_segments > 0) return {cap, 0};
@@ -823,8 +824,9 @@ static ScanForm seg_form(const FwdPlan& pl) {
         if (t < least) least = t, best = {g, 0};
     }
     for (int ns = 1; ns <= 2; ++ns) {
+        if (rounds(heads * (pl.d / 16 / ns)) > 1) continue;
         const float step = narrow ? (ns == 1 ? 0.87f : 1.0f) : (ns == 1 ? 1.1f : 1.42f);
-        const float t = rounds(heads * (pl.d / 16 / ns)) * (n_chunks * step + start);
+        const float t = n_chunks * step + start;
         if (t < least) least = t, best = {1, ns};
     }
     return best;

@@ -24,6 +24,9 @@ def form(H, chunks, d, dtype=nb.NATS_BF16, **kw):
     (64, 64, 32, (1, 1)), (64, 65, 32, (1, 2)), (64, 128, 64, (1, 2)),
     # ... and beyond 64 (128) heads segments: one, or three
     (128, 65, 17, (1, 0)), (128, 65, 18, (3, 0)), (128, 96, 64, (1, 0)), (64, 136, 32, (1, 0)),
+    # whatever the length and however many: slices in several rounds of blocks are not taken
+    (128, 128, 136, (1, 0)), (128, 128, 512, (1, 0)), (128, 320, 32, (1, 0)), (128, 576, 32, (1, 0)),
+    (64, 136, 512, (1, 0)), (64, 264, 32, (1, 0)), (64, 320, 8, (1, 0)), (64, 512, 32, (1, 0)), (64, 704, 256, (1, 0)),
 ])
 def test_lines(d, H, chunks, want):
     assert form(H, chunks, d) == want
