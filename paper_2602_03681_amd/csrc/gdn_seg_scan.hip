@@ -809,6 +809,10 @@ int gdn_segments(const FwdPlan& pl) {
 // 120 heads, L 256 30.8 / 33.6, L 2048 136 / 138; 96 heads, L 512 45.5 / 48.3, L 4096 285 / 312; 128 heads, L 8704 749 / 831; 576 heads,
 // L 2048 724 / 839; d 64, 136 heads, L 256 25.3 / 28.2, L 2048 104 / 116; 320 heads, L 2048 254 / 256, L 8192 1084 / 1078; 512 heads, L 2048
 // 371 / 388.  80 heads, L 1024, d 128 take one segment (75.1; three 86.4, two slices 77.4), L 2048 three (132.9; 134.0, 134.7).
+// From 33 to 64 heads of 64 columns a step of the one pass (and of one segment) grows with the length as the operands outgrow the
+// last cache: 0.87 up to some 64 chunks, then towards 1.1-1.4.  Segments there from 69 (40 heads at most) and 89 chunks on, in segments /
+// in one pass: 40 heads, L 4096 85.3 / 83.9, L 4608 92.9 / 94.4, L 8192 154 / 179, L 16384 344 / 417; 48 heads, L 5632 123 / 121, L 6144 132 / 134-144, L 6656
+// 144 / 156, L 8192 184 / 207; 64 heads, L 4096 114 / 102, L 6144 175 / 180, L 8192 239 / 248, L 16384 540 / 551 (one segment: 647).
 static ScanForm seg_form(const FwdPlan& pl) {
     const int n_chunks = pl.L / SC, cap = gdn_segments(pl);
     if (pl.gdn_segments > 0) return {cap, 0};
@@ -818,13 +822,14 @@ static ScanForm seg_form(const FwdPlan& pl) {
     const float seg_step = narrow ? 2.05f + 0.1f * heads : 3.1f, fix = narrow ? 0.55f : 1.4f;
     const float start = narrow ? 3.7f : 2.7f;
     ScanForm best{1, 0};
-    float least = rounds(heads) * (narrow ? n_chunks * (1.2f + 0.022f * heads) + 4.6f : n_chunks * (2.3f + 0.035f * heads) + start);
+    const bool no_pass = narrow && heads >= 5 && heads <= 8 && cap > 1 && n_chunks > (heads == 5 ? 68 : 88);
+    float least = no_pass ? HUGE_VALF : rounds(heads) * (narrow ? n_chunks * (1.2f + 0.022f * heads) + 4.6f : n_chunks * (2.3f + 0.035f * heads) + start);
     for (int g = 3; g <= cap; ++g) {
         const float t = 2 * rounds(heads * (g - 1)) * ((n_chunks + g - 1) / g) * seg_step + fix * g + 4.f + start;
         if (t < least) least = t, best = {g, 0};
     }
     for (int ns = 1; ns <= 2; ++ns) {
-        if (rounds(heads * (pl.d / 16 / ns)) > 1) continue;
+        if (no_pass || rounds(heads * (pl.d / 16 / ns)) > 1) continue;
         const float step = narrow ? (ns == 1 ? 0.87f : 1.0f) : (ns == 1 ? 1.1f : 1.42f);
         const float t = n_chunks * step + start;
         if (t < least) least = t, best = {1, ns};

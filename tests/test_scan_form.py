@@ -19,6 +19,9 @@ def form(H, chunks, d, dtype=nb.NATS_BF16, **kw):
     (128, 1, 1, (1, 1)), (128, 2, 39, (1, 1)), (128, 2, 40, (10, 0)), (128, 18, 39, (1, 1)), (128, 18, 40, (10, 0)),
     (128, 32, 47, (1, 1)), (128, 32, 48, (8, 0)),
     (64, 1, 1, (1, 1)), (64, 2, 31, (1, 1)), (64, 2, 32, (8, 0)), (64, 32, 37, (1, 1)), (64, 32, 38, (8, 0)),
+    # (33 to 64 heads of 64 columns: one pass up to 68 or 88 chunks)
+    (64, 40, 68, (1, 1)), (64, 40, 69, (6, 0)), (64, 40, 256, (6, 0)), (64, 48, 88, (1, 1)), (64, 48, 89, (5, 0)), (64, 64, 88, (1, 1)),
+    (64, 64, 89, (4, 0)), (64, 64, 384, (4, 0)), (64, 65, 384, (1, 2)),
     # ... then two ...
     (128, 33, 27, (1, 2)), (128, 33, 28, (7, 0)), (128, 48, 64, (1, 2)), (128, 48, 65, (5, 0)), (128, 64, 64, (1, 2)),
     (64, 64, 32, (1, 1)), (64, 65, 32, (1, 2)), (64, 128, 64, (1, 2)),
