@@ -527,6 +527,12 @@ static nats_status run_fwd(FwdPlan pl, const void* Q, const void* K, const void*
         ex.w_nla = w;
         ex.w_la = w + (size_t)pl.BHG * pl.L;
     }
+    if (pl.zero_rest && ex.Kc != nullptr && clears_cache_apart(pl, ex.cap)) {
+        ProfScope ps("clear_cache", stream);
+        st = launch_clear_cache(pl, ex.Kc, ex.Vc, ex.cap, stream);
+        if (st != NATS_OK) return st;
+        pl.zero_rest = 0;
+    }
     // The kernels run one after the other on the caller's stream.  (The softmax branch depends on nothing
     // the preparation of the linear branch computes, but the preparation kernel fills every CU by itself:
     // beside it on a second stream the softmax branch only waited for free slots, and nothing was gained.)

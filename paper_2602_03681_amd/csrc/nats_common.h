@@ -215,6 +215,9 @@ struct FwdPlan {
 nats_status launch_scan_compact(const FwdPlan& pl, const uint8_t* mask, const void* K, const void* V,
                                 int32_t* cnt, int32_t* idx, int32_t* n_s, void* Kc, void* Vc,
                                 void* Kc_user, void* Vc_user, int cap_user, void* Vh, hipStream_t st);
+// the caller's Kc, Vc [BHG][cap][d], cleared whole before the compaction, where its blocks would take longer over the rows behind L
+bool clears_cache_apart(const FwdPlan& pl, int cap);
+nats_status launch_clear_cache(const FwdPlan& pl, void* Kc_user, void* Vc_user, int cap, hipStream_t st);
 nats_status launch_gdn_recurrent(const FwdPlan& pl, const void* Q, const void* K, const void* V,
                                  const float* alpha, const float* beta, const uint8_t* mask,
                                  const float* S0, float* S_final, float* O_la, float* snap, const int32_t* redo,

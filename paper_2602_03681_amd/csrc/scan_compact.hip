@@ -36,4 +36,28 @@ nats_status launch_scan_compact(const FwdPlan& pl, const uint8_t* mask, const vo
     return check_launch("scan_compact");
 }
 
+// n pieces of 16 bytes of Kc (blockIdx.y 0) and Vc.  One piece per thread: 2152 MB (64 heads, 32832 rows of 512 bytes) in 314 us, 6.8 TB/s;
+// two pieces 346, four 360; head by head with the rows below L left out 174 instead of 159 (256 heads, 8256 rows of 256 bytes).
+__global__ __launch_bounds__(SCAN_THREADS) void clear_cache_kernel(uint4* Kc, uint4* Vc, size_t n) {
+    uint4* p = blockIdx.y ? Vc : Kc;
+    for (size_t e = (size_t)blockIdx.x * SCAN_THREADS + threadIdx.x; e < n; e += (size_t)gridDim.x * SCAN_THREADS)
+        p[e] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// The compaction's blocks, one per 1024 tokens of a head, clear what lies behind L on the side, at some 150 GB/s each: free up to 512 KB
+// per block (2.8 us less than a launch of its own, over 68 sizes from 1 head and L 64 on), even with it at 1 MB (0.5 us), 5 us behind at 2 MB,
+// 100 at 16 MB (16 heads, L 64, d 128, cap 32768 bf16: 144 us for the call, 59 with two fills beforehand).
+bool clears_cache_apart(const FwdPlan& pl, int cap) {
+    const size_t tail = cap > pl.L ? (size_t)(cap - pl.L) * pl.d * (pl.dtype == NATS_BF16 ? 4 : 8) : 0;   // of a head, both arrays
+    return tail / ((pl.L + SCAN_SEG - 1) / SCAN_SEG) >= (size_t)1 << 20;
+}
+
+nats_status launch_clear_cache(const FwdPlan& pl, void* Kc_user, void* Vc_user, int cap, hipStream_t st) {
+    const size_t n = (size_t)pl.BHG * cap * pl.d * (pl.dtype == NATS_BF16 ? 2 : 4) / 16, blocks = (n + SCAN_THREADS - 1) / SCAN_THREADS;
+    const size_t most = (size_t)1 << 23;   // a launch has fewer than 2^32 threads along x
+    hipLaunchKernelGGL(clear_cache_kernel, dim3((unsigned)(blocks < most ? blocks : most), 2), dim3(SCAN_THREADS), 0, st, (uint4*)Kc_user,
+                       (uint4*)Vc_user, n);
+    return check_launch("clear_cache");
+}
+
 }  // namespace nats

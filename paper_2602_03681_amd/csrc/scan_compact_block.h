@@ -115,7 +115,8 @@ __device__ __forceinline__ void scan_compact_block(const ScanArgs<T>& a, const i
 
     // ---- 2a. the caller's rows behind the compacted ones ----------------------------------
     // The tokens that are not compacted have the rows n_s .. L - 1 among them, the r-th of them row L - 1 - r: a block finds its
-    // share without knowing n_s, which the last block alone knows.  Rows from L on: an equal share per block.  Cleared whole
+    // share without knowing n_s, which the last block alone knows.  Rows from L on: an equal share per block
+    // (a large one: the arrays are cleared beforehand, see clears_cache_apart()).  Cleared whole
     // beforehand, two fill launches: a call of B 3, H 6, L 1216, d 128 bf16 with a fifth of the tokens compacted took 50.4 us, now 47.4,
     // B 1, H 16, L 8192 with a tenth 167, now 159.  (Blocks of 256 tokens, each with a shorter share: 46.3 and 164.)
     if (a.zero_rest && Kc_user != nullptr) {

@@ -9,7 +9,7 @@ import paper_2602_03681_amd as nats
 from paper_2602_03681_amd import binding as nb
 from nats_inputs import make_fwd_inputs
 
-from gpu_util import to_dev
+from gpu_util import launched, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -20,7 +20,8 @@ WAYS = {"bf16": ("bf16", {}), "f32": ("f32", {}), "bf16_as_fp32": ("bf16", dict(
 
 @pytest.mark.parametrize("way", WAYS)
 @pytest.mark.parametrize("mask_kind", ["some", "none", "all"])
-@pytest.mark.parametrize("L,cap", [(64, 64), (256, 100), (320, 320), (1216, 1216), (1088, 1500), (320, 1), (1344, 1343)])
+@pytest.mark.parametrize("L,cap", [(64, 64), (256, 100), (320, 320), (1216, 1216), (1088, 1500), (320, 1), (1344, 1343),
+                                   (64, 5000), (1088, 8300)])
 def test_rows_behind_the_compacted_ones_are_zeros(L, cap, mask_kind, way):
     dtype, kw = WAYS[way]
     d, G = (64, 1) if way == "f32" else (128, kw.get("group", 1))
@@ -42,6 +43,22 @@ def test_rows_behind_the_compacted_ones_are_zeros(L, cap, mask_kind, way):
                 want = torch.zeros_like(got)
                 want[:min(len(at), cap)] = src[at][:cap]
                 assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype,d,L,apart", [   # apart: the first capacity with it
+    # a block per 1024 tokens clears what lies behind L as long as its share is below 1 MB of Kc and Vc together ...
+    ("bf16", 128, 64, 64 + 2048), ("bf16", 64, 1024, 1024 + 4096), ("f32", 128, 128, 128 + 1024), ("f32", 64, 1088, 1088 + 4096),
+])
+def test_large_caches_are_cleared_by_a_launch_of_their_own(dtype, d, L, apart):
+    """... which some shares of a few blocks take several times as long over as a launch on all CUs"""
+    x = to_dev(make_fwd_inputs(1, 1, L, d, dtype, 0.2, seed=54), dtype)
+    args = [x[k] for k in ("Q", "K", "V", "alpha", "beta", "mask")]
+    for cap, own in ((L, False), (apart - 1, False), (apart, True), (2 * apart, True)):
+        r, kernels = launched(lambda: nats.hybrid_attn_fwd_ex(*args, want=("Kc", "Vc", "n_s"), cap=cap))
+        assert ("clear_cache" in kernels) == own, cap
+        n = int(r["n_s"][0, 0])
+        assert not r["Kc"][0, 0, n:].any() and not r["Vc"][0, 0, n:].any()
+        assert torch.equal(r["Vc"][0, 0, :n], x["V"][0, 0][x["mask"][0, 0].bool()])
 
 
 def test_the_plain_call_leaves_them():
