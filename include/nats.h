@@ -110,8 +110,8 @@ typedef struct nats_fwd_params {
     int32_t gdn_segments;  /* bf16 path: segments the sequence of every (batch, head) is cut into, which then
                               run side by side (the recurrence over chunks is affine in the state, so the
                               segments' start states are composed afterwards); 0 chooses automatically
-                              (about 256 / (B*H), at least 4 chunks per segment; for few chunks one pass with
-                              the value columns split over blocks instead).  The result does not depend
+                              (at most about 256 / (B*H), at least 4 chunks per segment; for few chunks one pass
+                              with the value columns split over blocks instead).  The result does not depend
                               on it beyond rounding                                                          */
     int32_t group;         /* head grouping (Section 4.3; the appendix's model sizes use 2 and 3): G = group
                               softmax heads share the mask of one linear head, 0 counts as 1, at most 8.
@@ -184,7 +184,8 @@ size_t nats_hybrid_attn_fwd_workspace_bytes(const nats_fwd_params* p);
  * V, the carried state, the rows V - S k that the delta rule writes and both branches' output rows are
  * rounded to fp16 on their way into a product.  Magnitudes up to 65504 are represented; anything
  * beyond saturates at +-65504 (the hardware's fp16 clamp is on, no infinity or NaN arises) and no
- * status reports it.  alpha is clamped below at 1e-30 per token.  The fp32 path (NATS_F32 tensors,
+ * status reports it; with V of 1e-4 and below fp16's subnormal numbers cost bits (at 1e-4 the final
+ * state is 1e-3 off, at 1e-5 1e-2).  alpha is clamped below at 1e-30 per token.  The fp32 path (NATS_F32 tensors,
  * or math = NATS_MATH_FP32) has neither limit; a NaN, an infinity or an alpha outside (0,1] acts from its token on, as in
  * the recurrence (a head that does not come out finite by chunks is done once more token by token).
  * Returns NATS_OK once everything is enqueued. */

@@ -1404,9 +1404,9 @@ template <typename T, typename TX, int D, int DIR>
 static bool launch_seq_t(const SeqArgs<T, TX>& a, hipStream_t st) {
     // A block takes a CU to itself.  One slice per block up to one block per CU; beyond, where it would take another round, two (n
     // against n / 2 blocks, never as many rounds).  Forwards / backwards in us, one slice -> two, d 128: 36 heads, L 2048
-    // 105 / 172 -> 75 / 128; 48 heads, L 4096 237 / 381 -> 167 / 278; 80 heads, L 2048 172 / 278 -> 149 / 257; 128 heads, L 2048
-    // 249 / 402 -> 175 / 293; d 64: 72 heads, L 2048 87 / 132 -> 60 / 98; 256 heads, L 2048 331 / 521 -> 189 / 278.  (32 heads,
-    // L 2048, one round either way: 63 / 95 with one.)  fp32 tensors, three terms each, leave no room for a second slice.
+    // 107 / 171 -> 75 / 133; 48 heads, L 4096 234 / 362 -> 167 / 270; 80 heads, L 2048 178 / 279 -> 150 / 254; 128 heads, L 2048
+    // 256 / 417 -> 177 / 298; d 64: 72 heads, L 2048 68 / 132 -> 60 / 97; 256 heads, L 2048 263 / 520 -> 191 / 277.  (32 heads,
+    // L 2048, one round: 62 / 94 with one.)  fp32 tensors, three terms each, leave no room for a second slice.
     if constexpr (sizeof(T) == 2) {
         if (a.BH * (D / CB_NV) > 256) return launch_seq_s<T, TX, D, DIR, 2>(a, st);
     }

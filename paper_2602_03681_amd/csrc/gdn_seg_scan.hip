@@ -31,7 +31,8 @@
 // T'', P and the gates.  (K^T, the operand of the state update, is made by the state wavefronts
 // from the K tile, a (contraction step, column half) share each: a product with a 0/1 selector hands a row-major
 // fragment back in the accumulator layout, exactly.  kd rides on U: one rounding to fp16 where kd K and U were two, and the
-// state a fifth nearer to 64 bits.)  They also store the output rows (fp16; the
+// state a sixth nearer to 64 bits, at values of 1e-3 and above; at 1e-4 and below, where U falls among fp16's subnormal
+// numbers, it is 1.3e-3 off instead of 4.7e-4.)  They also store the output rows (fp16; the
 // softmax kernel, which runs afterwards, merges the two branches), which the state wavefronts leave in an LDS
 // tile (computed transposed, S0 Q^T and U^T P^T, so that a lane holds four consecutive d_v of a token): whole
 // rows of 2 d bytes go out.
@@ -800,6 +801,7 @@ int gdn_segments(const FwdPlan& pl) {
 // * one segment: a step per chunk, 2.3 and 0.035 per head on an XCD (1.2, 0.022), and 2.7 (4.6);
 // * more segments: two passes of a step per chunk of a segment, 3.1 (2.05 and 0.1 per head on an XCD), 1.4 (0.55) per segment
 //   for the fix-up, 4 for two more launches, and 2.7 (3.7).
+// The numbers are fitted to where whole calls in the two forms take the same time; a step's own time lies up to a quarter below.
 // A CU takes one block at a time and the blocks of a head are dealt to one of the eight XCDs, 32 CUs each: more blocks than that on
 // the fullest XCD are another round (18 heads in 12 segments: 33 on two of the XCDs, L 3072, d 128 107.9 us for the whole
 // forward, 84.8 in one pass).  Measured, whole forwards, p 0.05, in segments / in one pass: d 128, 2 heads, L 512 34.2 / 24.9, L 2048

@@ -16,9 +16,10 @@
 //                              (fp16, for the merge in the softmax kernel);
 //   STAGING   (four)           the operands that the slices share, from memory to LDS a chunk ahead and in registers up to three
 //                              chunks before that: K and Q (converted to fp16 once), T'', P, the gates, V transposed.
-// One barrier per chunk; a block has NS slices, 1 or 2.  A step takes 1.05 us at d = 128 with one slice and 1.3 with two, 0.85 and
-// 0.95 at d = 64 (0.85 at d = 128 with operands that are in L2 already: a CU has at most its 32 KB of L1 lines in flight, so
-// 48 KB from HBM cost a step more than a memory latency).  In segments a step takes 3.1 and 2.1 us, for all of a head's
+// One barrier per chunk; a block has NS slices, 1 or 2.  A step takes 0.96 us at d = 128 with one slice and 1.17 with two, 0.65 and
+// 0.85 at d = 64, with 4-6 before the first, while the call's tensors fit the last cache (8 to 96 heads, L 512 against 2048); beyond
+// (48 heads, L 4096, d 128) 1.29 with two.  (A CU has at most its 32 KB of L1 lines in flight, so 48 KB from HBM cost a step more
+// than a memory latency.)  In segments a step takes 3.1 and 2.1 us, for all of a head's
 // columns, and there are 2 / n_seg as many: see seg_form() in gdn_seg_scan.hip for where the line lies.
 // Tried on the chain: four wavefronts per slice, a token tile and a quarter of the state each (three exchanges through LDS and
 // three barriers per chunk: 1.15 us and more); its operands touched by the slices of a head in turn, some chunks ahead, so that
