@@ -869,7 +869,7 @@ static nats_status check_rounded_apart(const FwdPlan& pl, int G, const RoundedGr
                                        const float* alpha, const float* beta, const uint8_t* mask, const void* dO, const float* dQ,
                                        const float* dK, const float* dV, const float* dalpha, const float* dbeta, const nats_bwd_extra& ex,
                                        const void* workspace, size_t workspace_bytes) {
-    const size_t tok = (size_t)pl.BH * pl.L, qk = tok * pl.d, v = qk * G, states = (size_t)pl.BH * G * pl.d * pl.d, chunks = tok / 64;
+    const size_t tok = (size_t)pl.BH * pl.L, qk = tok * pl.d, v = qk * G, states = (size_t)pl.BH * G * pl.d * pl.d, chunks = tok / pl.RC;
     struct Span {
         const char* name;
         const void* p;
@@ -1052,7 +1052,7 @@ static nats_status run_bwd(const nats_fwd_params* p, const void* Q, const void* 
         struct { float* sum; const float* part; size_t n; } adds[] = {
             {dQ, dQg, nd}, {dK, dKg, nd}, {dalpha, dag, n_tok}, {dbeta, dbg, n_tok},
             {ex.g_nla, e1.g_nla, n_tok}, {ex.g_la, e1.g_la, n_tok},
-            {ex.dscore_nla, e1.dscore_nla, n_tok / pl.C}, {ex.dscore_la, e1.dscore_la, n_tok / pl.C}};
+            {ex.dscore_nla, e1.dscore_nla, n_tok / pl.RC}, {ex.dscore_la, e1.dscore_la, n_tok / pl.RC}};
         for (const auto& a : adds) {
             if (a.sum == nullptr) continue;
             st = launch_add_f32(a.sum, a.part, a.n, stream);

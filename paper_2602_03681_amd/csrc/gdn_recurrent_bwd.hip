@@ -559,29 +559,35 @@ __device__ __forceinline__ float chunk_sum(double x) {
 // Score gradients with routing per token (Section 4.2).  Eq. 17 for one token: the sum over the state's entries
 // of (gradient w.r.t. the state after the token's write) x (what the token wrote) = beta_t (r_t . dS_t k_t), which is
 // beta_t times the gradient of beta_t that the reverse sweep has already reduced; zero for softmax tokens.  Eq. 16
-// and Eq. 17 per chunk of 64 tokens: the sums over the chunk.  One wavefront per (chunk, batch*head).
+// and Eq. 17 per chunk of C = 64 or 128 tokens: the sums over the chunk.  One wavefront per (chunk, batch*head).
 __global__ __launch_bounds__(64) void score_gradients_kernel(const float* __restrict__ beta, const uint8_t* __restrict__ mask,
                                                             const float* __restrict__ dbeta, const float* __restrict__ g_nla,
                                                             float* __restrict__ g_la, float* __restrict__ dscore_nla,
-                                                            float* __restrict__ dscore_la, int L) {
-    const size_t t = (size_t)blockIdx.y * L + (size_t)blockIdx.x * 64 + threadIdx.x;
-    const double gl = mask[t] ? 0. : (double)beta[t] * (double)dbeta[t];
-    if (g_la != nullptr) g_la[t] = (float)gl;
-    const size_t c = (size_t)blockIdx.y * (L / 64) + blockIdx.x;
+                                                            float* __restrict__ dscore_la, int L, int C) {
+    const size_t t0 = (size_t)blockIdx.y * L + (size_t)blockIdx.x * C + threadIdx.x;
+    double la = 0., nla = 0.;
+    for (int i = 0; i < C; i += 64) {
+        const size_t t = t0 + i;
+        const double gl = mask[t] ? 0. : (double)beta[t] * (double)dbeta[t];
+        if (g_la != nullptr) g_la[t] = (float)gl;
+        la += gl;
+        if (dscore_nla != nullptr) nla += g_nla[t];
+    }
+    const size_t c = (size_t)blockIdx.y * (L / C) + blockIdx.x;
     if (dscore_la != nullptr) {
-        const float s = chunk_sum(gl);
+        const float s = chunk_sum(la);
         if (threadIdx.x == 0) dscore_la[c] = s;
     }
     if (dscore_nla != nullptr) {
-        const float s = chunk_sum(g_nla[t]);
+        const float s = chunk_sum(nla);
         if (threadIdx.x == 0) dscore_nla[c] = s;
     }
 }
 
 nats_status launch_score_gradients(const FwdPlan& pl, const float* beta, const uint8_t* mask, const float* dbeta,
                                    const float* g_nla, float* g_la, float* dscore_nla, float* dscore_la, hipStream_t st) {
-    hipLaunchKernelGGL(score_gradients_kernel, dim3(pl.L / 64, pl.BH), dim3(64), 0, st, beta, mask, dbeta, g_nla, g_la,
-                       dscore_nla, dscore_la, pl.L);
+    hipLaunchKernelGGL(score_gradients_kernel, dim3(pl.L / pl.RC, pl.BH), dim3(64), 0, st, beta, mask, dbeta, g_nla, g_la,
+                       dscore_nla, dscore_la, pl.L, pl.RC);
     return check_launch("score_gradients");
 }
 
